@@ -57,17 +57,27 @@ const char* s3_last_error(void);
  * row always has exactly k distinct ids; vals = max(z, 0).  Within a row the order is
  * (z descending, id ascending).  z is accumulated in fp32 and never written to memory.
  * Inputs are assumed finite.
- * Limits: d_head in {64, 128, 256}; 1 <= k <= min(n_feat, S3_MAX_K); the candidate lists must
- * fit the 160 KB of LDS beside two 32-feature tiles of W_enc, which leaves k <= 128 for bf16 with
+ * Limits: d_head in {64, 128, 256}; 1 <= k <= min(n_feat, S3_MAX_K); k <= 128 for bf16 with
  * d_head <= 128 and fp32 with d_head 64, k <= 121 for bf16 with d_head 256 and fp32 with d_head
  * 128, k <= 78 for fp32 with d_head 256 (k = 128 is the sparsity the paper trains its SAEs with,
  * App. B.3); n_feat <= S3_MAX_FEAT; T >= 0 (T == 0 is a no-op); n_heads >= 1.  Otherwise S3_EINVAL.
  * bf16 with d_head 128, k <= 64 and n_feat a multiple of 128 takes the fast kernel.
- * No workspace is needed (so there is no workspace query for this call).
+ * No workspace is needed; s3_sae_encode_topk_ws is the same call with one.
  */
 int s3_sae_encode_topk(const void* x, int dtype, int T, int d_head, const void* w_enc,
                        const float* b_enc, int n_feat, int k, int n_heads, int32_t* ids,
                        float* vals, void* stream);
+
+/* s3_sae_encode_topk with scratch: a call with few tokens then spreads the features of a head over
+ * several workgroups and merges their selections.  The results are the same bit for bit.
+ *   ws   s3_sae_encode_topk_workspace(...) bytes (0: the call has no use for scratch, ws may be
+ *        NULL), 256-byte aligned, device; contents meaningless between calls.  With less than that the
+ *        call runs as s3_sae_encode_topk.
+ * Errors as s3_sae_encode_topk, and S3_EINVAL for a misaligned ws. */
+size_t s3_sae_encode_topk_workspace(int dtype, int T, int d_head, int n_feat, int k, int n_heads);
+int s3_sae_encode_topk_ws(const void* x, int dtype, int T, int d_head, const void* w_enc,
+                          const float* b_enc, int n_feat, int k, int n_heads, int32_t* ids,
+                          float* vals, void* ws, size_t ws_bytes, void* stream);
 
 /* The same operation for the chunks of one stream (Alg. 1, Phase 1: the prefill walks the context
  * chunk by chunk with the same encoder), with a selection threshold carried from chunk to chunk.

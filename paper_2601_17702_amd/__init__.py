@@ -34,6 +34,10 @@ def lib():
         vp, i32, i64, ci, sz = C.c_void_p, C.c_int32, C.c_int64, C.c_int, C.c_size_t
         L.s3_last_error.restype = C.c_char_p
         L.s3_sae_encode_topk.argtypes = [vp, ci, ci, ci, vp, vp, ci, ci, ci, vp, vp, vp]
+        L.s3_sae_encode_topk_workspace.argtypes = [ci, ci, ci, ci, ci, ci]
+        L.s3_sae_encode_topk_workspace.restype = sz
+        L.s3_sae_encode_topk_ws.argtypes = [vp, ci, ci, ci, vp, vp, ci, ci, ci, vp, vp, vp, sz, vp]
+        L.s3_sae_encode_topk_ws.restype = ci
         L.s3_sae_encode_topk_stream.argtypes = [vp, ci, ci, ci, vp, vp, ci, ci, ci, vp, vp, vp, vp, sz, vp]
         L.s3_sae_encode_topk_stream_workspace.argtypes = [ci, ci]
         L.s3_sae_encode_topk_stream_workspace.restype = sz
@@ -132,8 +136,11 @@ def sae_encode_topk(x, w_enc, b_enc, k: int, ids=None, vals=None):
         vals = torch.empty((n_heads, T, k), dtype=torch.float32, device=x.device)
     assert ids.is_contiguous() and vals.is_contiguous() and ids.dtype == torch.int32 and vals.dtype == torch.float32
     assert ids.numel() == n_heads * T * k and vals.numel() == n_heads * T * k
-    _check(lib().s3_sae_encode_topk(_ptr(x), _dtype_code(x), T, d, _ptr(w_enc), _ptr(b_enc), n_feat, k, n_heads,
-                                    _ptr(ids), _ptr(vals), _stream()))
+    dt = _dtype_code(x)
+    need = int(lib().s3_sae_encode_topk_workspace(dt, T, d, n_feat, k, n_heads))
+    ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need else None     # the caching allocator's, stream-ordered
+    _check(lib().s3_sae_encode_topk_ws(_ptr(x), dt, T, d, _ptr(w_enc), _ptr(b_enc), n_feat, k, n_heads,
+                                       _ptr(ids), _ptr(vals), _ptr(ws), need, _stream()))
     return ids, vals
 
 

@@ -1,367 +1,345 @@
-// Fused SAE encoder + Top-k for gfx950 (Sec. 3.3: encoder equation and Top-K equation).
+// Fused SAE encoder + Top-k for gfx950 (Sec. 3.3: encoder equation and Top-K equation), the tiled kernel: fp32 or bf16,
+// d_head 64, 128 or 256, any n_feat, any number of tokens.
 //
-// One workgroup = 4 wavefronts = 128 tokens of one (layer, head).  A wavefront keeps its 32
-// tokens' vectors in registers as the MFMA B operand for the whole kernel and walks over the
-// SAE features in tiles of 32 (the MFMA A operand, staged once per workgroup through LDS,
-// double-buffered).  With features on the M axis of the 32x32 MFMA, all 16 accumulators of a
-// lane belong to ONE token (column) and 16 different features, so the Top-k state is per lane:
+// One workgroup = 8 wavefronts = 32 tokens of one (layer, head) against one range of the SAE's features.  Features lie on
+// the M axis of the 32x32 MFMA; the 32 tokens' vectors stay in registers as the B operand.  Per chunk of 256 features:
 //
-//   - the accumulator is initialised with b_enc (bias costs nothing in the epilogue);
-//   - a running threshold tau per token (a certified lower bound on its k-th largest
-//     pre-activation so far); an accumulator survives only if z > tau (one compare);
-//   - survivors are appended to a small per-token candidate list in LDS (value fp32 + feature id
-//     u16); the two lanes that share a token push from the two ends of the same list;
-//   - when a list may overflow, the wavefront tightens tau for all its tokens by bisection on
-//     the value (count candidates >= mid across the two lanes) and compacts the lists;
-//   - after the last tile the lists are reduced to exactly k entries (ties: lower feature id)
-//     and written in (z descending, id ascending) order with ReLU applied.
+//   - every wavefront multiplies 32 features of its own: its W rows are fetched coalesced into registers one piece (256
+//     bytes of each row) ahead, written to an 8 KB LDS buffer that no other wavefront touches (xor-swizzled, so writes and
+//     fragment reads are conflict-free) and read back as fragments: no barrier inside the product;
+//   - the 256 x 32 pre-activations meet in an LDS tile (double-buffered where the lists leave room: one barrier a chunk);
+//   - every wavefront selects for 4 of the tokens: one 16-byte read brings a token's 256 values into its 64 lanes, one
+//     compare with the token's threshold finds the few that count, and those go to the token's list (topk_wave.h).
 //
-// The dense pre-activations never leave registers.  Selection is exact: every element that is
-// dropped is smaller than k candidates that are kept (or ties one with a lower id).
+// A token's list, count and threshold belong to one wavefront, so nothing is shared and the search for a new threshold is
+// steered by scalars.  (A kernel that kept the list in the two lanes that share a token and searched it through LDS took
+// 7 us per 32-feature step at d_head 128 or 256: 948 us for 2048 fp32 tokens x 4096 features, k = 16, and 2181 us for
+// 8 x 777 bf16 tokens x 10001 features of width 256, k = 48.)
+//
+// A call with few tokens splits the features over several workgroups (`parts`), which leave their Top-k of a range in
+// scratch; enc_merge_kernel selects from those.  Selection is exact everywhere.
 #include "s3_common.h"
+#include "topk_wave.h"
 
 #include <math.h>
 #include <stdlib.h>
 
+#include <type_traits>
+
 namespace {
+
+using namespace s3topk;
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-constexpr int kThreads = 256;
-constexpr int kWaves = 4;
-constexpr int kTokWave = 32;
-constexpr int kTokWG = kWaves * kTokWave;
-constexpr int kFT = 32;           // features per tile (MFMA M)
-constexpr int kHeadroom = 32;     // free list slots required at the start of a tile (16 per lane)
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * 64;
+constexpr int kTok = 32;                    // tokens per workgroup (MFMA N)
+constexpr int kFT = 32;                     // features per wavefront and chunk (MFMA M)
+constexpr int kChunk = kWaves * kFT;        // features per chunk
+constexpr int kZRow = kChunk + 4;           // floats per token in the tile (16-byte writes of 16 tokens hit 64 banks)
+constexpr int kTokWave = kTok / kWaves;     // tokens a wavefront selects for
 
-__device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-    return v;
-}
-
-// Candidate list of one token: `capt` slots, slot s of token n lives at element s * 32 + n.
-// The low lane of the token (half 0) fills slots 0, 1, ...; the high lane fills capt-1, capt-2, ...
-struct Cand {
-    float* cv;
-    uint16_t* ci;
-    int base, step;   // element index of this lane's entry i is base + i * step
-};
-
-__device__ __forceinline__ int count_ge(const Cand& c, int cnt, int maxc, float m) {
-    int local = 0;
-    for (int i = 0; i < maxc; ++i) {
-        float v = (i < cnt) ? c.cv[c.base + i * c.step] : -INFINITY;
-        local += (i < cnt && v >= m) ? 1 : 0;
-    }
-    return local + __shfl_xor(local, 32);
-}
-
-// Tighten tau and compact.  After the call every token that had >= k candidates holds between
-// k and `target` of them (exactly k when target == k), all >= the new tau, and every dropped
-// candidate is beaten by k kept ones.
-__device__ void refresh(const Cand& c, int k, int target, int& cnt, float& tau) {
-    const int maxc = wave_max_i(cnt);
-    const int total = cnt + __shfl_xor(cnt, 32);
-    const bool active = total >= k;
-
-    float mn = INFINITY, mx = -INFINITY;
-    for (int i = 0; i < maxc; ++i) {
-        if (i < cnt) {
-            float v = c.cv[c.base + i * c.step];
-            mn = fminf(mn, v);
-            mx = fmaxf(mx, v);
-        }
-    }
-    mn = fminf(mn, __shfl_xor(mn, 32));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-
-    // invariant: count(v >= lo) = clo >= k; count(v >= hi) < k or hi == lo
-    float lo = mn, hi = mx;
-    int clo = total;
-    bool done = !active || clo <= target;
-    bool split_failed = false;
-    {
-        int cm = count_ge(c, cnt, maxc, mx);
-        if (!done && cm >= k) { lo = mx; clo = cm; done = true; split_failed = true; }   // the k best all equal the maximum
-    }
-    while (__any(!done)) {
-        float mid = 0.5f * lo + 0.5f * hi;
-        bool can = (mid > lo) && (mid < hi);
-        int cm = count_ge(c, cnt, maxc, mid);
-        if (!done) {
-            if (!can) { done = true; split_failed = true; }
-            else if (cm >= k) { lo = mid; clo = cm; if (clo <= target) done = true; }
-            else hi = mid;
-        }
-    }
-    // Ties: lo and hi are neighbouring floats, so every candidate in [lo, hi) equals lo.  Keep
-    // only the `need` tied candidates with the lowest feature ids (bisection on the id).
-    bool tie = active && split_failed && clo > target;
-    int idcut = 0xFFFF;
-    if (__any(tie)) {
-        int cgt = 0;
-        for (int i = 0; i < maxc; ++i) {
-            float v = (i < cnt) ? c.cv[c.base + i * c.step] : -INFINITY;
-            cgt += (i < cnt && v > lo) ? 1 : 0;
-        }
-        cgt += __shfl_xor(cgt, 32);
-        const int need = k - cgt;
-        int ilo = -1, ihi = 0xFFFF;                 // count(id <= ilo) < need <= count(id <= ihi)
-        for (int it = 0; it < 16; ++it) {
-            int mid = (ilo + ihi) >> 1;
-            int ce = 0;
-            for (int i = 0; i < maxc; ++i) {
-                if (i < cnt) {
-                    float v = c.cv[c.base + i * c.step];
-                    int id = c.ci[c.base + i * c.step];
-                    ce += (v == lo && id <= mid) ? 1 : 0;
-                }
-            }
-            ce += __shfl_xor(ce, 32);
-            if (ce >= need) ihi = mid; else ilo = mid;
-        }
-        idcut = ihi;
-    }
-    int jw = 0;
-    for (int i = 0; i < maxc; ++i) {
-        if (i < cnt) {
-            float v = c.cv[c.base + i * c.step];
-            uint16_t id = c.ci[c.base + i * c.step];
-            bool keep = (v > lo) || (v == lo && (!tie || (int)id <= idcut));
-            if (keep) {
-                c.cv[c.base + jw * c.step] = v;
-                c.ci[c.base + jw * c.step] = id;
-                ++jw;
-            }
-        }
-    }
-    cnt = jw;
-    if (active) tau = lo;
-}
-
+// The MFMA operands of one element type.  The B fragments of the 32 tokens are held whole; a row of W is worked off in
+// pieces of up to 256 bytes.  offset(p, c): byte offset inside the row of 16-byte column c of piece p.
 template <int DT, int DH>
 struct Frag;
 
-// bf16: 32x32x16 MFMA, K step s covers stored columns [16 s, 16 s + 16); lane half h owns 8 of them.
+// bf16: 32x32x16 MFMA, K step s covers columns [16 s, 16 s + 16); lane half h owns 8 of them.
 template <int DH>
 struct Frag<S3_BF16, DH> {
-    static constexpr int ES = 2;
+    static constexpr int RB = DH * 2;
+    static constexpr int PB = RB < 256 ? RB : 256;
+    static constexpr int NP = RB / PB;
     static constexpr int NS = DH / 16;
     bf16x8 b[NS];
     __device__ __forceinline__ void load_b(const char* row, bool ok, int half) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            uint4 u = ok ? *(const uint4*)(row + (16 * s + 8 * half) * ES) : make_uint4(0, 0, 0, 0);
+            uint4 u = ok ? *(const uint4*)(row + (16 * s + 8 * half) * 2) : make_uint4(0, 0, 0, 0);
             b[s] = __builtin_bit_cast(bf16x8, u);
         }
     }
-    __device__ __forceinline__ void mma(const char* arow, int half, f32x16& acc) const {
+    static __device__ __forceinline__ int offset(int p, int c) { return p * PB + c * 16; }
+    template <int P>
+    __device__ __forceinline__ void mma(const char* arow, int sw, int half, f32x16& acc) const {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            uint4 u = *(const uint4*)(arow + (16 * s + 8 * half) * ES);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, u), b[s], acc, 0, 0, 0);
+        for (int s = 0; s < NS / NP; ++s) {
+            uint4 u = *(const uint4*)(arow + (((2 * s + half) ^ sw) << 4));
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, u), b[P * (NS / NP) + s], acc, 0, 0, 0);
         }
     }
 };
 
-// fp32: 32x32x2 MFMA, lane half h owns stored columns [h DH/2, (h+1) DH/2); step s uses column h DH/2 + s.
+// fp32: 32x32x2 MFMA, lane half h owns columns [h DH/2, (h+1) DH/2); step s uses column h DH/2 + s.  Piece p holds 128
+// bytes of either half.
 template <int DH>
 struct Frag<S3_FP32, DH> {
-    static constexpr int ES = 4;
+    static constexpr int RB = DH * 4;
+    static constexpr int PB = 256;
+    static constexpr int NP = RB / PB;
     static constexpr int NS = DH / 2;
     float b[NS];
     __device__ __forceinline__ void load_b(const char* row, bool ok, int half) {
 #pragma unroll
         for (int s = 0; s < NS; s += 4) {
-            f32x4 u = ok ? *(const f32x4*)(row + (half * NS + s) * ES) : f32x4{0, 0, 0, 0};
+            f32x4 u = ok ? *(const f32x4*)(row + (half * NS + s) * 4) : f32x4{0, 0, 0, 0};
             b[s] = u[0]; b[s + 1] = u[1]; b[s + 2] = u[2]; b[s + 3] = u[3];
         }
     }
-    __device__ __forceinline__ void mma(const char* arow, int half, f32x16& acc) const {
+    static __device__ __forceinline__ int offset(int p, int c) { return (c >> 3) * (RB / 2) + p * 128 + (c & 7) * 16; }
+    template <int P>
+    __device__ __forceinline__ void mma(const char* arow, int sw, int half, f32x16& acc) const {
 #pragma unroll
-        for (int s = 0; s < NS; s += 4) {
-            f32x4 u = *(const f32x4*)(arow + (half * NS + s) * ES);
+        for (int s = 0; s < 32; s += 4) {
+            f32x4 u = *(const f32x4*)(arow + (((half * 8 + s / 4) ^ sw) << 4));
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u[e], b[s + e], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u[e], b[P * 32 + s + e], acc, 0, 0, 0);
         }
     }
 };
 
-template <int DT, int DH>
-__global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(EncParams p) {
+struct TileArgs {
+    const char* x;
+    const char* w;
+    const float* b;
+    int32_t* ids;
+    float* vals;
+    uint2* part;             // [n_heads * T][parts][k] (key, id), key 0 = none; null when parts == 1
+    int T, n_feat, k, loose;
+    int tiles_per_head;      // token tiles of a head
+    int parts, range;        // feature ranges per head; features per range (a multiple of kChunk)
+    int n_groups;            // n_heads * parts
+};
+
+template <int DT, int DH, int LR>
+constexpr int tile_buffers() { return LR == 2 ? 2 : 1; }       // pre-activation tiles: two fit beside lists of 128
+template <int DT, int DH, int LR>
+constexpr size_t tile_lds() {
+    return (size_t)kWaves * kFT * Frag<DT, DH>::PB + (size_t)tile_buffers<DT, DH, LR>() * kTok * kZRow * 4 + kWaves * kFT * 4 +
+           (size_t)kTok * LR * 64 * 6 + kTok * 8;
+}
+
+template <int DT, int DH, int LR>
+__global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
     using F = Frag<DT, DH>;
-    constexpr int ES = F::ES;
-    constexpr int RB = DH * ES;            // bytes of one W row
-    constexpr int ROWB = RB + 16;          // padded LDS row (conflict-free 16-byte reads)
-    constexpr int VR = RB / 16;            // 16-byte vectors per row
-    constexpr int NV = (kFT * VR + kThreads - 1) / kThreads;
+    constexpr int CPR = F::PB / 16;                   // 16-byte columns per piece row
+    constexpr int RPI = 64 / CPR;                     // rows per load instruction
+    constexpr int NV = kFT / RPI;
+    constexpr int ZB = tile_buffers<DT, DH, LR>();
+    constexpr int CAP = 64 * LR;
+    static_assert(tile_lds<DT, DH, LR>() <= 160 * 1024, "LDS budget of one compute unit");
 
     extern __shared__ __align__(16) char smem[];
-    char* wst = smem;                                              // [2][kFT][ROWB]
-    float* bst = (float*)(smem + 2 * kFT * ROWB);                  // [2][kFT]
-    float* cval_all = bst + 2 * kFT;                               // [kWaves][capt][32]
-    uint16_t* cid_all = (uint16_t*)(cval_all + kWaves * p.capt * 32);
-
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, half = lane >> 5;
-    int head, tt;
-    s3_block_to_tile(blockIdx.x, p.n_heads, p.tiles_per_head, head, tt);
-    const int tok = tt * kTokWG + wv * kTokWave + n;
-    const bool tok_ok = tok < p.T;
+    char* const wbuf = smem + wv * kFT * F::PB;
+    float* const z = (float*)(smem + kWaves * kFT * F::PB);                     // [ZB][kTok][kZRow]
+    float* const bias = z + ZB * kTok * kZRow + wv * kFT;
+    unsigned* const lkey = (unsigned*)(z + ZB * kTok * kZRow + kWaves * kFT);   // [kTok][CAP]
+    int* const lcnt = (int*)(lkey + kTok * CAP);                                // [kTok]
+    unsigned* const lthr = (unsigned*)(lcnt + kTok);                            // [kTok]
+    uint16_t* const lid = (uint16_t*)(lthr + kTok);                             // [kTok][CAP]
 
-    const char* xh = p.x + (size_t)head * p.T * RB;
-    const char* wh = p.w + (size_t)head * p.n_feat * RB;
-    const float* bh = p.b + (size_t)head * p.n_feat;
+    int group, tt;
+    s3_block_to_tile(blockIdx.x, a.n_groups, a.tiles_per_head, group, tt);
+    const int head = group / a.parts, part = group - head * a.parts;
+    const int fbeg = part * a.range, fend = min(fbeg + a.range, a.n_feat);
+    const int nchunk = (fend - fbeg + kChunk - 1) / kChunk;
+    const int tok0 = tt * kTok;
 
     F frag;
-    frag.load_b(xh + (size_t)(tok_ok ? tok : 0) * RB, tok_ok, half);
+    {
+        const bool ok = tok0 + n < a.T;
+        frag.load_b(a.x + ((size_t)head * a.T + (ok ? tok0 + n : 0)) * F::RB, ok, half);
+    }
+    if (lane < kTokWave) {
+        lcnt[wv * kTokWave + lane] = 0;
+        lthr[wv * kTokWave + lane] = 0u;
+    }
+    wave_fence();
 
-    Cand c;
-    c.cv = cval_all + wv * p.capt * 32;
-    c.ci = cid_all + wv * p.capt * 32;
-    c.base = half ? (p.capt - 1) * 32 + n : n;
-    c.step = half ? -32 : 32;
-    int cnt = 0;
-    float tau = p.ablate ? INFINITY : -INFINITY;
-    const int k = p.k;
-    const int loose = min(k + (k >> 3) + 2, p.capt - p.headroom);
-
-    const int ntiles = (p.n_feat + kFT - 1) / kFT;
+    const char* const wh = a.w + (size_t)head * a.n_feat * F::RB;
+    const float* const bh = a.b + (size_t)head * a.n_feat;
+    const int lrow = lane / CPR, lcol = lane % CPR;
     uint4 wreg[NV];
     float breg = 0.f;
-
-    auto gload = [&](int j) {
-        const int f0 = j * kFT;
+    auto gload = [&](int chunk, int p) {
+        const int f0 = fbeg + chunk * kChunk + wv * kFT;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            int v = tid + i * kThreads;
-            int row = v / VR, col = v - row * VR;
-            bool ok = (v < kFT * VR) && (f0 + row < p.n_feat);
-            wreg[i] = ok ? *(const uint4*)(wh + (size_t)(f0 + row) * RB + col * 16) : make_uint4(0, 0, 0, 0);
+            const int f = f0 + i * RPI + lrow;
+            wreg[i] = f < fend ? *(const uint4*)(wh + (size_t)f * F::RB + F::offset(p, lcol)) : make_uint4(0, 0, 0, 0);
         }
-        if (tid < kFT) breg = (f0 + tid < p.n_feat) ? bh[f0 + tid] : -INFINITY;
+        if (p == 0) breg = f0 + n < fend ? bh[f0 + n] : -INFINITY;
     };
-    auto sstore = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            int v = tid + i * kThreads;
-            int row = v / VR, col = v - row * VR;
-            if (v < kFT * VR) *(uint4*)(wst + (buf * kFT + row) * ROWB + col * 16) = wreg[i];
-        }
-        if (tid < kFT) bst[buf * kFT + tid] = breg;
-    };
+    gload(0, 0);
 
-    gload(0);
-    sstore(0);
-    __syncthreads();
-
-    for (int j = 0; j < ntiles; ++j) {
-        const int cur = j & 1;
-        if (j + 1 < ntiles) gload(j + 1);
-
-        {   // make room: worst case every accumulator of the tile (headroom 32) or of its first half (headroom 16,
-            // used for k > 64 where LDS is short) is appended: 16 or 8 per lane, two lanes per token
-            int used = cnt + __shfl_xor(cnt, 32);
-            if (__any(used > p.capt - p.headroom)) refresh(c, k, loose, cnt, tau);
-        }
-
+    for (int c = 0; c < nchunk; ++c) {
+        float* const zt = z + (ZB == 2 ? (c & 1) * kTok * kZRow : 0);
         f32x16 acc;
-        {
-            const float* bs = bst + cur * kFT + half * 4;
+        auto piece = [&](auto P) {
+            constexpr int p = decltype(P)::value;
+            wave_fence();
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                f32x4 bq = *(const f32x4*)(bs + q * 8);
-                acc[q * 4 + 0] = bq[0]; acc[q * 4 + 1] = bq[1]; acc[q * 4 + 2] = bq[2]; acc[q * 4 + 3] = bq[3];
+            for (int i = 0; i < NV; ++i) {
+                const int row = i * RPI + lrow;
+                *(uint4*)(wbuf + row * F::PB + ((lcol ^ (row & (CPR - 1))) << 4)) = wreg[i];
             }
-        }
-        frag.mma(wst + (cur * kFT + n) * ROWB, half, acc);
-
-        const int fb = j * kFT + half * 4;
-        int wp = c.base + cnt * c.step;
+            if (p == 0 && half == 0) bias[n] = breg;
+            if (p + 1 < F::NP) gload(c, p + 1);
+            else if (c + 1 < nchunk) gload(c + 1, 0);
+            wave_fence();
+            if (p == 0) {
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            float v = acc[r];
-            if (v > tau) {
-                c.cv[wp] = v;
-                c.ci[wp] = (uint16_t)(fb + (r >> 2) * 8 + (r & 3));
-                wp += c.step;
-                ++cnt;
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 bq = *(const f32x4*)(bias + q * 8 + half * 4);
+                    acc[q * 4 + 0] = bq[0]; acc[q * 4 + 1] = bq[1]; acc[q * 4 + 2] = bq[2]; acc[q * 4 + 3] = bq[3];
+                }
             }
-        }
-        {   // room for the second half (never short when the tile started with 32 free slots)
-            int used = cnt + __shfl_xor(cnt, 32);
-            if (__any(used > p.capt - 16)) {
-                refresh(c, k, loose, cnt, tau);
-                wp = c.base + cnt * c.step;
-            }
-        }
+            frag.template mma<p>(wbuf + n * F::PB, n & (CPR - 1), half, acc);
+        };
+        piece(std::integral_constant<int, 0>{});
+        if constexpr (F::NP > 1) piece(std::integral_constant<int, 1>{});
+        if constexpr (F::NP > 2) { piece(std::integral_constant<int, 2>{}); piece(std::integral_constant<int, 3>{}); }
+        if (ZB == 1 && c) __syncthreads();             // the last chunk's selection reads the same tile
 #pragma unroll
-        for (int r = 8; r < 16; ++r) {
-            float v = acc[r];
-            if (v > tau) {
-                c.cv[wp] = v;
-                c.ci[wp] = (uint16_t)(fb + (r >> 2) * 8 + (r & 3));
-                wp += c.step;
-                ++cnt;
-            }
-        }
-
-        if (j + 1 < ntiles) sstore(cur ^ 1);
+        for (int q = 0; q < 4; ++q)
+            *(f32x4*)(zt + n * kZRow + wv * kFT + q * 8 + half * 4) =
+                f32x4{acc[q * 4 + 0], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
         __syncthreads();
+
+        const int f = fbeg + c * kChunk + 4 * lane;
+#pragma unroll 1
+        for (int q = 0; q < kTokWave; ++q) {
+            const int t = wv * kTokWave + q;
+            if (tok0 + t >= a.T) break;
+            const f32x4 v = *(const f32x4*)(zt + t * kZRow + 4 * lane);
+            unsigned thr = (unsigned)__builtin_amdgcn_readfirstlane((int)lthr[t]);
+            const float tf = value_of(thr);
+            const bool all = thr == 0;                 // no threshold yet: every element of the range counts
+            unsigned ck[4], cid[4];
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool hit = (all || v[j] > tf) && f + j < fend;
+                any |= hit;
+                ck[j] = hit ? key_of(v[j]) : 0u;
+                cid[j] = (unsigned)(f + j);
+            }
+            if (!__any(any)) continue;
+            int cnt = __builtin_amdgcn_readfirstlane(lcnt[t]);
+            const unsigned before = thr;
+            take<4, LR>(ck, cid, a.k, a.loose, lkey + t * CAP, lid + t * CAP, cnt, thr);
+            if (lane == 0) {
+                lcnt[t] = cnt;
+                if (thr != before) lthr[t] = thr;
+            }
+            wave_fence();
+        }
     }
 
-    // exactly k per token, then rank them: one candidate per lane, rank = number of candidates that beat it
-    refresh(c, k, k, cnt, tau);
-    int32_t* ids_h = p.ids + (size_t)head * p.T * k;
-    float* vals_h = p.vals + (size_t)head * p.T * k;
-    const int tok0 = tt * kTokWG + wv * kTokWave;
-    for (int nn = 0; nn < kTokWave; ++nn) {
-        if (tok0 + nn >= p.T) break;
-        const int clo = __builtin_amdgcn_readfirstlane(__shfl(cnt, nn));
-        const int chi = __builtin_amdgcn_readfirstlane(__shfl(cnt, nn + 32));
-        for (int c0 = 0; c0 < clo + chi; c0 += 64) {         // one candidate per lane, 64 at a time (k may exceed 64)
-            const int ci = c0 + lane;
-            const bool mine = ci < clo + chi;
-            const int slot = ci < clo ? ci : p.capt - 1 - (ci - clo);
-            float v = mine ? c.cv[slot * 32 + nn] : -INFINITY;
-            int id = mine ? (int)c.ci[slot * 32 + nn] : 0x7FFFFFFF;
-            int rank = 0;
-            for (int q = 0; q < clo; ++q) {
-                float vq = c.cv[q * 32 + nn];
-                int iq = c.ci[q * 32 + nn];
-                rank += (vq > v || (vq == v && iq < id)) ? 1 : 0;
-            }
-            for (int q = 0; q < chi; ++q) {
-                float vq = c.cv[(p.capt - 1 - q) * 32 + nn];
-                int iq = c.ci[(p.capt - 1 - q) * 32 + nn];
-                rank += (vq > v || (vq == v && iq < id)) ? 1 : 0;
-            }
-            if (mine && rank < k) {
-                size_t o = (size_t)(tok0 + nn) * k + rank;
-                ids_h[o] = id;
-                vals_h[o] = fmaxf(v, 0.f);
-            }
+#pragma unroll 1
+    for (int q = 0; q < kTokWave; ++q) {
+        const int t = wv * kTokWave + q;
+        if (tok0 + t >= a.T) break;
+        const int cnt = __builtin_amdgcn_readfirstlane(lcnt[t]);
+        const unsigned thr = (unsigned)__builtin_amdgcn_readfirstlane((int)lthr[t]);
+        unsigned key[LR], id[LR];
+        int rank[LR];
+        finish<LR>(a.k, lkey + t * CAP, lid + t * CAP, cnt, thr, key, id, rank);
+        const size_t row = (size_t)head * a.T + tok0 + t;
+        if (a.part) {
+            uint2* const out = a.part + (row * a.parts + part) * a.k;
+#pragma unroll
+            for (int i = 0; i < LR; ++i) if (rank[i] >= 0) out[rank[i]] = make_uint2(key[i], id[i]);
+            for (int e = cnt + lane; e < a.k; e += 64) out[e] = make_uint2(0u, 0u);        // a range of fewer than k features
+        } else {
+#pragma unroll
+            for (int i = 0; i < LR; ++i)
+                if (rank[i] >= 0) {
+                    a.ids[row * a.k + rank[i]] = (int32_t)id[i];
+                    a.vals[row * a.k + rank[i]] = fmaxf(value_of(key[i]), 0.f);
+                }
         }
     }
 }
 
-template <int DT, int DH>
-int launch(const EncParams& p, int n_heads, hipStream_t st) {
-    using F = Frag<DT, DH>;
-    constexpr int ROWB = DH * F::ES + 16;
-    size_t lds = 2 * kFT * ROWB + 2 * kFT * sizeof(float) + (size_t)kWaves * p.capt * 32 * (sizeof(float) + sizeof(uint16_t));
-    auto kern = sae_encode_topk_kernel<DT, DH>;
-    static S3LdsOnce once;             // per instantiation: allow the full 160 KB of LDS
-    if (int rc = s3_allow_lds(once, (const void*)kern, 160 * 1024)) return rc;
-    if (lds > 160 * 1024) return s3_fail(S3_EINVAL, "s3_sae_encode_topk: candidate lists need %zu bytes of LDS", lds);
-    dim3 grid((unsigned)(n_heads * p.tiles_per_head));
-    hipLaunchKernelGGL(kern, grid, dim3(kThreads), lds, st, p);
+// Selects every token's k best from its ranges' lists (each sorted, ids ascending from range to range): one wavefront per
+// token, 256 elements at a time.
+template <int LR>
+__global__ __launch_bounds__(256) void enc_merge_kernel(const uint2* __restrict__ part, long long rows, int parts, int k, int loose,
+                                                        int32_t* __restrict__ ids, float* __restrict__ vals) {
+    __shared__ unsigned lkey[4][64 * LR];
+    __shared__ uint16_t lid[4][64 * LR];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const long long row = (long long)blockIdx.x * 4 + wv;
+    if (row >= rows) return;
+    const int total = parts * k;
+    const uint2* const src = part + (size_t)row * total;
+    int cnt = 0;
+    unsigned thr = 0;
+    uint2 cur[4], nxt[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) cur[j] = j * 64 + lane < total ? src[j * 64 + lane] : make_uint2(0u, 0u);
+    for (int e0 = 0; e0 < total; e0 += 256) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = e0 + 256 + j * 64 + lane;
+            nxt[j] = e < total ? src[e] : make_uint2(0u, 0u);
+        }
+        unsigned ck[4], cid[4];
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            ck[j] = cur[j].x > thr ? cur[j].x : 0u;
+            cid[j] = cur[j].y;
+            any |= ck[j] != 0;
+        }
+        if (__any(any)) take<4, LR>(ck, cid, k, loose, lkey[wv], lid[wv], cnt, thr);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cur[j] = nxt[j];
+    }
+    unsigned key[LR], id[LR];
+    int rank[LR];
+    finish<LR>(k, lkey[wv], lid[wv], cnt, thr, key, id, rank);
+#pragma unroll
+    for (int i = 0; i < LR; ++i)
+        if (rank[i] >= 0) {
+            ids[(size_t)row * k + rank[i]] = (int32_t)id[i];
+            vals[(size_t)row * k + rank[i]] = fmaxf(value_of(key[i]), 0.f);
+        }
+}
+
+template <int DT, int DH, int LR>
+int launch(const TileArgs& a, hipStream_t st) {
+    constexpr size_t lds = tile_lds<DT, DH, LR>();
+    auto kern = sae_encode_topk_kernel<DT, DH, LR>;
+    static S3LdsOnce once;             // per instantiation
+    if (int rc = s3_allow_lds(once, (const void*)kern, (int)lds)) return rc;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.n_groups * a.tiles_per_head)), dim3(kThreads), lds, st, a);
     S3_HIP(hipGetLastError());
     return S3_OK;
+}
+
+// Feature ranges of a call: as many workgroups as fill the chip twice, whole chunks per range, a bounded number of list
+// entries in scratch.
+constexpr int kFillWGs = 512;
+constexpr long long kPartEntries = 4LL << 20;
+int parts_for(int n_heads, int T, int n_feat, int k) {
+    const long long tiles = (long long)n_heads * ((T + kTok - 1) / kTok);
+    const int chunks = (n_feat + kChunk - 1) / kChunk;
+    const long long rows = (long long)n_heads * T;
+    long long want = (kFillWGs + tiles - 1) / tiles;
+    want = want > chunks ? chunks : want;
+    while (want > 1 && rows * want * k > kPartEntries) --want;
+    if (want <= 1) return 1;
+    const int per = (int)((chunks + want - 1) / want);
+    return (chunks + per - 1) / per;
 }
 
 }  // namespace
@@ -372,6 +350,45 @@ int env_int(const char* name, int dflt) {
     return s && *s ? atoi(s) : dflt;
 }
 #endif
+
+// The k up to which a shape is accepted (stated in the header).
+static int largest_k(int dtype, int d_head) {
+    if (dtype == S3_BF16) return d_head == 256 ? 121 : S3_MAX_K;
+    return d_head == 64 ? S3_MAX_K : (d_head == 128 ? 121 : 78);
+}
+
+// The tiled kernel; `part` (parts_for() ranges' lists, or null: one range) is scratch.
+static int tiled_launch(const EncParams& p, int dtype, int d_head, int parts, uint2* part, hipStream_t st) {
+    TileArgs a;
+    a.x = p.x; a.w = p.w; a.b = p.b; a.ids = p.ids; a.vals = p.vals;
+    a.T = p.T; a.n_feat = p.n_feat; a.k = p.k;
+    a.loose = p.k + (p.k >> 3) + 2;
+    a.tiles_per_head = (p.T + kTok - 1) / kTok;
+    const int chunks = (p.n_feat + kChunk - 1) / kChunk;
+    a.parts = parts;
+    a.range = (chunks + parts - 1) / parts * kChunk;
+    a.n_groups = p.n_heads * parts;
+    a.part = parts > 1 ? part : nullptr;
+    int rc = S3_EINVAL;
+#define S3_CASE(DT, DH) \
+    if (dtype == DT && d_head == DH) rc = p.k <= 64 ? launch<DT, DH, 2>(a, st) : launch<DT, DH, 4>(a, st);
+    S3_CASE(S3_BF16, 64) S3_CASE(S3_BF16, 128) S3_CASE(S3_BF16, 256)
+    S3_CASE(S3_FP32, 64) S3_CASE(S3_FP32, 128) S3_CASE(S3_FP32, 256)
+#undef S3_CASE
+    if (rc || parts == 1) return rc;
+    const long long rows = (long long)p.n_heads * p.T;
+    auto merge = p.k <= 64 ? enc_merge_kernel<2> : enc_merge_kernel<4>;
+    hipLaunchKernelGGL(merge, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, (const uint2*)part, rows, parts, p.k, a.loose,
+                       p.ids, p.vals);
+    S3_HIP(hipGetLastError());
+    return S3_OK;
+}
+
+static size_t plain_workspace(int dtype, int T, int d_head, int n_feat, int k, int n_heads) {
+    if (s3_encode_fast_ok(dtype, d_head, n_feat, k)) return 0;
+    const int parts = parts_for(n_heads, T, n_feat, k);
+    return parts > 1 ? (size_t)n_heads * T * parts * k * sizeof(uint2) : 0;
+}
 
 static int encode_impl(const char* who, const void* x, int dtype, int T, int d_head, const void* w_enc, const float* b_enc,
                        int n_feat, int k, int n_heads, int32_t* ids, float* vals, float* tau_hint, void* ws,
@@ -384,10 +401,10 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
     if (n_feat < 1 || n_feat > S3_MAX_FEAT) return s3_fail(S3_EINVAL, "%s: n_feat %d not in [1, %d]", who, n_feat, S3_MAX_FEAT);
     if (k < 1 || k > n_feat || k > S3_MAX_K) return s3_fail(S3_EINVAL, "%s: k %d not in [1, min(n_feat, %d)]", who, k, S3_MAX_K);
     if (((uintptr_t)x | (uintptr_t)w_enc) & 15) return s3_fail(S3_EINVAL, "%s: x and w_enc must be 16-byte aligned", who);
-    if ((int64_t)n_heads * ((T + kTokWG - 1) / kTokWG) > 0x7FFFFFFFLL) return s3_fail(S3_EINVAL, "%s: grid too large", who);
+    if ((int64_t)n_heads * ((T + kTok - 1) / kTok) > 0x7FFFFFFFLL) return s3_fail(S3_EINVAL, "%s: grid too large", who);
+    if (ws && ((uintptr_t)ws & 255)) return s3_fail(S3_EINVAL, "%s: workspace must be 256-byte aligned", who);
     if (tau_hint) {
         if (!ws) return s3_fail(S3_EINVAL, "%s: null workspace", who);
-        if ((uintptr_t)ws & 255) return s3_fail(S3_EINVAL, "%s: workspace must be 256-byte aligned", who);
         const size_t need = s3_encode_fast_stream_workspace(n_heads, T);
         if (ws_bytes < need) return s3_fail(S3_ECAPACITY, "%s: workspace %zu < %zu bytes", who, ws_bytes, need);
     }
@@ -406,23 +423,11 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
     hipStream_t st = (hipStream_t)stream;
     if (fast)
         return tau_hint ? s3_encode_fast_stream(p, tau_hint, ws, st) : s3_encode_fast_launch(p, st);
-    p.tiles_per_head = (T + kTokWG - 1) / kTokWG;
-    // list capacity per token: k survivors + headroom for a run of appends + room for new candidates between refreshes;
-    // the headroom is a whole tile's worth (32) where that fits the LDS, else half a tile's (16, re-checked mid-tile)
-    const size_t fixed_lds = 2 * kFT * ((size_t)d_head * (dtype == S3_BF16 ? 2 : 4) + 16) + 2 * kFT * sizeof(float);
-    auto lists_fit = [&](int c) { return fixed_lds + (size_t)kWaves * c * 32 * 6 <= 160 * 1024; };
-    p.headroom = k <= 64 && lists_fit(k + kHeadroom + (k <= 32 ? 16 : 32)) ? kHeadroom : 16;
-    int capt = k + p.headroom + (k <= 32 ? 16 : 32);
-#ifdef S3_TUNING
-    capt = env_int("S3_ENC_CAPT", capt);
-    if (capt < k + p.headroom + 4 || capt > 512) return s3_fail(S3_EINVAL, "%s: bad S3_ENC_CAPT %d", who, capt);
-#endif
-    p.capt = capt;
-#define S3_CASE(DT, DH) if (dtype == DT && d_head == DH) return launch<DT, DH>(p, n_heads, st);
-    S3_CASE(S3_BF16, 64) S3_CASE(S3_BF16, 128) S3_CASE(S3_BF16, 256)
-    S3_CASE(S3_FP32, 64) S3_CASE(S3_FP32, 128) S3_CASE(S3_FP32, 256)
-#undef S3_CASE
-    return s3_fail(S3_EINVAL, "%s: unsupported configuration", who);
+    if (k > largest_k(dtype, d_head))
+        return s3_fail(S3_EINVAL, "%s: k %d > %d for this dtype and d_head", who, k, largest_k(dtype, d_head));
+    int parts = parts_for(n_heads, T, n_feat, k);
+    if (!ws || ws_bytes < (size_t)n_heads * T * parts * k * sizeof(uint2)) parts = 1;      // no scratch: one range
+    return tiled_launch(p, dtype, d_head, parts, (uint2*)ws, st);
 }
 
 extern "C" int s3_sae_encode_topk(const void* x, int dtype, int T, int d_head, const void* w_enc,
@@ -430,6 +435,18 @@ extern "C" int s3_sae_encode_topk(const void* x, int dtype, int T, int d_head, c
                                   float* vals, void* stream) {
     return encode_impl("s3_sae_encode_topk", x, dtype, T, d_head, w_enc, b_enc, n_feat, k, n_heads, ids, vals, nullptr,
                        nullptr, 0, stream);
+}
+
+extern "C" size_t s3_sae_encode_topk_workspace(int dtype, int T, int d_head, int n_feat, int k, int n_heads) {
+    if (n_heads < 1 || T < 1 || n_feat < 1 || k < 1 || k > S3_MAX_K) return 0;
+    return plain_workspace(dtype, T, d_head, n_feat, k, n_heads);
+}
+
+extern "C" int s3_sae_encode_topk_ws(const void* x, int dtype, int T, int d_head, const void* w_enc,
+                                     const float* b_enc, int n_feat, int k, int n_heads, int32_t* ids,
+                                     float* vals, void* ws, size_t ws_bytes, void* stream) {
+    return encode_impl("s3_sae_encode_topk_ws", x, dtype, T, d_head, w_enc, b_enc, n_feat, k, n_heads, ids, vals, nullptr,
+                       ws, ws_bytes, stream);
 }
 
 extern "C" size_t s3_sae_encode_topk_stream_workspace(int n_heads, int T) {

@@ -1,0 +1,187 @@
+// Exact Top-k of one token by one wavefront: a list of candidates in LDS that new elements are filtered into, cut to
+// (about) the k largest whenever it would overflow.  Shared by the tiled encoder and the merge of its feature ranges.
+//
+// Values travel as ordered keys (unsigned order = float order; 0 = no element).  -0 and +0 are one value, as in a float
+// compare; a NaN is below every number.  Elements arrive with ascending ids among equal values, so an element that only
+// equals the threshold of a list that holds k at or above it loses to all of those.
+//
+// Everything that steers the search (counts, thresholds) is uniform: a count is one compare per register whose mask is
+// counted by the scalar unit, so a bisection step over a 256-element list is 4 compares, 4 bit counts and 4 adds.
+#pragma once
+#include "s3_common.h"
+
+namespace s3topk {
+
+__device__ __forceinline__ unsigned key_of(float v) {
+    const unsigned u = __float_as_uint(v + 0.f);                   // -0 -> +0
+    const unsigned key = u ^ ((unsigned)((int)u >> 31) | 0x80000000u);
+    return v == v ? key : 1u;
+}
+__device__ __forceinline__ float value_of(unsigned key) {
+    return __uint_as_float(key ^ ((key >> 31) ? 0x80000000u : 0xFFFFFFFFu));
+}
+__device__ __forceinline__ int below(unsigned long long m) {       // set bits of m in lanes below this one
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+__device__ __forceinline__ unsigned wave_max_u(unsigned v) {
+#define S3_DPP_MAX(CTRL, ROWS) v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false))
+    S3_DPP_MAX(0x111, 0xf); S3_DPP_MAX(0x112, 0xf); S3_DPP_MAX(0x114, 0xf); S3_DPP_MAX(0x118, 0xf);
+    S3_DPP_MAX(0x142, 0xa); S3_DPP_MAX(0x143, 0xc);
+#undef S3_DPP_MAX
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ void wave_fence() {                     // LDS written by one lane is read by another one
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+template <int N>
+__device__ __forceinline__ int count_ge(const unsigned (&key)[N], unsigned m) {
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) c += (int)__popcll(__ballot(key[i] >= m));
+    return c;
+}
+
+// The largest threshold found with k <= count(key >= threshold) <= loose, starting from lo (count clo >= k).  Returns the
+// count; it exceeds `loose` only if more than loose - k elements equal the threshold.
+template <int N>
+__device__ __forceinline__ int raise(const unsigned (&key)[N], int k, int loose, unsigned& lo, int clo) {
+    if (clo <= loose) return clo;
+    unsigned mx = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) mx = max(mx, key[i]);
+    unsigned hi = wave_max_u(mx) + 1;                              // keys stay below 0xFF800001
+    while (clo > loose && hi - lo > 1) {
+        const unsigned mid = lo + (hi - lo) / 2;
+        const int c = count_ge(key, mid);
+        if (c >= k) { lo = mid; clo = c; } else hi = mid;
+    }
+    return clo;
+}
+
+// Cuts the N registers' elements to between k and `loose` (exactly k when loose == k) and stores them at lk / li[0 ..).
+// `lo`: in, a threshold with at least k elements at or above it (at least 1); out, the new one.  Returns the number kept.
+template <int N>
+__device__ __forceinline__ int cut_and_store(const unsigned (&key)[N], const unsigned (&id)[N], int k, int loose, unsigned& lo,
+                                             int clo, unsigned* lk, uint16_t* li) {
+    clo = raise(key, k, loose, lo, clo);
+    unsigned idcut = 0xFFFFu;
+    if (clo > loose) {                    // ties at the threshold: keep those with the lowest ids, k elements in all
+        const int need = k - count_ge(key, lo + 1);
+        int ilo = -1, ihi = 0xFFFF;       // count(tied, id <= ilo) < need <= count(tied, id <= ihi)
+        while (ihi - ilo > 1) {
+            const int mid = (ilo + ihi) >> 1;
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) c += (int)__popcll(__ballot(key[i] == lo && (int)id[i] <= mid));
+            if (c >= need) ihi = mid; else ilo = mid;
+        }
+        idcut = (unsigned)ihi;
+    }
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const bool keep = key[i] > lo || (key[i] == lo && id[i] <= idcut);
+        const unsigned long long m = __ballot(keep);
+        if (keep) {
+            const int at = n + below(m);
+            lk[at] = key[i];
+            li[at] = (uint16_t)id[i];
+        }
+        n += (int)__popcll(m);
+    }
+    wave_fence();
+    return n;
+}
+
+// Filters NC registers of new elements (key 0 = none; all above the list's threshold `thr`, or thr == 0: no threshold yet)
+// into a list of `cnt` with room for 64 * LR.
+template <int NC, int LR>
+__device__ __forceinline__ void take(const unsigned (&ck)[NC], const unsigned (&cid)[NC], int k, int loose, unsigned* lk,
+                                     uint16_t* li, int& cnt, unsigned& thr) {
+    unsigned long long m[NC];
+    int add = 0;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        m[i] = __ballot(ck[i] != 0);
+        add += (int)__popcll(m[i]);
+    }
+    if (cnt + add <= 64 * LR) {
+        int n = cnt;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            if (ck[i] != 0) {
+                const int at = n + below(m[i]);
+                lk[at] = ck[i];
+                li[at] = (uint16_t)cid[i];
+            }
+            n += (int)__popcll(m[i]);
+        }
+        cnt = n;
+        wave_fence();
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    unsigned key[NC + LR], id[NC + LR];
+#pragma unroll
+    for (int i = 0; i < LR; ++i) {
+        const int e = i * 64 + lane;
+        key[i] = e < cnt ? lk[e] : 0u;
+        id[i] = e < cnt ? (unsigned)li[e] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < NC; ++i) { key[LR + i] = ck[i]; id[LR + i] = cid[i]; }
+    // Every element is at or above max(thr, 1), and there are more than 64 * LR >= k of them.
+    unsigned lo = max(thr, 1u);
+    cnt = cut_and_store<NC + LR>(key, id, k, loose, lo, cnt + add, lk, li);
+    thr = lo;
+}
+
+// The list's k best (fewer if it holds fewer) in registers with their ranks (value descending, id ascending): element i of
+// lane l has rank rank[i], or -1.  Returns the key of the k-th best (0 if there are fewer than k).
+template <int LR>
+__device__ __forceinline__ unsigned finish(int k, unsigned* lk, uint16_t* li, int cnt, unsigned thr, unsigned (&key)[LR],
+                                           unsigned (&id)[LR], int (&rank)[LR]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < LR; ++i) {
+        const int e = i * 64 + lane;
+        key[i] = e < cnt ? lk[e] : 0u;
+        id[i] = e < cnt ? (unsigned)li[e] : 0u;
+    }
+    if (cnt > k) {
+        unsigned lo = max(thr, 1u);
+        wave_fence();
+        cnt = cut_and_store<LR>(key, id, k, k, lo, cnt, lk, li);
+#pragma unroll
+        for (int i = 0; i < LR; ++i) {
+            const int e = i * 64 + lane;
+            key[i] = e < cnt ? lk[e] : 0u;
+            id[i] = e < cnt ? (unsigned)li[e] : 0u;
+        }
+    }
+    unsigned long long mine[LR];
+    unsigned low = 0xFFFFFFFFu;
+#pragma unroll
+    for (int i = 0; i < LR; ++i) {
+        mine[i] = ((unsigned long long)key[i] << 32) | (0xFFFFFFFFu - id[i]);
+        rank[i] = 0;
+        if (key[i]) low = min(low, key[i]);
+    }
+#pragma unroll
+    for (int r = 0; r < LR; ++r) {
+        const int n = min(cnt - 64 * r, 64);
+        for (int s = 0; s < n; ++s) {
+            const unsigned ok = (unsigned)__builtin_amdgcn_readlane((int)key[r], s);
+            const unsigned oi = (unsigned)__builtin_amdgcn_readlane((int)id[r], s);
+            const unsigned long long other = ((unsigned long long)ok << 32) | (0xFFFFFFFFu - oi);
+#pragma unroll
+            for (int i = 0; i < LR; ++i) rank[i] += other > mine[i] ? 1 : 0;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < LR; ++i) if (!key[i]) rank[i] = -1;
+    return cnt < k ? 0u : 0xFFFFFFFFu - wave_max_u(0xFFFFFFFFu - low);
+}
+
+}  // namespace s3topk

@@ -1,0 +1,68 @@
+"""The tiled encoder (every shape outside the streamed bf16 / d_head 128 kernel): edges of its 32-token tiles, 256-feature
+chunks and feature ranges, against the fp64 oracle, and the split over workgroups against the unsplit call bit for bit."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2601_17702_amd import synth
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def unsplit(s3, x, W, b, k):
+    """The call without scratch: one workgroup walks all features of its tokens."""
+    import torch
+    heads, T, d = x.shape
+    ids = torch.full((heads, T, k), -7, dtype=torch.int32, device="cuda")
+    vals = torch.full((heads, T, k), -7.0, device="cuda")
+    p = lambda t: C.c_void_p(t.data_ptr())
+    s3._check(s3.lib().s3_sae_encode_topk(p(x), s3._dtype_code(x), T, d, p(W), p(b), W.shape[1], k, heads, p(ids), p(vals),
+                                          s3._stream()))
+    return ids, vals
+
+
+@pytest.mark.parametrize("dtype,d,heads,T,n_feat,k", [
+    ("bf16", 128, 3, 1, 257, 64),        # the last range holds one feature, fewer than k
+    ("bf16", 128, 1, 33, 20001, 61),     # many ranges, one token in the second tile
+    ("bf16", 64, 9, 31, 513, 65),        # lists of 256, heads beyond a multiple of 8
+    ("bf16", 256, 2, 64, 2303, 121),     # the largest k at width 256, ragged last chunk
+    ("fp32", 64, 2, 32, 4097, 128),
+    ("fp32", 128, 1, 95, 1000, 16),
+    ("fp32", 256, 5, 7, 1025, 78),
+    ("fp32", 256, 1, 700, 300, 1),
+])
+def test_split_and_unsplit_calls_match_the_oracle(dtype, d, heads, T, n_feat, k):
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(d + n_feat + k + T)
+    x = synth.to_storage(rng.standard_normal((heads, T, d)).astype(np.float32), dtype)
+    W = synth.to_storage((rng.standard_normal((heads, n_feat, d)) / np.sqrt(d)).astype(np.float32), dtype)
+    b = (0.1 * rng.standard_normal((heads, n_feat))).astype(np.float32)
+    xg, Wg, bg = parity.to_gpu(x, dtype), parity.to_gpu(W, dtype), parity.to_gpu(b, "fp32")
+    ids, vals = s3.sae_encode_topk(xg, Wg, bg, k)
+    ids1, vals1 = unsplit(s3, xg, Wg, bg, k)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, ids1) and torch.equal(vals, vals1)
+    parity.check_encode(ids.cpu().numpy(), vals.cpu().numpy(), x, W, b, k, dtype)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 256), ("fp32", 128)])
+@pytest.mark.parametrize("k", [5, 64, 78])
+def test_ties_across_chunks_and_ranges_take_the_lower_id(dtype, d, k):
+    """Few different feature vectors of small integers: exact sums, runs of equal values longer than the lists."""
+    import torch
+    import paper_2601_17702_amd as s3
+    from oracle import s3_oracle as orc
+    rng = np.random.default_rng(k + d)
+    n_feat, T = 1500, 37
+    base = rng.integers(-2, 3, (3, d)).astype(np.float32)
+    W = synth.to_storage(base[rng.integers(0, 3, n_feat)][None], dtype)
+    x = synth.to_storage(rng.integers(-2, 3, (1, T, d)).astype(np.float32), dtype)
+    b = np.zeros((1, n_feat), np.float32)
+    xg, Wg, bg = parity.to_gpu(x, dtype), parity.to_gpu(W, dtype), parity.to_gpu(b, "fp32")
+    o = orc.encode_topk(x[0], W[0], b[0], k, dtype)
+    for ids, vals in (s3.sae_encode_topk(xg, Wg, bg, k), unsplit(s3, xg, Wg, bg, k)):
+        torch.cuda.synchronize()
+        assert np.array_equal(ids[0].cpu().numpy(), o["ids"]) and np.array_equal(vals[0].cpu().numpy(), o["vals"])
