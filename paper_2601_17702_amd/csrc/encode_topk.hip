@@ -33,6 +33,7 @@ using namespace s3topk;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
@@ -65,11 +66,13 @@ struct Frag<S3_BF16, DH> {
     static __device__ __forceinline__ int offset(int p, int c) { return p * PB + c * 16; }
     template <int P>
     __device__ __forceinline__ void mma(const char* arow, int sw, int half, f32x16& acc) const {
+        u32x4 u[NS / NP];                      // all reads first: one LDS latency per piece
 #pragma unroll
-        for (int s = 0; s < NS / NP; ++s) {
-            uint4 u = *(const uint4*)(arow + (((2 * s + half) ^ sw) << 4));
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, u), b[P * (NS / NP) + s], acc, 0, 0, 0);
-        }
+        for (int s = 0; s < NS / NP; ++s) u[s] = *(const u32x4*)(arow + (((2 * s + half) ^ sw) << 4));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NS / NP; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, u[s]), b[P * (NS / NP) + s], acc, 0, 0, 0);
     }
 };
 
@@ -92,12 +95,17 @@ struct Frag<S3_FP32, DH> {
     static __device__ __forceinline__ int offset(int p, int c) { return (c >> 3) * (RB / 2) + p * 128 + (c & 7) * 16; }
     template <int P>
     __device__ __forceinline__ void mma(const char* arow, int sw, int half, f32x16& acc) const {
+        constexpr int kAhead = DH == 256 ? 2 : 4;      // fragments read ahead (d_head 256: few registers are left)
 #pragma unroll
-        for (int s = 0; s < 32; s += 4) {
-            f32x4 u = *(const f32x4*)(arow + (((half * 8 + s / 4) ^ sw) << 4));
+        for (int g = 0; g < 8; g += kAhead) {
+            f32x4 u[kAhead];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u[e], b[P * 32 + s + e], acc, 0, 0, 0);
+            for (int s = 0; s < kAhead; ++s) u[s] = *(const f32x4*)(arow + (((half * 8 + g + s) ^ sw) << 4));
+#pragma unroll
+            for (int s = 0; s < kAhead; ++s)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u[s][e], b[P * 32 + 4 * (g + s) + e], acc, 0, 0, 0);
         }
     }
 };
@@ -108,7 +116,7 @@ struct TileArgs {
     const float* b;
     int32_t* ids;
     float* vals;
-    uint2* part;             // [n_heads * T][parts][k] (key, id), key 0 = none; null when parts == 1
+    uint2* part;             // [n_heads * T][parts][k] (pre-activation, id), -inf = none; null when parts == 1
     int T, n_feat, k, loose;
     int tiles_per_head;      // token tiles of a head
     int parts, range;        // feature ranges per head; features per range (a multiple of kChunk)
@@ -120,7 +128,7 @@ constexpr int tile_buffers() { return LR == 2 ? 2 : 1; }       // pre-activation
 template <int DT, int DH, int LR>
 constexpr size_t tile_lds() {
     return (size_t)kWaves * kFT * Frag<DT, DH>::PB + (size_t)tile_buffers<DT, DH, LR>() * kTok * kZRow * 4 + kWaves * kFT * 4 +
-           (size_t)kTok * LR * 64 * 6 + kTok * 8;
+           (size_t)kTok * LR * 64 * 6;
 }
 
 template <int DT, int DH, int LR>
@@ -140,10 +148,8 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
     char* const wbuf = smem + wv * kFT * F::PB;
     float* const z = (float*)(smem + kWaves * kFT * F::PB);                     // [ZB][kTok][kZRow]
     float* const bias = z + ZB * kTok * kZRow + wv * kFT;
-    unsigned* const lkey = (unsigned*)(z + ZB * kTok * kZRow + kWaves * kFT);   // [kTok][CAP]
-    int* const lcnt = (int*)(lkey + kTok * CAP);                                // [kTok]
-    unsigned* const lthr = (unsigned*)(lcnt + kTok);                            // [kTok]
-    uint16_t* const lid = (uint16_t*)(lthr + kTok);                             // [kTok][CAP]
+    float* const lval = z + ZB * kTok * kZRow + kWaves * kFT;                   // [kTok][CAP]
+    uint16_t* const lid = (uint16_t*)(lval + kTok * CAP);                       // [kTok][CAP]
 
     int group, tt;
     s3_block_to_tile(blockIdx.x, a.n_groups, a.tiles_per_head, group, tt);
@@ -157,25 +163,27 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
         const bool ok = tok0 + n < a.T;
         frag.load_b(a.x + ((size_t)head * a.T + (ok ? tok0 + n : 0)) * F::RB, ok, half);
     }
-    if (lane < kTokWave) {
-        lcnt[wv * kTokWave + lane] = 0;
-        lthr[wv * kTokWave + lane] = 0u;
-    }
-    wave_fence();
+    int cnt[kTokWave] = {};
+    float tau[kTokWave];
+#pragma unroll
+    for (int q = 0; q < kTokWave; ++q) tau[q] = tok0 + wv * kTokWave + q < a.T ? -INFINITY : INFINITY;    // no token: nothing counts
 
     const char* const wh = a.w + (size_t)head * a.n_feat * F::RB;
     const float* const bh = a.b + (size_t)head * a.n_feat;
     const int lrow = lane / CPR, lcol = lane % CPR;
-    uint4 wreg[NV];
+    u32x4 wreg[NV];
     float breg = 0.f;
     auto gload = [&](int chunk, int p) {
         const int f0 = fbeg + chunk * kChunk + wv * kFT;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const int f = f0 + i * RPI + lrow;
-            wreg[i] = f < fend ? *(const uint4*)(wh + (size_t)f * F::RB + F::offset(p, lcol)) : make_uint4(0, 0, 0, 0);
+            const int f = min(f0 + i * RPI + lrow, fend - 1);      // rows past the end repeat the last one; their bias is -inf
+            wreg[i] = *(const u32x4*)(wh + (size_t)f * F::RB + F::offset(p, lcol));
         }
-        if (p == 0) breg = f0 + n < fend ? bh[f0 + n] : -INFINITY;
+        if (p == 0) {
+            breg = bh[min(f0 + n, fend - 1)];
+            breg = f0 + n < fend ? breg : -INFINITY;
+        }
     };
     gload(0, 0);
 
@@ -188,7 +196,7 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 const int row = i * RPI + lrow;
-                *(uint4*)(wbuf + row * F::PB + ((lcol ^ (row & (CPR - 1))) << 4)) = wreg[i];
+                *(u32x4*)(wbuf + row * F::PB + ((lcol ^ (row & (CPR - 1))) << 4)) = wreg[i];
             }
             if (p == 0 && half == 0) bias[n] = breg;
             if (p + 1 < F::NP) gload(c, p + 1);
@@ -213,51 +221,37 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
                 f32x4{acc[q * 4 + 0], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
         __syncthreads();
 
+        // A token's list, count and threshold are this wavefront's alone; the four tokens' reads are issued together.
         const int f = fbeg + c * kChunk + 4 * lane;
-#pragma unroll 1
-        for (int q = 0; q < kTokWave; ++q) {
-            const int t = wv * kTokWave + q;
-            if (tok0 + t >= a.T) break;
-            const f32x4 v = *(const f32x4*)(zt + t * kZRow + 4 * lane);
-            unsigned thr = (unsigned)__builtin_amdgcn_readfirstlane((int)lthr[t]);
-            const float tf = value_of(thr);
-            const bool all = thr == 0;                 // no threshold yet: every element of the range counts
-            unsigned ck[4], cid[4];
-            bool any = false;
+        f32x4 v[kTokWave];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool hit = (all || v[j] > tf) && f + j < fend;
-                any |= hit;
-                ck[j] = hit ? key_of(v[j]) : 0u;
-                cid[j] = (unsigned)(f + j);
-            }
-            if (!__any(any)) continue;
-            int cnt = __builtin_amdgcn_readfirstlane(lcnt[t]);
-            const unsigned before = thr;
-            take<4, LR>(ck, cid, a.k, a.loose, lkey + t * CAP, lid + t * CAP, cnt, thr);
-            if (lane == 0) {
-                lcnt[t] = cnt;
-                if (thr != before) lthr[t] = thr;
-            }
-            wave_fence();
+        for (int q = 0; q < kTokWave; ++q) v[q] = *(const f32x4*)(zt + (wv * kTokWave + q) * kZRow + 4 * lane);
+        unsigned long long hits[kTokWave];             // lanes with an element above the token's threshold
+#pragma unroll
+        for (int q = 0; q < kTokWave; ++q)
+            hits[q] = __ballot(fmaxf(fmaxf(v[q][0], v[q][1]), fmaxf(v[q][2], v[q][3])) > tau[q]);
+#pragma unroll
+        for (int q = 0; q < kTokWave; ++q) {
+            if (!hits[q]) continue;
+            const int t = wv * kTokWave + q;
+            const float e[4] = {v[q][0], v[q][1], v[q][2], v[q][3]};
+            take<4, LR>(e, [&](int j) { return f + j; }, a.k, a.loose, lval + t * CAP, lid + t * CAP, cnt[q], tau[q]);
         }
     }
 
-#pragma unroll 1
+#pragma unroll
     for (int q = 0; q < kTokWave; ++q) {
         const int t = wv * kTokWave + q;
         if (tok0 + t >= a.T) break;
-        const int cnt = __builtin_amdgcn_readfirstlane(lcnt[t]);
-        const unsigned thr = (unsigned)__builtin_amdgcn_readfirstlane((int)lthr[t]);
         unsigned key[LR], id[LR];
         int rank[LR];
-        finish<LR>(a.k, lkey + t * CAP, lid + t * CAP, cnt, thr, key, id, rank);
+        finish<LR>(a.k, lval + t * CAP, lid + t * CAP, cnt[q], key, id, rank);
         const size_t row = (size_t)head * a.T + tok0 + t;
         if (a.part) {
             uint2* const out = a.part + (row * a.parts + part) * a.k;
 #pragma unroll
-            for (int i = 0; i < LR; ++i) if (rank[i] >= 0) out[rank[i]] = make_uint2(key[i], id[i]);
-            for (int e = cnt + lane; e < a.k; e += 64) out[e] = make_uint2(0u, 0u);        // a range of fewer than k features
+            for (int i = 0; i < LR; ++i) if (rank[i] >= 0) out[rank[i]] = make_uint2(__float_as_uint(value_of(key[i])), id[i]);
+            for (int e = cnt[q] + lane; e < a.k; e += 64) out[e] = make_uint2(__float_as_uint(-INFINITY), 0u);        // a range of fewer than k features
         } else {
 #pragma unroll
             for (int i = 0; i < LR; ++i)
@@ -274,7 +268,7 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
 template <int LR>
 __global__ __launch_bounds__(256) void enc_merge_kernel(const uint2* __restrict__ part, long long rows, int parts, int k, int loose,
                                                         int32_t* __restrict__ ids, float* __restrict__ vals) {
-    __shared__ unsigned lkey[4][64 * LR];
+    __shared__ float lval[4][64 * LR];
     __shared__ uint16_t lid[4][64 * LR];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const long long row = (long long)blockIdx.x * 4 + wv;
@@ -282,31 +276,30 @@ __global__ __launch_bounds__(256) void enc_merge_kernel(const uint2* __restrict_
     const int total = parts * k;
     const uint2* const src = part + (size_t)row * total;
     int cnt = 0;
-    unsigned thr = 0;
+    float tau = -INFINITY;
     uint2 cur[4], nxt[4];
+    auto load = [&](uint2 (&to)[4], int e0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) cur[j] = j * 64 + lane < total ? src[j * 64 + lane] : make_uint2(0u, 0u);
+        for (int j = 0; j < 4; ++j) {
+            const int e = e0 + j * 64 + lane;
+            to[j] = src[min(e, total - 1)];
+            if (e >= total) to[j].x = __float_as_uint(-INFINITY);
+        }
+    };
+    load(cur, 0);
     for (int e0 = 0; e0 < total; e0 += 256) {
+        if (e0 + 256 < total) load(nxt, e0 + 256);
+        float v[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = e0 + 256 + j * 64 + lane;
-            nxt[j] = e < total ? src[e] : make_uint2(0u, 0u);
-        }
-        unsigned ck[4], cid[4];
-        bool any = false;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            ck[j] = cur[j].x > thr ? cur[j].x : 0u;
-            cid[j] = cur[j].y;
-            any |= ck[j] != 0;
-        }
-        if (__any(any)) take<4, LR>(ck, cid, k, loose, lkey[wv], lid[wv], cnt, thr);
+        for (int j = 0; j < 4; ++j) v[j] = __uint_as_float(cur[j].x);
+        if (__any(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) > tau))
+            take<4, LR>(v, [&](int j) { return cur[j].y; }, k, loose, lval[wv], lid[wv], cnt, tau);
 #pragma unroll
         for (int j = 0; j < 4; ++j) cur[j] = nxt[j];
     }
     unsigned key[LR], id[LR];
     int rank[LR];
-    finish<LR>(k, lkey[wv], lid[wv], cnt, thr, key, id, rank);
+    finish<LR>(k, lval[wv], lid[wv], cnt, key, id, rank);
 #pragma unroll
     for (int i = 0; i < LR; ++i)
         if (rank[i] >= 0) {

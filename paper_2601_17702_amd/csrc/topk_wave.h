@@ -1,8 +1,8 @@
 // Exact Top-k of one token by one wavefront: a list of candidates in LDS that new elements are filtered into, cut to
 // (about) the k largest whenever it would overflow.  Shared by the tiled encoder and the merge of its feature ranges.
 //
-// Values travel as ordered keys (unsigned order = float order; 0 = no element).  -0 and +0 are one value, as in a float
-// compare; a NaN is below every number.  Elements arrive with ascending ids among equal values, so an element that only
+// Searches work on ordered keys (unsigned order = float order; 0 = no element).  -0 and +0 are one value, as in a float
+// compare.  Inputs are finite; -inf marks the places that hold no element.  Elements arrive with ascending ids among equal values, so an element that only
 // equals the threshold of a list that holds k at or above it loses to all of those.
 //
 // Everything that steers the search (counts, thresholds) is uniform: a count is one compare per register whose mask is
@@ -43,27 +43,44 @@ __device__ __forceinline__ int count_ge(const unsigned (&key)[N], unsigned m) {
 }
 
 // The largest threshold found with k <= count(key >= threshold) <= loose, starting from lo (count clo >= k).  Returns the
-// count; it exceeds `loose` only if more than loose - k elements equal the threshold.
+// count; it exceeds `loose` only if more than loose - k elements equal the threshold.  Every other step interpolates on
+// the logarithm of the counts (the upper tail of the values is close to exponential), the steps between halve the keys:
+// about 6 steps instead of 20 for 256 fresh values.
 template <int N>
 __device__ __forceinline__ int raise(const unsigned (&key)[N], int k, int loose, unsigned& lo, int clo) {
     if (clo <= loose) return clo;
-    unsigned mx = 0;
+    unsigned mx = 0, mn = 0xFFFFFFFFu;
 #pragma unroll
-    for (int i = 0; i < N; ++i) mx = max(mx, key[i]);
+    for (int i = 0; i < N; ++i) {
+        mx = max(mx, key[i]);
+        mn = min(mn, key[i] - 1);                                  // no element: largest of all
+    }
     unsigned hi = wave_max_u(mx) + 1;                              // keys stay below 0xFF800001
+    lo = max(lo, 0xFFFFFFFFu - wave_max_u(0xFFFFFFFFu - mn) + 1);  // nothing lies below the smallest element
+    int chi = 0;
+    const float lwant = __log2f(0.5f * (float)(k + loose));
+    bool interp = true;
     while (clo > loose && hi - lo > 1) {
-        const unsigned mid = lo + (hi - lo) / 2;
+        unsigned mid = lo + (hi - lo) / 2;
+        if (interp) {
+            const float llo = __log2f((float)clo), lhi = __log2f((float)max(chi, 1));
+            const float t = fminf(fmaxf((llo - lwant) * __builtin_amdgcn_rcpf(llo - lhi), 0.0625f), 0.9375f);
+            const float flo = value_of(lo), fhi = value_of(hi);
+            const unsigned m = (unsigned)__builtin_amdgcn_readfirstlane((int)key_of(flo + (fhi - flo) * t));
+            if (m > lo && m < hi) mid = m;
+        }
+        interp = !interp;
         const int c = count_ge(key, mid);
-        if (c >= k) { lo = mid; clo = c; } else hi = mid;
+        if (c >= k) { lo = mid; clo = c; } else { hi = mid; chi = c; }
     }
     return clo;
 }
 
-// Cuts the N registers' elements to between k and `loose` (exactly k when loose == k) and stores them at lk / li[0 ..).
+// Cuts the N registers' elements to between k and `loose` (exactly k when loose == k) and stores them at lv / li[0 ..).
 // `lo`: in, a threshold with at least k elements at or above it (at least 1); out, the new one.  Returns the number kept.
 template <int N>
 __device__ __forceinline__ int cut_and_store(const unsigned (&key)[N], const unsigned (&id)[N], int k, int loose, unsigned& lo,
-                                             int clo, unsigned* lk, uint16_t* li) {
+                                             int clo, float* lv, uint16_t* li) {
     clo = raise(key, k, loose, lo, clo);
     unsigned idcut = 0xFFFFu;
     if (clo > loose) {                    // ties at the threshold: keep those with the lowest ids, k elements in all
@@ -85,7 +102,7 @@ __device__ __forceinline__ int cut_and_store(const unsigned (&key)[N], const uns
         const unsigned long long m = __ballot(keep);
         if (keep) {
             const int at = n + below(m);
-            lk[at] = key[i];
+            lv[at] = value_of(key[i]);
             li[at] = (uint16_t)id[i];
         }
         n += (int)__popcll(m);
@@ -94,30 +111,30 @@ __device__ __forceinline__ int cut_and_store(const unsigned (&key)[N], const uns
     return n;
 }
 
-// Filters NC registers of new elements (key 0 = none; all above the list's threshold `thr`, or thr == 0: no threshold yet)
-// into a list of `cnt` with room for 64 * LR.
-template <int NC, int LR>
-__device__ __forceinline__ void take(const unsigned (&ck)[NC], const unsigned (&cid)[NC], int k, int loose, unsigned* lk,
-                                     uint16_t* li, int& cnt, unsigned& thr) {
+// Takes the NC registers' elements above the list's threshold `tau` into a list of `cnt` with room for 64 * LR.  Element i of
+// the lane has id id_of(i).  An append is kept short (most chunks bring a token
+// one or two elements): four compares, and per register with a hit the position from the mask and two LDS writes.
+template <int NC, int LR, class IdOf>
+__device__ __forceinline__ void take(const float (&v)[NC], IdOf id_of, int k, int loose, float* lv, uint16_t* li, int& cnt,
+                                     float& tau) {
     unsigned long long m[NC];
     int add = 0;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-        m[i] = __ballot(ck[i] != 0);
+        m[i] = __ballot(v[i] > tau);
         add += (int)__popcll(m[i]);
     }
-    if (cnt + add <= 64 * LR) {
-        int n = cnt;
+    if (__builtin_expect(cnt + add <= 64 * LR, 1)) {
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            if (ck[i] != 0) {
-                const int at = n + below(m[i]);
-                lk[at] = ck[i];
-                li[at] = (uint16_t)cid[i];
+            if (!m[i]) continue;
+            if (v[i] > tau) {
+                const int at = cnt + below(m[i]);
+                lv[at] = v[i];
+                li[at] = (uint16_t)id_of(i);
             }
-            n += (int)__popcll(m[i]);
+            cnt += (int)__popcll(m[i]);
         }
-        cnt = n;
         wave_fence();
         return;
     }
@@ -126,47 +143,46 @@ __device__ __forceinline__ void take(const unsigned (&ck)[NC], const unsigned (&
 #pragma unroll
     for (int i = 0; i < LR; ++i) {
         const int e = i * 64 + lane;
-        key[i] = e < cnt ? lk[e] : 0u;
+        key[i] = e < cnt ? key_of(lv[e]) : 0u;
         id[i] = e < cnt ? (unsigned)li[e] : 0u;
     }
 #pragma unroll
-    for (int i = 0; i < NC; ++i) { key[LR + i] = ck[i]; id[LR + i] = cid[i]; }
-    // Every element is at or above max(thr, 1), and there are more than 64 * LR >= k of them.
-    unsigned lo = max(thr, 1u);
-    cnt = cut_and_store<NC + LR>(key, id, k, loose, lo, cnt + add, lk, li);
-    thr = lo;
+    for (int i = 0; i < NC; ++i) { key[LR + i] = v[i] > tau ? key_of(v[i]) : 0u; id[LR + i] = (unsigned)id_of(i); }
+    // Every element is at or above tau, and there are more than 64 * LR >= k of them.
+    unsigned lo = key_of(tau);
+    cnt = cut_and_store<NC + LR>(key, id, k, loose, lo, cnt + add, lv, li);
+    tau = value_of(lo);
 }
 
 // The list's k best (fewer if it holds fewer) in registers with their ranks (value descending, id ascending): element i of
-// lane l has rank rank[i], or -1.  Returns the key of the k-th best (0 if there are fewer than k).
+// lane l has rank rank[i], or -1.
 template <int LR>
-__device__ __forceinline__ unsigned finish(int k, unsigned* lk, uint16_t* li, int cnt, unsigned thr, unsigned (&key)[LR],
-                                           unsigned (&id)[LR], int (&rank)[LR]) {
+__device__ __forceinline__ void finish(int k, float* lv, uint16_t* li, int cnt, unsigned (&key)[LR], unsigned (&id)[LR],
+                                       int (&rank)[LR]) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < LR; ++i) {
         const int e = i * 64 + lane;
-        key[i] = e < cnt ? lk[e] : 0u;
+        key[i] = e < cnt ? key_of(lv[e]) : 0u;
         id[i] = e < cnt ? (unsigned)li[e] : 0u;
     }
-    if (cnt > k) {
-        unsigned lo = max(thr, 1u);
+    const int loose = k + (k >> 3) + 2;            // the ranks below tell the k best of a few more than k
+    if (cnt > loose) {
+        unsigned lo = 1u;
         wave_fence();
-        cnt = cut_and_store<LR>(key, id, k, k, lo, cnt, lk, li);
+        cnt = cut_and_store<LR>(key, id, k, loose, lo, cnt, lv, li);
 #pragma unroll
         for (int i = 0; i < LR; ++i) {
             const int e = i * 64 + lane;
-            key[i] = e < cnt ? lk[e] : 0u;
+            key[i] = e < cnt ? key_of(lv[e]) : 0u;
             id[i] = e < cnt ? (unsigned)li[e] : 0u;
         }
     }
     unsigned long long mine[LR];
-    unsigned low = 0xFFFFFFFFu;
 #pragma unroll
     for (int i = 0; i < LR; ++i) {
         mine[i] = ((unsigned long long)key[i] << 32) | (0xFFFFFFFFu - id[i]);
         rank[i] = 0;
-        if (key[i]) low = min(low, key[i]);
     }
 #pragma unroll
     for (int r = 0; r < LR; ++r) {
@@ -180,8 +196,7 @@ __device__ __forceinline__ unsigned finish(int k, unsigned* lk, uint16_t* li, in
         }
     }
 #pragma unroll
-    for (int i = 0; i < LR; ++i) if (!key[i]) rank[i] = -1;
-    return cnt < k ? 0u : 0xFFFFFFFFu - wave_max_u(0xFFFFFFFFu - low);
+    for (int i = 0; i < LR; ++i) if (!key[i] || rank[i] >= k) rank[i] = -1;
 }
 
 }  // namespace s3topk
