@@ -16,11 +16,15 @@
 
 namespace {
 
-constexpr int kConvThreads = 256;
-constexpr int kConvPer = 4;
-constexpr int kSelTile = kConvThreads * kConvPer;     // positions per tile (conv workgroup, peak search)
 constexpr int kMaxTaps = 4096;
-constexpr int kNmsThreads = 256;
+constexpr int kConvPer = 4;                 // consecutive positions per thread of the convolution
+constexpr int kConvSmall = 64, kConvLarge = 256;      // its workgroup sizes: below / from kConvLargeFrom positions
+constexpr int64_t kConvLargeFrom = 1 << 18; // 64 threads fill the chip up to 2^18 positions; beyond, the halo is shared by more
+constexpr int kTile = 64;                   // positions per density tile
+constexpr int kNmsThreads = 1024;
+constexpr int kNmsTiles = 8192;             // tile maxima that the peak search keeps in LDS (64 KB)
+constexpr int kNmsGroups = kNmsTiles / 64 / 64;       // groups of 64 tiles per lane
+constexpr int kNmsLds = 152 << 10;          // its LDS: tile maxima, centres, group maxima, and the whole curve if that fits
 
 struct SelArgs {
     const float* scores;
@@ -29,10 +33,10 @@ struct SelArgs {
     int K, n_centers, radius, max_half;
     float rel;
     float* dens;                 // [L]
-    unsigned char* dead;         // [L]
-    float* tmaxv;                // [ntile]
-    int* tmaxi;                  // [ntile]
+    unsigned long long* tkey;    // [ntile] best position of every tile of kTile positions (peak_key)
     int ntile;
+    int shift;                   // the peak search works on tiles of kTile << shift positions
+    int cached;                  // the curve is kept in LDS during the peak search
     int32_t* center;
     float* center_density;
     int32_t* span_lo;
@@ -40,134 +44,256 @@ struct SelArgs {
     int32_t* n_found;
 };
 
-// (value, index) argmax over the block: larger value wins, ties -> smaller index
-template <int NT>
-__device__ __forceinline__ void block_argmax_f(float& v, int& i, float* sv, int* si) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(v, o);
-        const int oi = __shfl_xor(i, o);
-        if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
-    }
-    const int wave = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) { sv[wave] = v; si[wave] = i; }
-    __syncthreads();
-    float bv = sv[0];
-    int bi = si[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; ++w) {
-        const float ov = sv[w];
-        const int oi = si[w];
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    }
-    v = bv; i = bi;
+// Orders positions by (density, smaller position first); 0 for a position that cannot be a centre (density not positive).
+__device__ __forceinline__ unsigned long long peak_key(float d, int64_t t) {
+    return d > 0.f ? ((unsigned long long)__float_as_uint(d) << 32) | (unsigned)~(unsigned)t : 0ull;
 }
 
-// D[t] = sum_j g[j] * S[t + j - floor(K / 2)] with zeros outside the context; one tile of positions per workgroup,
-// its inputs and the weights staged in LDS; also clears the tile's suppression flags and records its best position.
-__global__ __launch_bounds__(kConvThreads) void sel_conv_kernel(SelArgs a) {
-    extern __shared__ float lds[];
-    float* g = lds;                          // [K]
-    float* s = lds + a.K;                    // [kSelTile + K - 1]
-    __shared__ float sv[kConvThreads / 64];
-    __shared__ int si[kConvThreads / 64];
+__device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
+#define S3_DPP_MAX(CTRL, ROWS) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false))
+    S3_DPP_MAX(0x111, 0xf);
+    S3_DPP_MAX(0x112, 0xf);
+    S3_DPP_MAX(0x114, 0xf);
+    S3_DPP_MAX(0x118, 0xf);
+    S3_DPP_MAX(0x142, 0xa);
+    S3_DPP_MAX(0x143, 0xc);
+#undef S3_DPP_MAX
+    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+// Largest key of the wavefront, in every lane: the high words first, then the low words of the lanes that hold it.
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v) {
+    const unsigned hi = wave_max_u32((unsigned)(v >> 32));
+    const unsigned lo = wave_max_u32((unsigned)(v >> 32) == hi ? (unsigned)v : 0u);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// D[t] = sum_j g[j] * S[t + j - floor(K / 2)] with zeros outside the context, and the best position of every tile.
+// Inputs and weights are staged in LDS; a thread has four consecutive positions, so four taps cost two 16-byte reads
+// for 16 multiply-adds (one 4-byte read per operand before).
+template <int NT>
+__global__ __launch_bounds__(NT) void sel_conv_kernel(SelArgs a) {
+    extern __shared__ __align__(16) float lds[];
+    const int kp = (a.K + 3) & ~3;
+    float* g = lds;                          // [kp]
+    float* s = lds + kp;                     // [NT * kConvPer + kp + 4]
     const int tid = threadIdx.x;
-    const int64_t t0 = (int64_t)blockIdx.x * kSelTile;
+    const int64_t t0 = (int64_t)blockIdx.x * (NT * kConvPer);
     const int c = a.K / 2;
-    for (int j = tid; j < a.K; j += kConvThreads) g[j] = a.kernel[j];
-    for (int i = tid; i < kSelTile + a.K - 1; i += kConvThreads) {
+    for (int j = tid; j < a.K; j += NT) g[j] = a.kernel[j];
+    for (int i = tid; i < NT * kConvPer + a.K - 1; i += NT) {
         const int64_t u = t0 + i - c;
         s[i] = (u >= 0 && u < a.L) ? a.scores[u] : 0.f;
     }
     __syncthreads();
-    float bv = -INFINITY;
-    int bi = 0x7FFFFFFF;
+    double acc[kConvPer] = {0.0, 0.0, 0.0, 0.0};
+    const float4* sv = (const float4*)(s + tid * kConvPer);
+    float4 lo = sv[0];
+    int j = 0;
+    for (; j + 4 <= a.K; j += 4) {
+        const float4 hi = sv[j / 4 + 1];
+        const float4 gv = *(const float4*)(g + j);
+        const float w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        const float gg[4] = {gv.x, gv.y, gv.z, gv.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int q = 0; q < kConvPer; ++q) acc[q] += (double)gg[u] * (double)w[u + q];
+        lo = hi;
+    }
+    for (; j < a.K; ++j)
+#pragma unroll
+        for (int q = 0; q < kConvPer; ++q) acc[q] += (double)g[j] * (double)s[tid * kConvPer + q + j];
+    unsigned long long best = 0;
 #pragma unroll
     for (int q = 0; q < kConvPer; ++q) {
-        const int i = q * kConvThreads + tid;
-        const int64_t t = t0 + i;
+        const int64_t t = t0 + tid * kConvPer + q;
         if (t < a.L) {
-            double acc = 0.0;
-            for (int j = 0; j < a.K; ++j) acc += (double)g[j] * (double)s[i + j];
-            const float dv = (float)acc;
+            const float dv = (float)acc[q];
             a.dens[t] = dv;
-            a.dead[t] = 0;
-            if (dv > bv) { bv = dv; bi = (int)t; }      // ascending t per thread: the first best one is kept
+            const unsigned long long k = peak_key(dv, t);
+            best = k > best ? k : best;
         }
     }
-    block_argmax_f<kConvThreads>(bv, bi, sv, si);
-    if (tid == 0) { a.tmaxv[blockIdx.x] = bv; a.tmaxi[blockIdx.x] = bi; }
+    // the 16 lanes of a row hold one tile
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        const unsigned hi = (unsigned)__shfl_xor((int)(unsigned)(best >> 32), o), lw = (unsigned)__shfl_xor((int)(unsigned)best, o);
+        const unsigned long long other = ((unsigned long long)hi << 32) | lw;
+        best = other > best ? other : best;
+    }
+    const int64_t tile = t0 / kTile + tid / 16;
+    if ((tid & 15) == 0 && tile < a.ntile) a.tkey[tile] = best;
 }
 
-// Greedy peak selection, then the span of every peak.  One workgroup: the rounds depend on each other.
-__global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
-    __shared__ float sv[kNmsThreads / 64];
-    __shared__ int si[kNmsThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int found = 0;
-    for (int r = 0; r < a.n_centers; ++r) {
-        float v = -INFINITY;
-        int i = 0x7FFFFFFF;
-        for (int t = tid; t < a.ntile; t += kNmsThreads) {
-            const float tv = a.tmaxv[t];
-            const int ti = a.tmaxi[t];
-            if (tv > v || (tv == v && ti < i)) { v = tv; i = ti; }
+// This lane's best live positions of the tiles tl and th (which may be the same): U times 64 positions of both at a time,
+// all loads in flight, those within the radius of one of the centres cen[0 .. found) left out.
+template <int U>
+__device__ __forceinline__ void sel_rescan(const SelArgs& a, const int* cen, int found, int tl, int th,
+                                           int tlog, int lane, unsigned long long& kl, unsigned long long& kh) {
+    const int64_t r = a.radius;
+    for (int s0 = 0; s0 < (1 << a.shift); s0 += U) {
+        const int64_t b0 = ((int64_t)tl << tlog) + s0 * kTile, b1 = ((int64_t)th << tlog) + s0 * kTile;
+        float d0[U], d1[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p0 = b0 + u * kTile + lane, p1 = b1 + u * kTile + lane;
+            d0[u] = d1[u] = 0.f;
+            if (p0 < a.L) d0[u] = a.dens[p0];
+            if (p1 < a.L) d1[u] = a.dens[p1];
         }
-        block_argmax_f<kNmsThreads>(v, i, sv, si);
-        if (!(v > 0.f)) break;                       // only positive density makes a centre
-        if (tid == 0) {
-            a.center[r] = i;
-            a.center_density[r] = v;
-        }
-        found = r + 1;
-        const int64_t lo = max((int64_t)0, (int64_t)i - a.radius), hi = min(a.L - 1, (int64_t)i + a.radius);
-        for (int64_t t = lo + tid; t <= hi; t += kNmsThreads) a.dead[t] = 1;
-        __syncthreads();
-        for (int tl = (int)(lo / kSelTile); tl <= (int)(hi / kSelTile); ++tl) {
-            float tv = -INFINITY;
-            int ti = 0x7FFFFFFF;
-            for (int q = tid; q < kSelTile; q += kNmsThreads) {
-                const int64_t t = (int64_t)tl * kSelTile + q;
-                if (t < a.L && !a.dead[t]) {
-                    const float dv = a.dens[t];
-                    if (dv > tv) { tv = dv; ti = (int)t; }
+        for (int j0 = 0; j0 < found; j0 += 64) {
+            const bool on = j0 + lane < found;
+            const int64_t cj = on ? cen[j0 + lane] : 0;
+            unsigned long long near = __ballot(on && ((cj + r >= b0 && cj - r < b0 + U * kTile) ||
+                                                      (cj + r >= b1 && cj - r < b1 + U * kTile)));
+            while (near) {
+                const int64_t c = __builtin_amdgcn_readlane((int)cj, (int)__builtin_ctzll(near));
+                near &= near - 1;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t p0 = b0 + u * kTile + lane, p1 = b1 + u * kTile + lane;
+                    if (p0 >= c - r && p0 <= c + r) d0[u] = 0.f;
+                    if (p1 >= c - r && p1 <= c + r) d1[u] = 0.f;
                 }
             }
-            block_argmax_f<kNmsThreads>(tv, ti, sv, si);
-            if (tid == 0) { a.tmaxv[tl] = tv; a.tmaxi[tl] = ti; }
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned long long k0 = peak_key(d0[u], b0 + u * kTile + lane), k1 = peak_key(d1[u], b1 + u * kTile + lane);
+            kl = k0 > kl ? k0 : kl;
+            kh = k1 > kh ? k1 : kh;
+        }
+    }
+}
+
+// Greedy peak selection, then the span of every peak.  One workgroup: the rounds depend on each other, so what bounds
+// it is the latency of a round.  One wavefront walks the rounds without a barrier: the maxima of groups of 64 tiles
+// are in its registers, the tile maxima in LDS.  A round takes the best group, clears the tiles that the suppression
+// covers whole and searches the two at its ends again.  A short context's curve is kept in LDS and the suppressed
+// interval wiped out of that copy; a longer one is read from global memory, where a position is dead if it is within
+// the radius of a centre chosen before (there is no flag array).  The chain of a round is two reductions over the
+// wavefront and one LDS (or L2) latency.  With 256 threads, tiles of 1024 positions and flags in global memory a round
+// had ten barriers and three global round trips: 32768 positions, 40 centres, radius 48, the whole call with the fusion
+// behind it 181 us, now 56 us.
+__global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
+    extern __shared__ __align__(16) unsigned long long nms_lds[];
+    __shared__ int found_s;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tlog = 6 + a.shift;                                     // log2 of positions per tile
+    const int nt = (a.ntile + (1 << a.shift) - 1) >> a.shift, ng = (nt + 63) >> 6;
+    unsigned long long* key = nms_lds;                                // [nt]
+    unsigned long long* gkey = key + nt;                              // [ng]
+    int* cen = (int*)(gkey + ng);                                     // [n_centers]
+    float* cden = (float*)(cen + a.n_centers);                        // [n_centers]
+    float* cur = cden + a.n_centers;                                  // [L] if cached
+    if (a.cached) {
+        for (int64_t i0 = tid; i0 < a.L; i0 += 8 * kNmsThreads) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = i0 + u * kNmsThreads < a.L ? a.dens[i0 + u * kNmsThreads] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u * kNmsThreads < a.L) cur[i0 + u * kNmsThreads] = v[u];
+        }
+    }
+    for (int g = wave; g < ng; g += kNmsThreads / 64) {
+        const int t = g * 64 + lane;
+        unsigned long long best = 0;
+        if (t < nt) {
+            const int64_t e0 = (int64_t)t << a.shift, e1 = min((int64_t)a.ntile, e0 + (1 << a.shift));
+            for (int64_t e = e0; e < e1; ++e) best = a.tkey[e] > best ? a.tkey[e] : best;
+            key[t] = best;
+        }
+        best = wave_max_key(best);
+        if (lane == 0) gkey[g] = best;
     }
     __syncthreads();
-    // spans: a wavefront per centre walks outwards 64 positions at a time; the span ends before the first position
-    // whose density is below rel * D[centre] or that is farther than max_half from the centre
-    for (int r = wave; r < found; r += kNmsThreads / 64) {
-        const int c = a.center[r];
-        const double thr = (double)a.rel * (double)a.center_density[r];
-        int ext[2];
+    if (wave == 0) {
+        unsigned long long top[kNmsGroups];        // group q * 64 + lane; 0 while the group's tiles are in va / vb
 #pragma unroll
-        for (int side = 0; side < 2; ++side) {
-            const int64_t room = side == 0 ? (int64_t)c : a.L - 1 - c;          // positions available on this side
-            const int limit = (int)min((int64_t)a.max_half, room);
-            int n = 0;                                                           // positions taken so far
-            while (n < limit) {
-                const int d = n + 1 + lane;                                      // distance from the centre
-                bool ok = false;
-                if (d <= limit) {
-                    const int64_t t = side == 0 ? (int64_t)c - d : (int64_t)c + d;
-                    ok = (double)a.dens[t] >= thr;
-                }
+        for (int q = 0; q < kNmsGroups; ++q) top[q] = q * 64 + lane < ng ? gkey[q * 64 + lane] : 0ull;
+        unsigned long long va = 0, vb = 0;         // tile maxima (tile ga * 64 + lane, gb * 64 + lane) that changed last
+        int ga = -1, gb = -1;
+        int found = 0;
+        while (found < a.n_centers) {
+            unsigned long long best = va > vb ? va : vb;
+#pragma unroll
+            for (int q = 0; q < kNmsGroups; ++q) best = top[q] > best ? top[q] : best;
+            best = wave_max_key(best);
+            const unsigned long long ma = wave_max_key(va), mb = wave_max_key(vb);      // beside the reduction above, not behind it
+#pragma unroll
+            for (int q = 0; q < kNmsGroups; ++q) {
+                if (q * 64 + lane == ga) top[q] = ma;
+                if (q * 64 + lane == gb) top[q] = mb;
+            }
+            if (best == 0) break;                                     // only positive density makes a centre
+            const int64_t c = (int64_t)(unsigned)~(unsigned)best;
+            if (lane == 0) { cen[found] = (int)c; cden[found] = __uint_as_float((unsigned)(best >> 32)); }
+            ++found;
+            const int64_t lo = max((int64_t)0, c - a.radius), hi = min(a.L - 1, c + a.radius);
+            const int tl = (int)(lo >> tlog), th = (int)(hi >> tlog);
+            ga = tl >> 6;
+            gb = th >> 6;
+            for (int t = tl + 1 + lane; t < th; t += 64) key[t] = 0;
+#pragma unroll
+            for (int q = 0; q < kNmsGroups; ++q)
+                if (q * 64 + lane >= ga && q * 64 + lane <= gb) top[q] = 0;
+            va = ga * 64 + lane < nt ? key[ga * 64 + lane] : 0ull;
+            vb = gb * 64 + lane < nt ? key[gb * 64 + lane] : 0ull;
+            unsigned long long kl = 0, kh = 0;                        // best live position of the tile at either end
+            if (a.cached) {                                           // (shift is 0): the interval is wiped out of the curve in LDS
+                for (int64_t p = lo + lane; p <= hi; p += 64) cur[p] = 0.f;
+                const int64_t p0 = ((int64_t)tl << 6) + lane, p1 = ((int64_t)th << 6) + lane;
+                if (p0 < a.L) kl = peak_key(cur[p0], p0);
+                if (p1 < a.L) kh = peak_key(cur[p1], p1);
+            } else if (a.shift == 0) sel_rescan<1>(a, cen, found, tl, th, tlog, lane, kl, kh);
+            else if (a.shift == 1) sel_rescan<2>(a, cen, found, tl, th, tlog, lane, kl, kh);
+            else sel_rescan<4>(a, cen, found, tl, th, tlog, lane, kl, kh);
+            kl = wave_max_key(kl);
+            kh = wave_max_key(kh);
+            if (lane == 0) { key[tl] = kl; key[th] = kh; }            // the same value where tl == th
+            if (ga * 64 + lane == tl) va = kl;
+            if (ga * 64 + lane == th) va = kh;
+            if (gb * 64 + lane == tl) vb = kl;
+            if (gb * 64 + lane == th) vb = kh;
+        }
+        if (lane == 0) found_s = found;
+    }
+    __syncthreads();
+    const int found = found_s;
+    // spans: a wavefront per centre walks outwards 64 positions at a time, both sides at once; a side ends before the
+    // first position whose density is below rel * D[centre] or that is farther than max_half from the centre
+    for (int r = wave; r < found; r += kNmsThreads / 64) {
+        const int c = cen[r];
+        const double thr = (double)a.rel * (double)cden[r];
+        const int limit[2] = {(int)min((int64_t)a.max_half, (int64_t)c), (int)min((int64_t)a.max_half, a.L - 1 - c)};
+        int n[2] = {0, 0};
+        bool open[2] = {limit[0] > 0, limit[1] > 0};
+        while (open[0] || open[1]) {
+            float d[2];
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                const int64_t off = (int64_t)n[side] + 1 + lane;      // distance from the centre
+                const int64_t t = side == 0 ? c - off : c + off;
+                d[side] = -1.f;
+                if (open[side] && off <= limit[side]) d[side] = a.dens[t];
+            }
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                if (!open[side]) continue;
+                const bool ok = (int64_t)n[side] + 1 + lane <= limit[side] && (double)d[side] >= thr;
                 const unsigned long long m = __ballot(ok);
                 const int run = m == ~0ull ? 64 : (int)__builtin_ctzll(~m);      // leading positions that pass
-                n += run;
-                if (run < 64) break;
+                n[side] += run;
+                open[side] = run == 64 && n[side] < limit[side];
             }
-            ext[side] = min(n, limit);
         }
         if (lane == 0) {
-            a.span_lo[r] = c - ext[0];
-            a.span_hi[r] = c + ext[1];
+            a.center[r] = c;
+            a.center_density[r] = cden[r];
+            a.span_lo[r] = c - n[0];
+            a.span_hi[r] = c + n[1];
         }
     }
     for (int r = found + tid; r < a.n_centers; r += kNmsThreads) {
@@ -177,8 +303,80 @@ __global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
 }
 
 // ---- Phase 3 set operations ----
-constexpr int kFuseBlock = 4096;      // positions per workgroup in the count / compact passes
+// What bounds them at the lengths of a context is the number of launches.  Two are enough: fuse_block_kernel builds the
+// mask of a block of positions in LDS (every block looks through all spans and the whole index list) and counts it,
+// fuse_compact_kernel adds up the counts of the blocks before its own.  Both are quadratic in the context's length, so
+// beyond kFuseLookMax list entries looked at in all (64 MB through L2) the mask is marked in memory first, and beyond
+// kFuseSelfMax blocks the counts are scanned by a launch of their own.
 constexpr int kFuseThreads = 256;
+constexpr int kFusePer = 4;                             // consecutive positions per thread
+constexpr int kFuseBlock = kFuseThreads * kFusePer;     // positions per workgroup
+constexpr int64_t kFuseLookMax = 1 << 24;
+constexpr int kFuseSelfMax = 4096;
+
+// number of selected positions among a thread's four (bytes are 0 or 1), and the mask bytes themselves
+__device__ __forceinline__ uint32_t fuse_load4(const unsigned char* mask, int64_t t, int64_t L, bool aligned) {
+    if (aligned && t + kFusePer <= L) return *(const uint32_t*)(mask + t);
+    uint32_t v = 0;
+#pragma unroll
+    for (int j = 0; j < kFusePer; ++j)
+        if (t + j < L) v |= (uint32_t)mask[t + j] << (8 * j);
+    return v;
+}
+
+__global__ __launch_bounds__(kFuseThreads) void fuse_block_kernel(unsigned char* mask, int64_t L, const int32_t* lo, const int32_t* hi,
+                                                                  const int32_t* n_spans, int max_spans, const int32_t* extra,
+                                                                  int64_t n_extra, int lead, int tail, int* bsum) {
+    __shared__ uint32_t m4[kFuseThreads];
+    __shared__ int wsum[kFuseThreads / 64];
+    unsigned char* const m = (unsigned char*)m4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t t0 = (int64_t)blockIdx.x * kFuseBlock, t1 = min(L, t0 + kFuseBlock) - 1;      // first and last position
+    uint32_t v = 0;
+#pragma unroll
+    for (int j = 0; j < kFusePer; ++j) {
+        const int64_t t = t0 + tid * kFusePer + j;
+        if (t < L && (t < lead || t >= L - tail)) v |= 1u << (8 * j);
+    }
+    m4[tid] = v;
+    __syncthreads();
+    const int ns = n_spans ? min(*n_spans, max_spans) : max_spans;
+    for (int i0 = wave * 64; i0 < ns; i0 += kFuseThreads) {      // a wavefront looks at 64 spans, then marks those that meet the block
+        int a = 0, b = -1;
+        if (i0 + lane < ns) {
+            a = (int)(max((int64_t)lo[i0 + lane], t0) - t0);
+            b = (int64_t)lo[i0 + lane] > t1 ? -1 : (int)max((int64_t)-1, min((int64_t)hi[i0 + lane], t1) - t0);
+        }
+        unsigned long long hit = __ballot(a <= b);
+        while (hit) {
+            const int src = (int)__builtin_ctzll(hit);
+            hit &= hit - 1;
+            const int sa = __builtin_amdgcn_readlane(a, src), sb = __builtin_amdgcn_readlane(b, src);
+            for (int i = sa + lane; i <= sb; i += 64) m[i] = 1;
+        }
+    }
+    for (int64_t i0 = tid; i0 < n_extra; i0 += 8 * kFuseThreads) {
+        int32_t p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = i0 + u * kFuseThreads < n_extra ? extra[i0 + u * kFuseThreads] : -1;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if ((int64_t)p[u] >= t0 && (int64_t)p[u] <= t1) m[(int)(p[u] - t0)] = 1;
+    }
+    __syncthreads();
+    v = m4[tid];
+    const int64_t t = t0 + tid * kFusePer;
+    if (((uintptr_t)mask & 3) == 0 && t + kFusePer <= L) {
+        *(uint32_t*)(mask + t) = v;
+    } else {
+#pragma unroll
+        for (int j = 0; j < kFusePer; ++j)
+            if (t + j < L) mask[t + j] = (unsigned char)(v >> (8 * j));
+    }
+    int tot;
+    s3_block_excl_scan<kFuseThreads>(__popc(v), wsum, tot);
+    if (tid == 0) bsum[blockIdx.x] = tot;
+}
 
 __global__ void fuse_init_kernel(unsigned char* mask, int64_t L, int lead, int tail) {
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < L; t += (int64_t)gridDim.x * blockDim.x)
@@ -204,11 +402,10 @@ __global__ void fuse_mark_kernel(unsigned char* mask, int64_t L, const int32_t* 
 
 __global__ __launch_bounds__(kFuseThreads) void fuse_count_kernel(const unsigned char* mask, int64_t L, int* bsum) {
     __shared__ int wsum[kFuseThreads / 64];
-    const int64_t t0 = (int64_t)blockIdx.x * kFuseBlock;
-    int c = 0;
-    for (int i = threadIdx.x; i < kFuseBlock; i += kFuseThreads) c += (t0 + i < L && mask[t0 + i]) ? 1 : 0;
+    const int64_t t = (int64_t)blockIdx.x * kFuseBlock + threadIdx.x * kFusePer;
+    const uint32_t v = fuse_load4(mask, t, L, ((uintptr_t)mask & 3) == 0);
     int tot;
-    s3_block_excl_scan<kFuseThreads>(c, wsum, tot);
+    s3_block_excl_scan<kFuseThreads>(__popc(v), wsum, tot);
     if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
@@ -228,34 +425,38 @@ __global__ __launch_bounds__(kFuseThreads) void fuse_scan_kernel(int* bsum, int 
     if (threadIdx.x == 0) n_out[0] = carry;
 }
 
-// thread i of a workgroup owns 16 consecutive positions, so that the output order is the position order
-__global__ __launch_bounds__(kFuseThreads) void fuse_compact_kernel(const unsigned char* mask, int64_t L, const int* bsum,
-                                                                     int32_t* idx) {
+// Thread i of a workgroup owns four consecutive positions, so that the output order is the position order.  `scanned`:
+// bsum holds the exclusive prefix; else the block counts, and the last workgroup also writes the total.
+__global__ __launch_bounds__(kFuseThreads) void fuse_compact_kernel(const unsigned char* mask, int64_t L, const int* bsum, int scanned,
+                                                                     int32_t* idx, int32_t* n_out) {
     __shared__ int wsum[kFuseThreads / 64];
-    constexpr int kPer = kFuseBlock / kFuseThreads;
-    const int64_t t0 = (int64_t)blockIdx.x * kFuseBlock + (int64_t)threadIdx.x * kPer;
-    int c = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) c += (t0 + j < L && mask[t0 + j]) ? 1 : 0;
+    const int64_t t = (int64_t)blockIdx.x * kFuseBlock + threadIdx.x * kFusePer;
+    const uint32_t v = fuse_load4(mask, t, L, ((uintptr_t)mask & 3) == 0);
+    int before = 0;
+    if (scanned) {
+        before = bsum[blockIdx.x];
+    } else {
+        int part = 0;
+        for (int b = threadIdx.x; b < (int)blockIdx.x; b += kFuseThreads) part += bsum[b];
+        s3_block_excl_scan<kFuseThreads>(part, wsum, before);
+    }
     int tot;
-    int o = bsum[blockIdx.x] + s3_block_excl_scan<kFuseThreads>(c, wsum, tot);
+    int o = before + s3_block_excl_scan<kFuseThreads>(__popc(v), wsum, tot);
 #pragma unroll
-    for (int j = 0; j < kPer; ++j)
-        if (t0 + j < L && mask[t0 + j]) idx[o++] = (int32_t)(t0 + j);
+    for (int j = 0; j < kFusePer; ++j)
+        if ((v >> (8 * j)) & 1u) idx[o++] = (int32_t)(t + j);
+    if (!scanned && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) n_out[0] = before + tot;
 }
 
 struct SelLayout {
-    size_t dens, dead, tmaxv, tmaxi, total;
+    size_t dens, tkey, total;
 };
 SelLayout sel_layout(int64_t L) {
     SelLayout l;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += s3_align(bytes); return at; };
-    const size_t ntile = (size_t)(L + kSelTile - 1) / kSelTile;
     l.dens = take((size_t)L * 4);
-    l.dead = take((size_t)L);
-    l.tmaxv = take(ntile * 4);
-    l.tmaxi = take(ntile * 4);
+    l.tkey = take((size_t)((L + kTile - 1) / kTile) * 8);
     l.total = o;
     return l;
 }
@@ -307,15 +508,24 @@ extern "C" int s3_select_spans(const float* scores, int64_t n_positions, const f
     a.scores = scores; a.kernel = kernel; a.L = n_positions; a.K = K; a.n_centers = n_centers; a.radius = nms_radius;
     a.max_half = max_half_len; a.rel = rel_threshold;
     a.dens = density_out ? density_out : (float*)(base + l.dens);
-    a.dead = (unsigned char*)(base + l.dead);
-    a.tmaxv = (float*)(base + l.tmaxv);
-    a.tmaxi = (int*)(base + l.tmaxi);
-    a.ntile = (int)((n_positions + kSelTile - 1) / kSelTile);
+    a.tkey = (unsigned long long*)(base + l.tkey);
+    a.ntile = (int)((n_positions + kTile - 1) / kTile);
+    a.shift = 0;
+    while (((a.ntile + (1 << a.shift) - 1) >> a.shift) > kNmsTiles) ++a.shift;
     a.center = center; a.center_density = center_density; a.span_lo = span_lo; a.span_hi = span_hi; a.n_found = n_found;
     hipStream_t st = (hipStream_t)stream;
-    const size_t lds = (size_t)(2 * K - 1 + kSelTile) * 4;      // at most 36 KB: within the default limit
-    hipLaunchKernelGGL(sel_conv_kernel, dim3((unsigned)a.ntile), dim3(kConvThreads), lds, st, a);
-    hipLaunchKernelGGL(sel_nms_kernel, dim3(1), dim3(kNmsThreads), 0, st, a);
+    const bool large = n_positions >= kConvLargeFrom;
+    const int per_wg = (large ? kConvLarge : kConvSmall) * kConvPer;
+    const size_t lds = (size_t)(per_wg + 2 * ((K + 3) & ~3) + 4) * 4;      // at most 36 KB: within the default limit
+    const dim3 grid((unsigned)((n_positions + per_wg - 1) / per_wg));
+    if (large) hipLaunchKernelGGL(sel_conv_kernel<kConvLarge>, grid, dim3(kConvLarge), lds, st, a);
+    else hipLaunchKernelGGL(sel_conv_kernel<kConvSmall>, grid, dim3(kConvSmall), lds, st, a);
+    static S3LdsOnce once;
+    if (int rc = s3_allow_lds(once, (const void*)sel_nms_kernel, kNmsLds)) return rc;
+    const size_t nt = (size_t)((a.ntile + (1 << a.shift) - 1) >> a.shift);
+    const size_t fixed = (nt + (nt + 63) / 64) * 8 + (size_t)n_centers * 8;          // at most 97 KB
+    a.cached = fixed + (size_t)n_positions * 4 <= kNmsLds;                           // about 36000 positions
+    hipLaunchKernelGGL(sel_nms_kernel, dim3(1), dim3(kNmsThreads), fixed + (a.cached ? (size_t)n_positions * 4 : 0), st, a);
     S3_HIP(hipGetLastError());
     return S3_OK;
 }
@@ -343,16 +553,21 @@ extern "C" int s3_fuse_indices(int64_t n_positions, const int32_t* span_lo, cons
     hipStream_t st = (hipStream_t)stream;
     int* bsum = (int*)ws;
     const int nblocks = (int)((n_positions + kFuseBlock - 1) / kFuseBlock);
-    const unsigned gi = (unsigned)((n_positions + 255) / 256 > 4096 ? 4096 : (n_positions + 255) / 256);
-    hipLaunchKernelGGL(fuse_init_kernel, dim3(gi), dim3(256), 0, st, mask, n_positions, lead, tail);
-    const unsigned gm = (unsigned)max_spans + (unsigned)((n_extra + 255) / 256);
-    if (gm)
+    if ((int64_t)nblocks * (n_extra + max_spans) <= kFuseLookMax) {
+        hipLaunchKernelGGL(fuse_block_kernel, dim3((unsigned)nblocks), dim3(kFuseThreads), 0, st, mask, n_positions, span_lo,
+                           span_hi, n_spans, max_spans, extra, n_extra, lead, tail, bsum);
+    } else {
+        const unsigned gi = (unsigned)((n_positions + 255) / 256 > 4096 ? 4096 : (n_positions + 255) / 256);
+        hipLaunchKernelGGL(fuse_init_kernel, dim3(gi), dim3(256), 0, st, mask, n_positions, lead, tail);
+        const unsigned gm = (unsigned)max_spans + (unsigned)((n_extra + 255) / 256);
         hipLaunchKernelGGL(fuse_mark_kernel, dim3(gm), dim3(256), 0, st, mask, n_positions, span_lo, span_hi, n_spans,
                            max_spans, extra, n_extra);
-    hipLaunchKernelGGL(fuse_count_kernel, dim3((unsigned)nblocks), dim3(kFuseThreads), 0, st, mask, n_positions, bsum);
-    hipLaunchKernelGGL(fuse_scan_kernel, dim3(1), dim3(kFuseThreads), 0, st, bsum, nblocks, n_out);
-    hipLaunchKernelGGL(fuse_compact_kernel, dim3((unsigned)nblocks), dim3(kFuseThreads), 0, st, mask, n_positions, bsum,
-                       idx_out);
+        hipLaunchKernelGGL(fuse_count_kernel, dim3((unsigned)nblocks), dim3(kFuseThreads), 0, st, mask, n_positions, bsum);
+    }
+    const int scanned = nblocks > kFuseSelfMax;
+    if (scanned) hipLaunchKernelGGL(fuse_scan_kernel, dim3(1), dim3(kFuseThreads), 0, st, bsum, nblocks, n_out);
+    hipLaunchKernelGGL(fuse_compact_kernel, dim3((unsigned)nblocks), dim3(kFuseThreads), 0, st, mask, n_positions, bsum, scanned,
+                       idx_out, n_out);
     S3_HIP(hipGetLastError());
     return S3_OK;
 }

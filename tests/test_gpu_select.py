@@ -129,3 +129,43 @@ def test_scores_to_fused_indices_chain():
     assert n == len(c_o) and np.array_equal(c.cpu().numpy()[:n], c_o)
     m_o, idx_o = orc.fuse(T, lo_o, hi_o, np.zeros(0, np.int32), 16, 16)
     assert np.array_equal(idx.cpu().numpy()[:int(n_out.item())], idx_o) and np.array_equal(mask.cpu().numpy(), m_o)
+
+
+@pytest.mark.parametrize("L,radius,n_centers", [
+    (64, 3, 40), (65, 64, 5), (4096, 1, 300), (4097, 63, 70),      # one tile, one more; a group of 64 tiles, one more
+    (30_011, 4100, 9), (36_000, 48, 40), (40_000, 48, 100),        # suppression over whole groups; the curve in LDS and not
+    (1 << 18, 17, 64), ((1 << 19) + 1, 64, 40), (1_100_003, 200, 70),      # wide convolution; tiles of 128 and of 256 positions
+])
+def test_peak_search_at_the_edges_of_its_tiles(L, radius, n_centers):
+    """Few distinct densities (a box kernel over 0/1 scores), so that ties across tiles and groups are common."""
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(L)
+    S = (rng.random(L) < 0.3).astype(np.float32)
+    g = s3.smoothing_kernel(s3.KERNEL_BOX, 6)
+    c, dc, lo, hi, nf, D = s3.select_spans(torch.from_numpy(S).cuda(), g, n_centers, radius, 0.5, 70, want_density=True)
+    torch.cuda.synchronize()
+    D32, c_o, pk_o, lo_o, hi_o = oracle_select(S, g.cpu().numpy(), n_centers, radius, 0.5, 70)
+    n = int(nf.item())
+    assert np.array_equal(D.cpu().numpy(), D32) and n == len(c_o)
+    assert np.array_equal(c.cpu().numpy()[:n], c_o) and np.array_equal(dc.cpu().numpy()[:n], pk_o.astype(np.float32))
+    assert np.array_equal(lo.cpu().numpy()[:n], lo_o) and np.array_equal(hi.cpu().numpy()[:n], hi_o)
+
+
+@pytest.mark.parametrize("L,ns,n_extra", [(1023, 1, 1), (1024, 300, 257), (1025, 0, 3), (5 << 20, 70, 9), (100_000, 4000, 200_000)])
+def test_fuse_indices_block_edges(L, ns, n_extra):
+    """Around a block of positions, counts scanned by their own launch (5 M), lists too long for every block to look through."""
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(L)
+    lo = rng.integers(-5, L + 5, ns).astype(np.int32)
+    hi = (lo + rng.integers(-2, 20, ns)).astype(np.int32)                      # some empty, some outside
+    if ns:
+        lo[0], hi[0] = L - 3, -2 ** 31                                         # far below every block
+    extra = rng.integers(-10, L + 10, n_extra).astype(np.int32)
+    mask, idx, n_out = s3.fuse_indices(L, torch.from_numpy(lo).cuda(), torch.from_numpy(hi).cuda(), None,
+                                       torch.from_numpy(extra).cuda(), 3, 2)
+    torch.cuda.synchronize()
+    m_o, idx_o = orc.fuse(L, lo, hi, extra, 3, 2)
+    n = int(n_out.item())
+    assert n == len(idx_o) and np.array_equal(mask.cpu().numpy(), m_o) and np.array_equal(idx.cpu().numpy()[:n], idx_o)
