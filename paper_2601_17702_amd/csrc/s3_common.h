@@ -87,6 +87,19 @@ __device__ __forceinline__ int s3_wave_incl_scan(int x) {
     return x;
 }
 
+// Largest value of the wavefront, in every lane.
+__device__ __forceinline__ unsigned s3_wave_max_u32(unsigned x) {
+#define S3_DPP_MAX(CTRL, ROWS) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false))
+    S3_DPP_MAX(0x111, 0xf);
+    S3_DPP_MAX(0x112, 0xf);
+    S3_DPP_MAX(0x114, 0xf);
+    S3_DPP_MAX(0x118, 0xf);
+    S3_DPP_MAX(0x142, 0xa);
+    S3_DPP_MAX(0x143, 0xc);
+#undef S3_DPP_MAX
+    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 // Exclusive prefix sum of one int per thread over the block, in thread order.  wsum: one int per wavefront.
 template <int NT>
 __device__ __forceinline__ int s3_block_excl_scan(int v, int* wsum, int& total) {

@@ -53,9 +53,9 @@ struct ScoreArgs {
     unsigned long long* part;        // [ngroup][L] partial sums of head groups (ngroup > 1)
     int pb, npb, heads_per, ngroup, sorted;   // position blocks / head groups of the gather
     long long* wfix;                 // [nW]
-    long long* tmaxv;                // [ntile]
-    int* tmaxi;                      // [ntile]
-    int ntile;
+    unsigned long long* tmaxv;       // [nsub] best window of every kSubW starts: its sum + 1, 0 for none
+    int* tmaxi;                      // [nsub] its start
+    int ntile, nsub, topshift;       // tiles of kTileW starts; the Top-B search works on tiles of kSubW << topshift
     float* scores_out;
     int32_t* span_start;
     float* span_score;
@@ -66,7 +66,10 @@ constexpr int kRange = 16384;        // features whose sums one workgroup of sc_
 constexpr int kPrepThreads = 1024;
 constexpr int kRun = 32;             // consecutive windows per thread (sliding sum, exact in integers)
 constexpr int kTileW = 64 * kRun;    // windows per tile = per wavefront of the pooling kernel
+constexpr int kSubLog2 = 8;
+constexpr int kSubW = 1 << kSubLog2; // windows per entry of the tile maxima
 constexpr int kTopThreads = 256;
+constexpr int kTopTiles = 4096;      // tiles of the Top-B search (LDS)
 
 __device__ __forceinline__ int exp_s(unsigned long long wmax_bits, int hb) {   // weights are scaled by 2^exp_s: sums < 2^62
     double w = __longlong_as_double((long long)wmax_bits);
@@ -386,30 +389,13 @@ __global__ __launch_bounds__(kScatterThreads) void sc_scatter_lds_kernel(ScoreAr
     for (int64_t i = tid; i < (int64_t)span; i += kScatterThreads) dst[p0 + i] = sblk[i];
 }
 
-// (value, index) argmax over the block: larger value wins, ties -> smaller index; value -1 = nothing
-template <int NT>
-__device__ __forceinline__ void block_argmax(long long& v, int& i, long long* sv, int* si) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        unsigned int lo = (unsigned int)__shfl_xor((int)(unsigned int)(unsigned long long)v, o);
-        unsigned int hi = (unsigned int)__shfl_xor((int)(unsigned int)((unsigned long long)v >> 32), o);
-        long long ov = (long long)(((unsigned long long)hi << 32) | lo);
-        int oi = __shfl_xor(i, o);
-        if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
-    }
-    const int wave = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) { sv[wave] = v; si[wave] = i; }
-    __syncthreads();
-    long long bv = sv[0];
-    int bi = si[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; ++w) {
-        long long ov = sv[w];
-        int oi = si[w];
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    }
-    v = bv; i = bi;
+// The wavefront's best window, in every lane: largest key (sum + 1; 0: none), ties -> smallest start.
+__device__ __forceinline__ void wave_best(unsigned long long& key, int& start) {
+    const unsigned hi = s3_wave_max_u32((unsigned)(key >> 32));
+    const unsigned lo = s3_wave_max_u32((unsigned)(key >> 32) == hi ? (unsigned)key : 0u);
+    const unsigned long long best = ((unsigned long long)hi << 32) | lo;
+    start = (int)~s3_wave_max_u32(key == best ? ~(unsigned)start : 0u);
+    key = best;
 }
 
 // S = sum of the head groups' partial arrays.  64 positions per workgroup, four threads per position (each takes
@@ -451,7 +437,7 @@ __device__ __forceinline__ unsigned long long block_incl_scan_u64(unsigned long 
     return v + base;
 }
 
-// Span pooling, the fp32 scores, and the best window of every tile of kTileW windows (one workgroup per tile).
+// Span pooling, the fp32 scores, and the best window of every kSubW windows (one workgroup per kTileW windows).
 // The tile's positions are staged in LDS and turned into prefix sums there, so a window costs two LDS reads
 // whatever its length: W[s] = P[s + len - 1] - P[s - 1], exact in 64-bit integers.  Larger value wins, ties ->
 // smaller start.
@@ -461,46 +447,58 @@ constexpr int kPoolMaxLen = 4096;      // longer windows take sc_pool_wide_kerne
 __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
     extern __shared__ unsigned long long pre[];          // [kTileW + len - 1 (+ padding)] prefix sums
     __shared__ unsigned long long wsum[kPoolThreads / 64];
-    __shared__ long long sv[kPoolThreads / 64];
-    __shared__ int si[kPoolThreads / 64];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
     const int64_t s0 = (int64_t)blockIdx.x * kTileW;
     const int64_t tend = (int)blockIdx.x == a.ntile - 1 ? a.L : s0 + kTileW;      // positions whose fp32 score this tile writes
     const int n_in = (int)(min(a.L, s0 + kTileW + a.len - 1) - s0);               // positions the tile's windows read
-    constexpr int kPer = (kTileW + kPoolMaxLen + kPoolThreads - 1) / kPoolThreads;
-    const int per = (n_in + kPoolThreads - 1) / kPoolThreads;                     // consecutive positions per thread (<= kPer)
+    constexpr int kBatch = 5;                                                     // coalesced loads in flight per thread
+    for (int i0 = tid; i0 < n_in; i0 += kBatch * kPoolThreads) {
+        unsigned long long v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) v[u] = i0 + u * kPoolThreads < n_in ? a.sfix[s0 + i0 + u * kPoolThreads] : 0ull;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int i = i0 + u * kPoolThreads;
+            if (i >= n_in) continue;
+            pre[i] = v[u];
+            if (a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)v[u] * inv);
+        }
+    }
+    __syncthreads();
     // each thread sums its own run, the block scans the run totals, the thread writes its run's prefixes
+    const int per = (n_in + kPoolThreads - 1) / kPoolThreads;                     // consecutive positions per thread
     unsigned long long run = 0;
     for (int j = 0; j < per; ++j) {
         const int i = tid * per + j;
-        if (i < n_in) {
-            const unsigned long long v = a.sfix[s0 + i];
-            if (a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)v * inv);
-            run += v;
-            pre[i] = run;
-        }
+        if (i < n_in) run += pre[i];
     }
-    (void)kPer;
-    const unsigned long long incl = block_incl_scan_u64<kPoolThreads>(run, wsum);
-    const unsigned long long base = incl - run;
+    unsigned long long sum = block_incl_scan_u64<kPoolThreads>(run, wsum) - run;
     for (int j = 0; j < per; ++j) {
         const int i = tid * per + j;
-        if (i < n_in) pre[i] += base;
-    }
-    __syncthreads();
-    long long bv = -1;
-    int bi = 0x7FFFFFFF;
-    for (int q = tid; q < kTileW; q += kPoolThreads) {                            // ascending starts per thread
-        const int64_t sw = s0 + q;
-        if (sw < a.nW) {
-            const long long w = (long long)(pre[q + a.len - 1] - (q ? pre[q - 1] : 0ull));
-            a.wfix[sw] = w;
-            if (w > bv) { bv = w; bi = (int)sw; }
+        if (i < n_in) {
+            sum += pre[i];
+            pre[i] = sum;
         }
     }
-    block_argmax<kPoolThreads>(bv, bi, sv, si);
-    if (tid == 0) { a.tmaxv[blockIdx.x] = bv; a.tmaxi[blockIdx.x] = bi; }
+    __syncthreads();
+    for (int q = wave; q < kTileW / kSubW; q += kPoolThreads / 64) {
+        const int sub = (int)blockIdx.x * (kTileW / kSubW) + q;
+        if (sub >= a.nsub) break;
+        unsigned long long key = 0;
+        int start = 0x7FFFFFFF;
+#pragma unroll
+        for (int u = 0; u < kSubW / 64; ++u) {                                    // ascending starts per lane
+            const int i = q * kSubW + u * 64 + lane;
+            if (s0 + i < a.nW) {
+                const unsigned long long w = pre[i + a.len - 1] - (i ? pre[i - 1] : 0ull);
+                a.wfix[s0 + i] = (long long)w;
+                if (w + 1 > key) { key = w + 1; start = (int)(s0 + i); }
+            }
+        }
+        wave_best(key, start);
+        if (lane == 0) { a.tmaxv[sub] = key; a.tmaxi[sub] = start; }
+    }
 }
 
 // The same for windows longer than kPoolMaxLen: sliding sums from global memory, one wavefront per tile.
@@ -513,101 +511,110 @@ __global__ __launch_bounds__(256) void sc_pool_wide_kernel(ScoreArgs a) {
     const int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (tile >= a.ntile) return;
     const int64_t s0 = tile * kTileW + (int64_t)lane * kRun;
-    long long bv = -1;
-    int bi = 0x7FFFFFFF;
+    unsigned long long key = 0;
+    int start = 0x7FFFFFFF;
     if (s0 < a.nW) {
         unsigned long long acc = 0;
         for (int t = 0; t < a.len; ++t) acc += a.sfix[s0 + t];
         a.wfix[s0] = (long long)acc;
-        bv = (long long)acc;
-        bi = (int)s0;
+        key = acc + 1;
+        start = (int)s0;
         for (int j = 1; j < kRun && s0 + j < a.nW; ++j) {
             acc += a.sfix[s0 + j + a.len - 1] - a.sfix[s0 + j - 1];
             a.wfix[s0 + j] = (long long)acc;
-            if ((long long)acc > bv) { bv = (long long)acc; bi = (int)(s0 + j); }
+            if (acc + 1 > key) { key = acc + 1; start = (int)(s0 + j); }
         }
     }
+    constexpr int kLanes = kSubW / kRun;                  // lanes that share one entry of the tile maxima
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        unsigned int lo = (unsigned int)__shfl_xor((int)(unsigned int)(unsigned long long)bv, o);
-        unsigned int hi = (unsigned int)__shfl_xor((int)(unsigned int)((unsigned long long)bv >> 32), o);
-        long long ov = (long long)(((unsigned long long)hi << 32) | lo);
-        int oi = __shfl_xor(bi, o);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    for (int o = kLanes / 2; o > 0; o >>= 1) {
+        const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)key, o), hi = (unsigned)__shfl_xor((int)(unsigned)(key >> 32), o);
+        const unsigned long long other = ((unsigned long long)hi << 32) | lo;
+        const int os = __shfl_xor(start, o);
+        if (other > key || (other == key && os < start)) { key = other; start = os; }
     }
-    if (lane == 0) { a.tmaxv[tile] = bv; a.tmaxi[tile] = bi; }
+    const int64_t sub = tile * (kTileW / kSubW) + lane / kLanes;
+    if (lane % kLanes == 0 && sub < a.nsub) { a.tmaxv[sub] = key; a.tmaxi[sub] = start; }
 }
 
-// Greedy Top-B with optional suppression of overlapping windows.  One small workgroup: the rounds depend on each
-// other.  The tile maxima live in LDS (up to kTopCache tiles; in global memory beyond that); a round takes the best
-// one, then searches the tiles again that the new span's suppression touches.  Whether a window is still alive
-// follows from the spans chosen so far (kept in LDS): no flag array in memory, one global round trip per round.
-constexpr int kTopCache = 4096;
-
+// Greedy Top-B with optional suppression of overlapping windows.  The rounds depend on each other, so what bounds it is
+// the latency of a round: one wavefront walks them without a barrier over tile maxima in LDS.  A round takes the best
+// tile, clears the tiles that the suppression covers whole and searches the two at its ends again, loads of both in
+// flight together.  A window that is gone is marked -1 in memory; window s belongs to lane s % 64 in every round, so a
+// lane only ever reads back its own marks.  A tile without live windows stays so (its windows need not be marked).
+// With 256 threads, tiles of 2048 windows and a search through the spans chosen so far a round had nine barriers:
+// a look-up of one token in 256 indexes of 32768 positions (16 spans of 64) took 238 us, now 211 us.
 __global__ __launch_bounds__(kTopThreads) void sc_topb_kernel(ScoreArgs a) {
-    __shared__ long long sv[kTopThreads / 64];
-    __shared__ int si[kTopThreads / 64];
-    __shared__ long long cv[kTopCache];
-    __shared__ int ci[kTopCache];
-    __shared__ int sel[1024];
-    const int tid = threadIdx.x;
-    const bool cached = a.ntile <= kTopCache;
-    const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
-    if (cached)
-        for (int t = tid; t < a.ntile; t += kTopThreads) { cv[t] = a.tmaxv[t]; ci[t] = a.tmaxi[t]; }
-    __syncthreads();
-    int found = 0;
-    for (int r = 0; r < a.top_b; ++r) {
-        long long v = -1;
-        int i = 0x7FFFFFFF;
-        for (int t = tid; t < a.ntile; t += kTopThreads) {
-            const long long tv = cached ? cv[t] : a.tmaxv[t];
-            const int ti = cached ? ci[t] : a.tmaxi[t];
-            if (tv > v || (tv == v && ti < i)) { v = tv; i = ti; }
-        }
-        block_argmax<kTopThreads>(v, i, sv, si);
-        if (v < 0) break;
-        if (tid == 0) {
-            a.span_start[r] = i;
-            a.span_score[r] = (float)((double)v * inv);
-            sel[r] = i;
-        }
-        found = r + 1;
-        __syncthreads();
-        const int reach = a.nms ? a.len - 1 : 0;              // windows within `reach` of a chosen start are gone
-        const int64_t lo = max((int64_t)0, (int64_t)i - reach), hi = min(a.nW - 1, (int64_t)i + reach);
-        for (int t = (int)(lo / kTileW); t <= (int)(hi / kTileW); ++t) {
-            const int64_t t0 = (int64_t)t * kTileW;
-            long long w[kTileW / kTopThreads];
-#pragma unroll
-            for (int q = 0; q < kTileW / kTopThreads; ++q) {  // all loads first: one round trip
-                const int64_t sw = t0 + q * kTopThreads + tid;
-                w[q] = sw < a.nW ? a.wfix[sw] : -1;
-            }
-            for (int j = 0; j < found; ++j) {                 // chosen spans that reach into this tile
-                const int64_t c = sel[j];
-                if (c + reach < t0 || c - reach >= t0 + kTileW) continue;
-#pragma unroll
-                for (int q = 0; q < kTileW / kTopThreads; ++q) {
-                    const int64_t sw = t0 + q * kTopThreads + tid;
-                    if (sw >= c - reach && sw <= c + reach) w[q] = -1;
-                }
-            }
-            long long tv = -1;
-            int ti = 0x7FFFFFFF;
-#pragma unroll
-            for (int q = 0; q < kTileW / kTopThreads; ++q)    // ascending starts per thread: the first best one is kept
-                if (w[q] > tv) { tv = w[q]; ti = (int)(t0 + q * kTopThreads + tid); }
-            block_argmax<kTopThreads>(tv, ti, sv, si);
-            if (tid == 0) {
-                if (cached) { cv[t] = tv; ci[t] = ti; }
-                else { a.tmaxv[t] = tv; a.tmaxi[t] = ti; }
-            }
-        }
-        __syncthreads();
+    __shared__ unsigned long long cv[kTopTiles];
+    __shared__ int ci[kTopTiles];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int per = 1 << a.topshift, nt = (a.nsub + per - 1) >> a.topshift;
+    for (int t = tid; t < nt; t += kTopThreads) {
+        unsigned long long key = 0;
+        int start = 0x7FFFFFFF;
+        const int64_t e0 = (int64_t)t << a.topshift, e1 = min((int64_t)a.nsub, e0 + per);
+        for (int64_t e = e0; e < e1; ++e)
+            if (a.tmaxv[e] > key) { key = a.tmaxv[e]; start = a.tmaxi[e]; }
+        cv[t] = key;
+        ci[t] = start;
     }
-    for (int r = found + tid; r < a.top_b; r += kTopThreads) { a.span_start[r] = -1; a.span_score[r] = 0.f; }
-    if (tid == 0) a.n_found[0] = found;
+    __syncthreads();
+    if (tid >= 64) return;
+    const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
+    const int tlog = kSubLog2 + a.topshift;
+    const int reach = a.nms ? a.len - 1 : 0;              // windows within `reach` of a chosen start are gone
+    int found = 0;
+    while (found < a.top_b) {
+        unsigned long long key = 0;
+        int start = 0x7FFFFFFF;
+        for (int t = lane; t < nt; t += 64) {             // ascending starts per lane
+            const unsigned long long tv = cv[t];
+            const int ti = ci[t];
+            if (tv > key) { key = tv; start = ti; }
+        }
+        wave_best(key, start);
+        if (key == 0) break;
+        if (lane == 0) {
+            a.span_start[found] = start;
+            a.span_score[found] = (float)((double)(long long)(key - 1) * inv);
+        }
+        ++found;
+        const int64_t lo = max((int64_t)0, (int64_t)start - reach), hi = min(a.nW - 1, (int64_t)start + reach);
+        const int tl = (int)(lo >> tlog), th = (int)(hi >> tlog);
+        const bool live_l = cv[tl] != 0, live_h = cv[th] != 0;
+        for (int t = tl + 1 + lane; t < th; t += 64) cv[t] = 0;
+        unsigned long long kl = 0, kh = 0;
+        int sl = 0x7FFFFFFF, sh = 0x7FFFFFFF;
+        for (int s = 0; s < per; ++s) {
+            const int64_t b0 = ((int64_t)tl << tlog) + s * kSubW + lane, b1 = ((int64_t)th << tlog) + s * kSubW + lane;
+            constexpr int U = kSubW / 64;
+            long long w0[U], w1[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                w0[u] = b0 + u * 64 < a.nW ? a.wfix[b0 + u * 64] : -1;
+                w1[u] = b1 + u * 64 < a.nW ? a.wfix[b1 + u * 64] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {                 // one store per window and round where tl == th: the same mark
+                const int64_t p0 = b0 + u * 64, p1 = b1 + u * 64;
+                if (p0 >= lo && p0 <= hi) { w0[u] = -1; a.wfix[p0] = -1; }
+                if (p1 >= lo && p1 <= hi) { w1[u] = -1; a.wfix[p1] = -1; }
+                const unsigned long long k0 = (unsigned long long)(w0[u] + 1), k1 = (unsigned long long)(w1[u] + 1);
+                if (k0 > kl) { kl = k0; sl = (int)p0; }
+                if (k1 > kh) { kh = k1; sh = (int)p1; }
+            }
+        }
+        wave_best(kl, sl);
+        wave_best(kh, sh);
+        if (lane == 0) {                                  // the same values where tl == th
+            cv[tl] = live_l ? kl : 0ull;
+            ci[tl] = sl;
+            cv[th] = live_h ? kh : 0ull;
+            ci[th] = sh;
+        }
+    }
+    for (int r = found + lane; r < a.top_b; r += 64) { a.span_start[r] = -1; a.span_score[r] = 0.f; }
+    if (lane == 0) a.n_found[0] = found;
 }
 
 struct Layout {
@@ -620,14 +627,14 @@ Layout layout(int n_heads, int n_feat, int64_t L) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += s3_align(bytes); return at; };
     const int64_t nW_max = L;
-    const size_t ntile = (size_t)(nW_max + kTileW - 1) / kTileW;
+    const size_t nsub = (size_t)(nW_max + kSubW - 1) / kSubW;
     l.nr = (n_feat + kRange - 1) / kRange;
     l.wmax = take(((size_t)n_heads * l.nr + 1) * 8);
     l.nact = take((size_t)n_heads * l.nr * 4);
     l.sfix = take((size_t)L * 8);
     l.wfix = take((size_t)L * 8);
-    l.tmaxv = take(ntile * 8);
-    l.tmaxi = take(ntile * 4);
+    l.tmaxv = take(nsub * 8);
+    l.tmaxi = take(nsub * 4);
     // position blocks of at most kMaxPB scores (128 KB of LDS); enough head groups for about one workgroup per compute unit
     l.pb = (int)(L < kMaxPB ? (L + 63) / 64 * 64 : kMaxPB);
     l.npb = (int)((L + l.pb - 1) / l.pb);
@@ -690,11 +697,15 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.sfix = (unsigned long long*)(base + l.sfix);
     a.act = (ActiveList*)(base + l.act);
     a.wfix = (long long*)(base + l.wfix);
-    a.tmaxv = (long long*)(base + l.tmaxv);
+    a.tmaxv = (unsigned long long*)(base + l.tmaxv);
     a.tmaxi = (int*)(base + l.tmaxi);
     a.part = (unsigned long long*)(base + l.part);
     a.pb = l.pb; a.npb = l.npb; a.heads_per = l.heads_per; a.ngroup = l.ngroup; a.sorted = v.sorted ? 1 : 0;
     a.ntile = (int)((a.nW + kTileW - 1) / kTileW);
+    a.nsub = (int)((a.nW + kSubW - 1) / kSubW);
+    // the smallest tiles whose maxima fit the search's LDS: beyond 1M windows a round reads more windows instead
+    a.topshift = 0;
+    while (((a.nsub - 1) >> a.topshift) + 1 > kTopTiles) ++a.topshift;
     a.scores_out = scores_out; a.span_start = span_start; a.span_score = span_score; a.n_found = n_found;
 
     hipStream_t st = (hipStream_t)stream;

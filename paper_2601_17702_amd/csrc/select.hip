@@ -49,21 +49,10 @@ __device__ __forceinline__ unsigned long long peak_key(float d, int64_t t) {
     return d > 0.f ? ((unsigned long long)__float_as_uint(d) << 32) | (unsigned)~(unsigned)t : 0ull;
 }
 
-__device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
-#define S3_DPP_MAX(CTRL, ROWS) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false))
-    S3_DPP_MAX(0x111, 0xf);
-    S3_DPP_MAX(0x112, 0xf);
-    S3_DPP_MAX(0x114, 0xf);
-    S3_DPP_MAX(0x118, 0xf);
-    S3_DPP_MAX(0x142, 0xa);
-    S3_DPP_MAX(0x143, 0xc);
-#undef S3_DPP_MAX
-    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
-}
 // Largest key of the wavefront, in every lane: the high words first, then the low words of the lanes that hold it.
 __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v) {
-    const unsigned hi = wave_max_u32((unsigned)(v >> 32));
-    const unsigned lo = wave_max_u32((unsigned)(v >> 32) == hi ? (unsigned)v : 0u);
+    const unsigned hi = s3_wave_max_u32((unsigned)(v >> 32));
+    const unsigned lo = s3_wave_max_u32((unsigned)(v >> 32) == hi ? (unsigned)v : 0u);
     return ((unsigned long long)hi << 32) | lo;
 }
 

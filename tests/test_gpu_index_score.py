@@ -310,6 +310,31 @@ def test_scoring_of_long_contexts(T):
     check_score(run_gpu_score(ix, qids, qvals, T, 128, 16, 0, True), S, W, st_o, sc_o, 128, True)
 
 
+@pytest.mark.parametrize("T,span_len,top_b,nms", [
+    (256, 1, 256, True),          # one tile of 256 windows, all of them taken one by one
+    (257, 1, 257, False),         # a second tile with a single window
+    (64, 64, 3, True),            # one window
+    (2303, 256, 9, True),         # 2048 windows: suppressions that end at tile borders
+    (2304, 257, 9, True),
+    (5000, 100, 60, True),        # most tiles are searched again several times
+    (9000, 900, 12, True),        # the suppression covers whole tiles between the two at its ends
+    (9000, 900, 40, False),       # overlapping windows: one start goes per round
+    (12000, 4096, 4, True),       # longest window of the pooling kernel that stages its tile
+    (12000, 4097, 4, True),       # shortest one of the other
+])
+def test_greedy_spans_over_tile_borders(T, span_len, top_b, nms):
+    """Every position has a feature of its own and a weight drawn in 24 bits, so window sums differ by far more than the
+    fixed-point sums round (2^-44 of the largest weight here): the chosen starts are the oracle's, one by one."""
+    rng = np.random.default_rng(T + span_len)
+    ids = rng.permutation(T).astype(np.int32)[None, :, None]
+    qids, qvals = ids.copy(), (rng.random((1, T, 1)) + 0.01).astype(np.float32)
+    ix = gpu_index(ids, T)
+    S, W, st_o, sc_o = oracle_score(ids, qids, qvals, T, T, span_len, top_b, 0, nms)
+    out = run_gpu_score(ix, qids, qvals, T, span_len, top_b, 0, nms)
+    check_score(out, S, W, st_o, sc_o, span_len, nms)
+    assert out[0][:out[2]].tolist() == list(st_o)
+
+
 def test_scoring_with_shifted_positions_and_index_reuse():
     """Positions that start at an offset: inside the range the index's block table covers (table used), beyond it
     (lists are searched instead), and the same index object reset and fed another stream (table rebuilt)."""
