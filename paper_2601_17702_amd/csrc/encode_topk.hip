@@ -319,21 +319,35 @@ int launch(const TileArgs& a, hipStream_t st) {
     return S3_OK;
 }
 
-// Feature ranges of a call: as many workgroups as fill the chip twice, whole chunks per range, a bounded number of list
-// entries in scratch.
-constexpr int kFillWGs = 512;
-constexpr long long kPartEntries = 4LL << 20;
+// Feature ranges of a call.  A workgroup fills a compute unit's LDS, so a call takes as many turns as its workgroups are
+// multiples of 256; every turn costs its range's chunks and about kWarm more until the lists are full.  The number of
+// ranges with the smallest sum is taken (the smaller one of equals; 1 beyond two turns of whole tokens, where there is
+// little to gain).  2048 fp32 tokens x 4096 features of width 128, k 16: four ranges 53 us, eight ranges 69 us.
+constexpr int kSlots = 256;
+constexpr int kWarm = 4;
+constexpr long long kPartEntries = 4LL << 20;          // list entries in scratch at most
+long long token_tiles(int n_heads, int T) { return (long long)n_heads * ((T + kTok - 1) / kTok); }
 int parts_for(int n_heads, int T, int n_feat, int k) {
-    const long long tiles = (long long)n_heads * ((T + kTok - 1) / kTok);
+    const long long tiles = token_tiles(n_heads, T);
+    if (tiles > 2 * kSlots) return 1;
     const int chunks = (n_feat + kChunk - 1) / kChunk;
-    const long long rows = (long long)n_heads * T;
-    long long want = (kFillWGs + tiles - 1) / tiles;
-    want = want > chunks ? chunks : want;
-    while (want > 1 && rows * want * k > kPartEntries) --want;
-    if (want <= 1) return 1;
-    const int per = (int)((chunks + want - 1) / want);
-    return (chunks + per - 1) / per;
+    int best = 1;
+    long long least = 0;
+    for (int want = 1; want <= chunks; ++want) {
+        const int per = (chunks + want - 1) / want, parts = (chunks + per - 1) / per;
+        if (parts != want || (want > 1 && (long long)n_heads * T * want * k > kPartEntries)) continue;
+        const long long cost = (tiles * parts + kSlots - 1) / kSlots * (per + kWarm);
+        if (want == 1 || cost < least) { best = want; least = cost; }
+    }
+    return best;
 }
+
+// Whether a plain call of a shape that the fast kernel takes is better off here: while its token tiles fit the chip at
+// once.  The fast kernel has 64 to 256 tokens per workgroup and walks all features in each.  us, fast / this kernel, of
+// 16384 features: 4 tokens of 8 heads, k 32: 224 / 34; 4096 tokens of one head, k 32: 439 / 130, k 128: 500 / 227;
+// at the line, 256 tiles: 8192 tokens of one head, k 8 / 32 / 64 / 128: 343 / 154, 440 / 193, 437 / 232, 506 / 294.  Beyond
+// it a second turn costs as much again, and the fast kernel's time does not grow before its own workgroups fill the chip.
+bool tiled_pays(int n_heads, int T) { return token_tiles(n_heads, T) <= kSlots; }
 
 }  // namespace
 
@@ -378,7 +392,7 @@ static int tiled_launch(const EncParams& p, int dtype, int d_head, int parts, ui
 }
 
 static size_t plain_workspace(int dtype, int T, int d_head, int n_feat, int k, int n_heads) {
-    if (s3_encode_fast_ok(dtype, d_head, n_feat, k)) return 0;
+    if (s3_encode_fast_ok(dtype, d_head, n_feat, k) && !tiled_pays(n_heads, T)) return 0;
     const int parts = parts_for(n_heads, T, n_feat, k);
     return parts > 1 ? (size_t)n_heads * T * parts * k * sizeof(uint2) : 0;
 }
@@ -408,7 +422,10 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
     p.T = T; p.n_feat = n_feat; p.k = k; p.n_heads = n_heads;
     p.ablate = 0;
     p.fsplit = 1;
-    bool fast = s3_encode_fast_ok(dtype, d_head, n_feat, k);
+    int parts = tau_hint ? 1 : parts_for(n_heads, T, n_feat, k);
+    const bool room = parts == 1 || (ws && ws_bytes >= (size_t)n_heads * T * parts * k * sizeof(uint2));
+    if (!room) parts = 1;                                    // no scratch: one range
+    bool fast = s3_encode_fast_ok(dtype, d_head, n_feat, k) && (tau_hint || !room || !tiled_pays(n_heads, T));
 #ifdef S3_TUNING
     p.ablate = env_int("S3_ENC_ABLATE", 0);
     if (env_int("S3_ENC_GENERIC", 0)) fast = false;
@@ -418,8 +435,6 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
         return tau_hint ? s3_encode_fast_stream(p, tau_hint, ws, st) : s3_encode_fast_launch(p, st);
     if (k > largest_k(dtype, d_head))
         return s3_fail(S3_EINVAL, "%s: k %d > %d for this dtype and d_head", who, k, largest_k(dtype, d_head));
-    int parts = parts_for(n_heads, T, n_feat, k);
-    if (!ws || ws_bytes < (size_t)n_heads * T * parts * k * sizeof(uint2)) parts = 1;      // no scratch: one range
     return tiled_launch(p, dtype, d_head, parts, (uint2*)ws, st);
 }
 

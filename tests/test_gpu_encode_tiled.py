@@ -66,3 +66,25 @@ def test_ties_across_chunks_and_ranges_take_the_lower_id(dtype, d, k):
     for ids, vals in (s3.sae_encode_topk(xg, Wg, bg, k), unsplit(s3, xg, Wg, bg, k)):
         torch.cuda.synchronize()
         assert np.array_equal(ids[0].cpu().numpy(), o["ids"]) and np.array_equal(vals[0].cpu().numpy(), o["vals"])
+
+
+@pytest.mark.parametrize("heads,T,n_feat,k", [
+    (2, 4, 32768, 128),      # as many ranges as there are chunks
+    (1, 4096, 1024, 128),    # 128 token tiles: two ranges
+    (1, 4097, 640, 33),      # 129 tiles: one range
+    (8, 1024, 384, 64),      # 256 tiles, the most that are taken here
+    (1, 8193, 384, 7),       # one more: the fast kernel
+    (260, 3, 128, 1),
+])
+def test_bf16_128_calls_of_few_tokens_match_the_fast_kernel(heads, T, n_feat, k):
+    """A plain call of few tokens runs tiled, a streamed one on the fast kernel: both accumulate alike, so equal bits."""
+    import torch
+    import paper_2601_17702_amd as s3
+    g = torch.Generator(device="cuda").manual_seed(heads + T + n_feat + k)
+    x = torch.randn(heads, T, 128, generator=g, device="cuda").bfloat16()
+    W = (torch.randn(heads, n_feat, 128, generator=g, device="cuda") / 11).bfloat16()
+    b = 0.1 * torch.randn(heads, n_feat, generator=g, device="cuda")
+    ids0, vals0 = s3.sae_encode_topk_stream(x, W, b, k, s3.new_tau_hint(heads))
+    for ids, vals in (s3.sae_encode_topk(x, W, b, k), unsplit(s3, x, W, b, k)):
+        torch.cuda.synchronize()
+        assert torch.equal(ids, ids0) and torch.equal(vals, vals0)
