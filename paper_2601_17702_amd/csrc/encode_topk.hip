@@ -322,7 +322,7 @@ int launch(const TileArgs& a, hipStream_t st) {
 // Feature ranges of a call.  A workgroup fills a compute unit's LDS, so a call takes as many turns as its workgroups are
 // multiples of 256; every turn costs its range's chunks and about kWarm more until the lists are full.  The number of
 // ranges with the smallest sum is taken (the smaller one of equals; 1 beyond two turns of whole tokens, where there is
-// little to gain).  2048 fp32 tokens x 4096 features of width 128, k 16: four ranges 53 us, eight ranges 69 us.
+// little to gain).  2048 fp32 tokens x 4096 features of width 128, k 16: four ranges 50 us, eight ranges 69 us.
 constexpr int kSlots = 256;
 constexpr int kWarm = 4;
 constexpr long long kPartEntries = 4LL << 20;          // list entries in scratch at most
