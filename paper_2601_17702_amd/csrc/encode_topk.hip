@@ -42,6 +42,7 @@ constexpr int kFT = 32;                     // features per wavefront and chunk 
 constexpr int kChunk = kWaves * kFT;        // features per chunk
 constexpr int kZRow = kChunk + 4;           // floats per token in the tile (16-byte writes of 16 tokens hit 64 banks)
 constexpr int kTokWave = kTok / kWaves;     // tokens a wavefront selects for
+static_assert(kTokWave == 4);
 
 // The MFMA operands of one element type.  The B fragments of the 32 tokens are held whole; a row of W is worked off in
 // pieces of up to 256 bytes.  offset(p, c): byte offset inside the row of 16-byte column c of piece p.
@@ -239,6 +240,7 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
         }
     }
 
+    int shorts = 0;
 #pragma unroll
     for (int q = 0; q < kTokWave; ++q) {
         const int t = wv * kTokWave + q;
@@ -259,7 +261,14 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
                     a.ids[row * a.k + rank[i]] = (int32_t)id[i];
                     a.vals[row * a.k + rank[i]] = fmaxf(value_of(key[i]), 0.f);
                 }
+            shorts |= cnt[q] < a.k ? 1 << q : 0;
         }
+    }
+    while (__builtin_expect(shorts != 0, 0)) {         // rows that their lists do not fill; beside the loop above, which stays short
+        const int q = __builtin_ctz(shorts), t = wv * kTokWave + q;
+        shorts &= shorts - 1;
+        const size_t row = (size_t)head * a.T + tok0 + t;
+        fill_short(a.k, q < 2 ? (q ? cnt[1] : cnt[0]) : (q == 2 ? cnt[2] : cnt[3]), lid + t * CAP, a.ids + row * a.k, a.vals + row * a.k);
     }
 }
 
@@ -306,6 +315,7 @@ __global__ __launch_bounds__(256) void enc_merge_kernel(const uint2* __restrict_
             ids[(size_t)row * k + rank[i]] = (int32_t)id[i];
             vals[(size_t)row * k + rank[i]] = fmaxf(value_of(key[i]), 0.f);
         }
+    if (cnt < k) fill_short(k, cnt, lid[wv], ids + (size_t)row * k, vals + (size_t)row * k);
 }
 
 template <int DT, int DH, int LR>

@@ -88,3 +88,35 @@ def test_bf16_128_calls_of_few_tokens_match_the_fast_kernel(heads, T, n_feat, k)
     for ids, vals in (s3.sae_encode_topk(x, W, b, k), unsplit(s3, x, W, b, k)):
         torch.cuda.synchronize()
         assert torch.equal(ids, ids0) and torch.equal(vals, vals0)
+
+
+@pytest.mark.parametrize("dtype,d,heads,T,n_feat,k,live", [
+    ("bf16", 128, 2, 3, 512, 64, 63),      # one element short of a full row; two ranges
+    ("bf16", 128, 1, 1, 640, 128, 0),      # no element at all; lists of 256
+    ("bf16", 64, 1, 33, 300, 65, 64),
+    ("fp32", 128, 1, 5, 16, 16, 5),        # every feature is in the row
+    ("fp32", 256, 3, 2, 1025, 2, 1),
+])
+def test_rows_with_fewer_than_k_elements_are_whole(dtype, d, heads, T, n_feat, k, live):
+    """A bias of -inf on all but `live` features: they come first, then the lowest other ids with value 0, as in a stable sort
+    of the pre-activations; a token of NaN has ids 0 .. k - 1.  Small integers, so the sums are exact."""
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(n_feat + k)
+    xf = rng.integers(-2, 3, (heads, T, d)).astype(np.float32)
+    Wf = rng.integers(-2, 3, (heads, n_feat, d)).astype(np.float32)
+    b = np.full((heads, n_feat), -np.inf, np.float32)
+    for h in range(heads):
+        b[h, rng.permutation(n_feat)[:live]] = 500.0
+    xf[0, T - 1, d // 2] = np.nan
+    z = np.einsum("htd,hfd->htf", xf, Wf) + b[:, None]
+    z = np.where(np.isnan(z), -np.inf, z)
+    want = np.argsort(-z, axis=2, kind="stable")[:, :, :k]
+    want_v = np.maximum(np.take_along_axis(z, want, axis=2), 0)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    xg, Wg, bg = torch.from_numpy(xf).cuda().to(dt), torch.from_numpy(Wf).cuda().to(dt), torch.from_numpy(b).cuda()
+    ids = torch.full((heads, T, k), -7, dtype=torch.int32, device="cuda")
+    vals = torch.full((heads, T, k), -7.0, device="cuda")
+    s3.sae_encode_topk(xg, Wg, bg, k, ids, vals)
+    torch.cuda.synchronize()
+    assert np.array_equal(ids.cpu().numpy(), want) and np.array_equal(vals.cpu().numpy(), want_v)
