@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
         f32x16 acc;
         auto piece = [&](auto P) {
             constexpr int p = decltype(P)::value;
-            wave_fence();
+            s3_wave_fence();
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 const int row = i * RPI + lrow;
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
             if (p == 0 && half == 0) bias[n] = breg;
             if (p + 1 < F::NP) gload(c, p + 1);
             else if (c + 1 < nchunk) gload(c + 1, 0);
-            wave_fence();
+            s3_wave_fence();
             if (p == 0) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {

@@ -100,6 +100,11 @@ __device__ __forceinline__ unsigned s3_wave_max_u32(unsigned x) {
     return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
 }
 
+// Between an access to LDS by one lane and an access to the same place by another lane of its wavefront.  The hardware runs a
+// wavefront's LDS accesses in order, but the compiler orders accesses only where one lane alone could meet the same place
+// twice.  No instruction comes of it.
+__device__ __forceinline__ void s3_wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // Exclusive prefix sum of one int per thread over the block, in thread order.  wsum: one int per wavefront.
 template <int NT>
 __device__ __forceinline__ int s3_block_excl_scan(int v, int* wsum, int& total) {

@@ -582,6 +582,7 @@ __global__ __launch_bounds__(kTopThreads) void sc_topb_kernel(ScoreArgs a) {
         const int64_t lo = max((int64_t)0, (int64_t)start - reach), hi = min(a.nW - 1, (int64_t)start + reach);
         const int tl = (int)(lo >> tlog), th = (int)(hi >> tlog);
         const bool live_l = cv[tl] != 0, live_h = cv[th] != 0;
+        s3_wave_fence();                                  // the maxima are read before lane 0 and the clearing lanes write them
         for (int t = tl + 1 + lane; t < th; t += 64) cv[t] = 0;
         unsigned long long kl = 0, kh = 0;
         int sl = 0x7FFFFFFF, sh = 0x7FFFFFFF;
@@ -612,6 +613,7 @@ __global__ __launch_bounds__(kTopThreads) void sc_topb_kernel(ScoreArgs a) {
             cv[th] = live_h ? kh : 0ull;
             ci[th] = sh;
         }
+        s3_wave_fence();
     }
     for (int r = found + lane; r < a.top_b; r += 64) { a.span_start[r] = -1; a.span_score[r] = 0.f; }
     if (lane == 0) a.n_found[0] = found;

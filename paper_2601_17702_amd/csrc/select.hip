@@ -228,11 +228,13 @@ __global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
 #pragma unroll
             for (int q = 0; q < kNmsGroups; ++q)
                 if (q * 64 + lane >= ga && q * 64 + lane <= gb) top[q] = 0;
+            if (a.cached)                                             // (shift is 0): the interval is wiped out of the curve in LDS
+                for (int64_t p = lo + lane; p <= hi; p += 64) cur[p] = 0.f;
+            s3_wave_fence();                                          // centre, cleared tiles and wiped positions are read by other lanes
             va = ga * 64 + lane < nt ? key[ga * 64 + lane] : 0ull;
             vb = gb * 64 + lane < nt ? key[gb * 64 + lane] : 0ull;
             unsigned long long kl = 0, kh = 0;                        // best live position of the tile at either end
-            if (a.cached) {                                           // (shift is 0): the interval is wiped out of the curve in LDS
-                for (int64_t p = lo + lane; p <= hi; p += 64) cur[p] = 0.f;
+            if (a.cached) {
                 const int64_t p0 = ((int64_t)tl << 6) + lane, p1 = ((int64_t)th << 6) + lane;
                 if (p0 < a.L) kl = peak_key(cur[p0], p0);
                 if (p1 < a.L) kh = peak_key(cur[p1], p1);
@@ -241,7 +243,9 @@ __global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
             else sel_rescan<4>(a, cen, found, tl, th, tlog, lane, kl, kh);
             kl = wave_max_key(kl);
             kh = wave_max_key(kh);
+            s3_wave_fence();                                          // va and vb are read
             if (lane == 0) { key[tl] = kl; key[th] = kh; }            // the same value where tl == th
+            s3_wave_fence();
             if (ga * 64 + lane == tl) va = kl;
             if (ga * 64 + lane == th) va = kh;
             if (gb * 64 + lane == tl) vb = kl;

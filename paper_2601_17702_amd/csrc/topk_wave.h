@@ -30,9 +30,6 @@ __device__ __forceinline__ unsigned wave_max_u(unsigned v) {
 #undef S3_DPP_MAX
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
-__device__ __forceinline__ void wave_fence() {                     // LDS written by one lane is read by another one
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-}
 
 template <int N>
 __device__ __forceinline__ int count_ge(const unsigned (&key)[N], unsigned m) {
@@ -107,7 +104,7 @@ __device__ __forceinline__ int cut_and_store(const unsigned (&key)[N], const uns
         }
         n += (int)__popcll(m);
     }
-    wave_fence();
+    s3_wave_fence();
     return n;
 }
 
@@ -135,7 +132,7 @@ __device__ __forceinline__ void take(const float (&v)[NC], IdOf id_of, int k, in
             }
             cnt += (int)__popcll(m[i]);
         }
-        wave_fence();
+        s3_wave_fence();
         return;
     }
     const int lane = threadIdx.x & 63;
@@ -169,7 +166,7 @@ __device__ __forceinline__ void finish(int k, float* lv, uint16_t* li, int cnt, 
     const int loose = k + (k >> 3) + 2;            // the ranks below tell the k best of a few more than k
     if (cnt > loose) {
         unsigned lo = 1u;
-        wave_fence();
+        s3_wave_fence();
         cnt = cut_and_store<LR>(key, id, k, loose, lo, cnt, lv, li);
 #pragma unroll
         for (int i = 0; i < LR; ++i) {
