@@ -336,7 +336,7 @@ int launch(const TileArgs& a, hipStream_t st) {
 constexpr int kSlots = 256;
 constexpr int kWarm = 4;
 constexpr long long kPartEntries = 4LL << 20;          // list entries in scratch at most
-long long token_tiles(int n_heads, int T) { return (long long)n_heads * ((T + kTok - 1) / kTok); }
+long long token_tiles(int n_heads, int T) { return (long long)n_heads * (((long long)T + kTok - 1) / kTok); }
 int parts_for(int n_heads, int T, int n_feat, int k) {
     const long long tiles = token_tiles(n_heads, T);
     if (tiles > 2 * kSlots) return 1;
@@ -380,7 +380,7 @@ static int tiled_launch(const EncParams& p, int dtype, int d_head, int parts, ui
     a.x = p.x; a.w = p.w; a.b = p.b; a.ids = p.ids; a.vals = p.vals;
     a.T = p.T; a.n_feat = p.n_feat; a.k = p.k;
     a.loose = p.k + (p.k >> 3) + 2;
-    a.tiles_per_head = (p.T + kTok - 1) / kTok;
+    a.tiles_per_head = (int)token_tiles(1, p.T);
     const int chunks = (p.n_feat + kChunk - 1) / kChunk;
     a.parts = parts;
     a.range = (chunks + parts - 1) / parts * kChunk;
@@ -401,6 +401,27 @@ static int tiled_launch(const EncParams& p, int dtype, int d_head, int parts, ui
     return S3_OK;
 }
 
+// A launch holds fewer than 2^32 threads, 2^23 workgroups: calls of more token tiles (268 M tokens) go in slices of whole
+// heads, or of one head's tokens where a head alone has more.
+constexpr long long kGridMax = 1LL << 22;
+static int tiled_slices(const EncParams& p, int dtype, int d_head, hipStream_t st) {
+    const size_t row = (size_t)d_head * (dtype == S3_BF16 ? 2 : 4);
+    const long long per_head = token_tiles(1, p.T);
+    const int heads = per_head < kGridMax ? (int)(kGridMax / per_head) : 1;
+    const int toks = (int)(per_head < kGridMax ? p.T : kGridMax * kTok);
+    for (long long h = 0; h < p.n_heads; h += heads)
+        for (long long t = 0; t < p.T; t += toks) {            // more than one step only where heads == 1
+            EncParams q = p;
+            const size_t at = (size_t)h * p.T + (size_t)t;
+            q.x += at * row; q.ids += at * p.k; q.vals += at * p.k;
+            q.w += (size_t)h * p.n_feat * row; q.b += (size_t)h * p.n_feat;
+            q.n_heads = (int)(p.n_heads - h < heads ? p.n_heads - h : heads);
+            q.T = (int)(p.T - t < toks ? p.T - t : toks);
+            if (int rc = tiled_launch(q, dtype, d_head, 1, nullptr, st)) return rc;
+        }
+    return S3_OK;
+}
+
 static size_t plain_workspace(int dtype, int T, int d_head, int n_feat, int k, int n_heads) {
     if (s3_encode_fast_ok(dtype, d_head, n_feat, k) && !tiled_pays(n_heads, T)) return 0;
     const int parts = parts_for(n_heads, T, n_feat, k);
@@ -418,7 +439,7 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
     if (n_feat < 1 || n_feat > S3_MAX_FEAT) return s3_fail(S3_EINVAL, "%s: n_feat %d not in [1, %d]", who, n_feat, S3_MAX_FEAT);
     if (k < 1 || k > n_feat || k > S3_MAX_K) return s3_fail(S3_EINVAL, "%s: k %d not in [1, min(n_feat, %d)]", who, k, S3_MAX_K);
     if (((uintptr_t)x | (uintptr_t)w_enc) & 15) return s3_fail(S3_EINVAL, "%s: x and w_enc must be 16-byte aligned", who);
-    if ((int64_t)n_heads * ((T + kTok - 1) / kTok) > 0x7FFFFFFFLL) return s3_fail(S3_EINVAL, "%s: grid too large", who);
+    if (token_tiles(n_heads, T) > 0x7FFFFFFFLL) return s3_fail(S3_EINVAL, "%s: grid too large", who);
     if (ws && ((uintptr_t)ws & 255)) return s3_fail(S3_EINVAL, "%s: workspace must be 256-byte aligned", who);
     if (tau_hint) {
         if (!ws) return s3_fail(S3_EINVAL, "%s: null workspace", who);
@@ -445,6 +466,7 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
         return tau_hint ? s3_encode_fast_stream(p, tau_hint, ws, st) : s3_encode_fast_launch(p, st);
     if (k > largest_k(dtype, d_head))
         return s3_fail(S3_EINVAL, "%s: k %d > %d for this dtype and d_head", who, k, largest_k(dtype, d_head));
+    if (token_tiles(n_heads, T) > kGridMax) return tiled_slices(p, dtype, d_head, st);
     return tiled_launch(p, dtype, d_head, parts, (uint2*)ws, st);
 }
 

@@ -120,3 +120,32 @@ def test_rows_with_fewer_than_k_elements_are_whole(dtype, d, heads, T, n_feat, k
     s3.sae_encode_topk(xg, Wg, bg, k, ids, vals)
     torch.cuda.synchronize()
     assert np.array_equal(ids.cpu().numpy(), want) and np.array_equal(vals.cpu().numpy(), want_v)
+
+
+@pytest.mark.parametrize("heads,T", [(1, (1 << 28) + 33), ((1 << 23) + 5, 1), (3, (1 << 27) + 32)])
+def test_more_workgroups_than_one_launch_holds(heads, T):
+    """Over 2^23 token tiles: more than 2^32 threads.  All rows are zero, so their id is the largest bias of the head, but for
+    some at the ends and around the middle; those must come out as in calls of their own."""
+    import torch
+    import paper_2601_17702_amd as s3
+    d, n_feat = 64, 8
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GB of device memory")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    W = torch.randn(heads, n_feat, d, generator=g, device="cuda", dtype=torch.bfloat16)
+    b = torch.rand(heads, n_feat, generator=g, device="cuda")
+    x = torch.zeros(heads, T, d, dtype=torch.bfloat16, device="cuda")
+    flat = x.view(heads * T, d)
+    n = heads * T
+    rows = torch.cat([torch.arange(c, c + 70, device="cuda") for c in (0, n // 4 - 35, n // 2 - 35, n // 2 + n // 4 - 35, n - 70)])
+    flat[rows] = torch.randn(len(rows), d, generator=g, device="cuda").bfloat16()
+    ids, vals = s3.sae_encode_topk(x, W, b, 1)
+    of = rows // T
+    ids1, vals1 = s3.sae_encode_topk(flat[rows][:, None].contiguous(), W[of], b[of], 1)      # each row as a head of one token
+    torch.cuda.synchronize()
+    assert torch.equal(ids.view(-1)[rows], ids1.view(-1)) and torch.equal(vals.view(-1)[rows], vals1.view(-1))
+    top_v, top = b.max(dim=1)
+    plain = torch.ones(n, dtype=torch.bool, device="cuda")
+    plain[rows] = False
+    plain = plain.view(heads, T)
+    assert not bool(((ids[:, :, 0] != top[:, None]) & plain).any()) and not bool(((vals[:, :, 0] != top_v[:, None]) & plain).any())
