@@ -68,8 +68,9 @@ constexpr int kRun = 32;             // consecutive windows per thread (sliding 
 constexpr int kTileW = 64 * kRun;    // windows per tile = per wavefront of the pooling kernel
 constexpr int kSubLog2 = 8;
 constexpr int kSubW = 1 << kSubLog2; // windows per entry of the tile maxima
-constexpr int kTopThreads = 256;
-constexpr int kTopTiles = 4096;      // tiles of the Top-B search (LDS)
+constexpr int kTopRegs = 4;          // registers per lane for the maxima of a short context
+constexpr int kTopThreads = 1024;    // long contexts: all of them load the tile maxima, one wavefront searches
+constexpr int kTopTiles = 4096;      // tiles of the Top-B search: 64 groups of 64, one group per lane
 
 __device__ __forceinline__ int exp_s(unsigned long long wmax_bits, int hb) {   // weights are scaled by 2^exp_s: sums < 2^62
     double w = __longlong_as_double((long long)wmax_bits);
@@ -538,85 +539,203 @@ __global__ __launch_bounds__(256) void sc_pool_wide_kernel(ScoreArgs a) {
 }
 
 // Greedy Top-B with optional suppression of overlapping windows.  The rounds depend on each other, so what bounds it is
-// the latency of a round: one wavefront walks them without a barrier over tile maxima in LDS.  A round takes the best
-// tile, clears the tiles that the suppression covers whole and searches the two at its ends again, loads of both in
-// flight together.  A window that is gone is marked -1 in memory; window s belongs to lane s % 64 in every round, so a
-// lane only ever reads back its own marks.  A tile without live windows stays so (its windows need not be marked).
-// With 256 threads, tiles of 2048 windows and a search through the spans chosen so far a round had nine barriers:
-// a look-up of one token in 256 indexes of 32768 positions (16 spans of 64) took 238 us, now 211 us.
-__global__ __launch_bounds__(kTopThreads) void sc_topb_kernel(ScoreArgs a) {
-    __shared__ unsigned long long cv[kTopTiles];
-    __shared__ int ci[kTopTiles];
+// the latency of a round: one wavefront walks them without a barrier, with maxima in its registers.  A round takes the
+// best, clears the tiles that the suppression covers whole and searches the two blocks of kSubW windows at its ends again,
+// loads of both in flight together.  A window that is gone is marked -1 in memory; window s belongs to lane s % 64 in every
+// round, so a lane only ever reads back its own marks.  A tile without live windows stays so (its windows need not be marked).
+//
+// sc_topb_kernel: the registers hold the maxima of up to kTopRegs * 64 tiles of one block.
+// sc_topb_long_kernel: tile maxima in LDS, those of groups of 64 tiles in registers, so that a round costs the same at any
+// length; the groups at both ends are reduced again in the next round, beside its search and not behind this one's.  Beyond
+// kTopTiles blocks a tile has several; their maxima come from memory beside the windows, block e belongs to the same lane in
+// every round, too.
+//
+// us for a whole look-up of 4 short lists, spans of 64: 256 threads, tiles of 2048 windows and a search through the spans
+// chosen so far / one wavefront that looks through up to 4096 tile maxima in LDS every round / this:
+//   32768 positions, 16 spans: 82 / 53 / 51, 1024 spans: 7240 / 714 / 675
+//   524288 positions, 16 spans: 81 / 94 / 59     1048576 positions, 16 spans: 86 / 142 / 65, 64 spans: 361 / 458 / 165
+//   16777216 positions, 64 spans: 1059 / 1114 / 343
+// The line between the kernels, 16 spans: 65536 positions take 51 us in 4 registers, 57 in groups; with 8 registers 131072
+// take 55.5 instead of 56.5, but 32768 take 56 instead of 51.
+struct TopBest {
+    unsigned long long key;                               // window sum + 1; 0: none
+    int start;
+};
+constexpr int kTopNone = 0x7FFFFFFF;
+__device__ __forceinline__ void top_take(TopBest& b, const TopBest& o) {
+    if (o.key > b.key || (o.key == b.key && o.start < b.start)) b = o;
+}
+
+// The best live windows of the blocks of kSubW windows that hold windows lo and hi, after [lo, hi] is marked.
+__device__ __forceinline__ void top_search_ends(const ScoreArgs& a, int64_t lo, int64_t hi, int lane, TopBest& l, TopBest& h) {
+    constexpr int U = kSubW / 64;
+    const int64_t b0 = (lo >> kSubLog2 << kSubLog2) + lane, b1 = (hi >> kSubLog2 << kSubLog2) + lane;
+    long long w0[U], w1[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        w0[u] = b0 + u * 64 < a.nW ? a.wfix[b0 + u * 64] : -1;
+        w1[u] = b1 + u * 64 < a.nW ? a.wfix[b1 + u * 64] : -1;
+    }
+    l = h = TopBest{0, kTopNone};
+#pragma unroll
+    for (int u = 0; u < U; ++u) {                         // one store per window and round where the blocks are one: the same mark
+        const int64_t p0 = b0 + u * 64, p1 = b1 + u * 64;
+        if (p0 >= lo && p0 <= hi) { w0[u] = -1; a.wfix[p0] = -1; }
+        if (p1 >= lo && p1 <= hi) { w1[u] = -1; a.wfix[p1] = -1; }
+        const unsigned long long k0 = (unsigned long long)(w0[u] + 1), k1 = (unsigned long long)(w1[u] + 1);
+        if (k0 > l.key) { l.key = k0; l.start = (int)p0; }
+        if (k1 > h.key) { h.key = k1; h.start = (int)p1; }
+    }
+    wave_best(l.key, l.start);
+    wave_best(h.key, h.start);
+}
+
+__device__ __forceinline__ void top_finish(const ScoreArgs& a, int found, int lane) {
+    for (int r = found + lane; r < a.top_b; r += 64) { a.span_start[r] = -1; a.span_score[r] = 0.f; }
+    if (lane == 0) a.n_found[0] = found;
+}
+
+__global__ __launch_bounds__(64) void sc_topb_kernel(ScoreArgs a) {
+    const int lane = threadIdx.x;
+    TopBest t[kTopRegs];
+#pragma unroll
+    for (int q = 0; q < kTopRegs; ++q) {
+        t[q] = TopBest{0, kTopNone};
+        if (q * 64 + lane < a.nsub) t[q] = TopBest{a.tmaxv[q * 64 + lane], a.tmaxi[q * 64 + lane]};
+    }
+    const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
+    const int reach = a.nms ? a.len - 1 : 0;              // windows within `reach` of a chosen start are gone
+    int found = 0;
+    while (found < a.top_b) {
+        TopBest best = t[0];
+#pragma unroll
+        for (int q = 1; q < kTopRegs; ++q) top_take(best, t[q]);
+        wave_best(best.key, best.start);
+        if (best.key == 0) break;
+        if (lane == 0) {
+            a.span_start[found] = best.start;
+            a.span_score[found] = (float)((double)(long long)(best.key - 1) * inv);
+        }
+        ++found;
+        const int64_t lo = max((int64_t)0, (int64_t)best.start - reach), hi = min(a.nW - 1, (int64_t)best.start + reach);
+        const int tl = (int)(lo >> kSubLog2), th = (int)(hi >> kSubLog2);
+        TopBest l, h;
+        top_search_ends(a, lo, hi, lane, l, h);
+#pragma unroll
+        for (int q = 0; q < kTopRegs; ++q) {
+            const int i = q * 64 + lane;
+            if (i > tl && i < th) t[q].key = 0;
+            if (i == tl && t[q].key) t[q] = l;
+            if (i == th && t[q].key) t[q] = h;            // the same where tl == th
+        }
+    }
+    top_finish(a, found, lane);
+}
+
+__global__ __launch_bounds__(kTopThreads) void sc_topb_long_kernel(ScoreArgs a) {
+    __shared__ unsigned long long cv[kTopTiles], gv[64];
+    __shared__ int ci[kTopTiles], gi[64];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int per = 1 << a.topshift, nt = (a.nsub + per - 1) >> a.topshift;
-    for (int t = tid; t < nt; t += kTopThreads) {
-        unsigned long long key = 0;
-        int start = 0x7FFFFFFF;
-        const int64_t e0 = (int64_t)t << a.topshift, e1 = min((int64_t)a.nsub, e0 + per);
-        for (int64_t e = e0; e < e1; ++e)
-            if (a.tmaxv[e] > key) { key = a.tmaxv[e]; start = a.tmaxi[e]; }
-        cv[t] = key;
-        ci[t] = start;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int per = 1 << a.topshift, nt = (a.nsub + per - 1) >> a.topshift, ng = (nt + 63) >> 6;
+    for (int g = wave; g < ng; g += kTopThreads / 64) {
+        const int t = g * 64 + lane;
+        TopBest b{0, kTopNone};
+        if (t < nt) {
+            const int64_t e0 = (int64_t)t << a.topshift, e1 = min((int64_t)a.nsub, e0 + per);
+            int64_t at = e0;
+            for (int64_t e = e0; e < e1; ++e) {           // ascending starts
+                const unsigned long long v = a.tmaxv[e];
+                if (v > b.key) { b.key = v; at = e; }
+            }
+            if (b.key) b.start = a.tmaxi[at];
+            cv[t] = b.key;
+            ci[t] = b.start;
+        }
+        wave_best(b.key, b.start);
+        if (lane == 0) { gv[g] = b.key; gi[g] = b.start; }
     }
     __syncthreads();
     if (tid >= 64) return;
     const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
     const int tlog = kSubLog2 + a.topshift;
     const int reach = a.nms ? a.len - 1 : 0;              // windows within `reach` of a chosen start are gone
-    int found = 0;
+    TopBest top{lane < ng ? gv[lane] : 0ull, lane < ng ? gi[lane] : kTopNone};      // this lane's group; none while its tiles are in va / vb
+    TopBest va{0, kTopNone}, vb{0, kTopNone};                   // tiles of the groups ga, gb, which changed last
+    int ga = -1, gb = -1, found = 0;
     while (found < a.top_b) {
-        unsigned long long key = 0;
-        int start = 0x7FFFFFFF;
-        for (int t = lane; t < nt; t += 64) {             // ascending starts per lane
-            const unsigned long long tv = cv[t];
-            const int ti = ci[t];
-            if (tv > key) { key = tv; start = ti; }
-        }
-        wave_best(key, start);
-        if (key == 0) break;
+        TopBest best = top, ma = va, mb = vb;
+        top_take(best, va);
+        top_take(best, vb);
+        wave_best(best.key, best.start);
+        wave_best(ma.key, ma.start);                      // beside the reduction above, not behind it
+        wave_best(mb.key, mb.start);
+        if (lane == ga) top = ma;
+        if (lane == gb) top = mb;
+        if (best.key == 0) break;
         if (lane == 0) {
-            a.span_start[found] = start;
-            a.span_score[found] = (float)((double)(long long)(key - 1) * inv);
+            a.span_start[found] = best.start;
+            a.span_score[found] = (float)((double)(long long)(best.key - 1) * inv);
         }
         ++found;
-        const int64_t lo = max((int64_t)0, (int64_t)start - reach), hi = min(a.nW - 1, (int64_t)start + reach);
+        const int64_t lo = max((int64_t)0, (int64_t)best.start - reach), hi = min(a.nW - 1, (int64_t)best.start + reach);
         const int tl = (int)(lo >> tlog), th = (int)(hi >> tlog);
-        const bool live_l = cv[tl] != 0, live_h = cv[th] != 0;
-        s3_wave_fence();                                  // the maxima are read before lane 0 and the clearing lanes write them
+        const int64_t el = lo >> kSubLog2, eh = hi >> kSubLog2;
         for (int t = tl + 1 + lane; t < th; t += 64) cv[t] = 0;
-        unsigned long long kl = 0, kh = 0;
-        int sl = 0x7FFFFFFF, sh = 0x7FFFFFFF;
-        for (int s = 0; s < per; ++s) {
-            const int64_t b0 = ((int64_t)tl << tlog) + s * kSubW + lane, b1 = ((int64_t)th << tlog) + s * kSubW + lane;
-            constexpr int U = kSubW / 64;
-            long long w0[U], w1[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                w0[u] = b0 + u * 64 < a.nW ? a.wfix[b0 + u * 64] : -1;
-                w1[u] = b1 + u * 64 < a.nW ? a.wfix[b1 + u * 64] : -1;
+        s3_wave_fence();                                  // the cleared tiles are read by other lanes
+        ga = tl >> 6;
+        gb = th >> 6;
+        if (lane >= ga && lane <= gb) top = TopBest{0, kTopNone};
+        va = vb = TopBest{0, kTopNone};
+        const int la = ga * 64 + lane, lb = gb * 64 + lane;
+        if (la < nt) va = TopBest{cv[la], ci[la]};
+        if (lb < nt) vb = TopBest{cv[lb], ci[lb]};
+        TopBest l, h;
+        top_search_ends(a, lo, hi, lane, l, h);
+        if (a.topshift) {                                 // from the two blocks to their tiles
+            TopBest nl{0, kTopNone}, nh{0, kTopNone};
+            for (int s = lane; s < per; s += 64) {
+                const int64_t e0 = ((int64_t)tl << a.topshift) + s, e1 = ((int64_t)th << a.topshift) + s;
+                unsigned long long v0 = e0 < a.nsub ? a.tmaxv[e0] : 0ull, v1 = e1 < a.nsub ? a.tmaxv[e1] : 0ull;
+                int i0 = e0 < a.nsub ? a.tmaxi[e0] : kTopNone, i1 = e1 < a.nsub ? a.tmaxi[e1] : kTopNone;
+                if (v0 && e0 >= el && e0 <= eh) {         // a block without live windows stays so
+                    v0 = e0 == el ? l.key : (e0 == eh ? h.key : 0ull);
+                    i0 = e0 == el ? l.start : h.start;
+                    a.tmaxv[e0] = v0;
+                    a.tmaxi[e0] = i0;
+                }
+                if (v1 && e1 >= el && e1 <= eh) {         // where tl == th: the same block, the same values
+                    v1 = e1 == eh ? h.key : (e1 == el ? l.key : 0ull);
+                    i1 = e1 == eh ? h.start : l.start;
+                    a.tmaxv[e1] = v1;
+                    a.tmaxi[e1] = i1;
+                }
+                top_take(nl, TopBest{v0, i0});
+                top_take(nh, TopBest{v1, i1});
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {                 // one store per window and round where tl == th: the same mark
-                const int64_t p0 = b0 + u * 64, p1 = b1 + u * 64;
-                if (p0 >= lo && p0 <= hi) { w0[u] = -1; a.wfix[p0] = -1; }
-                if (p1 >= lo && p1 <= hi) { w1[u] = -1; a.wfix[p1] = -1; }
-                const unsigned long long k0 = (unsigned long long)(w0[u] + 1), k1 = (unsigned long long)(w1[u] + 1);
-                if (k0 > kl) { kl = k0; sl = (int)p0; }
-                if (k1 > kh) { kh = k1; sh = (int)p1; }
-            }
+            wave_best(nl.key, nl.start);
+            wave_best(nh.key, nh.start);
+            l = nl;
+            h = nh;
         }
-        wave_best(kl, sl);
-        wave_best(kh, sh);
+        // a tile without live windows stays so
+        const unsigned long long tv = cv[tl], uv = cv[th];
+        if (!tv) l = TopBest{0, kTopNone};
+        if (!uv) h = TopBest{0, kTopNone};
+        s3_wave_fence();                                  // va, vb, tv and uv are read
         if (lane == 0) {                                  // the same values where tl == th
-            cv[tl] = live_l ? kl : 0ull;
-            ci[tl] = sl;
-            cv[th] = live_h ? kh : 0ull;
-            ci[th] = sh;
+            cv[tl] = l.key;
+            ci[tl] = l.start;
+            cv[th] = h.key;
+            ci[th] = h.start;
         }
         s3_wave_fence();
+        if (la == tl) va = l;
+        if (la == th) va = h;
+        if (lb == tl) vb = l;
+        if (lb == th) vb = h;
     }
-    for (int r = found + lane; r < a.top_b; r += 64) { a.span_start[r] = -1; a.span_score[r] = 0.f; }
-    if (lane == 0) a.n_found[0] = found;
+    top_finish(a, found, lane);
 }
 
 struct Layout {
@@ -705,7 +824,7 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.pb = l.pb; a.npb = l.npb; a.heads_per = l.heads_per; a.ngroup = l.ngroup; a.sorted = v.sorted ? 1 : 0;
     a.ntile = (int)((a.nW + kTileW - 1) / kTileW);
     a.nsub = (int)((a.nW + kSubW - 1) / kSubW);
-    // the smallest tiles whose maxima fit the search's LDS: beyond 1M windows a round reads more windows instead
+    // the smallest tiles of which the search's lanes hold all groups: beyond 1M windows a tile has several blocks
     a.topshift = 0;
     while (((a.nsub - 1) >> a.topshift) + 1 > kTopTiles) ++a.topshift;
     a.scores_out = scores_out; a.span_start = span_start; a.span_score = span_score; a.n_found = n_found;
@@ -731,7 +850,8 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     } else {
         hipLaunchKernelGGL(sc_pool_wide_kernel, dim3((unsigned)((a.ntile + 3) / 4)), dim3(256), 0, st, a);
     }
-    hipLaunchKernelGGL(sc_topb_kernel, dim3(1), dim3(kTopThreads), 0, st, a);
+    if (a.nsub <= kTopRegs * 64) hipLaunchKernelGGL(sc_topb_kernel, dim3(1), dim3(64), 0, st, a);
+    else hipLaunchKernelGGL(sc_topb_long_kernel, dim3(1), dim3(kTopThreads), 0, st, a);
     S3_HIP(hipGetLastError());
     return S3_OK;
 }

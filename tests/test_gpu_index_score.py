@@ -335,6 +335,31 @@ def test_greedy_spans_over_tile_borders(T, span_len, top_b, nms):
     assert out[0][:out[2]].tolist() == list(st_o)
 
 
+@pytest.mark.parametrize("T,span_len,top_b,nms", [
+    (65_536 + 255, 256, 50, True),         # 256 blocks of windows, the most that registers hold; one more below
+    (65_536 + 256, 256, 50, True),
+    ((1 << 20) + 63, 64, 300, True),       # 4096 tiles of one block, the most that the search's lanes hold
+    ((1 << 20) + 64, 64, 300, False),      # two blocks per tile from here on
+    ((1 << 20) + 5000, 4000, 100, True),   # suppressions over several tiles of two blocks
+    ((1 << 20) + 9000, 5000, 30, True),    # the other pooling kernel
+    ((1 << 21) + 700, 700, 200, True),     # four blocks per tile, gone and live ones in the same tile
+])
+def test_greedy_spans_of_long_contexts(T, span_len, top_b, nms):
+    """As above with every 37th position or so: the others have a feature that no query names."""
+    rng = np.random.default_rng(T + span_len)
+    n = 28_000
+    at = np.sort(rng.permutation(T)[:n])
+    ids = np.zeros((1, T, 1), np.int32)
+    ids[0, at, 0] = 1 + rng.permutation(n)
+    qids = (1 + np.arange(n, dtype=np.int32))[None, :, None].copy()
+    qvals = (rng.random((1, n, 1)) + 0.01).astype(np.float32)
+    ix = gpu_index(ids, n + 1)
+    S, W, st_o, sc_o = oracle_score(ids, qids, qvals, n + 1, T, span_len, top_b, 0, nms)
+    out = run_gpu_score(ix, qids, qvals, T, span_len, top_b, 0, nms)
+    check_score(out, S, W, st_o, sc_o, span_len, nms)
+    assert out[0][:out[2]].tolist() == list(st_o)
+
+
 def test_scoring_with_shifted_positions_and_index_reuse():
     """Positions that start at an offset: inside the range the index's block table covers (table used), beyond it
     (lists are searched instead), and the same index object reset and fed another stream (table rebuilt)."""

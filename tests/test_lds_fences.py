@@ -28,7 +28,7 @@ def wavefront_fences(src: str) -> dict:
 
 @pytest.mark.parametrize("src,kernel,least", [
     ("select.hip", "sel_nms_kernel", 3),      # before the tiles are read again, before and after their new maxima
-    ("score.hip", "sc_topb_kernel", 2),       # before the tile maxima change, after it
+    ("score.hip", "sc_topb_long_kernel", 3),  # behind the cleared tiles, before and behind the new maxima
 ])
 def test_greedy_searches_fence_their_hand_overs(src, kernel, least):
     found = {f: n for f, n in wavefront_fences(src).items() if kernel in f and "stub" not in f}
