@@ -298,12 +298,19 @@ __global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
 // ---- Phase 3 set operations ----
 // What bounds them at the lengths of a context is the number of launches.  Two are enough: fuse_block_kernel builds the
 // mask of a block of positions in LDS (every block looks through all spans and the whole index list) and counts it,
-// fuse_compact_kernel adds up the counts of the blocks before its own.  Both are quadratic in the context's length, so
-// beyond kFuseLookMax list entries looked at in all (64 MB through L2) the mask is marked in memory first, and beyond
-// kFuseSelfMax blocks the counts are scanned by a launch of their own.
+// fuse_compact_kernel adds up the counts of the blocks before its own.  A block's look through a long list takes longer than
+// two more launches, and the looks of all blocks are quadratic in the context's length, so beyond kFuseListMax list entries
+// or kFuseLookMax entries looked at in all (64 MB through L2) the mask is marked in memory first.  Device time in us, looked
+// through / marked, of 1000 and of 131072 positions: 300 entries 4.8 / 7.3 and 5.7 / 8.2, 32768 entries 12.2 / 7.4 and
+// 13.0 / 8.5, 262144 entries 68 / 8.0 and 69 / 9.4; on the host four launches take 22, two 17, so the line lies where the
+// look still hides behind those (about 14 us, as long as the five launches that these replaced).  A span costs about four
+// entries (two loads, two adds in LDS): 4096 of them 6.8 / 7.8 and 7.6 / 9.1.  (A wavefront that marked one span after the
+// other took 118 us for 4096 spans in 1000 positions.)  Beyond kFuseSelfMax blocks the counts are scanned by a launch of
+// their own.
 constexpr int kFuseThreads = 256;
 constexpr int kFusePer = 4;                             // consecutive positions per thread
 constexpr int kFuseBlock = kFuseThreads * kFusePer;     // positions per workgroup
+constexpr int64_t kFuseListMax = 9 << 12;
 constexpr int64_t kFuseLookMax = 1 << 24;
 constexpr int kFuseSelfMax = 4096;
 
@@ -321,9 +328,11 @@ __global__ __launch_bounds__(kFuseThreads) void fuse_block_kernel(unsigned char*
                                                                   const int32_t* n_spans, int max_spans, const int32_t* extra,
                                                                   int64_t n_extra, int lead, int tail, int* bsum) {
     __shared__ uint32_t m4[kFuseThreads];
+    __shared__ __align__(16) int step[kFuseBlock + 4];          // spans that start here less spans that ended before
     __shared__ int wsum[kFuseThreads / 64];
+    __shared__ int met;                                         // whether any span meets the block
     unsigned char* const m = (unsigned char*)m4;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.x * kFuseBlock, t1 = min(L, t0 + kFuseBlock) - 1;      // first and last position
     uint32_t v = 0;
 #pragma unroll
@@ -332,21 +341,16 @@ __global__ __launch_bounds__(kFuseThreads) void fuse_block_kernel(unsigned char*
         if (t < L && (t < lead || t >= L - tail)) v |= 1u << (8 * j);
     }
     m4[tid] = v;
+    *(int4*)(step + tid * kFusePer) = make_int4(0, 0, 0, 0);
+    if (tid == 0) met = 0;
     __syncthreads();
     const int ns = n_spans ? min(*n_spans, max_spans) : max_spans;
-    for (int i0 = wave * 64; i0 < ns; i0 += kFuseThreads) {      // a wavefront looks at 64 spans, then marks those that meet the block
-        int a = 0, b = -1;
-        if (i0 + lane < ns) {
-            a = (int)(max((int64_t)lo[i0 + lane], t0) - t0);
-            b = (int64_t)lo[i0 + lane] > t1 ? -1 : (int)max((int64_t)-1, min((int64_t)hi[i0 + lane], t1) - t0);
-        }
-        unsigned long long hit = __ballot(a <= b);
-        while (hit) {
-            const int src = (int)__builtin_ctzll(hit);
-            hit &= hit - 1;
-            const int sa = __builtin_amdgcn_readlane(a, src), sb = __builtin_amdgcn_readlane(b, src);
-            for (int i = sa + lane; i <= sb; i += 64) m[i] = 1;
-        }
+    for (int i = tid; i < ns; i += kFuseThreads) {
+        const int64_t a = max((int64_t)lo[i], t0), b = min((int64_t)hi[i], t1);
+        if (a > b) continue;
+        met = 1;
+        atomicAdd(step + (int)(a - t0), 1);
+        atomicAdd(step + (int)(b - t0) + 1, -1);                // the place behind the block is read by nobody
     }
     for (int64_t i0 = tid; i0 < n_extra; i0 += 8 * kFuseThreads) {
         int32_t p[8];
@@ -359,6 +363,17 @@ __global__ __launch_bounds__(kFuseThreads) void fuse_block_kernel(unsigned char*
     __syncthreads();
     v = m4[tid];
     const int64_t t = t0 + tid * kFusePer;
+    if (met) {
+        const int4 d = *(const int4*)(step + tid * kFusePer);
+        int all;
+        int open = s3_block_excl_scan<kFuseThreads>(d.x + d.y + d.z + d.w, wsum, all);      // spans that reach this thread's positions
+        const int dj[kFusePer] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+        for (int j = 0; j < kFusePer; ++j) {
+            open += dj[j];
+            if (open > 0) v |= 1u << (8 * j);
+        }
+    }
     if (((uintptr_t)mask & 3) == 0 && t + kFusePer <= L) {
         *(uint32_t*)(mask + t) = v;
     } else {
@@ -546,7 +561,7 @@ extern "C" int s3_fuse_indices(int64_t n_positions, const int32_t* span_lo, cons
     hipStream_t st = (hipStream_t)stream;
     int* bsum = (int*)ws;
     const int nblocks = (int)((n_positions + kFuseBlock - 1) / kFuseBlock);
-    if ((int64_t)nblocks * (n_extra + max_spans) <= kFuseLookMax) {
+    if (n_extra + 4 * (int64_t)max_spans <= kFuseListMax && (int64_t)nblocks * (n_extra + max_spans) <= kFuseLookMax) {
         hipLaunchKernelGGL(fuse_block_kernel, dim3((unsigned)nblocks), dim3(kFuseThreads), 0, st, mask, n_positions, span_lo,
                            span_hi, n_spans, max_spans, extra, n_extra, lead, tail, bsum);
     } else {

@@ -152,9 +152,11 @@ def test_peak_search_at_the_edges_of_its_tiles(L, radius, n_centers):
     assert np.array_equal(lo.cpu().numpy()[:n], lo_o) and np.array_equal(hi.cpu().numpy()[:n], hi_o)
 
 
-@pytest.mark.parametrize("L,ns,n_extra", [(1023, 1, 1), (1024, 300, 257), (1025, 0, 3), (5 << 20, 70, 9), (100_000, 4000, 200_000)])
+@pytest.mark.parametrize("L,ns,n_extra", [(1023, 1, 1), (1024, 300, 257), (1025, 0, 3), (5 << 20, 70, 9), (100_000, 4000, 200_000),
+                                          (1000, 5000, 16_864), (1000, 5000, 16_865), (3000, 40_000, 0)])
 def test_fuse_indices_block_edges(L, ns, n_extra):
-    """Around a block of positions, counts scanned by their own launch (5 M), lists too long for every block to look through."""
+    """Around a block of positions, counts scanned by their own launch (5 M), lists too long for every block to look through
+    (by all blocks together, by any one of them), many spans over every position."""
     import torch
     import paper_2601_17702_amd as s3
     rng = np.random.default_rng(L)
