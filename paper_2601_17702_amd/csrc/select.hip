@@ -20,10 +20,13 @@ constexpr int kMaxTaps = 4096;
 constexpr int kConvPer = 4;                 // consecutive positions per thread of the convolution
 constexpr int kConvSmall = 64, kConvLarge = 256;      // its workgroup sizes: below / from kConvLargeFrom positions
 constexpr int64_t kConvLargeFrom = 1 << 18; // 64 threads fill the chip up to 2^18 positions; beyond, the halo is shared by more
-constexpr int kTile = 64;                   // positions per density tile
+constexpr int kTile = 64;                   // positions per block: one bit or one lane each
+constexpr int kConvKeyShift = 4;            // blocks per workgroup of the large convolution: 2^4
 constexpr int kNmsThreads = 1024;
-constexpr int kNmsTiles = 8192;             // tile maxima that the peak search keeps in LDS (64 KB)
-constexpr int kNmsGroups = kNmsTiles / 64 / 64;       // groups of 64 tiles per lane
+constexpr int kNmsTiles = 16384;            // tile maxima that the peak search keeps in LDS at most (128 KB): four groups of 64 per lane
+constexpr int kNmsTilesMin = 8192;          // as many fit beside the most centres
+static_assert(kConvLarge * kConvPer == kTile << kConvKeyShift && kConvLargeFrom <= (int64_t)kNmsTilesMin * kTile);
+constexpr int kShortGroups = 1;             // groups per lane of a curve that is kept in LDS (below 40000 positions)
 constexpr int kNmsLds = 152 << 10;          // its LDS: tile maxima, centres, group maxima, and the whole curve if that fits
 
 struct SelArgs {
@@ -33,10 +36,11 @@ struct SelArgs {
     int K, n_centers, radius, max_half;
     float rel;
     float* dens;                 // [L]
-    unsigned long long* tkey;    // [ntile] best position of every tile of kTile positions (peak_key)
-    int ntile;
-    int shift;                   // the peak search works on tiles of kTile << shift positions
-    int cached;                  // the curve is kept in LDS during the peak search
+    unsigned long long* tkey;    // [nblk] best position of every block of kTile positions (peak_key)
+    unsigned long long* ckey;    // [nckey] best position of every kTile << kshift positions (kshift > 0 only)
+    unsigned long long* dead;    // [nblk] positions of every block that are gone, a bit each; null if the curve is kept in LDS
+    int nblk, nckey;
+    int shift, kshift;           // the peak search works on tiles of kTile << shift positions, shift >= kshift
     int32_t* center;
     float* center_density;
     int32_t* span_lo;
@@ -56,7 +60,8 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v)
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// D[t] = sum_j g[j] * S[t + j - floor(K / 2)] with zeros outside the context, and the best position of every tile.
+// D[t] = sum_j g[j] * S[t + j - floor(K / 2)] with zeros outside the context, and the best position of every block and of
+// every kTile << kshift positions.
 // Inputs and weights are staged in LDS; a thread has four consecutive positions, so four taps cost two 16-byte reads
 // for 16 multiply-adds (one 4-byte read per operand before).
 template <int NT>
@@ -103,158 +108,140 @@ __global__ __launch_bounds__(NT) void sel_conv_kernel(SelArgs a) {
             best = k > best ? k : best;
         }
     }
-    // the 16 lanes of a row hold one tile
+    // the 16 lanes of a row hold one block
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) {
         const unsigned hi = (unsigned)__shfl_xor((int)(unsigned)(best >> 32), o), lw = (unsigned)__shfl_xor((int)(unsigned)best, o);
         const unsigned long long other = ((unsigned long long)hi << 32) | lw;
         best = other > best ? other : best;
     }
-    const int64_t tile = t0 / kTile + tid / 16;
-    if ((tid & 15) == 0 && tile < a.ntile) a.tkey[tile] = best;
-}
-
-// This lane's best live positions of the tiles tl and th (which may be the same): U times 64 positions of both at a time,
-// all loads in flight, those within the radius of one of the centres cen[0 .. found) left out.
-template <int U>
-__device__ __forceinline__ void sel_rescan(const SelArgs& a, const int* cen, int found, int tl, int th,
-                                           int tlog, int lane, unsigned long long& kl, unsigned long long& kh) {
-    const int64_t r = a.radius;
-    for (int s0 = 0; s0 < (1 << a.shift); s0 += U) {
-        const int64_t b0 = ((int64_t)tl << tlog) + s0 * kTile, b1 = ((int64_t)th << tlog) + s0 * kTile;
-        float d0[U], d1[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t p0 = b0 + u * kTile + lane, p1 = b1 + u * kTile + lane;
-            d0[u] = d1[u] = 0.f;
-            if (p0 < a.L) d0[u] = a.dens[p0];
-            if (p1 < a.L) d1[u] = a.dens[p1];
-        }
-        for (int j0 = 0; j0 < found; j0 += 64) {
-            const bool on = j0 + lane < found;
-            const int64_t cj = on ? cen[j0 + lane] : 0;
-            unsigned long long near = __ballot(on && ((cj + r >= b0 && cj - r < b0 + U * kTile) ||
-                                                      (cj + r >= b1 && cj - r < b1 + U * kTile)));
-            while (near) {
-                const int64_t c = __builtin_amdgcn_readlane((int)cj, (int)__builtin_ctzll(near));
-                near &= near - 1;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int64_t p0 = b0 + u * kTile + lane, p1 = b1 + u * kTile + lane;
-                    if (p0 >= c - r && p0 <= c + r) d0[u] = 0.f;
-                    if (p1 >= c - r && p1 <= c + r) d1[u] = 0.f;
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned long long k0 = peak_key(d0[u], b0 + u * kTile + lane), k1 = peak_key(d1[u], b1 + u * kTile + lane);
-            kl = k0 > kl ? k0 : kl;
-            kh = k1 > kh ? k1 : kh;
-        }
+    const int64_t blk = t0 / kTile + tid / 16;
+    if ((tid & 15) == 0 && blk < a.nblk) {
+        a.tkey[blk] = best;
+        if (a.dead) a.dead[blk] = 0;
+    }
+    if (NT == kConvSmall || a.kshift == 0) return;
+    __shared__ unsigned long long bk[NT / 16];
+    if ((tid & 15) == 0) bk[tid / 16] = best;
+    __syncthreads();
+    const int64_t at = (t0 / kTile >> a.kshift) + tid;
+    if (tid < (NT / 16 >> a.kshift) && at < a.nckey) {
+        best = 0;
+        for (int j = tid << a.kshift; j < (tid + 1) << a.kshift; ++j) best = bk[j] > best ? bk[j] : best;
+        a.ckey[at] = best;
     }
 }
 
 // Greedy peak selection, then the span of every peak.  One workgroup: the rounds depend on each other, so what bounds
 // it is the latency of a round.  One wavefront walks the rounds without a barrier: the maxima of groups of 64 tiles
 // are in its registers, the tile maxima in LDS.  A round takes the best group, clears the tiles that the suppression
-// covers whole and searches the two at its ends again.  A short context's curve is kept in LDS and the suppressed
-// interval wiped out of that copy; a longer one is read from global memory, where a position is dead if it is within
-// the radius of a centre chosen before (there is no flag array).  The chain of a round is two reductions over the
-// wavefront and one LDS (or L2) latency.  With 256 threads, tiles of 1024 positions and flags in global memory a round
-// had ten barriers and three global round trips: 32768 positions, 40 centres, radius 48, the whole call with the fusion
-// behind it 181 us, now 56 us.
-__global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
-    extern __shared__ __align__(16) unsigned long long nms_lds[];
-    __shared__ int found_s;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tlog = 6 + a.shift;                                     // log2 of positions per tile
-    const int nt = (a.ntile + (1 << a.shift) - 1) >> a.shift, ng = (nt + 63) >> 6;
-    unsigned long long* key = nms_lds;                                // [nt]
-    unsigned long long* gkey = key + nt;                              // [ng]
-    int* cen = (int*)(gkey + ng);                                     // [n_centers]
-    float* cden = (float*)(cen + a.n_centers);                        // [n_centers]
-    float* cur = cden + a.n_centers;                                  // [L] if cached
-    if (a.cached) {
-        for (int64_t i0 = tid; i0 < a.L; i0 += 8 * kNmsThreads) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = i0 + u * kNmsThreads < a.L ? a.dens[i0 + u * kNmsThreads] : 0.f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (i0 + u * kNmsThreads < a.L) cur[i0 + u * kNmsThreads] = v[u];
-        }
-    }
-    for (int g = wave; g < ng; g += kNmsThreads / 64) {
+// covers whole and searches the two blocks of 64 positions at its ends again; the groups at both ends are reduced in the
+// next round, beside its search and not behind this one's.  The chain of a round is two reductions over the wavefront and
+// one LDS (or L2) latency.
+//
+// sel_nms_kernel: a short context's curve is kept in LDS and the suppressed interval wiped out of that copy.
+// sel_nms_long_kernel: the curve is read from memory beside a bit per position that says which ones are gone (word e belongs
+// to lane e % 64 in every round, so a lane only ever reads back its own marks).  A tile or block without live positions stays
+// so (its bits need not be set).  Beyond kNmsTilesMin blocks a tile may have several; from four on their keys come from
+// memory, too, and the convolution leaves the first maxima of up to 1024 positions, so that one workgroup has fewer to load.
+//
+// us for a whole selection, K 48, radius 48: 256 threads, tiles of 1024 positions, flags in memory and ten barriers a round /
+// one wavefront that searched whole tiles again and looked through all centres for what is gone / this:
+//   32768 positions, 40 centres: 173 / 50 / 48        131072 positions, 40 centres: 183 / 56 / 56, 4000: 6480 / 5942 / 2392
+//   524288 positions, 4000 centres: 14000 / 18020 / 4743
+//   1048576 positions, 40 centres: 214 / 71 / 69, 4000: 16440 / 19970 / 6040
+//   16777216 positions, 1 centre: 130 / 194 / 75, 4000: 59700 / 128600 / 7250
+struct NmsLds {
+    unsigned long long* key;                                          // [nt] tile maxima
+    unsigned long long* gkey;                                         // [ng] maxima of groups of 64 tiles
+    int* cen;                                                         // [n_centers]
+    float* cden;                                                      // [n_centers]
+    float* cur;                                                       // [L] the curve (short contexts)
+    int nt, ng;
+};
+__device__ __forceinline__ NmsLds nms_lds_of(const SelArgs& a, unsigned long long* lds) {
+    NmsLds l;
+    l.nt = (a.nblk + (1 << a.shift) - 1) >> a.shift;
+    l.ng = (l.nt + 63) >> 6;
+    l.key = lds;
+    l.gkey = l.key + l.nt;
+    l.cen = (int*)(l.gkey + l.ng);
+    l.cden = (float*)(l.cen + a.n_centers);
+    l.cur = l.cden + a.n_centers;
+    return l;
+}
+
+// Tile and group maxima from `per` keys a tile, of which there are n.
+__device__ __forceinline__ void nms_load_keys(const NmsLds& l, const unsigned long long* keys, int n, int per, int wave, int lane) {
+    for (int g = wave; g < l.ng; g += kNmsThreads / 64) {
         const int t = g * 64 + lane;
         unsigned long long best = 0;
-        if (t < nt) {
-            const int64_t e0 = (int64_t)t << a.shift, e1 = min((int64_t)a.ntile, e0 + (1 << a.shift));
-            for (int64_t e = e0; e < e1; ++e) best = a.tkey[e] > best ? a.tkey[e] : best;
-            key[t] = best;
+        if (t < l.nt) {
+            const int64_t e0 = (int64_t)t * per, e1 = min((int64_t)n, e0 + per);
+            for (int64_t e = e0; e < e1; ++e) {
+                const unsigned long long v = keys[e];
+                best = v > best ? v : best;
+            }
+            l.key[t] = best;
         }
         best = wave_max_key(best);
-        if (lane == 0) gkey[g] = best;
+        if (lane == 0) l.gkey[g] = best;
     }
-    __syncthreads();
-    if (wave == 0) {
-        unsigned long long top[kNmsGroups];        // group q * 64 + lane; 0 while the group's tiles are in va / vb
+}
+
+// The state of the walk: maxima of the lane's groups (0 while their tiles are in va / vb), and the tiles (ga * 64 + lane,
+// gb * 64 + lane) that changed last.
+template <int G>                                                      // groups per lane
+struct NmsTop {
+    unsigned long long top[G], va, vb;
+    int ga, gb;
+};
+template <int G>
+__device__ __forceinline__ void nms_start(NmsTop<G>& w, const NmsLds& l, int lane) {
 #pragma unroll
-        for (int q = 0; q < kNmsGroups; ++q) top[q] = q * 64 + lane < ng ? gkey[q * 64 + lane] : 0ull;
-        unsigned long long va = 0, vb = 0;         // tile maxima (tile ga * 64 + lane, gb * 64 + lane) that changed last
-        int ga = -1, gb = -1;
-        int found = 0;
-        while (found < a.n_centers) {
-            unsigned long long best = va > vb ? va : vb;
+    for (int q = 0; q < G; ++q) w.top[q] = q * 64 + lane < l.ng ? l.gkey[q * 64 + lane] : 0ull;
+    w.va = w.vb = 0;
+    w.ga = w.gb = -1;
+}
+// The best live position; the groups that changed last go back to their lanes' registers.
+template <int G>
+__device__ __forceinline__ unsigned long long nms_best(NmsTop<G>& w, int lane) {
+    unsigned long long best = w.va > w.vb ? w.va : w.vb;
 #pragma unroll
-            for (int q = 0; q < kNmsGroups; ++q) best = top[q] > best ? top[q] : best;
-            best = wave_max_key(best);
-            const unsigned long long ma = wave_max_key(va), mb = wave_max_key(vb);      // beside the reduction above, not behind it
+    for (int q = 0; q < G; ++q) best = w.top[q] > best ? w.top[q] : best;
+    best = wave_max_key(best);
+    const unsigned long long ma = wave_max_key(w.va), mb = wave_max_key(w.vb);      // beside the reduction above, not behind it
 #pragma unroll
-            for (int q = 0; q < kNmsGroups; ++q) {
-                if (q * 64 + lane == ga) top[q] = ma;
-                if (q * 64 + lane == gb) top[q] = mb;
-            }
-            if (best == 0) break;                                     // only positive density makes a centre
-            const int64_t c = (int64_t)(unsigned)~(unsigned)best;
-            if (lane == 0) { cen[found] = (int)c; cden[found] = __uint_as_float((unsigned)(best >> 32)); }
-            ++found;
-            const int64_t lo = max((int64_t)0, c - a.radius), hi = min(a.L - 1, c + a.radius);
-            const int tl = (int)(lo >> tlog), th = (int)(hi >> tlog);
-            ga = tl >> 6;
-            gb = th >> 6;
-            for (int t = tl + 1 + lane; t < th; t += 64) key[t] = 0;
-#pragma unroll
-            for (int q = 0; q < kNmsGroups; ++q)
-                if (q * 64 + lane >= ga && q * 64 + lane <= gb) top[q] = 0;
-            if (a.cached)                                             // (shift is 0): the interval is wiped out of the curve in LDS
-                for (int64_t p = lo + lane; p <= hi; p += 64) cur[p] = 0.f;
-            s3_wave_fence();                                          // centre, cleared tiles and wiped positions are read by other lanes
-            va = ga * 64 + lane < nt ? key[ga * 64 + lane] : 0ull;
-            vb = gb * 64 + lane < nt ? key[gb * 64 + lane] : 0ull;
-            unsigned long long kl = 0, kh = 0;                        // best live position of the tile at either end
-            if (a.cached) {
-                const int64_t p0 = ((int64_t)tl << 6) + lane, p1 = ((int64_t)th << 6) + lane;
-                if (p0 < a.L) kl = peak_key(cur[p0], p0);
-                if (p1 < a.L) kh = peak_key(cur[p1], p1);
-            } else if (a.shift == 0) sel_rescan<1>(a, cen, found, tl, th, tlog, lane, kl, kh);
-            else if (a.shift == 1) sel_rescan<2>(a, cen, found, tl, th, tlog, lane, kl, kh);
-            else sel_rescan<4>(a, cen, found, tl, th, tlog, lane, kl, kh);
-            kl = wave_max_key(kl);
-            kh = wave_max_key(kh);
-            s3_wave_fence();                                          // va and vb are read
-            if (lane == 0) { key[tl] = kl; key[th] = kh; }            // the same value where tl == th
-            s3_wave_fence();
-            if (ga * 64 + lane == tl) va = kl;
-            if (ga * 64 + lane == th) va = kh;
-            if (gb * 64 + lane == tl) vb = kl;
-            if (gb * 64 + lane == th) vb = kh;
-        }
-        if (lane == 0) found_s = found;
+    for (int q = 0; q < G; ++q) {
+        if (q * 64 + lane == w.ga) w.top[q] = ma;
+        if (q * 64 + lane == w.gb) w.top[q] = mb;
     }
-    __syncthreads();
-    const int found = found_s;
+    return best;
+}
+// Reads the tiles of the groups at both ends, behind a fence.
+template <int G>
+__device__ __forceinline__ void nms_open(NmsTop<G>& w, const NmsLds& l, int tl, int th, int lane) {
+    w.ga = tl >> 6;
+    w.gb = th >> 6;
+#pragma unroll
+    for (int q = 0; q < G; ++q)
+        if (q * 64 + lane >= w.ga && q * 64 + lane <= w.gb) w.top[q] = 0;
+    w.va = w.ga * 64 + lane < l.nt ? l.key[w.ga * 64 + lane] : 0ull;
+    w.vb = w.gb * 64 + lane < l.nt ? l.key[w.gb * 64 + lane] : 0ull;
+}
+// Stores the new maxima of the tiles at both ends.
+template <int G>
+__device__ __forceinline__ void nms_close(NmsTop<G>& w, const NmsLds& l, int tl, int th, unsigned long long kl, unsigned long long kh, int lane) {
+    s3_wave_fence();                                                  // va and vb are read
+    if (lane == 0) { l.key[tl] = kl; l.key[th] = kh; }                // the same value where tl == th
+    s3_wave_fence();
+    if (w.ga * 64 + lane == tl) w.va = kl;
+    if (w.ga * 64 + lane == th) w.va = kh;
+    if (w.gb * 64 + lane == tl) w.vb = kl;
+    if (w.gb * 64 + lane == th) w.vb = kh;
+}
+
+__device__ __forceinline__ void nms_spans(const SelArgs& a, const int* cen, const float* cden, int found, int tid, int lane, int wave) {
     // spans: a wavefront per centre walks outwards 64 positions at a time, both sides at once; a side ends before the
     // first position whose density is below rel * D[centre] or that is farther than max_half from the centre
     for (int r = wave; r < found; r += kNmsThreads / 64) {
@@ -293,6 +280,172 @@ __global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
         a.center[r] = -1; a.center_density[r] = 0.f; a.span_lo[r] = -1; a.span_hi[r] = -1;
     }
     if (tid == 0) a.n_found[0] = found;
+}
+
+__global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
+    extern __shared__ __align__(16) unsigned long long nms_lds[];
+    __shared__ int found_s;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const NmsLds l = nms_lds_of(a, nms_lds);
+    for (int64_t i0 = tid; i0 < a.L; i0 += 8 * kNmsThreads) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = i0 + u * kNmsThreads < a.L ? a.dens[i0 + u * kNmsThreads] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i0 + u * kNmsThreads < a.L) l.cur[i0 + u * kNmsThreads] = v[u];
+    }
+    nms_load_keys(l, a.tkey, a.nblk, 1, wave, lane);
+    __syncthreads();
+    if (wave == 0) {
+        NmsTop<kShortGroups> w;
+        nms_start(w, l, lane);
+        int found = 0;
+        while (found < a.n_centers) {
+            const unsigned long long best = nms_best(w, lane);
+            if (best == 0) break;                                     // only positive density makes a centre
+            const int64_t c = (int64_t)(unsigned)~(unsigned)best;
+            if (lane == 0) { l.cen[found] = (int)c; l.cden[found] = __uint_as_float((unsigned)(best >> 32)); }
+            ++found;
+            const int64_t lo = max((int64_t)0, c - a.radius), hi = min(a.L - 1, c + a.radius);
+            const int tl = (int)(lo >> 6), th = (int)(hi >> 6);
+            for (int t = tl + 1 + lane; t < th; t += 64) l.key[t] = 0;
+            for (int64_t p = lo + lane; p <= hi; p += 64) l.cur[p] = 0.f;
+            s3_wave_fence();                                          // cleared tiles and wiped positions are read by other lanes
+            nms_open(w, l, tl, th, lane);
+            unsigned long long kl = 0, kh = 0;                        // best live position of the tile at either end
+            const int64_t p0 = ((int64_t)tl << 6) + lane, p1 = ((int64_t)th << 6) + lane;
+            if (p0 < a.L) kl = peak_key(l.cur[p0], p0);
+            if (p1 < a.L) kh = peak_key(l.cur[p1], p1);
+            kl = wave_max_key(kl);
+            kh = wave_max_key(kh);
+            nms_close(w, l, tl, th, kl, kh, lane);
+        }
+        if (lane == 0) found_s = found;
+    }
+    __syncthreads();
+    nms_spans(a, l.cen, l.cden, found_s, tid, lane, wave);
+}
+
+__device__ __forceinline__ unsigned long long lane_value(unsigned long long v, int src) {
+    return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(v >> 32), src) << 32) |
+           (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, src);
+}
+
+// The word of block e with the positions of [lo, hi] marked.
+__device__ __forceinline__ unsigned long long nms_mark(unsigned long long m, int e, int64_t lo, int64_t hi) {
+    const int64_t p = (int64_t)e << 6;
+    const int from = (int)max((int64_t)0, lo - p), upto = (int)min((int64_t)63, hi - p);
+    return from <= upto ? m | (~0ull << from & ~0ull >> (63 - upto)) : m;
+}
+
+// U > 0: tiles of U blocks, searched whole.  U == 0: tiles of more blocks, searched by their keys.
+template <int U, int G>
+__global__ __launch_bounds__(kNmsThreads) void sel_nms_long_kernel(SelArgs a) {
+    extern __shared__ __align__(16) unsigned long long nms_lds[];
+    __shared__ int found_s;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const NmsLds l = nms_lds_of(a, nms_lds);
+    if (U == 1) nms_load_keys(l, a.tkey, a.nblk, 1, wave, lane);
+    else nms_load_keys(l, a.ckey, a.nckey, 1 << (a.shift - a.kshift), wave, lane);
+    __syncthreads();
+    if (wave == 0) {
+        const int tlog = 6 + a.shift, per = 1 << a.shift;             // blocks per tile
+        NmsTop<G> w;
+        nms_start(w, l, lane);
+        int found = 0;
+        while (found < a.n_centers) {
+            const unsigned long long best = nms_best(w, lane);
+            if (best == 0) break;                                     // only positive density makes a centre
+            const int64_t c = (int64_t)(unsigned)~(unsigned)best;
+            if (lane == 0) { l.cen[found] = (int)c; l.cden[found] = __uint_as_float((unsigned)(best >> 32)); }
+            ++found;
+            const int64_t lo = max((int64_t)0, c - a.radius), hi = min(a.L - 1, c + a.radius);
+            const int tl = (int)(lo >> tlog), th = (int)(hi >> tlog);
+            const int b0 = tl << a.shift, b1 = th << a.shift;         // first blocks of both tiles
+            const int g0 = (b0 & ~63) + lane, g1 = (b1 & ~63) + lane; // blocks of this lane (the first of them, if a tile has more than 64)
+            const bool in0 = g0 >= b0 && g0 < b0 + per && g0 < a.nblk, in1 = g1 >= b1 && g1 < b1 + per && g1 < a.nblk;
+            const bool live_l = l.key[tl] != 0, live_h = l.key[th] != 0;
+            unsigned long long kl = 0, kh = 0;                        // best live position of the tile at either end
+            if constexpr (U > 0) {
+                float d0[U], d1[U];
+                unsigned long long m0 = 0, m1 = 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t p0 = ((int64_t)(b0 + u) << 6) + lane, p1 = ((int64_t)(b1 + u) << 6) + lane;
+                    d0[u] = d1[u] = 0.f;
+                    if (p0 < a.L) d0[u] = a.dens[p0];
+                    if (p1 < a.L) d1[u] = a.dens[p1];
+                }
+                if (in0) m0 = a.dead[g0];
+                if (in1) m1 = a.dead[g1];
+                for (int t = tl + 1 + lane; t < th; t += 64) l.key[t] = 0;
+                s3_wave_fence();                                      // the cleared tiles are read by other lanes
+                nms_open(w, l, tl, th, lane);
+                unsigned long long s0 = m0, s1 = m1;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i0 = (b0 & 63) + u, i1 = (b1 & 63) + u; // lanes that own the blocks; the words are scalars
+                    const unsigned long long w0 = nms_mark(lane_value(m0, i0), b0 + u, lo, hi);
+                    const unsigned long long w1 = nms_mark(lane_value(m1, i1), b1 + u, lo, hi);
+                    if (lane == i0) s0 = w0;
+                    if (lane == i1) s1 = w1;
+                    const int64_t p0 = ((int64_t)(b0 + u) << 6) + lane, p1 = ((int64_t)(b1 + u) << 6) + lane;
+                    if (!(w0 >> lane & 1)) kl = max(kl, peak_key(d0[u], p0));
+                    if (!(w1 >> lane & 1)) kh = max(kh, peak_key(d1[u], p1));
+                }
+                if (in0) a.dead[g0] = s0;
+                if (in1) a.dead[g1] = s1;                             // the same words and values where tl == th
+                kl = wave_max_key(kl);
+                kh = wave_max_key(kh);
+            } else {
+                const int el = (int)(lo >> 6), eh = (int)(hi >> 6);
+                const int64_t p0 = ((int64_t)el << 6) + lane, p1 = ((int64_t)eh << 6) + lane;
+                const bool own0 = lane == (el & 63), own1 = lane == (eh & 63);
+                float d0 = 0.f, d1 = 0.f;
+                unsigned long long m0 = 0, m1 = 0, t0 = 0, t1 = 0, v0 = 0, v1 = 0;
+                if (p0 < a.L) d0 = a.dens[p0];
+                if (p1 < a.L) d1 = a.dens[p1];
+                if (own0) { m0 = a.dead[el]; t0 = a.tkey[el]; }
+                if (own1) { m1 = a.dead[eh]; t1 = a.tkey[eh]; }
+                if (in0) v0 = a.tkey[g0];
+                if (in1) v1 = a.tkey[g1];
+                for (int t = tl + 1 + lane; t < th; t += 64) l.key[t] = 0;
+                s3_wave_fence();                                      // the cleared tiles are read by other lanes
+                nms_open(w, l, tl, th, lane);
+                m0 = nms_mark(lane_value(m0, el & 63), el, lo, hi);
+                m1 = nms_mark(lane_value(m1, eh & 63), eh, lo, hi);
+                if (own0) a.dead[el] = m0;
+                if (own1) a.dead[eh] = m1;                            // the same where el == eh
+                unsigned long long k0 = 0, k1 = 0;                    // (a block without live positions stays so)
+                if (!(m0 >> lane & 1) && lane_value(t0, el & 63)) k0 = peak_key(d0, p0);
+                if (!(m1 >> lane & 1) && lane_value(t1, eh & 63)) k1 = peak_key(d1, p1);
+                // both tiles: the positions of the blocks at the ends, the keys of the blocks outside the interval
+                unsigned long long n0 = tl == th ? max(k0, k1) : k0, n1 = tl == th ? max(k0, k1) : k1;
+                auto outside = [&](int e, unsigned long long v, unsigned long long& n) {
+                    if (e < el || e > eh) n = max(n, v);
+                    if (v && e > el && e < eh) a.tkey[e] = 0;
+                };
+                outside(g0, v0, n0);
+                outside(g1, v1, n1);
+                for (int s = 64; s < per; s += 64) {
+                    if (g0 + s < a.nblk) outside(g0 + s, a.tkey[g0 + s], n0);
+                    if (g1 + s < a.nblk) outside(g1 + s, a.tkey[g1 + s], n1);
+                }
+                kl = wave_max_key(n0);
+                kh = wave_max_key(n1);
+                const unsigned long long e0 = wave_max_key(k0), e1 = wave_max_key(k1);
+                if (own0) a.tkey[el] = e0;
+                if (own1) a.tkey[eh] = e1;                            // the same where el == eh
+            }
+            nms_close(w, l, tl, th, live_l ? kl : 0ull, live_h ? kh : 0ull, lane);      // a tile without live positions stays so
+        }
+        if (lane == 0) found_s = found;
+    }
+    __syncthreads();
+    nms_spans(a, l.cen, l.cden, found_s, tid, lane, wave);
 }
 
 // ---- Phase 3 set operations ----
@@ -457,14 +610,18 @@ __global__ __launch_bounds__(kFuseThreads) void fuse_compact_kernel(const unsign
 }
 
 struct SelLayout {
-    size_t dens, tkey, total;
+    size_t dens, tkey, ckey, dead, total;
+    int nblk;
 };
 SelLayout sel_layout(int64_t L) {
     SelLayout l;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += s3_align(bytes); return at; };
+    l.nblk = (int)((L + kTile - 1) / kTile);
     l.dens = take((size_t)L * 4);
-    l.tkey = take((size_t)((L + kTile - 1) / kTile) * 8);
+    l.tkey = take((size_t)l.nblk * 8);
+    l.ckey = take(l.nblk > kNmsTilesMin ? (size_t)(l.nblk + 1) / 2 * 8 : 0);      // kshift is at least 1 where there are any
+    l.dead = take((size_t)l.nblk * 8);
     l.total = o;
     return l;
 }
@@ -517,9 +674,22 @@ extern "C" int s3_select_spans(const float* scores, int64_t n_positions, const f
     a.max_half = max_half_len; a.rel = rel_threshold;
     a.dens = density_out ? density_out : (float*)(base + l.dens);
     a.tkey = (unsigned long long*)(base + l.tkey);
-    a.ntile = (int)((n_positions + kTile - 1) / kTile);
-    a.shift = 0;
-    while (((a.ntile + (1 << a.shift) - 1) >> a.shift) > kNmsTiles) ++a.shift;
+    a.ckey = (unsigned long long*)(base + l.ckey);
+    a.nblk = l.nblk;
+    // Tiles of one block as long as their maxima fit the search's LDS beside the centres; from there on no more tiles than it
+    // takes, since loading them costs more than searching longer ones (2^21 positions, one centre: 24 us with
+    // 16384 tiles, 20 with 8192)
+    size_t nt, fixed;
+    for (a.shift = 0;; ++a.shift) {
+        nt = (size_t)((l.nblk + (1 << a.shift) - 1) >> a.shift);
+        fixed = (nt + (nt + 63) / 64) * 8 + (size_t)n_centers * 8;
+        if (nt <= kNmsTilesMin || (a.shift == 0 && nt <= kNmsTiles && fixed <= kNmsLds)) break;
+    }
+    // the convolution leaves one key per tile of the search, as far as a workgroup's positions reach
+    a.kshift = a.shift < kConvKeyShift ? a.shift : kConvKeyShift;
+    a.nckey = a.kshift ? (l.nblk + (1 << a.kshift) - 1) >> a.kshift : 0;
+    const bool cached = fixed + (size_t)n_positions * 4 <= kNmsLds;                  // about 36000 positions (shift is 0)
+    a.dead = cached ? nullptr : (unsigned long long*)(base + l.dead);
     a.center = center; a.center_density = center_density; a.span_lo = span_lo; a.span_hi = span_hi; a.n_found = n_found;
     hipStream_t st = (hipStream_t)stream;
     const bool large = n_positions >= kConvLargeFrom;
@@ -528,12 +698,15 @@ extern "C" int s3_select_spans(const float* scores, int64_t n_positions, const f
     const dim3 grid((unsigned)((n_positions + per_wg - 1) / per_wg));
     if (large) hipLaunchKernelGGL(sel_conv_kernel<kConvLarge>, grid, dim3(kConvLarge), lds, st, a);
     else hipLaunchKernelGGL(sel_conv_kernel<kConvSmall>, grid, dim3(kConvSmall), lds, st, a);
-    static S3LdsOnce once;
-    if (int rc = s3_allow_lds(once, (const void*)sel_nms_kernel, kNmsLds)) return rc;
-    const size_t nt = (size_t)((a.ntile + (1 << a.shift) - 1) >> a.shift);
-    const size_t fixed = (nt + (nt + 63) / 64) * 8 + (size_t)n_centers * 8;          // at most 97 KB
-    a.cached = fixed + (size_t)n_positions * 4 <= kNmsLds;                           // about 36000 positions
-    hipLaunchKernelGGL(sel_nms_kernel, dim3(1), dim3(kNmsThreads), fixed + (a.cached ? (size_t)n_positions * 4 : 0), st, a);
+    // us a round, radius 48: 1.2 in tiles of one block (two or four groups per lane), 1.5 of two blocks, 2.0 of four
+    // searched whole and 1.7 to 1.8 by their keys
+    static S3LdsOnce once[5];
+    void (*const ways[5])(SelArgs) = {sel_nms_kernel, sel_nms_long_kernel<1, 2>, sel_nms_long_kernel<1, 4>, sel_nms_long_kernel<2, 2>,
+                                      sel_nms_long_kernel<0, 2>};
+    const int way = cached ? 0 : (a.shift == 0 ? (nt <= kNmsTilesMin ? 1 : 2) : (a.shift == 1 ? 3 : 4));
+    const auto nms = ways[way];
+    if (int rc = s3_allow_lds(once[way], (const void*)nms, kNmsLds)) return rc;
+    hipLaunchKernelGGL(nms, dim3(1), dim3(kNmsThreads), fixed + (cached ? (size_t)n_positions * 4 : 0), st, a);
     S3_HIP(hipGetLastError());
     return S3_OK;
 }

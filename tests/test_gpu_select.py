@@ -134,7 +134,11 @@ def test_scores_to_fused_indices_chain():
 @pytest.mark.parametrize("L,radius,n_centers", [
     (64, 3, 40), (65, 64, 5), (4096, 1, 300), (4097, 63, 70),      # one tile, one more; a group of 64 tiles, one more
     (30_011, 4100, 9), (36_000, 48, 40), (40_000, 48, 100),        # suppression over whole groups; the curve in LDS and not
-    (1 << 18, 17, 64), ((1 << 19) + 1, 64, 40), (1_100_003, 200, 70),      # wide convolution; tiles of 128 and of 256 positions
+    (1 << 18, 17, 64), ((1 << 19) + 1, 64, 40), (1_100_003, 200, 70),      # wide convolution; two and four groups per lane; two blocks per tile
+    (150_000, 17, 4096), (150_000, 40, 4096), (300_000, 0, 200),           # the most centres; every block wiped in parts; single positions
+    ((1 << 21) + 777, 40, 600), ((1 << 21) + 777, 3000, 60),               # four blocks per tile, gone and live ones in the same tile
+    ((1 << 20) + 1, 64, 40), (1_000_000, 100_000, 4096), (1_000_000, 100_000, 2000),      # two blocks per tile, by length and by centres
+    (9_000_001, 300, 40), (9_000_001, 300_000, 3000),                      # tiles as long as a workgroup of the convolution, and longer
 ])
 def test_peak_search_at_the_edges_of_its_tiles(L, radius, n_centers):
     """Few distinct densities (a box kernel over 0/1 scores), so that ties across tiles and groups are common."""
