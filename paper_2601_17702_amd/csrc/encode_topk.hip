@@ -452,7 +452,6 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
     p.x = (const char*)x; p.w = (const char*)w_enc; p.b = b_enc; p.ids = ids; p.vals = vals;
     p.T = T; p.n_feat = n_feat; p.k = k; p.n_heads = n_heads;
     p.ablate = 0;
-    p.fsplit = 1;
     int parts = tau_hint ? 1 : parts_for(n_heads, T, n_feat, k);
     const bool room = parts == 1 || (ws && ws_bytes >= (size_t)n_heads * T * parts * k * sizeof(uint2));
     if (!room) parts = 1;                                    // no scratch: one range

@@ -278,8 +278,8 @@ static int fast_dispatch(EncParams p, hipStream_t st) {
     }
 #endif
     if (large_k) {
-        // A call whose token tiles would leave most compute units without a workgroup (an SAE training batch: one
-        // head, a few thousand tokens) runs in one-wavefront workgroups instead.
+        // A call whose token tiles would leave compute units without a workgroup (a streamed chunk of few heads, a plain call of
+        // more token tiles than the tiled kernel takes) runs in one-wavefront workgroups instead.
         const long long tiles = (long long)p.n_heads * ((p.T + k128::kTokWG - 1) / k128::kTokWG);
         return tiles < kFillWGs ? k128n::launch_fast<0>(p, st) : k128::launch_fast<0>(p, st);
     }

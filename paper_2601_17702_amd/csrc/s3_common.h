@@ -132,8 +132,6 @@ struct EncParams {
     int T, n_feat, k, n_heads, capt, tiles_per_head;
     int ablate;    // tuning builds (-DS3_TUNING) only: parts of the kernel compiled out; always 0 in the product
     int soft;      // fast path: list length per lane that asks for a workgroup-wide refresh (0: off)
-    int fsplit;    // fast path: 1 (F > 1: the call's heads are F feature ranges of each real head).  The kernel keeps the argument
-                   // because a build without it was 1.2 % slower at 256 heads x 32768 tokens (46.4 -> 47.0 ms)
     // streamed calls (threshold carried from the previous chunk), fast path only
     float margin;              // relative margin below the carried bound
     int mode;                  // 0 plain, 1 start from the carried bound, 2 redo the tokens listed in redo_list,
