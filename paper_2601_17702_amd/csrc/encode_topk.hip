@@ -354,9 +354,11 @@ int parts_for(int n_heads, int T, int n_feat, int k) {
 
 // Whether a plain call of a shape that the fast kernel takes is better off here: while its token tiles fit the chip at
 // once.  The fast kernel has 64 to 256 tokens per workgroup and walks all features in each.  us, fast / this kernel, of
-// 16384 features: 4 tokens of 8 heads, k 32: 224 / 34; 4096 tokens of one head, k 32: 439 / 130, k 128: 500 / 227;
-// at the line, 256 tiles: 8192 tokens of one head, k 8 / 32 / 64 / 128: 343 / 154, 440 / 193, 437 / 232, 506 / 294.  Beyond
-// it a second turn costs as much again, and the fast kernel's time does not grow before its own workgroups fill the chip.
+// 16384 features: 4 tokens of 8 heads, k 32: 229 / 33; 4096 tokens of one head, k 32: 439 / 130, k 128: 500 / 227; at the
+// line, 256 tiles: 8192 tokens of one head, k 8 / 32 / 64 / 128: 343 / 154, 440 / 193, 437 / 232, 506 / 294.  Many heads read
+// many weights, but so they do there: 4 tokens of 64, 128 and 256 heads, k 32: 236 / 71, 254 / 119, 274 / 217, of 256 heads, k 64
+// and 128: 349 / 227, 394 / 267; 32 tokens of 256 heads, k 32: 314 / 244; of 4096 features 142 / 86.  Beyond the line a second
+// turn costs as much again, and the fast kernel's time does not grow before its own workgroups fill the chip.
 bool tiled_pays(int n_heads, int T) { return token_tiles(n_heads, T) <= kSlots; }
 
 }  // namespace
@@ -368,7 +370,8 @@ int env_int(const char* name, int dflt) {
 }
 #endif
 
-// The k up to which a shape is accepted (stated in the header).
+// The k up to which a shape is accepted (stated in the header).  The lists have room for S3_MAX_K at every width; callers may
+// rely on the refusal, so it stays.
 static int largest_k(int dtype, int d_head) {
     if (dtype == S3_BF16) return d_head == 256 ? 121 : S3_MAX_K;
     return d_head == 64 ? S3_MAX_K : (d_head == 128 ? 121 : 78);

@@ -3,8 +3,8 @@
 // 8 wavefronts with 40 list slots per lane for k <= 32, 4 wavefronts with 80 slots per lane for k <= 64, 2 wavefronts
 // with 140 slots per lane for k <= 128.
 //
-// Same method as the generic kernel (features on the MFMA M axis, per-token threshold tau,
-// candidate lists in LDS, exact selection), laid out for two wavefronts per SIMD:
+// Features on the MFMA M axis, a threshold tau per token, candidate lists in LDS and exact selection, as in the tiled kernel;
+// the Top-k state of a token belongs to the two lanes that hold its accumulators.  Laid out for two wavefronts per SIMD:
 //
 //   - workgroup = 8 (k <= 32) or 4 (k <= 64) wavefronts of 32 tokens.  W_enc streams through a ring of four 32-feature
 //     stages in LDS.  Each wavefront copies 4 rows of a stage per step straight from global memory

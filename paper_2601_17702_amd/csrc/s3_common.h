@@ -122,7 +122,7 @@ __device__ __forceinline__ int s3_block_excl_scan(int v, int* wsum, int& total) 
     return base + x - v;
 }
 
-// ---- encoder internals shared by the generic and the fast kernel ----
+// ---- encoder internals shared by the tiled and the fast kernel ----
 struct EncParams {
     const char* x;
     const char* w;

@@ -2,8 +2,9 @@
 // (about) the k largest whenever it would overflow.  Shared by the tiled encoder and the merge of its feature ranges.
 //
 // Searches work on ordered keys (unsigned order = float order; 0 = no element).  -0 and +0 are one value, as in a float
-// compare.  Inputs are finite; -inf marks the places that hold no element.  Elements arrive with ascending ids among equal values, so an element that only
-// equals the threshold of a list that holds k at or above it loses to all of those.
+// compare.  Inputs are finite; -inf marks the places that hold no element (nor does a NaN).  Elements arrive with ascending ids
+// among equal values, so an element that only equals the threshold of a list that holds k at or above it loses to all of
+// those.
 //
 // Everything that steers the search (counts, thresholds) is uniform: a count is one compare per register whose mask is
 // counted by the scalar unit, so a bisection step over a 256-element list is 4 compares, 4 bit counts and 4 adds.
@@ -22,13 +23,6 @@ __device__ __forceinline__ float value_of(unsigned key) {
 }
 __device__ __forceinline__ int below(unsigned long long m) {       // set bits of m in lanes below this one
     return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-}
-__device__ __forceinline__ unsigned wave_max_u(unsigned v) {
-#define S3_DPP_MAX(CTRL, ROWS) v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false))
-    S3_DPP_MAX(0x111, 0xf); S3_DPP_MAX(0x112, 0xf); S3_DPP_MAX(0x114, 0xf); S3_DPP_MAX(0x118, 0xf);
-    S3_DPP_MAX(0x142, 0xa); S3_DPP_MAX(0x143, 0xc);
-#undef S3_DPP_MAX
-    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 template <int N>
@@ -52,8 +46,8 @@ __device__ __forceinline__ int raise(const unsigned (&key)[N], int k, int loose,
         mx = max(mx, key[i]);
         mn = min(mn, key[i] - 1);                                  // no element: largest of all
     }
-    unsigned hi = wave_max_u(mx) + 1;                              // keys stay below 0xFF800001
-    lo = max(lo, 0xFFFFFFFFu - wave_max_u(0xFFFFFFFFu - mn) + 1);  // nothing lies below the smallest element
+    unsigned hi = s3_wave_max_u32(mx) + 1;                              // keys stay below 0xFF800001
+    lo = max(lo, 0xFFFFFFFFu - s3_wave_max_u32(0xFFFFFFFFu - mn) + 1);  // nothing lies below the smallest element
     int chi = 0;
     const float lwant = __log2f(0.5f * (float)(k + loose));
     bool interp = true;
@@ -109,8 +103,8 @@ __device__ __forceinline__ int cut_and_store(const unsigned (&key)[N], const uns
 }
 
 // Takes the NC registers' elements above the list's threshold `tau` into a list of `cnt` with room for 64 * LR.  Element i of
-// the lane has id id_of(i).  An append is kept short (most chunks bring a token
-// one or two elements): four compares, and per register with a hit the position from the mask and two LDS writes.
+// the lane has id id_of(i).  An append is kept short (most chunks bring a token one or two elements): four compares, and per
+// register with a hit the position from the mask and two LDS writes.
 template <int NC, int LR, class IdOf>
 __device__ __forceinline__ void take(const float (&v)[NC], IdOf id_of, int k, int loose, float* lv, uint16_t* li, int& cnt,
                                      float& tau) {
