@@ -360,6 +360,31 @@ def test_greedy_spans_of_long_contexts(T, span_len, top_b, nms):
     assert out[0][:out[2]].tolist() == list(st_o)
 
 
+def test_greedy_spans_with_more_blocks_per_tile_than_lanes():
+    """Above 2^26 windows: 128 blocks per tile.  Few positions have postings, most of them in three tiles; whole numbers as
+    weights, so that the window sums of the reference are exact (the common IDF does not change their order)."""
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(7)
+    L, span_len, top_b, n = (1 << 26) + (1 << 20), 700, 30, 6000
+    tile = 256 * 128
+    at = np.unique(np.concatenate([rng.integers(t * tile, (t + 1) * tile, 1800) for t in (0, 1, 777)] + [rng.integers(0, L, 400)]))[:n]
+    n = len(at)
+    vals = rng.integers(1, 1 << 22, n)
+    ids = torch.from_numpy(rng.permutation(n).astype(np.int32)[None, :, None]).cuda()
+    ix = s3.Index(1, n, 1, n)
+    ix.append(ids, positions=torch.from_numpy(at.astype(np.int32)).cuda())
+    ix.finalize()
+    st, _, nf, _ = ix.coactivate_score(ids, torch.from_numpy(vals.astype(np.float32)[None, :, None]).cuda(), L, span_len, top_b)
+    torch.cuda.synchronize()
+    S = np.zeros(L + 1, np.int64)
+    S[at + 1] = vals
+    P = np.cumsum(S)
+    W = (P[span_len:] - P[:-span_len]).astype(np.float64)
+    st_o, _ = orc.topb(W, span_len, top_b, nms=True)
+    assert int(nf.item()) == top_b and st.cpu().numpy().tolist() == list(st_o)
+
+
 def test_scoring_with_shifted_positions_and_index_reuse():
     """Positions that start at an offset: inside the range the index's block table covers (table used), beyond it
     (lists are searched instead), and the same index object reset and fed another stream (table rebuilt)."""

@@ -139,6 +139,7 @@ def test_scores_to_fused_indices_chain():
     ((1 << 21) + 777, 40, 600), ((1 << 21) + 777, 3000, 60),               # four blocks per tile, gone and live ones in the same tile
     ((1 << 20) + 1, 64, 40), (1_000_000, 100_000, 4096), (1_000_000, 100_000, 2000),      # two blocks per tile, by length and by centres
     (9_000_001, 300, 40), (9_000_001, 300_000, 3000),                      # tiles as long as a workgroup of the convolution, and longer
+    (40_000_000, 1000, 40),                                                # more blocks per tile than a wavefront has lanes
 ])
 def test_peak_search_at_the_edges_of_its_tiles(L, radius, n_centers):
     """Few distinct densities (a box kernel over 0/1 scores), so that ties across tiles and groups are common."""
