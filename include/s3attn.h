@@ -60,7 +60,8 @@ const char* s3_last_error(void);
  * Limits: d_head in {64, 128, 256}; 1 <= k <= min(n_feat, S3_MAX_K); k <= 128 for bf16 with
  * d_head <= 128 and fp32 with d_head 64, k <= 121 for bf16 with d_head 256 and fp32 with d_head
  * 128, k <= 78 for fp32 with d_head 256 (k = 128 is the sparsity the paper trains its SAEs with,
- * App. B.3); n_feat <= S3_MAX_FEAT; T >= 0 (T == 0 is a no-op); n_heads >= 1.  Otherwise S3_EINVAL.
+ * App. B.3; the smaller limits are what candidate lists of two lanes per token left room for, and
+ * stay although the lists have more now); n_feat <= S3_MAX_FEAT; T >= 0 (T == 0 is a no-op); n_heads >= 1.  Otherwise S3_EINVAL.
  * bf16 with d_head 128 and n_feat a multiple of 128 takes the fast kernel, unless the tokens are few
  * (at most 256 tiles of 32 over all heads) and one workgroup per tile fills the chip or there is scratch.
  * No workspace is needed; s3_sae_encode_topk_ws is the same call with one.
