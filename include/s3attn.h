@@ -64,14 +64,16 @@ const char* s3_last_error(void);
  * stay although the lists have more now); n_feat <= S3_MAX_FEAT; T >= 0 (T == 0 is a no-op); n_heads >= 1.  Otherwise S3_EINVAL.
  * bf16 with d_head 128 and n_feat a multiple of 128 takes the fast kernel, unless the tokens are few
  * (at most 256 tiles of 32 over all heads) and one workgroup per tile fills the chip or there is scratch.
- * No workspace is needed; s3_sae_encode_topk_ws is the same call with one.
+ * No workspace is needed; s3_sae_encode_topk_ws is the same call with one, and the faster one for many
+ * tokens and features as well (candidate lists in scratch: up to 440 MB).
  */
 int s3_sae_encode_topk(const void* x, int dtype, int T, int d_head, const void* w_enc,
                        const float* b_enc, int n_feat, int k, int n_heads, int32_t* ids,
                        float* vals, void* stream);
 
 /* s3_sae_encode_topk with scratch: a call with few tokens then spreads the features of a head over
- * several workgroups and merges their selections.  The results are the same bit for bit.
+ * several workgroups and merges their selections; one with many keeps its candidate lists there.  The
+ * results are the same bit for bit.
  *   ws   s3_sae_encode_topk_workspace(...) bytes (0: the call has no use for scratch, ws may be
  *        NULL), 256-byte aligned, device; contents meaningless between calls.  With less than that the
  *        call runs as s3_sae_encode_topk.
@@ -92,10 +94,10 @@ int s3_sae_encode_topk_ws(const void* x, int dtype, int T, int d_head, const voi
  *   tau_hint [n_heads][2] fp32, device, read and overwritten: the smallest tau_t / |x_t| and the
  *            smallest tau_t over the tokens of the previous call; only the one that was the tighter
  *            predictor on that call is kept, the other is -INFINITY.  Fill with -INFINITY before
- *            the first chunk of a stream: a head without a bound has its first 256 tokens (128 for
- *            k > 32) selected from scratch first, and their thresholds start the rest of the chunk.
- *   ws       s3_sae_encode_topk_stream_workspace(n_heads, T) bytes, 256-byte aligned, device;
- *            scratch, contents meaningless between calls.
+ *            the first chunk of a stream: a head without a bound takes its tokens' first thresholds
+ *            from a sample of the features, or from a first tile of tokens.
+ *   ws       s3_sae_encode_topk_stream_workspace(n_heads, T) bytes (candidate lists: up to 440 MB), 256-byte
+ *            aligned, device; scratch, contents meaningless between calls.  No smaller for a larger T.
  * Shapes the threshold-carrying kernel is not built for (anything but bf16, d_head 128,
  * n_feat % 128 == 0) run exactly as s3_sae_encode_topk and leave tau_hint untouched.
  * Errors as s3_sae_encode_topk; S3_ECAPACITY if ws_bytes is too small. */

@@ -425,8 +425,17 @@ static int tiled_slices(const EncParams& p, int dtype, int d_head, hipStream_t s
     return S3_OK;
 }
 
+// What a streamed call of up to T tokens may need, whatever its n_feat and k.
+static size_t stream_workspace(int n_heads, int T) {
+    const size_t a = s3_encode_fast_stream_workspace(n_heads, T), b = s3_encode_scan_workspace_max(n_heads, T);
+    return a > b ? a : b;
+}
+
 static size_t plain_workspace(int dtype, int T, int d_head, int n_feat, int k, int n_heads) {
-    if (s3_encode_fast_ok(dtype, d_head, n_feat, k) && !tiled_pays(n_heads, T)) return 0;
+    if (s3_encode_fast_ok(dtype, d_head, n_feat, k)) {
+        if (s3_encode_scan_pays(n_heads, T, n_feat, k, false)) return s3_encode_scan_workspace(n_heads, T, n_feat, k);
+        if (!tiled_pays(n_heads, T)) return 0;
+    }
     const int parts = parts_for(n_heads, T, n_feat, k);
     return parts > 1 ? (size_t)n_heads * T * parts * k * sizeof(uint2) : 0;
 }
@@ -446,7 +455,7 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
     if (ws && ((uintptr_t)ws & 255)) return s3_fail(S3_EINVAL, "%s: workspace must be 256-byte aligned", who);
     if (tau_hint) {
         if (!ws) return s3_fail(S3_EINVAL, "%s: null workspace", who);
-        const size_t need = s3_encode_fast_stream_workspace(n_heads, T);
+        const size_t need = stream_workspace(n_heads, T);
         if (ws_bytes < need) return s3_fail(S3_ECAPACITY, "%s: workspace %zu < %zu bytes", who, ws_bytes, need);
     }
     if (T == 0) return S3_OK;
@@ -455,6 +464,9 @@ static int encode_impl(const char* who, const void* x, int dtype, int T, int d_h
     p.x = (const char*)x; p.w = (const char*)w_enc; p.b = b_enc; p.ids = ids; p.vals = vals;
     p.T = T; p.n_feat = n_feat; p.k = k; p.n_heads = n_heads;
     p.ablate = 0;
+    if (s3_encode_fast_ok(dtype, d_head, n_feat, k) && ws && s3_encode_scan_pays(n_heads, T, n_feat, k, tau_hint != nullptr) &&
+        (tau_hint || ws_bytes >= s3_encode_scan_workspace(n_heads, T, n_feat, k)))
+        return s3_encode_scan(p, tau_hint, ws, (hipStream_t)stream);
     int parts = tau_hint ? 1 : parts_for(n_heads, T, n_feat, k);
     const bool room = parts == 1 || (ws && ws_bytes >= (size_t)n_heads * T * parts * k * sizeof(uint2));
     if (!room) parts = 1;                                    // no scratch: one range
@@ -493,7 +505,7 @@ extern "C" int s3_sae_encode_topk_ws(const void* x, int dtype, int T, int d_head
 
 extern "C" size_t s3_sae_encode_topk_stream_workspace(int n_heads, int T) {
     if (n_heads < 1 || T < 0) return 0;
-    return s3_encode_fast_stream_workspace(n_heads, T);
+    return stream_workspace(n_heads, T);
 }
 
 extern "C" int s3_sae_encode_topk_stream(const void* x, int dtype, int T, int d_head, const void* w_enc,

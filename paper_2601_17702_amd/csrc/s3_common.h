@@ -151,6 +151,10 @@ bool s3_encode_fast_ok(int dtype, int d_head, int n_feat, int k);   // shapes th
 int s3_encode_fast_launch(EncParams p, hipStream_t st);
 size_t s3_encode_fast_stream_workspace(int n_heads, int T);
 int s3_encode_fast_stream(EncParams p, float* hint, void* ws, hipStream_t st);   // hint [n_heads][2] device, in/out
+bool s3_encode_scan_pays(int n_heads, int T, int n_feat, int k, bool streamed);
+size_t s3_encode_scan_workspace(int n_heads, int T, int n_feat, int k);
+size_t s3_encode_scan_workspace_max(int n_heads, int T);
+int s3_encode_scan(const EncParams& p, float* hint, void* ws, hipStream_t st);
 
 // Workgroup -> (head, token tile).  Workgroups are dealt round-robin to the 8 XCDs (each with its own
 // L2), so consecutive tiles of one head are placed on the SAME XCD: they stream the same W_enc rows at

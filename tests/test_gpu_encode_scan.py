@@ -1,0 +1,151 @@
+"""The scan encoder (csrc/encode_topk_scan.hip) at the edges of its tiles, lists and ranges: bit for bit the same as the tiled
+kernel (the C entry point without scratch), which the oracle checks element by element elsewhere, and against the oracle itself."""
+import numpy as np
+import pytest
+import torch  # noqa: F401  before the library, whose HIP runtime is then torch's
+
+from paper_2601_17702_amd import synth
+from tests import parity
+
+NF = 16384
+
+
+def test_stream_scratch_of_a_shorter_or_narrower_call_is_no_larger():
+    """A caller sizes the scratch once for its longest chunk; the ragged last one runs with the same."""
+    import paper_2601_17702_amd as s3
+    for heads in (1, 3, 8, 32, 100, 256):
+        need = [s3.sae_encode_topk_stream_workspace(heads, T) for T in (1, 255, 256, 257, 511, 1000, 2048, 4097, 70000)]
+        assert need == sorted(need) and need[0] > 0
+    for T in (1, 300, 2048):
+        need = [s3.sae_encode_topk_stream_workspace(h, T) for h in (1, 2, 8, 9, 31, 64, 256)]
+        assert need == sorted(need)
+
+
+def plain_without_scratch(x, W, b, k):
+    """s3_sae_encode_topk: no scratch, so never the scan encoder."""
+    import torch
+    import paper_2601_17702_amd as s3
+    H, T, d = x.shape
+    ids = torch.full((H, T, k), -7, dtype=torch.int32, device="cuda")
+    vals = torch.full((H, T, k), -7.0, device="cuda")
+    rc = s3.lib().s3_sae_encode_topk(s3._ptr(x), 0, T, d, s3._ptr(W), s3._ptr(b), W.shape[1], k, H, s3._ptr(ids), s3._ptr(vals), s3._stream())
+    assert rc == 0
+    return ids, vals
+
+
+def problem(H, T, nf, seed):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    W = torch.randn(H, nf, 128, generator=g, device="cuda")
+    W = (W / W.norm(dim=2, keepdim=True)).to(torch.bfloat16)
+    x = torch.randn(H, T, 128, generator=g, device="cuda").to(torch.bfloat16)
+    return x, W, 0.01 * torch.randn(H, nf, generator=g, device="cuda")
+
+
+def same(a, b):
+    import torch
+    torch.cuda.synchronize()
+    ok = torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    assert ok
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,T,nf,k", [
+    (1, 256, NF, 1),          # one tile, sixteen ranges, the smallest k
+    (1, 257, NF, 32),         # a tile with one token
+    (3, 300, NF, 33),         # rows that no 16-byte store can take
+    (2, 321, 12288, 64),      # ranges that do not divide the stages
+    (5, 511, NF, 65),
+    (9, 449, NF, 128),        # heads beyond a multiple of eight, a wavefront with one token
+    (65, 256, NF, 40),        # more tiles than are split: one range each
+    (130, 700, NF, 30),       # the grid walks more tiles than it has workgroups
+])
+@pytest.mark.timeout(100)
+def test_streamed_and_plain_calls_equal_the_tiled_kernel(H, T, nf, k):
+    import paper_2601_17702_amd as s3
+    x, W, b = problem(H, T, nf, H * 1000 + T + k)
+    want = plain_without_scratch(x, W, b, k)
+    same(s3.sae_encode_topk(x, W, b, k), want)
+    hint = s3.new_tau_hint(H)
+    for _ in range(3):                       # without a bound, then with one as tight as it gets
+        same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+        h = hint.cpu().numpy()
+        assert np.all(np.isfinite(h).sum(axis=1) == 1)
+        # the carried value is a lower bound of the k-th values
+        kth = want[1][:, :, -1].cpu().numpy()
+        assert np.all(np.where(np.isfinite(h[:, 1]), h[:, 1], -np.inf) <= kth.min(axis=1) + 1e-6)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,T,k", [(8, 512, 32), (70, 512, 48), (70, 512, 128)])
+@pytest.mark.timeout(100)
+def test_some_tokens_start_too_high(H, T, k):
+    """A bound in the middle of the tokens' thresholds: some wavefronts of a workgroup have tokens to walk again, some have none."""
+    import torch
+    import paper_2601_17702_amd as s3
+    x, W, b = problem(H, T, NF, 5 + k)
+    want = plain_without_scratch(x, W, b, k)
+    r = want[1][:, :, -1] / x.float().norm(dim=2)
+    for q in (0.002, 0.3, 0.99):
+        hint = s3.new_tau_hint(H)
+        hint[:, 0] = torch.quantile(r, q, dim=1) / 0.96          # the call starts 4 % below it
+        same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+    for bad in (float("inf"), float("nan"), -1e30):
+        hint = torch.full((H, 2), bad, device="cuda")
+        same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,T,k", [(2, 300, 32), (70, 256, 64), (66, 300, 128)])
+@pytest.mark.timeout(100)
+def test_ties_masked_features_and_sorted_dictionaries(H, T, k):
+    import torch
+    import paper_2601_17702_amd as s3
+    x, W, b = problem(H, T, NF, 77 + k)
+    # every pre-activation the same: the lowest ids, from lists that are cut again and again
+    zero = torch.zeros_like(W)
+    same(s3.sae_encode_topk(x, zero, torch.ones_like(b), k), plain_without_scratch(x, zero, torch.ones_like(b), k))
+    # few different values
+    g = torch.Generator(device="cuda").manual_seed(3)
+    xi = torch.randint(-1, 2, x.shape, generator=g, device="cuda").to(torch.bfloat16)
+    Wi = W[:, :64].sign().repeat(1, NF // 64, 1).contiguous()
+    for hint in (None, s3.new_tau_hint(H)):
+        got = s3.sae_encode_topk(xi, Wi, torch.zeros_like(b), k) if hint is None else s3.sae_encode_topk_stream(xi, Wi, torch.zeros_like(b), k, hint)
+        same(got, plain_without_scratch(xi, Wi, torch.zeros_like(b), k))
+    # ascending and descending biases: all that counts comes last, or first (the sample's thresholds are then far off)
+    for sign in (1.0, -1.0):
+        bs = (sign * torch.linspace(-9, 9, NF, device="cuda")).repeat(H, 1).contiguous()
+        same(s3.sae_encode_topk(x, W, bs, k), plain_without_scratch(x, W, bs, k))
+    # features masked with -inf: first all but a hundred, then all but fewer than k: rows are filled with the lowest other ids
+    for left in (200, k - 5):
+        bm = torch.full_like(b, float("-inf"))
+        bm[:, torch.randperm(NF, generator=torch.Generator().manual_seed(1))[:left].cuda()] = 0.0
+        same(s3.sae_encode_topk(x, W, bm, k), tiled_rows(x, W, bm, k))
+
+
+def tiled_rows(x, W, b, k):
+    """The tiled kernel by a call of few tokens at a time (64 rows of every head)."""
+    import torch
+    import paper_2601_17702_amd as s3
+    out = [s3.sae_encode_topk(x[h:h + 1, t:t + 64].contiguous(), W[h:h + 1], b[h:h + 1], k) for h in range(x.shape[0]) for t in range(0, x.shape[1], 64)]
+    per = (x.shape[1] + 63) // 64
+    rows = [torch.cat([o[i] for o in out[h * per:(h + 1) * per]], dim=1) for i in (0, 1) for h in range(x.shape[0])]
+    return torch.cat(rows[:x.shape[0]]), torch.cat(rows[x.shape[0]:])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,T,k", [("c2_llama8b", 1030, 32), ("c3_long", 1000, 32), ("c6_paper_sae", 520, 128)])
+@pytest.mark.timeout(100)
+def test_against_the_oracle(name, T, k):
+    import torch
+    import paper_2601_17702_amd as s3
+    w = synth.shrink(synth.WORKLOADS[name], T=T, L=2 * T, n_feat=NF)
+    heads = [0, 1, 5, 7]
+    W, b = np.stack([synth.gen_w_enc(w, h) for h in heads]), np.stack([synth.gen_b_enc(w, h) for h in heads])
+    Wg, bg, hint = parity.to_gpu(W, w.dtype), parity.to_gpu(b, "fp32"), s3.new_tau_hint(len(heads))
+    rows = np.r_[0:40, T - 40:T]             # the oracle's own time: some rows of each chunk
+    for c in range(2):
+        x = np.stack([synth.gen_keys(w, h, c) for h in heads])
+        ids, vals = s3.sae_encode_topk_stream(parity.to_gpu(x, w.dtype), Wg, bg, k, hint)
+        torch.cuda.synchronize()
+        parity.check_encode(ids.cpu().numpy()[:, rows], vals.cpu().numpy()[:, rows], x[:, rows], W, b, k, w.dtype)
