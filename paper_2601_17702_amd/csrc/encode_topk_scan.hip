@@ -699,6 +699,7 @@ __global__ __launch_bounds__(kThreads, 2) void enc_scan_kernel(ScanArgs a) {
             if (active && mine) {
                 int total = 0;
                 if (REDO)
+#pragma unroll 8
                     for (int p = 0; p < 2 * a.parts; ++p) total += count[(p >> 1) * (kWaves * kLanes) + list_of(lane, p & 1)];
                 else
                     total = cnt[list_of(lane, 0)] + cnt[list_of(lane, 1)];

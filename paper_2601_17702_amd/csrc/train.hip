@@ -160,13 +160,18 @@ struct FeatArgs {
 };
 
 // Step 5: one wavefront per feature; its postings (flat slot = token * k + slot in the row, ascending) are taken 64 at
-// a time -- each lane fetches one posting's scalars, then the wavefront walks them in order.
-__global__ __launch_bounds__(kTokThreads) void tr_feature_kernel(FeatArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int f = blockIdx.x * (kTokThreads / 64) + (threadIdx.x >> 6);
-    if (f >= a.n_feat) return;
-    const int beg = a.offsets[f], end = a.offsets[f + 1];
-    float ex = 0.f, ey = 0.f, dx = 0.f, dy = 0.f, sb = 0.f;
+// a time -- each lane fetches one posting's scalars, then the wavefront walks them in order.  A posting is 8 bytes a lane from
+// two rows (latency, four in flight: 0.125 us each), so one list of all 4096 tokens took 511 us: lists of more than kLongList are
+// split over the sixteen wavefronts of the workgroup, whose sums are added in list order (4096 x 128 tokens, a few features in
+// every token's selection).
+constexpr int kFeatWaves = 16;
+constexpr int kLongList = 128;
+
+struct FeatSums {
+    float ex, ey, dx, dy, sb;
+};
+__device__ __forceinline__ FeatSums feature_sums(const FeatArgs& a, int beg, int end, int lane) {
+    FeatSums r = {0.f, 0.f, 0.f, 0.f, 0.f};
     for (int j0 = beg; j0 < end; j0 += 64) {
         const int n = min(64, end - j0);
         int my_t = 0;
@@ -192,17 +197,57 @@ __global__ __launch_bounds__(kTokThreads) void tr_feature_kernel(FeatArgs a) {
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                dx += v[j] * gv[j].x;
-                dy += v[j] * gv[j].y;
-                ex += dz[j] * __uint_as_float(uu[j] << 16);
-                ey += dz[j] * __uint_as_float(uu[j] & 0xFFFF0000u);
-                sb += dz[j];
+                r.dx += v[j] * gv[j].x;
+                r.dy += v[j] * gv[j].y;
+                r.ex += dz[j] * __uint_as_float(uu[j] << 16);
+                r.ey += dz[j] * __uint_as_float(uu[j] & 0xFFFF0000u);
+                r.sb += dz[j];
             }
         }
     }
-    *(float2*)(a.g_w_enc + (size_t)f * DH + 2 * lane) = make_float2(ex, ey);
-    *(float2*)(a.g_w_dec + (size_t)f * DH + 2 * lane) = make_float2(dx, dy);
-    if (lane == 0) a.g_b_enc[f] = sb;
+    return r;
+}
+__device__ __forceinline__ void feature_store(const FeatArgs& a, int f, int lane, const FeatSums& r) {
+    *(float2*)(a.g_w_enc + (size_t)f * DH + 2 * lane) = make_float2(r.ex, r.ey);
+    *(float2*)(a.g_w_dec + (size_t)f * DH + 2 * lane) = make_float2(r.dx, r.dy);
+    if (lane == 0) a.g_b_enc[f] = r.sb;
+}
+__global__ __launch_bounds__(kFeatWaves * 64) void tr_feature_kernel(FeatArgs a) {
+    __shared__ float4 part[kFeatWaves][64];
+    __shared__ float part_b[kFeatWaves];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int f0 = blockIdx.x * kFeatWaves, fn = min(kFeatWaves, a.n_feat - f0);
+    int beg = 0, end = 0;
+    if (wv < fn) {
+        beg = a.offsets[f0 + wv];
+        end = a.offsets[f0 + wv + 1];
+        if (end - beg <= kLongList) feature_store(a, f0 + wv, lane, feature_sums(a, beg, end, lane));
+    }
+    if (!__syncthreads_or(end - beg > kLongList)) return;
+    for (int i = 0; i < fn; ++i) {
+        beg = a.offsets[f0 + i];                 // the same in every wavefront
+        end = a.offsets[f0 + i + 1];
+        if (end - beg <= kLongList) continue;
+        const int per = ((end - beg + kFeatWaves - 1) / kFeatWaves + 3) & ~3;
+        const FeatSums r = feature_sums(a, min(beg + wv * per, end), min(beg + (wv + 1) * per, end), lane);
+        part[wv][lane] = make_float4(r.ex, r.ey, r.dx, r.dy);
+        if (lane == 0) part_b[wv] = r.sb;
+        __syncthreads();
+        if (wv == 0) {
+            FeatSums t = {0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kFeatWaves; ++w) {
+                const float4 p = part[w][lane];
+                t.ex += p.x;
+                t.ey += p.y;
+                t.dx += p.z;
+                t.dy += p.w;
+                t.sb += part_b[w];
+            }
+            feature_store(a, f0 + i, lane, t);
+        }
+        __syncthreads();
+    }
 }
 
 // Step 6, first half: column sums of g - du and the loss parts of one chunk of tokens, rows in order.
@@ -360,7 +405,7 @@ int s3_sae_train_step(const float* x, int B, int d_head, int n_feat, int k, floa
     float* g_b_dec = g_w_dec + n_w;
     FeatArgs fa{offsets, slots, vals, dz, g, u_bf, g_w_enc, g_b_enc, g_w_dec, n_feat, k,
                 k > 1 ? (uint32_t)(((1ull << 32) + (uint32_t)k - 1) / (uint32_t)k) : 0u};
-    hipLaunchKernelGGL(tr_feature_kernel, dim3((unsigned)((n_feat + 3) / 4)), dim3(kTokThreads), 0, st, fa);
+    hipLaunchKernelGGL(tr_feature_kernel, dim3((unsigned)((n_feat + kFeatWaves - 1) / kFeatWaves)), dim3(kFeatWaves * 64), 0, st, fa);
     const int nchunk = (B + kChunk - 1) / kChunk;
     hipLaunchKernelGGL(tr_colpart_kernel, dim3((unsigned)nchunk), dim3(DH), 0, st, (const float*)g, (const float*)du,
                        (const double*)lossp, B, colpart, losspart);

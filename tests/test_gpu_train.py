@@ -135,3 +135,15 @@ def test_errors():
     tr.ws = tr.ws[:1024]
     with pytest.raises(s3.S3Error):
         tr.step(torch.from_numpy(x).cuda())
+
+
+@pytest.mark.parametrize("B,n_feat,k", [(129, 128, 128), (700, 128, 64), (2500, 256, 97)])
+def test_lists_that_several_wavefronts_share(B, n_feat, k):
+    """Few features: every list is longer than one wavefront takes (128 postings), the last parts of it ragged."""
+    import torch
+    import paper_2601_17702_amd as s3
+    x, P = make_problem(B + k, B, n_feat)
+    P64 = [p.astype(np.float64) for p in P]
+    M, V = [np.zeros_like(p) for p in P64], [np.zeros_like(p) for p in P64]
+    tr = s3.SaeTrainer(*[torch.from_numpy(p).cuda() for p in P], k=k, batch=B)
+    check_step(tr, x, P64, M, V, k, 1, 1e-3)
