@@ -257,15 +257,19 @@ __global__ __launch_bounds__(kScatterThreads) void sc_scatter_lds_kernel(ScoreAr
         const bool cmp_empty = CMP && blk >= a.nblk;              // the compact index holds nothing beyond its blocks
         const ActiveList* act = a.act + (size_t)h * a.n_feat + (size_t)r * kRange;
         const int n_act = a.nact[hr];
-        constexpr int kStep = (kScatterThreads / 64) * 64;
+        // A batch of lists per wavefront: 64 where there are enough, else an equal share (the few lists of a decoding step, 128 a
+        // head, were two wavefronts' work while fourteen waited).
+        constexpr int kW = kScatterThreads / 64;
+        const int share = min((n_act + kW - 1) / kW, 64), step = kW * share;
+        const bool mine = lane < share;
         uint4 raw_next = make_uint4(0, 0, 0, 0);
-        if (wave * 64 + lane < n_act) raw_next = *reinterpret_cast<const uint4*>(act + wave * 64 + lane);
-        for (int i0 = wave * 64; i0 < n_act; i0 += kStep) {
+        if (mine && wave * share + lane < n_act) raw_next = *reinterpret_cast<const uint4*>(act + wave * share + lane);
+        for (int i0 = wave * share; i0 < n_act; i0 += step) {
             unsigned long long wf = 0;
             int b = 0, e = 0;
             const uint4 raw = raw_next;                      // weight and feature in one load, fetched one batch ahead
-            if (i0 + kStep + lane < n_act) raw_next = *reinterpret_cast<const uint4*>(act + i0 + kStep + lane);
-            if (i0 + lane < n_act) {
+            if (mine && i0 + step + lane < n_act) raw_next = *reinterpret_cast<const uint4*>(act + i0 + step + lane);
+            if (mine && i0 + lane < n_act) {
                 const double lw = __longlong_as_double((long long)(((unsigned long long)raw.y << 32) | raw.x));
                 wf = (unsigned long long)llrint(lw * scale);
                 if (wf) {
