@@ -242,8 +242,9 @@ def main():
     score_bytes = post_bytes + 2.0 * H * w.nq * w.k * 4 + 4.0 * w.L
     idx_ms = float(np.sum(app_ms)) / args.steps + float(np.mean(fin_ms))
     traffic, traffic_src = measured_traffic(w.name)
-    fast = w.dtype == "bf16" and w.d_head == 128 and w.k <= 128 and w.n_feat % 128 == 0     # shapes the fast kernel takes
-    enc_kernel = (("k32" if w.k <= 32 else "k64" if w.k <= 64 else "k128") + "::sae_encode_topk_fast_kernel<0>") if fast else "sae_encode_topk_kernel"
+    # the chunks of every workload that the streamed kernels are built for go to the scan encoder
+    fast = w.dtype == "bf16" and w.d_head == 128 and w.k <= 128 and w.n_feat % 128 == 0
+    enc_kernel = f"enc_scan_kernel<{1 if w.k <= 32 else 2 if w.k <= 64 else 4}, false>" if fast else "sae_encode_topk_kernel"
 
     def hbm(nbytes, ms):
         return {"bound": "hbm", "bytes": nbytes, "ms": ms, "achieved": nbytes / ms / 1e6, "peak": HBM_PEAK_GBS,
