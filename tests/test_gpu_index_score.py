@@ -106,6 +106,35 @@ def test_one_shot_index_build_matches():
         assert np.array_equal(off.cpu().numpy(), off_o) and np.array_equal(pos.cpu().numpy(), pos_o)
 
 
+@pytest.mark.parametrize("T,k,n_feat,hot", [
+    (32768, 1, 1, False),             # one bucket of two rounds
+    (150001, 8, 40, False),           # single-feature buckets, three workgroups each
+    (20000, 128, 300, True),          # ragged buckets, one feature in every row beside empty ones
+    (4300001, 1, 4096, True),         # 32-bit intermediate entries; buckets below and above a round
+    (9000001, 1, 5000, False),        # more tiles than threads: piece words counted in several passes
+])
+def test_one_shot_index_build_of_long_buckets(T, k, n_feat, hot):
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(T)
+    if k == 1:
+        ids = rng.integers(0, n_feat, (T, 1), dtype=np.int32)
+        if hot:
+            ids[rng.random(T) < 0.7] = n_feat // 3
+            ids[(ids >= 64) & (ids < 96)] = 5              # whole buckets without an entry
+    else:                                                  # distinct in a row: steps of a number coprime to n_feat
+        step = 7
+        ids = ((rng.integers(0, n_feat, (T, 1)) + step * np.arange(k)) % n_feat).astype(np.int32)
+        if hot:
+            ids = np.where((ids == 11).any(axis=1, keepdims=True), ids, np.where(np.arange(k) == T % k, 11, ids)).astype(np.int32)
+    off, pos = s3.index_build(torch.from_numpy(ids).cuda(), n_feat)
+    torch.cuda.synchronize()
+    flat = ids.reshape(-1)
+    want = np.argsort(flat, kind="stable") // k
+    assert np.array_equal(off.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(flat, minlength=n_feat))]))
+    assert np.array_equal(pos.cpu().numpy(), want)
+
+
 def test_index_state_and_capacity_errors():
     import torch
     import paper_2601_17702_amd as s3
