@@ -268,7 +268,8 @@ __global__ __launch_bounds__(kThreads) void sae_encode_topk_kernel(TileArgs a) {
         const int q = __builtin_ctz(shorts), t = wv * kTokWave + q;
         shorts &= shorts - 1;
         const size_t row = (size_t)head * a.T + tok0 + t;
-        fill_short(a.k, q < 2 ? (q ? cnt[1] : cnt[0]) : (q == 2 ? cnt[2] : cnt[3]), lid + t * CAP, a.ids + row * a.k, a.vals + row * a.k);
+        fill_short(a.k, q < 2 ? (q ? cnt[1] : cnt[0]) : (q == 2 ? cnt[2] : cnt[3]), [&](int s) { return lid[t * CAP + s]; },
+                   a.ids + row * a.k, a.vals + row * a.k);
     }
 }
 
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(256) void enc_merge_kernel(const uint2* __restrict_
             ids[(size_t)row * k + rank[i]] = (int32_t)id[i];
             vals[(size_t)row * k + rank[i]] = fmaxf(value_of(key[i]), 0.f);
         }
-    if (cnt < k) fill_short(k, cnt, lid[wv], ids + (size_t)row * k, vals + (size_t)row * k);
+    if (cnt < k) fill_short(k, cnt, [&](int s) { return lid[wv][s]; }, ids + (size_t)row * k, vals + (size_t)row * k);
 }
 
 template <int DT, int DH, int LR>

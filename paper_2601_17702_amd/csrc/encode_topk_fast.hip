@@ -31,6 +31,7 @@
 // copies (it cannot tell which bytes a copy writes), which would drain the copy pipeline in every step.
 // The waits that the ring really needs are the explicit s_waitcnt before each barrier.
 #include "s3_common.h"
+#include "topk_wave.h"
 
 #include <float.h>
 #include <math.h>
@@ -115,6 +116,11 @@ struct Refreshed {
     int passes;   // search passes taken (read by the profiling build only)
     unsigned t[4];   // profiling build: cycles of load / bracket / search / compaction
 };
+
+// Rows with fewer than k elements above -inf: the lowest other ids, value 0.  c0, c1: the ids of the token's two lists.
+__device__ __attribute__((noinline)) void fill_row(const lds_u16* c0, const lds_u16* c1, int n0, int n1, int k, int32_t* ids, float* vals) {
+    s3topk::fill_short(k, n0 + n1, [&](int s) { return s < n0 ? c0[32 * s] : c1[32 * (s - n0)]; }, ids, vals);
+}
 
 // Streamed calls: counters and this call's minima start empty; afterwards the minima become the carried bounds.
 __global__ void enc_stream_prep_kernel(int32_t* redo_cnt, unsigned* hint_out, float* hint_sum, int n_heads) {

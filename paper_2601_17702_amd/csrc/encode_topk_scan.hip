@@ -586,21 +586,9 @@ __device__ __forceinline__ void select_list(const ScanArgs& a, int head, int tok
 
 // Rows with fewer than k elements above -inf: the lowest other ids, value 0.
 __device__ __attribute__((noinline)) void fill_row(const uint2* list, int t, int n0, int n1, int k, int32_t* ids, float* vals) {
-    const int lane = threadIdx.x & 63;
-    int at = n0 + n1;
-    for (int f0 = 0; f0 < k; f0 += 64) {
-        const int f = f0 + lane;
-        bool open = f < k;
-        for (int s = 0; s < n0; ++s) open = open && (int)list[(size_t)s * kLanes + list_of(t, 0)].y != f;
-        for (int s = 0; s < n1; ++s) open = open && (int)list[(size_t)s * kLanes + list_of(t, 1)].y != f;
-        const unsigned long long m = __ballot(open);
-        const int o = at + s3topk::below(m);
-        if (open && o < k) {
-            ids[o] = f;
-            vals[o] = 0.f;
-        }
-        at += (int)__popcll(m);
-    }
+    s3topk::fill_short(k, n0 + n1, [&](int s) {
+        return s < n0 ? list[(size_t)s * kLanes + list_of(t, 0)].y : list[(size_t)(s - n0) * kLanes + list_of(t, 1)].y;
+    }, ids, vals);
 }
 
 // ------------------------------------------------------------------------------------------------ kernels

@@ -191,15 +191,16 @@ __device__ __forceinline__ void finish(int k, float* lv, uint16_t* li, int cnt, 
 }
 
 // The places [cnt, k) of a row with fewer than k elements above -inf (a bias of -inf, an overflow, a NaN): the lowest ids that
-// are not in its list li[0 .. cnt) (k <= n_feat, so the first k ids are enough).  A row always holds k different ids below
-// n_feat, in the order in which elements that equal -inf sort; with the ReLU their value is 0.
-__device__ __forceinline__ void fill_short(int k, int cnt, const uint16_t* li, int32_t* ids, float* vals) {
+// are not in its list, id_at(0 .. cnt - 1) (k <= n_feat, so the first k ids are enough).  A row always holds k different ids
+// below n_feat, in the order in which elements that equal -inf sort; with the ReLU their value is 0.
+template <class IdAt>
+__device__ __forceinline__ void fill_short(int k, int cnt, IdAt id_at, int32_t* ids, float* vals) {
     const int lane = threadIdx.x & 63;
     int at = cnt;
     for (int f0 = 0; f0 < k; f0 += 64) {
         const int f = f0 + lane;
         bool open = f < k;
-        for (int s = 0; s < cnt; ++s) open = open && li[s] != f;
+        for (int s = 0; s < cnt; ++s) open = open && (int)id_at(s) != f;
         const unsigned long long m = __ballot(open);
         const int o = at + below(m);
         if (open && o < k) {

@@ -193,3 +193,41 @@ def test_fast_kernel_edge_shapes_plain_and_streamed(T, n_feat, k, heads):
         ids1, vals1 = s3.sae_encode_topk_stream(xg, Wg, bg, k, hint)
         torch.cuda.synchronize()
         assert torch.equal(ids0, ids1) and torch.equal(vals0, vals1)
+
+
+@pytest.mark.parametrize("heads,T,n_feat,k,live", [
+    (2, 200, 512, 32, 31),       # one element short of a full row
+    (1, 33, 640, 128, 0),        # no element at all
+    (3, 129, 1024, 64, 64),      # the live features fill the row; one token in a workgroup of its own
+    (1, 300, 256, 100, 3),
+])
+def test_streamed_rows_with_fewer_than_k_elements_are_whole(heads, T, n_feat, k, live):
+    """A bias of -inf on all but `live` features, a token of NaN: the live ones come first, then the lowest other ids with value 0,
+    whatever bound is carried in.  All tokens are walked again then, and their queue must not outgrow the scratch.  Small
+    integers, so the sums are exact."""
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(n_feat + k)
+    xf = rng.integers(-2, 3, (heads, T, 128)).astype(np.float32)
+    Wf = rng.integers(-2, 3, (heads, n_feat, 128)).astype(np.float32)
+    b = np.full((heads, n_feat), -np.inf, np.float32)
+    for h in range(heads):
+        b[h, rng.permutation(n_feat)[:live]] = 900.0
+    z = np.einsum("htd,hfd->htf", xf, Wf) + b[:, None]
+    xf[0, T - 1, 64] = np.nan
+    z[0, T - 1] = -np.inf
+    want = np.argsort(-z, axis=2, kind="stable")[:, :, :k]
+    want_v = np.maximum(np.take_along_axis(z, want, axis=2), 0)
+    xg, Wg, bg = torch.from_numpy(xf).cuda().bfloat16(), torch.from_numpy(Wf).cuda().bfloat16(), torch.from_numpy(b).cuda()
+    ids = torch.empty((heads, T, k), dtype=torch.int32, device="cuda")
+    vals = torch.empty((heads, T, k), device="cuda")
+    need = s3.sae_encode_topk_stream_workspace(heads, T)
+    ws = torch.full((need + 4 * T + 256,), 77, dtype=torch.uint8, device="cuda")
+    for start in (float("-inf"), 1e30, 20.0, float("nan")):
+        hint = torch.full((heads, 2), start, device="cuda")
+        ids.fill_(-7), vals.fill_(-7)
+        rc = s3.lib().s3_sae_encode_topk_stream(s3._ptr(xg), 0, T, 128, s3._ptr(Wg), s3._ptr(bg), n_feat, k, heads, s3._ptr(ids),
+                                                s3._ptr(vals), s3._ptr(hint), s3._ptr(ws), need, s3._stream())
+        torch.cuda.synchronize()
+        assert rc == 0 and torch.all(ws[need:] == 77), start
+        assert np.array_equal(ids.cpu().numpy(), want) and np.array_equal(vals.cpu().numpy(), want_v), start
