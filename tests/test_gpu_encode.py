@@ -231,3 +231,24 @@ def test_streamed_rows_with_fewer_than_k_elements_are_whole(heads, T, n_feat, k,
         torch.cuda.synchronize()
         assert rc == 0 and torch.all(ws[need:] == 77), start
         assert np.array_equal(ids.cpu().numpy(), want) and np.array_equal(vals.cpu().numpy(), want_v), start
+
+
+@pytest.mark.parametrize("n_feat,k,inf", [(512, 32, 40), (1024, 64, 40), (640, 100, 300), (512, 32, 31)])
+def test_streamed_rows_with_elements_of_infinity(n_feat, k, inf):
+    """More, or fewer, than k elements of +inf: among equal ones the lowest ids, then the largest finite ones.  Small integers."""
+    import torch
+    import paper_2601_17702_amd as s3
+    heads, T = 2, 200
+    rng = np.random.default_rng(n_feat + k)
+    xf = rng.integers(-2, 3, (heads, T, 128)).astype(np.float32)
+    Wf = rng.integers(-2, 3, (heads, n_feat, 128)).astype(np.float32)
+    b = np.zeros((heads, n_feat), np.float32)
+    b[0, rng.permutation(n_feat)[:inf]] = np.inf
+    z = np.einsum("htd,hfd->htf", xf, Wf) + b[:, None]
+    want = np.argsort(-z, axis=2, kind="stable")[:, :, :k]
+    want_v = np.maximum(np.take_along_axis(z, want, axis=2), 0)
+    xg, Wg, bg = torch.from_numpy(xf).cuda().bfloat16(), torch.from_numpy(Wf).cuda().bfloat16(), torch.from_numpy(b).cuda()
+    for start in (float("-inf"), 1e30, float("inf")):
+        ids, vals = s3.sae_encode_topk_stream(xg, Wg, bg, k, torch.full((heads, 2), start, device="cuda"))
+        torch.cuda.synchronize()
+        assert np.array_equal(ids.cpu().numpy(), want) and np.array_equal(vals.cpu().numpy(), want_v), start
