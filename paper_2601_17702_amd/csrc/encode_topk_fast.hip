@@ -155,8 +155,8 @@ __global__ void enc_stream_post_kernel(const unsigned* hint_out, const float* hi
     const float waste_r = r > -INFINITY ? s_tau - r * s_x : INFINITY;
     const float waste_a = a > -INFINITY ? s_tau - a * s_n : INFINITY;
     const bool use_r = waste_r <= waste_a;
-    hint[2 * h] = use_r ? r - extra * fabsf(r) : -INFINITY;
-    hint[2 * h + 1] = use_r ? -INFINITY : a - extra * fabsf(a);
+    hint[2 * h] = use_r ? s3_carried(r, extra) : -INFINITY;
+    hint[2 * h + 1] = use_r ? -INFINITY : s3_carried(a, extra);
 }
 
 // One build of the kernel per list geometry: 8 wavefronts x 40 slots per lane for k <= 32, 4 wavefronts x 80 slots

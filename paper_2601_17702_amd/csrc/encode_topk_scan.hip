@@ -939,8 +939,8 @@ __global__ void enc_carry_kernel(ScanArgs a) {
     const float waste_r = r > -INFINITY ? s_tau - r * s_x : INFINITY;
     const float waste_m = m > -INFINITY ? s_tau - m * s_n : INFINITY;
     const bool use_r = waste_r <= waste_m;
-    a.hint_next[2 * h] = use_r ? r - extra * fabsf(r) : -INFINITY;
-    a.hint_next[2 * h + 1] = use_r ? -INFINITY : m - extra * fabsf(m);
+    a.hint_next[2 * h] = use_r ? s3_carried(r, extra) : -INFINITY;
+    a.hint_next[2 * h + 1] = use_r ? -INFINITY : s3_carried(m, extra);
 }
 
 // How a call is laid out.

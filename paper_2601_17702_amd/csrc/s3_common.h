@@ -1,6 +1,7 @@
 // Internal declarations shared by the library's translation units (not part of the C ABI).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -155,6 +156,11 @@ bool s3_encode_scan_pays(int n_heads, int T, int n_feat, int k, bool streamed);
 size_t s3_encode_scan_workspace(int n_heads, int T, int n_feat, int k);
 size_t s3_encode_scan_workspace_max(int n_heads, int T);
 int s3_encode_scan(const EncParams& p, float* hint, void* ws, hipStream_t st);
+
+// A bound of the call's thresholds as it is carried on, lowered by a share of itself; what is not finite is no bound.
+__device__ __forceinline__ float s3_carried(float bound, float by) {
+    return fabsf(bound) < INFINITY ? bound - by * fabsf(bound) : -INFINITY;
+}
 
 // Workgroup -> (head, token tile).  Workgroups are dealt round-robin to the 8 XCDs (each with its own
 // L2), so consecutive tiles of one head are placed on the SAME XCD: they stream the same W_enc rows at

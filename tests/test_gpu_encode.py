@@ -252,3 +252,26 @@ def test_streamed_rows_with_elements_of_infinity(n_feat, k, inf):
         ids, vals = s3.sae_encode_topk_stream(xg, Wg, bg, k, torch.full((heads, 2), start, device="cuda"))
         torch.cuda.synchronize()
         assert np.array_equal(ids.cpu().numpy(), want) and np.array_equal(vals.cpu().numpy(), want_v), start
+
+
+@pytest.mark.parametrize("T,n_feat", [(200, 512), (300, 8192)])      # the two kernels that carry thresholds
+def test_heads_without_a_finite_threshold_carry_no_bound(T, n_feat):
+    """Head 0 has k - 1 elements above -inf, head 1 an element of +inf in every place of the row: the next call starts both from
+    nothing.  Head 2 carries a bound beside them."""
+    import torch
+    import paper_2601_17702_amd as s3
+    k, heads = 32, 3
+    g = torch.Generator(device="cuda").manual_seed(n_feat)
+    x = torch.randn(heads, T, 128, generator=g, device="cuda").bfloat16()
+    W = (torch.randn(heads, n_feat, 128, generator=g, device="cuda") / 11).bfloat16()
+    b = torch.zeros(heads, n_feat, device="cuda")
+    b[0, k - 1:] = float("-inf")
+    b[1, 5:5 + k] = float("inf")
+    hint = s3.new_tau_hint(heads)
+    for _ in range(2):                       # without bounds, then with head 2's
+        ids, vals = s3.sae_encode_topk_stream(x, W, b, k, hint)
+        torch.cuda.synchronize()
+        h = hint.cpu().numpy()
+        assert np.all(h[:2] == -np.inf) and np.isfinite(h[2]).sum() == 1, h
+        assert torch.all(ids[1] == torch.arange(5, 5 + k, device="cuda", dtype=torch.int32)) and torch.all(vals[1] == float("inf"))
+        assert torch.all(ids[0].sort(dim=1).values == torch.arange(k, device="cuda", dtype=torch.int32))
