@@ -63,6 +63,7 @@ constexpr int kFront = NS - 3;          // MFMAs of a chain that run before the 
 // Entries of one lane's list at which the lists are cut, and that there is room for: all of the about k survivors may be one lane's.
 __host__ __device__ constexpr int cap_of(int k) { return k <= 32 ? 112 : (k <= 64 ? 168 : 208); }
 constexpr int trim_regs(int G) { return G == 1 ? 64 : (G == 2 ? 96 : 144); }
+constexpr int cut_regs(int G) { return (2 * cap_of(32 * G) + 63) / 64; }           // a token's two lists over 64 lanes
 constexpr int kRoom = 16;                            // a lane can take this many candidates of a stage
 
 constexpr float kHintMargin = 0.04f;    // a stream's tokens start this far below the carried bound
@@ -147,12 +148,65 @@ struct Lane {
     unsigned off;            // byte offset of the end of its list
 };
 
-// Cuts the lists of 32 tokens (the set of this lane) that hold more than about k elements to about k, and raises the tokens'
-// thresholds to the smallest value kept: k or more elements reach it, all with lower ids than what is still to come, so an
-// element that only equals it has lost.  The two lanes of a token count their lists together.  The search for the k-th value
-// alternates interpolation on the logarithm of the counts (the upper tail is close to exponential) with halving of the keys;
-// the first NR values of a lane are held in registers, further ones are read again in every pass.
-template <int NR>
+// Cuts the lists of the set's tokens in `which` to about k elements, one token after the other, and raises their thresholds to
+// the smallest value kept: k or more elements reach it, all with lower ids than what is still to come, so an element that only
+// equals it has lost.  A token's two lists (at most 64 N entries) are read once, by the whole wavefront, and searched by
+// counts of ballots; what is kept is dealt to both lists in turn.  For lists that are full inside the walk and for ties.  When every
+// lane searched its own lists there, and read them again in each pass because the walk leaves few registers, a cut took 65
+// us: later chunks of 64 heads x 2048 tokens x 16384 skewed features, k 32, 845 -> 735 us, of 32768 1628 -> 1537; with a row of zeros
+// and no biases (all pre-activations equal), 256 x 2048 x 16384, 6647 -> 4197, k 128, 32 x 2048, 1915 -> 965.
+template <int N>
+__device__ __attribute__((noinline)) Lane cut_tokens(char* list, Lane l, unsigned which, int k) {
+    constexpr unsigned per = kLanes * sizeof(uint2);
+    const int lane = threadIdx.x & 63, loose = k + (k >> 3) + 2;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    for (; which; which &= which - 1) {
+        const int t = __builtin_ctz(which);
+        const unsigned o0 = (unsigned)__builtin_amdgcn_readlane((int)l.off, t), o1 = (unsigned)__builtin_amdgcn_readlane((int)l.off, t + 32);
+        const float tau = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(l.tau), t));
+        const int c0 = (int)(o0 / per), total = c0 + (int)(o1 / per);
+        char* const p = list + o0 % per;                                       // the other list begins 32 entries of a row further
+        uint2 u[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int e = i * 64 + lane;
+            u[i] = *(const uint2*)(p + (e < c0 ? e * per : (e < total ? (e - c0) * per + 32 * (unsigned)sizeof(uint2) : 0u)));
+        }
+        unsigned key[N], id[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            key[i] = i * 64 + lane < total ? key_of(__uint_as_float(u[i].x)) : 0u;
+            id[i] = u[i].y;
+        }
+        unsigned lo = tau > -INFINITY ? key_of(tau) : 1u;
+        const unsigned idcut = s3topk::raise(key, k, loose, lo, total) > loose ? s3topk::tie_cut(key, id, k, lo) : 0xFFFFu;
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const bool keep = key[i] > lo || (key[i] == lo && id[i] <= idcut);
+            const unsigned long long m = __ballot(keep);
+            const unsigned at = (unsigned)(n + s3topk::below(m));
+            if (keep) *(uint2*)(p + (at >> 1) * per + (at & 1) * 32 * (unsigned)sizeof(uint2)) = u[i];
+            n += (int)__popcll(m);
+        }
+        if ((lane & 31) == t) {
+            l.off = l.off % per + (unsigned)(lane < 32 ? (n + 1) >> 1 : n >> 1) * per;
+            l.tau = value_of(lo);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    return l;
+}
+__device__ __forceinline__ unsigned tokens_of(bool lane) {           // the set's tokens of which one lane or both say so
+    const unsigned long long m = __ballot(lane);
+    return (unsigned)m | (unsigned)(m >> 32);
+}
+
+// Cuts the lists of 32 tokens (the set of this lane) that hold more than about k elements, all at once: every lane searches
+// its own list, the two lanes of a token count theirs together.  The search for the k-th value alternates interpolation on the
+// logarithm of the counts (the upper tail is close to exponential) with halving of the keys; the first NR values of a lane are
+// held in registers, further ones are read again in every pass.
+template <int NR, int N>
 __device__ __forceinline__ Lane trim(char* list, Lane l, int k) {
     constexpr unsigned per = kLanes * sizeof(uint2);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
@@ -163,20 +217,16 @@ __device__ __forceinline__ Lane trim(char* list, Lane l, int k) {
         return (int)(r[0] + r[1]);
     };
     const int total = both(cnt), loose = k + (k >> 3) + 2;
-    const bool open = total > loose;
+    bool open = total > loose;
     const int n = (int)s3_wave_max_u32(open ? (unsigned)cnt : 0u);
-    float held[NR > 0 ? NR : 1];
-    if constexpr (NR > 0) {
+    float held[NR];
 #pragma unroll
-        for (int i = 0; i < NR; ++i) held[i] = *(const float*)(p + (unsigned)(i < cnt ? i : 0) * per);
+    for (int i = 0; i < NR; ++i) held[i] = *(const float*)(p + (unsigned)(i < cnt ? i : 0) * per);
 #pragma unroll
-        for (int i = 0; i < NR; ++i) held[i] = i < cnt ? held[i] : -INFINITY;
-    }
+    for (int i = 0; i < NR; ++i) held[i] = i < cnt ? held[i] : -INFINITY;
     const auto pass = [&](auto f) {                   // f(value) of every entry
-        if constexpr (NR > 0) {
 #pragma unroll
-            for (int i = 0; i < NR; ++i) f(held[i]);
-        }
+        for (int i = 0; i < NR; ++i) f(held[i]);
         for (int i0 = NR; i0 < n; i0 += 24) {
             float v[24];
 #pragma unroll
@@ -210,46 +260,26 @@ __device__ __forceinline__ Lane trim(char* list, Lane l, int k) {
             busy = clo > loose && khi - klo > 1u;
         }
     }
+    const unsigned tied = tokens_of(open && clo > loose);       // more elements equal the threshold than there is room for
+    open = open && clo <= loose;
     const float lo = value_of(klo);
-    int idcut = 0xFFFF;
-    if (__builtin_expect(__any(open && clo > loose), 0)) {      // ties at the threshold: those with the lowest ids, k elements in all
-        int above = 0;
-        pass([&](float v) { above += v > lo ? 1 : 0; });
-        const int need = k - both(above);
-        int ilo = -1, ihi = 0xFFFF;
-        for (int it = 0; it < 16; ++it) {
-            const int mid = (ilo + ihi) >> 1;
-            int c = 0;
-            for (int i = 0; i < n; ++i) {
-                const uint2 u = *(const uint2*)(p + (i < cnt ? i : 0) * per);
-                c += i < cnt && __uint_as_float(u.x) == lo && (int)u.y <= mid ? 1 : 0;
-            }
-            if (both(c) >= need) ihi = mid; else ilo = mid;
-        }
-        if (clo > loose) idcut = ihi;
-    }
     int m = 0;
-    constexpr int NB = NR > 0 ? 16 : 8;
-    for (int i0 = 0; i0 < n; i0 += NB) {              // every list keeps its order; entries are read before their places are written
-        uint2 u[NB];
+    for (int i0 = 0; i0 < n; i0 += 16) {              // every list keeps its order; entries are read before their places are written
+        uint2 u[16];
 #pragma unroll
-        for (int i = 0; i < NB; ++i) u[i] = *(const uint2*)(p + (unsigned)(i0 + i < cnt ? i0 + i : 0) * per);
+        for (int i = 0; i < 16; ++i) u[i] = *(const uint2*)(p + (unsigned)(i0 + i < cnt ? i0 + i : 0) * per);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const float v = __uint_as_float(u[i].x);
-            if (open && i0 + i < cnt && (v > lo || (v == lo && (int)u[i].y <= idcut))) *(uint2*)(p + m++ * per) = u[i];
-        }
+        for (int i = 0; i < 16; ++i)
+            if (open && i0 + i < cnt && __uint_as_float(u[i].x) >= lo) *(uint2*)(p + m++ * per) = u[i];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     if (open) {
         l.off = l.off % per + m * per;
         l.tau = lo;
     }
+    if (__builtin_expect(tied != 0, 0)) l = cut_tokens<N>(list, l, tied, k);
     return l;
 }
-
-// Inside the walk, where few registers are free: rare, a list is about to overflow.
-__device__ __attribute__((noinline)) Lane trim_now(char* list, Lane l, int k) { return trim<0>(list, l, k); }
 
 __device__ __forceinline__ void store_one(char* list, unsigned& off, float z, unsigned id) {
     *(uint2*)(list + off) = make_uint2(__float_as_uint(z), id);
@@ -259,7 +289,7 @@ __device__ __forceinline__ void store_one(char* list, unsigned& off, float z, un
 // Appends what the lane's 16 accumulators hold above its token's threshold.  A stage brings a lane seldom more than one: the
 // first quad that has one is picked under scalar masks, then the first element inside it.  Lanes with more take the rest one
 // by one.  The masks are combined by the scalar unit.
-template <int SET, class Mfma>
+template <int SET, int N, class Mfma>
 __device__ __forceinline__ void append(const f32x16& z, Lane& l, char* list, unsigned f0, unsigned lim, int k, Mfma mfma) {
     typedef unsigned long long mask;
 #pragma unroll
@@ -325,10 +355,14 @@ __device__ __forceinline__ void append(const f32x16& z, Lane& l, char* list, uns
         rest(M3, q3, f0 + 24);
     }
     mfma(kFront + 2);
-    if (__builtin_expect(__any(l.off > lim), 0)) l = trim_now(list, l, k);
+    if (__builtin_expect(__any(l.off > lim), 0)) {
+        l = cut_tokens<N>(list, l, tokens_of(l.off > lim), k);
+        __builtin_amdgcn_s_waitcnt(0x0F70);    // vmcnt(0): registers restored behind the call would be waited for in every stage, and W with them
+    }
 }
 
-// Walks stages [s0, s0 + ns) (ns even) of the head's features for the wavefront's tokens.
+// Walks stages [s0, s0 + ns) (ns even) of the head's features for the wavefront's tokens.  64 N: a token's entries at most.
+template <int N>
 __device__ __forceinline__ void scan_stages(char* smem, const ScanArgs& a, int head, int tok0, Lane& la, Lane& lb, char* list, int cap, int k,
                                             const char* wsrc, const float* bsrc, int s0, int ns, bool active) {
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, half = lane >> 5;
@@ -401,12 +435,12 @@ __device__ __forceinline__ void scan_stages(char* smem, const ScanArgs& a, int h
         const int nxt = (s + 1) % kRing;
         put(r, bb, (s + kPeriod) % kRing);
         gload(r, bb, s + kPeriod + 2);
-        append<1>(accB, lb, list, (unsigned)(s0 + s - 1) * kFT + fh, lim, k, [&](int i) {
+        append<1, N>(accB, lb, list, (unsigned)(s0 + s - 1) * kFT + fh, lim, k, [&](int i) {
             accA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], tk.a[i], i ? accA : c, 0, 0, 0);
         });
         if (sync) lds_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        append<0>(accA, la, list, (unsigned)(s0 + s) * kFT + fh, lim, k, [&](int i) {
+        append<0, N>(accA, la, list, (unsigned)(s0 + s) * kFT + fh, lim, k, [&](int i) {
             accB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], tk.b[i], i ? accB : c, 0, 0, 0);
             f[i] = fread(i, nxt);
             if (i < 4) cread(nxt, i);
@@ -420,7 +454,7 @@ __device__ __forceinline__ void scan_stages(char* smem, const ScanArgs& a, int h
         stage(r0, b0, s, s % kPeriod == 0);
         stage(r1, b1, s + 1, false);
     }
-    append<1>(accB, lb, list, (unsigned)(s0 + ns - 1) * kFT + fh, lim, k, [](int) {});
+    append<1, N>(accB, lb, list, (unsigned)(s0 + ns - 1) * kFT + fh, lim, k, [](int) {});
 }
 
 // ------------------------------------------------------------------------------------------------ selection
@@ -663,7 +697,7 @@ __global__ __launch_bounds__(kThreads, 2) void enc_scan_kernel(ScanArgs a) {
                 const int end = to;
                 if (parts == 1 && ns >= 64) to = s0 + (ns >> 4) * 2;
                 for (;;) {
-                    scan_stages(smem, a, head, tok0, la, lb, (char*)list, a.cap, a.k, wh, bh, from, to - from, go);
+                    scan_stages<cut_regs(G)>(smem, a, head, tok0, la, lb, (char*)list, a.cap, a.k, wh, bh, from, to - from, go);
                     if (to >= end) break;
                     constexpr unsigned per = kLanes * sizeof(uint2);
                     const unsigned many = (unsigned)(a.k - (a.k >> 2)) * per;
@@ -673,8 +707,8 @@ __global__ __launch_bounds__(kThreads, 2) void enc_scan_kernel(ScanArgs a) {
                         rough = __syncthreads_count(some) + kThreads * (dense ? 1 : 0) > kThreads / 4;
                         rough = __syncthreads_or(rough);
                     }
-                    if (go && __any(la.off > many)) la = trim<trim_regs(G)>((char*)list, la, a.k);
-                    if (go && __any(lb.off > many)) lb = trim<trim_regs(G)>((char*)list, lb, a.k);
+                    if (go && __any(la.off > many)) la = trim<trim_regs(G), cut_regs(G)>((char*)list, la, a.k);
+                    if (go && __any(lb.off > many)) lb = trim<trim_regs(G), cut_regs(G)>((char*)list, lb, a.k);
                     from = to;
                     to = rough ? min(s0 + 2 * (to - s0), end) : end;
                 }

@@ -67,25 +67,29 @@ __device__ __forceinline__ int raise(const unsigned (&key)[N], int k, int loose,
     return clo;
 }
 
+// Of more than k elements at or above lo with fewer than k above it: the largest id up to which those that equal lo belong to
+// the k best.
+template <int N>
+__device__ __forceinline__ unsigned tie_cut(const unsigned (&key)[N], const unsigned (&id)[N], int k, unsigned lo) {
+    const int need = k - count_ge(key, lo + 1);
+    int ilo = -1, ihi = 0xFFFF;           // count(tied, id <= ilo) < need <= count(tied, id <= ihi)
+    while (ihi - ilo > 1) {
+        const int mid = (ilo + ihi) >> 1;
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) c += (int)__popcll(__ballot(key[i] == lo && (int)id[i] <= mid));
+        if (c >= need) ihi = mid; else ilo = mid;
+    }
+    return (unsigned)ihi;
+}
+
 // Cuts the N registers' elements to between k and `loose` (exactly k when loose == k) and stores them at lv / li[0 ..).
 // `lo`: in, a threshold with at least k elements at or above it (at least 1); out, the new one.  Returns the number kept.
 template <int N>
 __device__ __forceinline__ int cut_and_store(const unsigned (&key)[N], const unsigned (&id)[N], int k, int loose, unsigned& lo,
                                              int clo, float* lv, uint16_t* li) {
     clo = raise(key, k, loose, lo, clo);
-    unsigned idcut = 0xFFFFu;
-    if (clo > loose) {                    // ties at the threshold: keep those with the lowest ids, k elements in all
-        const int need = k - count_ge(key, lo + 1);
-        int ilo = -1, ihi = 0xFFFF;       // count(tied, id <= ilo) < need <= count(tied, id <= ihi)
-        while (ihi - ilo > 1) {
-            const int mid = (ilo + ihi) >> 1;
-            int c = 0;
-#pragma unroll
-            for (int i = 0; i < N; ++i) c += (int)__popcll(__ballot(key[i] == lo && (int)id[i] <= mid));
-            if (c >= need) ihi = mid; else ilo = mid;
-        }
-        idcut = (unsigned)ihi;
-    }
+    const unsigned idcut = clo > loose ? tie_cut(key, id, k, lo) : 0xFFFFu;     // ties at the threshold: k elements in all
     int n = 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {

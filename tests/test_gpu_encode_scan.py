@@ -123,6 +123,29 @@ def test_ties_masked_features_and_sorted_dictionaries(H, T, k):
         same(s3.sae_encode_topk(x, W, bm, k), tiled_rows(x, W, bm, k))
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,T,k", [(8, 512, 32), (70, 300, 48), (66, 600, 128), (130, 520, 20)])
+@pytest.mark.timeout(100)
+def test_rows_of_zeros_and_outliers_without_biases(H, T, k):
+    """A row of zeros has all pre-activations equal: it starts too high wherever the others' thresholds are, and its lists are full of
+    ties inside the walk.  Rows that are a multiple of the others meet a bound that is far too low and fill theirs over and over."""
+    import torch
+    import paper_2601_17702_amd as s3
+    x, W, b = problem(H, T, NF, 31 + k)
+    b.zero_()
+    x[:, 3] = 0
+    x[:, T - 1] = 0
+    x[:, 17::64] *= 40
+    want = plain_without_scratch(x, W, b, k)
+    assert torch.all(want[0][:, T - 1] == torch.arange(k, device="cuda", dtype=torch.int32))
+    hint = s3.new_tau_hint(H)
+    for _ in range(2):
+        same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+    hint.fill_(float("-inf"))
+    hint[:, 1] = 1.0                         # a bound on the threshold itself: outliers bring half of all features
+    same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+
+
 def tiled_rows(x, W, b, k):
     """The tiled kernel by a call of few tokens at a time (64 rows of every head)."""
     import torch
