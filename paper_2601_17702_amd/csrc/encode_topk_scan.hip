@@ -642,7 +642,13 @@ __global__ __launch_bounds__(kThreads, 2) void enc_scan_kernel(ScanArgs a) {
     int* const cnt = (int*)(mem + kWCnt);
     const int parts = REDO ? 1 : a.parts;      // ranges that are workgroups of their own here
 
-    for (int unit = blockIdx.x; unit < a.n_tiles * parts; unit += gridDim.x) {
+    // Where a workgroup would take the same tile of every head, turn after turn (a power of two of tiles a head), its tiles move on by
+    // one: rows that are walked twice often stand at the same place in all heads (padding, a first token).  One row of zeros a
+    // head and no biases, 256 heads x 2048 tokens, k 32: 4077 -> 3077 us.  A step of 8 stays on the XCD.
+    const unsigned shift = (gridDim.x >> 3) % (unsigned)a.tiles_per_head == 0 ? 8u : 0u;
+    for (int turn = 0; turn * (int)gridDim.x < a.n_tiles * parts; ++turn) {
+        const int unit = turn * (int)gridDim.x + (int)((blockIdx.x + shift * (unsigned)turn) % gridDim.x);
+        if (unit >= a.n_tiles * parts) continue;
         int group, tt;
         s3_block_to_tile((unsigned)unit, a.n_heads * parts, a.tiles_per_head, group, tt);
         const int head = group / parts, part = group - head * parts;
