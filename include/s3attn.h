@@ -65,7 +65,7 @@ const char* s3_last_error(void);
  * bf16 with d_head 128 and n_feat a multiple of 128 takes the fast kernel, unless the tokens are few
  * (at most 256 tiles of 32 over all heads) and one workgroup per tile fills the chip or there is scratch.
  * No workspace is needed; s3_sae_encode_topk_ws is the same call with one, and the faster one for many
- * tokens and features as well (candidate lists in scratch: up to 440 MB).
+ * tokens and features as well.
  */
 int s3_sae_encode_topk(const void* x, int dtype, int T, int d_head, const void* w_enc,
                        const float* b_enc, int n_feat, int k, int n_heads, int32_t* ids,
@@ -75,7 +75,8 @@ int s3_sae_encode_topk(const void* x, int dtype, int T, int d_head, const void* 
  * several workgroups and merges their selections; one with many keeps its candidate lists there.  The
  * results are the same bit for bit.
  *   ws   s3_sae_encode_topk_workspace(...) bytes (0: the call has no use for scratch, ws may be
- *        NULL), 256-byte aligned, device; contents meaningless between calls.  With less than that the
+ *        NULL; lists of candidates are up to 236, 354 and 438 MB for k <= 32, 64 and 128, and 4 bytes a
+ *        token), 256-byte aligned, device; contents meaningless between calls.  With less than that the
  *        call runs as s3_sae_encode_topk.
  * Errors as s3_sae_encode_topk, and S3_EINVAL for a misaligned ws. */
 size_t s3_sae_encode_topk_workspace(int dtype, int T, int d_head, int n_feat, int k, int n_heads);
@@ -96,8 +97,10 @@ int s3_sae_encode_topk_ws(const void* x, int dtype, int T, int d_head, const voi
  *            predictor on that call is kept, the other is -INFINITY.  Fill with -INFINITY before
  *            the first chunk of a stream: a head without a bound takes its tokens' first thresholds
  *            from a sample of the features, or from a first tile of tokens.
- *   ws       s3_sae_encode_topk_stream_workspace(n_heads, T) bytes (candidate lists: up to 440 MB), 256-byte
- *            aligned, device; scratch, contents meaningless between calls.  No smaller for a larger T.
+ *   ws       s3_sae_encode_topk_stream_workspace(n_heads, T) bytes, 256-byte aligned, device; scratch,
+ *            contents meaningless between calls.  No smaller for a larger T.  4 bytes a token and head below
+ *            256 tokens a head; from there on also the candidate lists that any n_feat and k may need: 14 MB
+ *            for one head, up to 438 MB for many.
  * Shapes the threshold-carrying kernel is not built for (anything but bf16, d_head 128,
  * n_feat % 128 == 0) run exactly as s3_sae_encode_topk and leave tau_hint untouched.
  * Errors as s3_sae_encode_topk; S3_ECAPACITY if ws_bytes is too small. */

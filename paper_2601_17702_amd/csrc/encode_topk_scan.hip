@@ -1015,7 +1015,7 @@ Plan plan(int n_heads, int T, int n_feat, int k) {
     p.hout = take((size_t)n_heads * 8);
     p.hsum = take((size_t)n_heads * 12);
     p.tau0 = take((size_t)n_heads * T * 4);
-    p.norm = take((size_t)n_heads * T * 4);
+    p.norm = take(p.parts > 1 ? (size_t)n_heads * T * 4 : 0);
     p.count = take((size_t)p.units * kWaves * kLanes * 4);
     p.list = take((size_t)p.units * kWaves * kLanes * p.cap * sizeof(uint2));
     p.total = o;
@@ -1069,11 +1069,13 @@ size_t s3_encode_scan_workspace(int n_heads, int T, int n_feat, int k) { return 
 
 // The most that a call of this many tokens or fewer takes, whatever n_feat and k are.
 size_t s3_encode_scan_workspace_max(int n_heads, int T) {
+    if (T < kTokWG) return 0;                          // s3_encode_scan_pays refuses them
     const long long tiles = (long long)n_heads * ((T + kTokWG - 1) / kTokWG);
     const long long split = tiles > kFewTiles ? kSlots : (tiles * kMaxParts < kSlots ? tiles * kMaxParts : kSlots), whole = tiles < kSlots ? tiles : kSlots;
     const long long units = split > whole ? split : whole;
-    return s3_align((size_t)n_heads * 4) + s3_align((size_t)n_heads * 8) + s3_align((size_t)n_heads * 12) + 2 * s3_align((size_t)n_heads * T * 4) +
-           s3_align((size_t)units * kWaves * kLanes * 4) + s3_align((size_t)units * kWaves * kLanes * cap_of(S3_MAX_K) * sizeof(uint2));
+    const size_t tokens = (size_t)n_heads * T, norms = tokens < (size_t)kFewTiles * kTokWG ? tokens : (size_t)kFewTiles * kTokWG;
+    return s3_align((size_t)n_heads * 4) + s3_align((size_t)n_heads * 8) + s3_align((size_t)n_heads * 12) + s3_align(tokens * 4) +
+           s3_align(norms * 4) + s3_align((size_t)units * kWaves * kLanes * 4) + s3_align((size_t)units * kWaves * kLanes * cap_of(S3_MAX_K) * sizeof(uint2));
 }
 
 int s3_encode_scan(const EncParams& e, float* hint, void* ws, hipStream_t st) {

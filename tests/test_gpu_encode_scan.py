@@ -21,6 +21,19 @@ def test_stream_scratch_of_a_shorter_or_narrower_call_is_no_larger():
         assert need == sorted(need)
 
 
+def test_scratch_holds_what_a_call_can_use():
+    """Chunks of under 256 tokens never keep candidate lists there: a place in the queue of the second walk (4 bytes) a token, a few
+    bytes a head.  Longer ones: lists of 512 workgroups (436 MB at k = 128) and no more than 4 bytes a token beside them."""
+    import paper_2601_17702_amd as s3
+    lists = 512 * 512 * 208 * 8
+    for heads, T in ((1, 1), (8, 4), (256, 1), (256, 255)):
+        assert s3.sae_encode_topk_stream_workspace(heads, T) <= 4 * heads * T + 28 * heads + 5 * 256
+    for heads, T in ((256, 2048), (256, 32768), (112, 2048)):
+        assert s3.sae_encode_topk_stream_workspace(heads, T) <= lists + 512 * 512 * 4 + 4 * heads * T + (1 << 18)
+    for k, cap in ((32, 112), (64, 168), (128, 208)):                # a call without a stream: its own k's lists
+        assert 0 < s3.lib().s3_sae_encode_topk_workspace(0, 2048, 128, 16384, k, 256) <= 512 * 512 * (8 * cap + 4) + 4 * 256 * 2048 + (1 << 18)
+
+
 def plain_without_scratch(x, W, b, k):
     """s3_sae_encode_topk: no scratch, so never the scan encoder."""
     import torch
