@@ -157,14 +157,18 @@ struct FeatArgs {
     float* g_w_dec;
     int n_feat, k;
     uint32_t kinv;        // ceil(2^32 / k): slot / k for slot < 2^24
+    int per_wg;           // features per workgroup
 };
 
 // Step 5: one wavefront per feature; its postings (flat slot = token * k + slot in the row, ascending) are taken 64 at
 // a time -- each lane fetches one posting's scalars, then the wavefront walks them in order.  A posting is 8 bytes a lane from
 // two rows (latency, four in flight: 0.125 us each), so one list of all 4096 tokens took 511 us: lists of more than kLongList are
 // split over the sixteen wavefronts of the workgroup, whose sums are added in list order (4096 x 128 tokens, a few features in
-// every token's selection).
+// every token's selection).  A workgroup has sixteen features, or fewer where that would be less than a workgroup per compute unit:
+// there the lists are long, and a workgroup takes its long lists one after the other (a step of 4096 tokens, k 128, 128
+// latents: 876 us with a wavefront a list, 1065 with sixteen features a workgroup, 209 now; 8192 x 1024, k 64: 356 / 328 / 220).
 constexpr int kFeatWaves = 16;
+constexpr int kFeatUnits = 256;
 constexpr int kLongList = 128;
 
 struct FeatSums {
@@ -216,7 +220,7 @@ __global__ __launch_bounds__(kFeatWaves * 64) void tr_feature_kernel(FeatArgs a)
     __shared__ float4 part[kFeatWaves][64];
     __shared__ float part_b[kFeatWaves];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int f0 = blockIdx.x * kFeatWaves, fn = min(kFeatWaves, a.n_feat - f0);
+    const int f0 = blockIdx.x * a.per_wg, fn = min(a.per_wg, a.n_feat - f0);
     int beg = 0, end = 0;
     if (wv < fn) {
         beg = a.offsets[f0 + wv];
@@ -404,8 +408,9 @@ int s3_sae_train_step(const float* x, int B, int d_head, int n_feat, int k, floa
     float* g_w_dec = g_b_enc + n_feat;
     float* g_b_dec = g_w_dec + n_w;
     FeatArgs fa{offsets, slots, vals, dz, g, u_bf, g_w_enc, g_b_enc, g_w_dec, n_feat, k,
-                k > 1 ? (uint32_t)(((1ull << 32) + (uint32_t)k - 1) / (uint32_t)k) : 0u};
-    hipLaunchKernelGGL(tr_feature_kernel, dim3((unsigned)((n_feat + kFeatWaves - 1) / kFeatWaves)), dim3(kFeatWaves * 64), 0, st, fa);
+                k > 1 ? (uint32_t)(((1ull << 32) + (uint32_t)k - 1) / (uint32_t)k) : 0u,
+                n_feat >= kFeatWaves * kFeatUnits ? kFeatWaves : (n_feat + kFeatUnits - 1) / kFeatUnits};
+    hipLaunchKernelGGL(tr_feature_kernel, dim3((unsigned)((n_feat + fa.per_wg - 1) / fa.per_wg)), dim3(kFeatWaves * 64), 0, st, fa);
     const int nchunk = (B + kChunk - 1) / kChunk;
     hipLaunchKernelGGL(tr_colpart_kernel, dim3((unsigned)nchunk), dim3(DH), 0, st, (const float*)g, (const float*)du,
                        (const double*)lossp, B, colpart, losspart);

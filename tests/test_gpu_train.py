@@ -137,9 +137,10 @@ def test_errors():
         tr.step(torch.from_numpy(x).cuda())
 
 
-@pytest.mark.parametrize("B,n_feat,k", [(129, 128, 128), (700, 128, 64), (2500, 256, 97)])
+@pytest.mark.parametrize("B,n_feat,k", [(129, 128, 128), (700, 128, 64), (2500, 256, 97), (700, 640, 128)])
 def test_lists_that_several_wavefronts_share(B, n_feat, k):
-    """Few features: every list is longer than one wavefront takes (128 postings), the last parts of it ragged."""
+    """Few features: most lists are longer than one wavefront takes (128 postings), the last parts of them ragged, and a workgroup
+    has one to three of them."""
     import torch
     import paper_2601_17702_amd as s3
     x, P = make_problem(B + k, B, n_feat)
