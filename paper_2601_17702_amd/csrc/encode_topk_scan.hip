@@ -13,8 +13,8 @@
 //     a token's accumulators has its own, so nothing is shared), 2.3 k a token where thresholds are carried.  LDS
 //     holds W alone, which is what allows two wavefronts per SIMD at every k.
 //   - The accumulators of one set are looked through between the MFMAs of the next one: four quad maxima, the first quad with
-//     a hit by selects under scalar masks, the first element inside it, one store.  39 vector instructions a set.  (A queue of
-//     hit groups in LDS, worked off 64 at a time, cost as much again in LDS writes: 2655 us.)
+//     a hit by selects under scalar masks, the first element inside it, one store: 43 to 48 vector instructions a set with the
+//     ring's addresses.  (A queue of hit groups in LDS, worked off 64 at a time, cost as much again in LDS writes: 2655 us.)
 //   - W comes through registers into a ring of eight 32-feature stages, a barrier every four: a wavefront that is delayed by a
 //     second hit or a cut does not hold the other three up at once (2505 us with a barrier a stage).
 //   - A tile ends with its selection: a lane or a few sort a token's candidates as doubles (value and id in one number),
@@ -79,7 +79,7 @@ struct ScanArgs {
     int tiles_per_head, n_tiles;     // 256-token tiles
     int parts, per;                  // feature ranges, stages per range
     int cap;                         // entries of a list
-    int sample;                      // stages of the sample (0: none)
+    int sample;                      // stages of the sample
     int vec;                         // outputs can be written 16 bytes at a time
     uint2* list;                     // [slot][wave][cap][128]
     int* count;                      // [tile][part][wave][128] (parts > 1)
@@ -676,7 +676,7 @@ __global__ __launch_bounds__(kThreads, 2) void enc_scan_kernel(ScanArgs a) {
                 const float t0 = fmaxf(hr > -INFINITY ? hr * xn : -INFINITY, ha);
                 const float t1 = t0 - kHintMargin * fabsf(t0);         // a NaN where the bound is infinite
                 start = t1 > -INFINITY ? t1 : -INFINITY;
-            } else if (a.sample && mine) {
+            } else if (mine) {
                 start = a.tau0[(size_t)head * a.T + tok0 + lane];
             }
             s3_wave_fence();
@@ -882,7 +882,7 @@ __global__ __launch_bounds__(256) void enc_join_kernel(ScanArgs a) {
 
 // First thresholds of tokens whose head carries no bound: the R-th largest maximum of 16 features over every eighth stage, the
 // smaller one of the token's two lanes.  R is 3 standard deviations above the number that the sample is expected to hold of the k best, so
-// about one token in 10^6 starts too high; the others have about R 16 candidates (160 for k 32).  WS wavefronts share 64 tokens' stages; W
+// about one token in 10^6 starts too high; the others have about 16 R candidates (128 for k 32).  WS wavefronts share 64 tokens' stages; W
 // comes straight from L2 (a wavefront's stages are its own, or its neighbours read the same lines).
 template <int R, int WS>
 __global__ __launch_bounds__(kThreads) void enc_start_kernel(ScanArgs a) {
@@ -894,7 +894,6 @@ __global__ __launch_bounds__(kThreads) void enc_start_kernel(ScanArgs a) {
         for (int i = tid; i < 2 * a.n_heads; i += kThreads) a.hint_out[i] = 0xFFFFFFFFu;
         for (int i = tid; i < 3 * a.n_heads; i += kThreads) a.hint_sum[i] = 0.f;
     }
-    if (!a.sample) return;
     constexpr int kTok = WS > 1 ? kTokWave : kTokWG;
     const int per_head = (a.T + kTok - 1) / kTok;
     for (int unit = blockIdx.x; unit < a.n_heads * per_head; unit += gridDim.x) {
@@ -990,8 +989,10 @@ struct Plan {
 };
 constexpr int kMaxParts = 16;
 constexpr int kFewTiles = 128;          // so many tiles or fewer are split: 256 tiles in two ranges each waited longer for their join (k 128: 916 / 617 us)
+// One lane's half of a sample of an eighth holds mu = k / 16 of the k best; mu + 3 sqrt(mu) + 1 is at most 7.3, 11 and 17.5.
 int sample_rank(int k) { return k <= 32 ? 8 : (k <= 64 ? 12 : 18); }
 
+// For calls that s3_encode_scan_pays takes: 8192 features, 256 stages, and more.
 Plan plan(int n_heads, int T, int n_feat, int k) {
     Plan p;
     const int nst = n_feat / kFT;
@@ -999,16 +1000,11 @@ Plan plan(int n_heads, int T, int n_feat, int k) {
     p.n_tiles = n_heads * p.tiles_per_head;
     int parts = p.n_tiles <= kFewTiles ? kSlots / p.n_tiles : 1;
     parts = parts > kMaxParts ? kMaxParts : parts;
-    parts = parts > nst / 8 ? (nst / 8 < 1 ? 1 : nst / 8) : parts;
     p.per = ((nst + parts - 1) / parts + 1) & ~1;
     p.parts = (nst + p.per - 1) / p.per;
     p.cap = cap_of(k);
     p.units = p.parts > 1 ? p.n_tiles * p.parts : (p.n_tiles < kSlots ? p.n_tiles : kSlots);
-    // an eighth of the stages; none where so few features hold so large a k that the R-th maximum would be too high too often
-    const int R = sample_rank(k);
-    p.sample = nst / 8 > R ? nst / 8 : R;
-    const float mu = 0.5f * (float)k * (float)p.sample / (float)nst;           // of the k best, what one lane's half of the sample holds
-    if (2 * p.sample > nst || mu + 3.f * sqrtf(mu) + 1.f > (float)R) p.sample = 0;
+    p.sample = nst / 8;
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t at = o; o += s3_align(bytes); return at; };
     p.fail = take((size_t)n_heads * 4);
@@ -1095,12 +1091,10 @@ int s3_encode_scan(const EncParams& e, float* hint, void* ws, hipStream_t st) {
     a.hint_out = (unsigned*)(base + p.hout);
     a.hint_sum = (float*)(base + p.hsum);
     a.n_fail = (int*)(base + p.fail);
-    if (a.sample || hint) {
-        switch (sample_rank(e.k)) {
-            case 8: launch_start<8>(a, st); break;
-            case 12: launch_start<12>(a, st); break;
-            default: launch_start<18>(a, st);
-        }
+    switch (sample_rank(e.k)) {
+        case 8: launch_start<8>(a, st); break;
+        case 12: launch_start<12>(a, st); break;
+        default: launch_start<18>(a, st);
     }
     int rc = e.k <= 32 ? launch_scan<1, 2>(a, p, st) : (e.k <= 64 ? launch_scan<2, 2>(a, p, st) : launch_scan<4, 4>(a, p, st));
     if (rc) return rc;
