@@ -1,5 +1,6 @@
-"""The scan encoder (csrc/encode_topk_scan.hip) at the edges of its tiles, lists and ranges: bit for bit the same as the tiled
-kernel (the C entry point without scratch), which the oracle checks element by element elsewhere, and against the oracle itself."""
+"""The scan encoder (csrc/encode_topk_scan.hip) at the edges of its tiles, lists and ranges: bit for bit the same as the fast kernel
+(the C entry point without scratch, at these sizes) and as the tiled one (calls of few tokens), which the oracle checks element
+by element elsewhere, and against the oracle itself."""
 import numpy as np
 import pytest
 import torch  # noqa: F401  before the library, whose HIP runtime is then torch's
@@ -35,7 +36,7 @@ def test_scratch_holds_what_a_call_can_use():
 
 
 def plain_without_scratch(x, W, b, k):
-    """s3_sae_encode_topk: no scratch, so never the scan encoder."""
+    """s3_sae_encode_topk: no scratch, so never the scan encoder but, at this file's sizes, the fast one."""
     import torch
     import paper_2601_17702_amd as s3
     H, T, d = x.shape
@@ -55,6 +56,12 @@ def problem(H, T, nf, seed):
     return x, W, 0.01 * torch.randn(H, nf, generator=g, device="cuda")
 
 
+def plain_takes_the_scan_encoder(H, T, nf, k):
+    """By its scratch: the ranges of a call that runs tiled take at most 2^22 entries of 8 bytes."""
+    import paper_2601_17702_amd as s3
+    return s3.lib().s3_sae_encode_topk_workspace(0, T, 128, nf, k, H) > (8 << 22)
+
+
 def same(a, b):
     import torch
     torch.cuda.synchronize()
@@ -63,21 +70,31 @@ def same(a, b):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("H,T,nf,k", [
-    (1, 256, NF, 1),          # one tile, sixteen ranges, the smallest k
-    (1, 257, NF, 32),         # a tile with one token
-    (3, 300, NF, 33),         # rows that no 16-byte store can take
-    (2, 321, 12288, 64),      # ranges that do not divide the stages
-    (5, 511, NF, 65),
-    (9, 449, NF, 128),        # heads beyond a multiple of eight, a wavefront with one token
-    (65, 256, NF, 40),        # more tiles than are split: one range each
-    (130, 700, NF, 30),       # the grid walks more tiles than it has workgroups
+@pytest.mark.parametrize("H,T,nf,k,plain", [          # plain: a call without a stream takes the scan encoder too
+    (1, 256, NF, 1, False),          # one tile, sixteen ranges, the smallest k
+    (1, 257, NF, 32, False),         # a tile with one token
+    (3, 300, NF, 33, False),         # rows that no 16-byte store can take
+    (2, 321, 12288, 64, False),      # ranges that do not divide the stages
+    (5, 511, NF, 65, False),
+    (9, 449, NF, 128, False),        # heads beyond a multiple of eight, a wavefront with one token
+    (16, 256, NF, 32, True),         # as few tokens as a plain call may have
+    (9, 456, 8192, 128, True),
+    (65, 256, NF, 40, True),         # seven ranges
+    (129, 256, NF, 40, True),        # more tiles than are split, one tile a head
+    (130, 700, NF, 30, False),       # fewer whole tiles than run at once
+    (172, 513, NF, 30, True),        # 516 tiles: a workgroup takes a second one; one build each
+    (172, 513, NF, 48, True),
+    (172, 513, NF, 100, True),
+    (130, 900, 12288, 64, True),     # 520 tiles, four a head: the second turn is moved on by one
 ])
 @pytest.mark.timeout(100)
-def test_streamed_and_plain_calls_equal_the_tiled_kernel(H, T, nf, k):
+def test_streamed_and_plain_calls_equal_the_other_kernels(H, T, nf, k, plain):
     import paper_2601_17702_amd as s3
     x, W, b = problem(H, T, nf, H * 1000 + T + k)
     want = plain_without_scratch(x, W, b, k)
+    if H < 10:
+        same(tiled_rows(x, W, b, k), want)
+    assert plain_takes_the_scan_encoder(H, T, nf, k) == plain
     same(s3.sae_encode_topk(x, W, b, k), want)
     hint = s3.new_tau_hint(H)
     for _ in range(3):                       # without a bound, then with one as tight as it gets
@@ -109,31 +126,95 @@ def test_some_tokens_start_too_high(H, T, k):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("H,T,k", [(2, 300, 32), (70, 256, 64), (66, 300, 128)])
+@pytest.mark.parametrize("H,T,k,plain", [
+    (2, 300, 32, False),
+    (16, 257, 32, True),             # ranges and their join
+    (172, 520, 32, True),            # whole tiles
+    (70, 256, 64, True),             # seven ranges
+    (66, 300, 128, True),            # whole tiles
+])
 @pytest.mark.timeout(100)
-def test_ties_masked_features_and_sorted_dictionaries(H, T, k):
+def test_ties_masked_features_and_sorted_dictionaries(H, T, k, plain):
     import torch
     import paper_2601_17702_amd as s3
+    assert plain_takes_the_scan_encoder(H, T, NF, k) == plain
     x, W, b = problem(H, T, NF, 77 + k)
+
+    def check(x, W, b, want):                # with a sample's thresholds, and with a stream's
+        same(s3.sae_encode_topk(x, W, b, k), want)
+        hint = s3.new_tau_hint(H)
+        for _ in range(2):
+            same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+
     # every pre-activation the same: the lowest ids, from lists that are cut again and again
     zero = torch.zeros_like(W)
-    same(s3.sae_encode_topk(x, zero, torch.ones_like(b), k), plain_without_scratch(x, zero, torch.ones_like(b), k))
+    check(x, zero, torch.ones_like(b), plain_without_scratch(x, zero, torch.ones_like(b), k))
+    del zero
     # few different values
     g = torch.Generator(device="cuda").manual_seed(3)
     xi = torch.randint(-1, 2, x.shape, generator=g, device="cuda").to(torch.bfloat16)
     Wi = W[:, :64].sign().repeat(1, NF // 64, 1).contiguous()
-    for hint in (None, s3.new_tau_hint(H)):
-        got = s3.sae_encode_topk(xi, Wi, torch.zeros_like(b), k) if hint is None else s3.sae_encode_topk_stream(xi, Wi, torch.zeros_like(b), k, hint)
-        same(got, plain_without_scratch(xi, Wi, torch.zeros_like(b), k))
+    check(xi, Wi, torch.zeros_like(b), plain_without_scratch(xi, Wi, torch.zeros_like(b), k))
+    del Wi
     # ascending and descending biases: all that counts comes last, or first (the sample's thresholds are then far off)
     for sign in (1.0, -1.0):
         bs = (sign * torch.linspace(-9, 9, NF, device="cuda")).repeat(H, 1).contiguous()
-        same(s3.sae_encode_topk(x, W, bs, k), plain_without_scratch(x, W, bs, k))
+        check(x, W, bs, plain_without_scratch(x, W, bs, k))
     # features masked with -inf: first all but a hundred, then all but fewer than k: rows are filled with the lowest other ids
     for left in (200, k - 5):
         bm = torch.full_like(b, float("-inf"))
         bm[:, torch.randperm(NF, generator=torch.Generator().manual_seed(1))[:left].cuda()] = 0.0
-        same(s3.sae_encode_topk(x, W, bm, k), tiled_rows(x, W, bm, k))
+        check(x, W, bm, tiled_rows(x, W, bm, k))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,T,k", [(16, 300, 32), (172, 520, 32), (70, 256, 64), (66, 300, 128)])
+@pytest.mark.timeout(100)
+def test_tokens_of_nan_and_overflowing_ones(H, T, k):
+    """A token of NaN has no element, one whose products overflow has elements of +inf and NaN beside finite ones; the rows of the
+    other tokens of their tiles and the bounds carried on are not touched by them."""
+    import torch
+    import paper_2601_17702_amd as s3
+    x, W, b = problem(H, T, NF, 5 + T)
+    clean = s3.new_tau_hint(H)
+    s3.sae_encode_topk_stream(x, W, b, k, clean)
+    x[:, 3, 17] = float("nan")
+    x[0, T - 1, 0] = float("inf")
+    x[:, 130] = 2e38 * x[:, 130].sign()
+    want = tiled_rows(x, W, b, k)
+    same(s3.sae_encode_topk(x, W, b, k), want)
+    hint = s3.new_tau_hint(H)
+    for _ in range(2):
+        same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+        assert not torch.any(torch.isnan(hint)) and torch.all(torch.isfinite(hint).sum(dim=1) == 1)
+        assert torch.all(hint[:, 0] <= 1.001 * clean[:, 0] + 1.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,T,k", [(12, 300, 32), (70, 520, 64), (70, 520, 128), (140, 520, 32)])
+@pytest.mark.timeout(100)
+def test_heads_with_and_without_a_bound_and_outputs_at_any_int(H, T, k):
+    """Half of the heads start from a carried bound, the others from the sample; rows of a multiple of four that are not aligned to 16
+    bytes; and scratch that calls of other shapes have used before on the same stream."""
+    import torch
+    import paper_2601_17702_amd as s3
+    x, W, b = problem(H, T, NF, 3 * k + T)
+    want = plain_without_scratch(x, W, b, k)
+    hint = s3.new_tau_hint(H)
+    s3.sae_encode_topk_stream(x, W, b, k, hint)
+    full = hint.clone()
+    ws = torch.randint(0, 256, (s3.sae_encode_topk_stream_workspace(H, T),), dtype=torch.uint8, device="cuda")
+    ids = torch.full((H * T * k + 8,), -7, dtype=torch.int32, device="cuda")
+    vals = torch.full((H * T * k + 8,), -7.0, device="cuda")
+    for off in (0, 1, 2):
+        hint = full.clone()
+        hint[1::2] = float("-inf")
+        o = (ids[off:off + H * T * k].view(H, T, k), vals[off:off + H * T * k].view(H, T, k))
+        same(s3.sae_encode_topk_stream(x, W, b, k, hint, ws, *o), want)
+        assert torch.all(torch.isfinite(hint).sum(dim=1) == 1)
+        assert torch.all(ids[off + H * T * k:] == -7) and torch.all(vals[off + H * T * k:] == -7)
+        ids.fill_(-7), vals.fill_(-7)
+        s3.sae_encode_topk_stream(x[:3, :257].contiguous(), W[:3], b[:3], 7, s3.new_tau_hint(3), ws)     # other lists in the same place
 
 
 @pytest.mark.gpu
