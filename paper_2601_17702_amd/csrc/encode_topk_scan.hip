@@ -642,14 +642,14 @@ __global__ __launch_bounds__(kThreads, 2) void enc_scan_kernel(ScanArgs a) {
     int* const cnt = (int*)(mem + kWCnt);
     const int parts = REDO ? 1 : a.parts;      // ranges that are workgroups of their own here
 
-    int turn = 0;
-    for (int unit = blockIdx.x; unit < a.n_tiles * parts; unit += gridDim.x, ++turn) {
+    for (int unit = blockIdx.x; unit < a.n_tiles * parts; unit += gridDim.x) {
         int group, tt;
         s3_block_to_tile((unsigned)unit, a.n_heads * parts, a.tiles_per_head, group, tt);
         // Where a turn takes whole heads, a workgroup would take the same tile of a head every time: it moves on by one.  Rows that are
         // walked twice often stand at one place in all heads (padding, a first token).  One row of zeros a head and no biases,
         // 256 heads x 2048 tokens, k 32: 4077 -> 3150 us.
-        if ((gridDim.x >> 3) % (unsigned)a.tiles_per_head == 0) tt = (tt + turn) % a.tiles_per_head;
+        if (__builtin_expect(!REDO && unit >= (int)gridDim.x, 0) && (gridDim.x >> 3) % (unsigned)a.tiles_per_head == 0)
+            tt = (tt + unit / (int)gridDim.x) % a.tiles_per_head;
         const int head = group / parts, part = group - head * parts;
         const int tok0 = tt * kTokWG + wv * kTokWave;
         const bool active = tok0 < a.T, mine = tok0 + lane < a.T;     // lane t answers for token t of the wavefront
