@@ -1,17 +1,19 @@
 // Scan encoder: the fused SAE encoder + Top-k (Sec. 3.3) of bf16, d_head 128, n_feat a multiple of 128, k <= 128, for calls that
 // have scratch and enough features and tokens (s3_encode_scan_pays).
 //
-// What bounds it: power.  At 2048 tokens x 256 heads x 16384 features (k 32, a later chunk of a stream) the MFMAs are busy 47 % of
-// the cycles at 1.85 GHz; a large plain matrix product (1366 TFLOP/s) is held back the same way.  Every vector instruction
-// that goes, every LDS read and every waiting cycle counts; 2756 -> 2365 us there against the kernel with lists in LDS, 1387 -> 617
-// us for 32 heads and k 128 (198 -> 446 TFLOP/s), 3337 -> 2146 us for 112 heads x 32768 features and k 64.
+// What bounds it: for k <= 64 the clock and the vector instructions beside the MFMAs.  At 2048 tokens x 256 heads x 16384 features
+// (k 32, a later chunk of a stream) the chip runs at 1.8 to 1.9 GHz, as it does in a large plain matrix product (1366 TFLOP/s, MFMAs
+// 72 % of the cycles); MFMAs are busy 46 % of them here, vector issue 44 %.  Every vector instruction that goes, every LDS
+// read and every waiting cycle counts; 2756 -> 2365 us there against the kernel with lists in LDS, 3337 -> 2146 us for 112 heads x
+// 32768 features and k 64.  For k <= 128 latency: 2.3 GHz and more, 45 % of the wavefronts' cycles waiting; 1387 -> 617 us for 32
+// heads (198 -> 446 TFLOP/s), one wavefront per SIMD.
 //
 //   - Features lie on the M axis of the 32x32x16 MFMA, tokens on N.  A wavefront has 64 tokens (two sets of 32 in registers), so that a
 //     fragment of W that is read from LDS serves two MFMAs; a workgroup is four wavefronts, two workgroups share a compute unit.
 //   - Every token has a threshold from the start: from the bound that a stream carries, or from a sample of the features
 //     (enc_start_kernel).  What exceeds it is a candidate.  Candidates go to lists in scratch (each of the two lanes that hold
-//     a token's accumulators has its own, so nothing is shared), 2.3 k a token where thresholds are carried.  LDS
-//     holds W alone, which is what allows two wavefronts per SIMD at every k.
+//     a token's accumulators has its own, so nothing is shared), 76 a token for k 32 and 216 for k 128 where thresholds are
+//     carried.  LDS holds W alone, which is what allows two wavefronts per SIMD at every k.
 //   - The accumulators of one set are looked through between the MFMAs of the next one: four quad maxima, the first quad with
 //     a hit by selects under scalar masks, the first element inside it, one store: 43 to 48 vector instructions a set with the
 //     ring's addresses.  (A queue of hit groups in LDS, worked off 64 at a time, cost as much again in LDS writes: 2655 us.)
@@ -151,10 +153,11 @@ struct Lane {
 // Cuts the lists of the set's tokens in `which` to about k elements, one token after the other, and raises their thresholds to
 // the smallest value kept: k or more elements reach it, all with lower ids than what is still to come, so an element that only
 // equals it has lost.  A token's two lists (at most 64 N entries) are read once, by the whole wavefront, and searched by
-// counts of ballots; what is kept is dealt to both lists in turn.  For lists that are full inside the walk and for ties.  When every
-// lane searched its own lists there, and read them again in each pass because the walk leaves few registers, a cut took 65
-// us: later chunks of 64 heads x 2048 tokens x 16384 skewed features, k 32, 845 -> 735 us, of 32768 1628 -> 1537; with a row of zeros
-// and no biases (all pre-activations equal), 256 x 2048 x 16384, 6647 -> 4197, k 128, 32 x 2048, 1915 -> 965.
+// counts of ballots; what is kept is dealt to both lists in turn.  For lists that are full inside the walk, for ties and for
+// few long lists.  A call takes 7000 to 10000 cycles.  When every lane searched its own list in the walk, and read it again in each
+// pass because the walk leaves few registers, it took 100000 to 137000, and 1.45 million among ties: later chunks of 64 heads x 2048
+// tokens x 16384 skewed features, k 32, 845 -> 735 us, of 32768 1628 -> 1537; with a row of zeros and no biases (all
+// pre-activations equal), 256 x 2048 x 16384, 6647 -> 4197, k 128, 32 x 2048, 1915 -> 965.
 template <int N>
 __device__ __attribute__((noinline)) Lane cut_tokens(char* list, Lane l, unsigned which, int k) {
     constexpr unsigned per = kLanes * sizeof(uint2);
@@ -1052,8 +1055,10 @@ void launch_start(const ScanArgs& a, hipStream_t st) {
 //   - k <= 32 from 65 to 256 tiles: less than two workgroups per compute unit, or a join of many tokens (16 heads x 2048: 334 /
 //     380); beyond, 48 x 2048: 653 / 527, 256 x 2048: 2756 / 2365.
 //   - Skewed features (Zipf) bring a token more candidates in narrow dictionaries: 128 x 2048, k 32: of 8192 features 1009 /
-//     1167 (evenly used ones 64 x 2048, k 16: 810 / 666), of 16384 1408 / 1444; k 64: of 8192 941 / 1028, of 32768 3491 / 2674; k 128:
-//     of 16384 2936 / 1929, of 8192 (even) 288 / 227.
+//     1167 (evenly used ones 64 x 2048, k 16: 810 / 666), of 16384 1525 / 1526, of 32768, 64 x 2048, 1322 / 1483 (first chunks 1992 / 1411,
+//     even ones 1342 / 1090); k 64: of 8192 941 / 1028, of 32768 3491 / 2674; k 128: of 16384 2936 / 1929, of 8192 (even) 288 / 227.
+//   - First chunks pay for the sample: k 32, 256 x 2048 3330 / 3468, later ones 2793 / 2381; x 1025 (a fifth tile with one token) 1842 /
+//     2077 and 1638 / 1453.
 //   - Plain calls have no carried thresholds and pay for the sample: k 32, 64 x 256: 449 / 168, 128 x 512: 496 / 560, 256 x 512:
 //     942 / 914.
 bool s3_encode_scan_pays(int n_heads, int T, int n_feat, int k, bool streamed) {
