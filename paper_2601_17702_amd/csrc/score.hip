@@ -13,6 +13,7 @@
 // depend on the order in which wavefronts reach a position, run-to-run output is bit-identical,
 // and a window's score is exactly the sum of its members.  Values are rounded to fp32 once, on
 // output.
+#include "greedy.h"
 #include "s3_common.h"
 
 #include <math.h>
@@ -53,9 +54,11 @@ struct ScoreArgs {
     unsigned long long* part;        // [ngroup][L] partial sums of head groups (ngroup > 1)
     int pb, npb, heads_per, ngroup, sorted;   // position blocks / head groups of the gather
     long long* wfix;                 // [nW]
-    unsigned long long* tmaxv;       // [nsub] best window of every kSubW starts: its sum + 1, 0 for none
+    unsigned long long* tmaxv;       // [nsub] best window of every 2^sublog starts: its sum + 1, 0 for none
     int* tmaxi;                      // [nsub] its start
-    int ntile, nsub, topshift;       // tiles of kTileW starts; the Top-B search works on tiles of kSubW << topshift
+    int sublog;                      // 6 where the search brings blocks into LDS, else kSubLog2
+    int need, room;                  // blocks that it brings there at least, entries of its list of choices
+    int ntile, nsub, topshift;       // tiles of kTileW starts; sc_topb_long_kernel works on tiles of kSubW << topshift
     float* scores_out;
     int32_t* span_start;
     float* span_score;
@@ -67,7 +70,9 @@ constexpr int kPrepThreads = 1024;
 constexpr int kRun = 32;             // consecutive windows per thread (sliding sum, exact in integers)
 constexpr int kTileW = 64 * kRun;    // windows per tile = per wavefront of the pooling kernel
 constexpr int kSubLog2 = 8;
-constexpr int kSubW = 1 << kSubLog2; // windows per entry of the tile maxima
+constexpr int kSubW = 1 << kSubLog2; // windows per entry of the tile maxima (sc_topb_kernel, sc_topb_long_kernel)
+constexpr int kTopFew = 4;           // for so many spans or fewer that is not worth its beginning (4 spans of 1000 to 1000000 positions: as long; 1: 6 us more)
+constexpr int kTopSlots = 256;       // blocks of 64 windows that sc_topb_slots_kernel holds in LDS at most (131 KB)
 constexpr int kTopRegs = 4;          // registers per lane for the maxima of a short context
 constexpr int kTopThreads = 1024;    // long contexts: all of them load the tile maxima, one wavefront searches
 constexpr int kTopTiles = 4096;      // tiles of the Top-B search: 64 groups of 64, one group per lane
@@ -489,7 +494,29 @@ __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
     __syncthreads();
     for (int q = wave; q < kTileW / kSubW; q += kPoolThreads / 64) {
         const int sub = (int)blockIdx.x * (kTileW / kSubW) + q;
-        if (sub >= a.nsub) break;
+        if (s0 + q * kSubW >= a.nW) break;
+        if (a.sublog == 6) {                                                      // a maximum for every 64 windows
+            unsigned long long w[kSubW / 64];
+#pragma unroll
+            for (int u = 0; u < kSubW / 64; ++u) {
+                const int i = q * kSubW + u * 64 + lane;
+                w[u] = 0;
+                if (s0 + i < a.nW) {
+                    const unsigned long long v = pre[i + a.len - 1] - (i ? pre[i - 1] : 0ull);
+                    a.wfix[s0 + i] = (long long)v;
+                    w[u] = v + 1;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kSubW / 64; ++u) {
+                const unsigned top = s3_wave_max_u32((unsigned)(w[u] >> 32));
+                unsigned long long m = __ballot((unsigned)(w[u] >> 32) == top);
+                s3greedy::settle(w[u], top, m);                                   // ties -> the first lane, the smaller start
+                const int e = sub * (kSubW / 64) + u, src = (int)__builtin_ctzll(m);
+                if (lane == src && e < a.nsub) { a.tmaxv[e] = w[u]; a.tmaxi[e] = (int)(s0 + q * kSubW + u * 64 + src); }
+            }
+            continue;
+        }
         unsigned long long key = 0;
         int start = 0x7FFFFFFF;
 #pragma unroll
@@ -530,23 +557,27 @@ __global__ __launch_bounds__(256) void sc_pool_wide_kernel(ScoreArgs a) {
             if (acc + 1 > key) { key = acc + 1; start = (int)(s0 + j); }
         }
     }
-    constexpr int kLanes = kSubW / kRun;                  // lanes that share one entry of the tile maxima
-#pragma unroll
-    for (int o = kLanes / 2; o > 0; o >>= 1) {
+    const int share = (1 << a.sublog) / kRun;             // lanes that share one entry of the tile maxima
+    for (int o = share / 2; o > 0; o >>= 1) {
         const unsigned lo = (unsigned)__shfl_xor((int)(unsigned)key, o), hi = (unsigned)__shfl_xor((int)(unsigned)(key >> 32), o);
         const unsigned long long other = ((unsigned long long)hi << 32) | lo;
         const int os = __shfl_xor(start, o);
         if (other > key || (other == key && os < start)) { key = other; start = os; }
     }
-    const int64_t sub = tile * (kTileW / kSubW) + lane / kLanes;
-    if (lane % kLanes == 0 && sub < a.nsub) { a.tmaxv[sub] = key; a.tmaxi[sub] = start; }
+    const int64_t sub = tile * (64 / share) + lane / share;
+    if (lane % share == 0 && sub < a.nsub) { a.tmaxv[sub] = key; a.tmaxi[sub] = start; }
 }
 
 // Greedy Top-B with optional suppression of overlapping windows.  The rounds depend on each other, so what bounds it is
-// the latency of a round: one wavefront walks them without a barrier, with maxima in its registers.  A round takes the
-// best, clears the tiles that the suppression covers whole and searches the two blocks of kSubW windows at its ends again,
-// loads of both in flight together.  A window that is gone is marked -1 in memory; window s belongs to lane s % 64 in every
-// round, so a lane only ever reads back its own marks.  A tile without live windows stays so (its windows need not be marked).
+// the latency of a round.
+//
+// sc_topb_rounds_kernel, sc_topb_slots_kernel: the blocks of 64 windows that the choices can lie in are brought into LDS (greedy.h),
+// for up to kTopSlots such blocks.  The first takes all choices that do not depend on each other at once, the second (few
+// windows suppressed by each, or none) one a round.
+// The others, for more: one wavefront walks the rounds without a barrier, with maxima of blocks of 256 windows in its registers.
+// A round takes the best, clears the tiles that the suppression covers whole and searches the two blocks of kSubW windows at its
+// ends again, loads of both in flight together.  A window that is gone is marked -1 in memory; window s belongs to lane s % 64 in
+// every round, so a lane only ever reads back its own marks.  A tile without live windows stays so (its windows need not be marked).
 //
 // sc_topb_kernel: the registers hold the maxima of up to kTopRegs * 64 tiles of one block.
 // sc_topb_long_kernel: tile maxima in LDS, those of groups of 64 tiles in registers, so that a round costs the same at any
@@ -554,12 +585,10 @@ __global__ __launch_bounds__(256) void sc_pool_wide_kernel(ScoreArgs a) {
 // kTopTiles blocks a tile has several; their maxima come from memory beside the windows, block e belongs to the same lane in
 // every round, too.
 //
-// us for a whole look-up of 4 short lists, spans of 64: 256 threads, tiles of 2048 windows and a search through the spans
-// chosen so far / one wavefront that looks through up to 4096 tile maxima in LDS every round / this:
-//   32768 positions, 16 spans: 82 / 53 / 51, 1024 spans: 7240 / 714 / 675
-//   524288 positions, 16 spans: 81 / 94 / 59     1048576 positions, 16 spans: 86 / 142 / 65, 64 spans: 361 / 458 / 165
-//   16777216 positions, 64 spans: 1059 / 1114 / 343
-// The line between the kernels, 16 spans: 65536 positions take 51 us in 4 registers, 57 in groups; with 8 registers 131072
+// us for a whole look-up of 4 queries in one index, with these two / with blocks in LDS: 16 spans of 64, 8000 positions 51 / 33,
+// 200000 57 / 33, 1000000 64 / 41; 64 spans of 64, 8000 positions 133 / 36, 200000 156 / 42; 16 spans of 8, 33000 positions 47 / 31; 16
+// spans of 256 53 / 40; 16 windows that may overlap, 33000 positions 45 / 36.
+// The line between these two, 16 spans: 65536 positions take 51 us in 4 registers, 57 in groups; with 8 registers 131072
 // take 55.5 instead of 56.5, but 32768 take 56 instead of 51.
 struct TopBest {
     unsigned long long key;                               // window sum + 1; 0: none
@@ -742,6 +771,55 @@ __global__ __launch_bounds__(kTopThreads) void sc_topb_long_kernel(ScoreArgs a) 
     top_finish(a, found, lane);
 }
 
+// The blocks' maxima and their windows, P a thread, and with them the slots.
+template <int P>
+__device__ __forceinline__ void top_fill(const ScoreArgs& a, const s3greedy::Slots<unsigned long long>& slots) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned long long key[P];
+    int at[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        const int b = (wave * P + q) * 64 + lane;
+        key[q] = b < a.nsub ? a.tmaxv[b] : 0ull;
+        at[q] = b < a.nsub ? a.tmaxi[b] : 0;
+    }
+    s3greedy::fill<unsigned long long, P>(slots, key, at, a.need, a.nW, [&](int64_t w) { return a.wfix[w]; },
+                                          [](long long w) { return (unsigned long long)(w + 1); });
+}
+
+template <int P, int C>                                // maxima per thread, slots
+__global__ __launch_bounds__(s3greedy::kThreads) void sc_topb_rounds_kernel(ScoreArgs a) {
+    extern __shared__ __align__(16) unsigned long long top_lds[];
+    const auto slots = s3greedy::slots_of<unsigned long long>(top_lds, C);
+    unsigned long long* const list_key = (unsigned long long*)((char*)top_lds + s3greedy::lds_bytes<unsigned long long>(C));
+    const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
+    top_fill<P>(a, slots);
+    const int found = s3greedy::rounds<C, unsigned long long>(slots, list_key, (int*)(list_key + a.room), (unsigned)a.nW, (unsigned)(a.len - 1), a.top_b,
+                                                              [&](int r, unsigned long long k, int w) {
+        a.span_start[r] = w;
+        a.span_score[r] = (float)((double)(long long)(k - 1) * inv);
+    });
+    if (threadIdx.x < 64) top_finish(a, found, threadIdx.x);
+}
+
+template <int P, int R>                                // maxima per thread, slots per lane
+__global__ __launch_bounds__(s3greedy::kThreads) void sc_topb_slots_kernel(ScoreArgs a) {
+    extern __shared__ __align__(16) unsigned long long top_lds[];
+    const int lane = threadIdx.x & 63;
+    const auto slots = s3greedy::slots_of<unsigned long long>(top_lds, 64 * R);
+    const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
+    top_fill<P>(a, slots);
+    if (threadIdx.x >= 64) return;
+    const int found = s3greedy::walk<R, unsigned long long>(slots, (unsigned)a.nW, a.nms ? (unsigned)(a.len - 1) : 0u, a.top_b,
+                                                            [&](int r, unsigned long long k, int w) {
+        if (lane == 0) {
+            a.span_start[r] = w;
+            a.span_score[r] = (float)((double)(long long)(k - 1) * inv);
+        }
+    });
+    top_finish(a, found, lane);
+}
+
 struct Layout {
     size_t wmax, nact, sfix, wfix, tmaxv, tmaxi, part, act, total;
     int nr, pb, npb, heads_per, ngroup;   // feature ranges per head; position blocks and head groups of the gather
@@ -752,7 +830,7 @@ Layout layout(int n_heads, int n_feat, int64_t L) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += s3_align(bytes); return at; };
     const int64_t nW_max = L;
-    const size_t nsub = (size_t)(nW_max + kSubW - 1) / kSubW;
+    const size_t nsub = (size_t)(nW_max + 63) / 64;
     l.nr = (n_feat + kRange - 1) / kRange;
     l.wmax = take(((size_t)n_heads * l.nr + 1) * 8);
     l.nact = take((size_t)n_heads * l.nr * 4);
@@ -827,7 +905,13 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.part = (unsigned long long*)(base + l.part);
     a.pb = l.pb; a.npb = l.npb; a.heads_per = l.heads_per; a.ngroup = l.ngroup; a.sorted = v.sorted ? 1 : 0;
     a.ntile = (int)((a.nW + kTileW - 1) / kTileW);
-    a.nsub = (int)((a.nW + kSubW - 1) / kSubW);
+    const int64_t reach = a.nms ? a.len - 1 : 0, most_found = s3greedy::choices(a.nW, reach, top_b), need = s3greedy::slots_needed(a.nW, reach, most_found);
+    const bool slots = most_found > kTopFew && need <= kTopSlots && (a.nW + 63) / 64 <= 16 * s3greedy::kThreads;
+    const s3greedy::Way sw = s3greedy::way_of(need, reach);
+    a.need = (int)(slots ? need : 0);
+    a.room = sw.room;
+    a.sublog = slots ? 6 : kSubLog2;
+    a.nsub = (int)((a.nW + (1 << a.sublog) - 1) >> a.sublog);
     // the smallest tiles of which the search's lanes hold all groups: beyond 1M windows a tile has several blocks
     a.topshift = 0;
     while (((a.nsub - 1) >> a.topshift) + 1 > kTopTiles) ++a.topshift;
@@ -854,7 +938,20 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     } else {
         hipLaunchKernelGGL(sc_pool_wide_kernel, dim3((unsigned)((a.ntile + 3) / 4)), dim3(256), 0, st, a);
     }
-    if (a.nsub <= kTopRegs * 64) hipLaunchKernelGGL(sc_topb_kernel, dim3(1), dim3(64), 0, st, a);
+    if (slots) {
+        static void (*const ways[18])(ScoreArgs) = {
+            sc_topb_rounds_kernel<1, 64>, sc_topb_rounds_kernel<1, 128>, sc_topb_rounds_kernel<1, 256>,
+            sc_topb_rounds_kernel<4, 64>, sc_topb_rounds_kernel<4, 128>, sc_topb_rounds_kernel<4, 256>,
+            sc_topb_rounds_kernel<16, 64>, sc_topb_rounds_kernel<16, 128>, sc_topb_rounds_kernel<16, 256>,
+            sc_topb_slots_kernel<1, 1>, sc_topb_slots_kernel<1, 2>, sc_topb_slots_kernel<1, 4>,
+            sc_topb_slots_kernel<4, 1>, sc_topb_slots_kernel<4, 2>, sc_topb_slots_kernel<4, 4>,
+            sc_topb_slots_kernel<16, 1>, sc_topb_slots_kernel<16, 2>, sc_topb_slots_kernel<16, 4>};
+        const int way = (sw.rounds ? 0 : 9) + (a.nsub <= s3greedy::kThreads ? 0 : (a.nsub <= 4 * s3greedy::kThreads ? 3 : 6)) + sw.up;
+        const int fixed = s3greedy::lds_bytes<unsigned long long>(sw.cap);
+        static S3LdsOnce once_top[18];
+        if (int rc = s3_allow_lds(once_top[way], (const void*)ways[way], fixed + (sw.rounds ? s3greedy::kListMax * 12 : 0))) return rc;
+        hipLaunchKernelGGL(ways[way], dim3(1), dim3(s3greedy::kThreads), (size_t)(fixed + (sw.rounds ? sw.room * 12 : 0)), st, a);
+    } else if (a.nsub <= kTopRegs * 64) hipLaunchKernelGGL(sc_topb_kernel, dim3(1), dim3(64), 0, st, a);
     else hipLaunchKernelGGL(sc_topb_long_kernel, dim3(1), dim3(kTopThreads), 0, st, a);
     S3_HIP(hipGetLastError());
     return S3_OK;

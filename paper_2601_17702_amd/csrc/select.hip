@@ -10,6 +10,7 @@
 // is exact in fp64, so the sum does not depend on whether the compiler fuses the multiply-add) and rounded to fp32
 // once; every decision -- which position is a peak, where a span ends -- is taken on those fp32 values, with the
 // threshold product formed in fp64.  A CPU reference that follows the same steps reaches the same integers.
+#include "greedy.h"
 #include "s3_common.h"
 
 #include <math.h>
@@ -22,12 +23,15 @@ constexpr int kConvSmall = 64, kConvLarge = 256;      // its workgroup sizes: be
 constexpr int64_t kConvLargeFrom = 1 << 18; // 64 threads fill the chip up to 2^18 positions; beyond, the halo is shared by more
 constexpr int kTile = 64;                   // positions per block: one bit or one lane each
 constexpr int kConvKeyShift = 4;            // blocks per workgroup of the large convolution: 2^4
-constexpr int kNmsThreads = 1024;
+constexpr int kNmsThreads = s3greedy::kThreads;
+constexpr int kNmsFew = 8;                  // for so many centres or fewer that is not worth its beginning: us for a whole selection without
+                                            // / with it, 1 centre of 8000 positions 9.4 / 14.3, 8 of 1000 to 300000 15 to 20 / 14 to 20,
+                                            // at a radius of 1000 20 / 25 to 38; 40 of 8000 48 / 19
+constexpr int kNmsSlots = 576;              // blocks that the peak search holds in LDS at most (151 KB)
 constexpr int kNmsTiles = 16384;            // tile maxima that the peak search keeps in LDS at most (128 KB): four groups of 64 per lane
 constexpr int kNmsTilesMin = 8192;          // as many fit beside the most centres
 static_assert(kConvLarge * kConvPer == kTile << kConvKeyShift && kConvLargeFrom <= (int64_t)kNmsTilesMin * kTile);
-constexpr int kShortGroups = 1;             // groups per lane of a curve that is kept in LDS (below 40000 positions)
-constexpr int kNmsLds = 152 << 10;          // its LDS: tile maxima, centres, group maxima, and the whole curve if that fits
+constexpr int kNmsLds = 152 << 10;          // its LDS: tile maxima, centres, group maxima
 
 struct SelArgs {
     const float* scores;
@@ -38,8 +42,9 @@ struct SelArgs {
     float* dens;                 // [L]
     unsigned long long* tkey;    // [nblk] best position of every block of kTile positions (peak_key)
     unsigned long long* ckey;    // [nckey] best position of every kTile << kshift positions (kshift > 0 only)
-    unsigned long long* dead;    // [nblk] positions of every block that are gone, a bit each; null if the curve is kept in LDS
+    unsigned long long* dead;    // [nblk] positions of every block that are gone, a bit each (sel_nms_long_kernel)
     int nblk, nckey;
+    int need, room;              // blocks that the peak search brings into LDS at least, and entries of its list of choices
     int shift, kshift;           // the peak search works on tiles of kTile << shift positions, shift >= kshift
     int32_t* center;
     float* center_density;
@@ -132,31 +137,29 @@ __global__ __launch_bounds__(NT) void sel_conv_kernel(SelArgs a) {
     }
 }
 
-// Greedy peak selection, then the span of every peak.  One workgroup: the rounds depend on each other, so what bounds
-// it is the latency of a round.  One wavefront walks the rounds without a barrier: the maxima of groups of 64 tiles
-// are in its registers, the tile maxima in LDS.  A round takes the best group, clears the tiles that the suppression
+// Greedy peak selection, then the span of every peak.  One workgroup: the rounds depend on each other, so what bounds it is
+// the latency of a round.
+//
+// sel_peaks_kernel, sel_nms_kernel: the blocks that the choices can lie in are brought into LDS (greedy.h), for up to 512 or 576
+// such blocks (always below 32769 or 36865 positions, else three a centre at a radius of 64).  The first takes all choices that do not
+// depend on each other at once, the second (small radii, where there may be many) one a round.
+// sel_nms_long_kernel, for more centres: one wavefront walks the rounds without a barrier over all tiles: maxima of groups of 64
+// tiles are in its registers, the tile maxima in LDS.  A round takes the best group, clears the tiles that the suppression
 // covers whole and searches the two blocks of 64 positions at its ends again; the groups at both ends are reduced in the
-// next round, beside its search and not behind this one's.  The chain of a round is two reductions over the wavefront and
-// one LDS (or L2) latency.
+// next round, beside its search and not behind this one's.  The curve is read from memory beside a bit per position that says
+// which ones are gone (word e belongs to lane e % 64 in every round, so a lane only ever reads back its own marks).  A tile or
+// block without live positions stays so (its bits need not be set).  Beyond kNmsTilesMin blocks a tile may have several; from
+// four on their keys come from memory, too, and the convolution leaves the first maxima of up to 1024 positions, so that one
+// workgroup has fewer to load.
 //
-// sel_nms_kernel: a short context's curve is kept in LDS and the suppressed interval wiped out of that copy.
-// sel_nms_long_kernel: the curve is read from memory beside a bit per position that says which ones are gone (word e belongs
-// to lane e % 64 in every round, so a lane only ever reads back its own marks).  A tile or block without live positions stays
-// so (its bits need not be set).  Beyond kNmsTilesMin blocks a tile may have several; from four on their keys come from
-// memory, too, and the convolution leaves the first maxima of up to 1024 positions, so that one workgroup has fewer to load.
-//
-// us for a whole selection, K 48, radius 48: 256 threads, tiles of 1024 positions, flags in memory and ten barriers a round /
-// one wavefront that searched whole tiles again and looked through all centres for what is gone / this:
-//   32768 positions, 40 centres: 173 / 50 / 48        131072 positions, 40 centres: 183 / 56 / 56, 4000: 6480 / 5942 / 2392
-//   524288 positions, 4000 centres: 14000 / 18020 / 4743
-//   1048576 positions, 40 centres: 214 / 71 / 69, 4000: 16440 / 19970 / 6040
-//   16777216 positions, 1 centre: 130 / 194 / 75, 4000: 59700 / 128600 / 7250
+// us for a whole selection, K 48, half lengths of 64, by one choice a round over all tiles (below 36000 positions with the curve in
+// LDS) / with blocks in LDS: 40 centres, radius 64: 8000 positions 48 / 19, 36000 51 / 19, 300000 59 / 27, 1000000 70 / 29; radius 0
+// 46 / 32, 49 / 33, 56 / 34, 67 / 38; 128 centres, radius 64, 36000 positions 141 / 40.
 struct NmsLds {
     unsigned long long* key;                                          // [nt] tile maxima
     unsigned long long* gkey;                                         // [ng] maxima of groups of 64 tiles
     int* cen;                                                         // [n_centers]
     float* cden;                                                      // [n_centers]
-    float* cur;                                                       // [L] the curve (short contexts)
     int nt, ng;
 };
 __device__ __forceinline__ NmsLds nms_lds_of(const SelArgs& a, unsigned long long* lds) {
@@ -167,7 +170,6 @@ __device__ __forceinline__ NmsLds nms_lds_of(const SelArgs& a, unsigned long lon
     l.gkey = l.key + l.nt;
     l.cen = (int*)(l.gkey + l.ng);
     l.cden = (float*)(l.cen + a.n_centers);
-    l.cur = l.cden + a.n_centers;
     return l;
 }
 
@@ -243,37 +245,55 @@ __device__ __forceinline__ void nms_close(NmsTop<G>& w, const NmsLds& l, int tl,
 
 __device__ __forceinline__ void nms_spans(const SelArgs& a, const int* cen, const float* cden, int found, int tid, int lane, int wave) {
     // spans: a wavefront per centre walks outwards 64 positions at a time, both sides at once; a side ends before the
-    // first position whose density is below rel * D[centre] or that is farther than max_half from the centre
-    for (int r = wave; r < found; r += kNmsThreads / 64) {
-        const int c = cen[r];
-        const double thr = (double)a.rel * (double)cden[r];
-        const int limit[2] = {(int)min((int64_t)a.max_half, (int64_t)c), (int)min((int64_t)a.max_half, a.L - 1 - c)};
-        int n[2] = {0, 0};
-        bool open[2] = {limit[0] > 0, limit[1] > 0};
-        while (open[0] || open[1]) {
-            float d[2];
+    // first position whose density is below rel * D[centre] or that is farther than max_half from the centre.  The first 64
+    // positions of four centres are asked for together (40 centres, half lengths of 64: 2.9 -> 2.3 us).
+    constexpr int kW = kNmsThreads / 64, U = 4;
+    for (int r0 = wave; r0 < found; r0 += U * kW) {
+        float ahead[U][2];
+        int c[U];
+        double thr[U];
 #pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                const int64_t off = (int64_t)n[side] + 1 + lane;      // distance from the centre
-                const int64_t t = side == 0 ? c - off : c + off;
-                d[side] = -1.f;
-                if (open[side] && off <= limit[side]) d[side] = a.dens[t];
-            }
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                if (!open[side]) continue;
-                const bool ok = (int64_t)n[side] + 1 + lane <= limit[side] && (double)d[side] >= thr;
-                const unsigned long long m = __ballot(ok);
-                const int run = m == ~0ull ? 64 : (int)__builtin_ctzll(~m);      // leading positions that pass
-                n[side] += run;
-                open[side] = run == 64 && n[side] < limit[side];
-            }
+        for (int u = 0; u < U; ++u) {
+            const int r = min(r0 + u * kW, found - 1);
+            c[u] = cen[r];
+            thr[u] = (double)a.rel * (double)cden[r];
         }
-        if (lane == 0) {
-            a.center[r] = c;
-            a.center_density[r] = cden[r];
-            a.span_lo[r] = c - n[0];
-            a.span_hi[r] = c + n[1];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                const int64_t t = side == 0 ? (int64_t)c[u] - 1 - lane : (int64_t)c[u] + 1 + lane;
+                ahead[u][side] = t >= 0 && t < a.L ? a.dens[t] : -1.f;
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * kW;
+            if (r >= found) break;
+            const int limit[2] = {(int)min((int64_t)a.max_half, (int64_t)c[u]), (int)min((int64_t)a.max_half, a.L - 1 - c[u])};
+            int n[2] = {0, 0};
+            bool open[2] = {limit[0] > 0, limit[1] > 0};
+            float d[2] = {ahead[u][0], ahead[u][1]};
+            while (open[0] || open[1]) {
+#pragma unroll
+                for (int side = 0; side < 2; ++side) {
+                    if (!open[side]) continue;
+                    const bool ok = (int64_t)n[side] + 1 + lane <= limit[side] && (double)d[side] >= thr[u];
+                    const unsigned long long m = __ballot(ok);
+                    const int run = m == ~0ull ? 64 : (int)__builtin_ctzll(~m);      // leading positions that pass
+                    n[side] += run;
+                    open[side] = run == 64 && n[side] < limit[side];
+                }
+#pragma unroll
+                for (int side = 0; side < 2; ++side) {
+                    const int64_t off = (int64_t)n[side] + 1 + lane;      // distance from the centre
+                    if (open[side] && off <= limit[side]) d[side] = a.dens[side == 0 ? c[u] - off : c[u] + off];
+                }
+            }
+            if (lane == 0) {
+                if (cen != a.center) { a.center[r] = c[u]; a.center_density[r] = cden[r]; }
+                a.span_lo[r] = c[u] - n[0];
+                a.span_hi[r] = c[u] + n[1];
+            }
         }
     }
     for (int r = found + tid; r < a.n_centers; r += kNmsThreads) {
@@ -282,50 +302,53 @@ __device__ __forceinline__ void nms_spans(const SelArgs& a, const int* cen, cons
     if (tid == 0) a.n_found[0] = found;
 }
 
-__global__ __launch_bounds__(kNmsThreads) void sel_nms_kernel(SelArgs a) {
+// The blocks' maxima and their places, P a thread, and with them the slots.
+template <int P>
+__device__ __forceinline__ void nms_fill(const SelArgs& a, const s3greedy::Slots<unsigned>& slots) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned key[P];
+    int at[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        const int b = (wave * P + q) * 64 + lane;
+        const unsigned long long v = b < a.nblk ? a.tkey[b] : 0ull;
+        key[q] = (unsigned)(v >> 32);
+        at[q] = (int)~(unsigned)v;
+    }
+    s3greedy::fill<unsigned, P>(slots, key, at, a.need, a.L, [&](int64_t t) { return a.dens[t]; },
+                                [](float d) { return d > 0.f ? __float_as_uint(d) : 0u; });
+}
+
+template <int P, int C>                       // maxima per thread, slots
+__global__ __launch_bounds__(s3greedy::kThreads) void sel_peaks_kernel(SelArgs a) {
+    extern __shared__ __align__(16) unsigned long long nms_lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const auto slots = s3greedy::slots_of<unsigned>(nms_lds, C);
+    unsigned* const list_key = (unsigned*)((char*)nms_lds + s3greedy::lds_bytes<unsigned>(C));
+    nms_fill<P>(a, slots);
+    const int found = s3greedy::rounds<C, unsigned>(slots, list_key, (int*)(list_key + a.room), (unsigned)a.L, (unsigned)a.radius, a.n_centers,
+                                                    [&](int r, unsigned k, int t) { a.center[r] = t; a.center_density[r] = __uint_as_float(k); });
+    __syncthreads();                          // the centres were written by this workgroup
+    nms_spans(a, a.center, a.center_density, found, tid, lane, wave);
+}
+
+template <int P, int R>                       // maxima per thread, slots per lane
+__global__ __launch_bounds__(s3greedy::kThreads) void sel_nms_kernel(SelArgs a) {
     extern __shared__ __align__(16) unsigned long long nms_lds[];
     __shared__ int found_s;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const NmsLds l = nms_lds_of(a, nms_lds);
-    for (int64_t i0 = tid; i0 < a.L; i0 += 8 * kNmsThreads) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = i0 + u * kNmsThreads < a.L ? a.dens[i0 + u * kNmsThreads] : 0.f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (i0 + u * kNmsThreads < a.L) l.cur[i0 + u * kNmsThreads] = v[u];
-    }
-    nms_load_keys(l, a.tkey, a.nblk, 1, wave, lane);
-    __syncthreads();
+    const auto slots = s3greedy::slots_of<unsigned>(nms_lds, 64 * R);
+    nms_fill<P>(a, slots);
     if (wave == 0) {
-        NmsTop<kShortGroups> w;
-        nms_start(w, l, lane);
-        int found = 0;
-        while (found < a.n_centers) {
-            const unsigned long long best = nms_best(w, lane);
-            if (best == 0) break;                                     // only positive density makes a centre
-            const int64_t c = (int64_t)(unsigned)~(unsigned)best;
-            if (lane == 0) { l.cen[found] = (int)c; l.cden[found] = __uint_as_float((unsigned)(best >> 32)); }
-            ++found;
-            const int64_t lo = max((int64_t)0, c - a.radius), hi = min(a.L - 1, c + a.radius);
-            const int tl = (int)(lo >> 6), th = (int)(hi >> 6);
-            for (int t = tl + 1 + lane; t < th; t += 64) l.key[t] = 0;
-            for (int64_t p = lo + lane; p <= hi; p += 64) l.cur[p] = 0.f;
-            s3_wave_fence();                                          // cleared tiles and wiped positions are read by other lanes
-            nms_open(w, l, tl, th, lane);
-            unsigned long long kl = 0, kh = 0;                        // best live position of the tile at either end
-            const int64_t p0 = ((int64_t)tl << 6) + lane, p1 = ((int64_t)th << 6) + lane;
-            if (p0 < a.L) kl = peak_key(l.cur[p0], p0);
-            if (p1 < a.L) kh = peak_key(l.cur[p1], p1);
-            kl = wave_max_key(kl);
-            kh = wave_max_key(kh);
-            nms_close(w, l, tl, th, kl, kh, lane);
-        }
+        const int found = s3greedy::walk<R, unsigned>(slots, (unsigned)a.L, (unsigned)a.radius, a.n_centers, [&](int r, unsigned k, int t) {
+            if (lane == 0) { a.center[r] = t; a.center_density[r] = __uint_as_float(k); }
+        });
         if (lane == 0) found_s = found;
     }
-    __syncthreads();
-    nms_spans(a, l.cen, l.cden, found_s, tid, lane, wave);
+    __syncthreads();                          // the centres were written by this workgroup
+    nms_spans(a, a.center, a.center_density, found_s, tid, lane, wave);
 }
 
 __device__ __forceinline__ unsigned long long lane_value(unsigned long long v, int src) {
@@ -676,8 +699,13 @@ extern "C" int s3_select_spans(const float* scores, int64_t n_positions, const f
     a.tkey = (unsigned long long*)(base + l.tkey);
     a.ckey = (unsigned long long*)(base + l.ckey);
     a.nblk = l.nblk;
-    // Tiles of one block as long as their maxima fit the search's LDS beside the centres; from there on no more tiles than it
-    // takes, since loading them costs more than searching longer ones (2^21 positions, one centre: 24 us with
+    const int64_t most_found = s3greedy::choices(n_positions, nms_radius, n_centers), need = s3greedy::slots_needed(n_positions, nms_radius, most_found);
+    const bool slots = most_found > kNmsFew && need <= kNmsSlots && l.nblk <= 16 * kNmsThreads;
+    const s3greedy::Way sw = s3greedy::way_of(need, nms_radius);
+    a.need = (int)(slots ? need : 0);
+    a.room = sw.room;
+    // sel_nms_long_kernel: tiles of one block as long as their maxima fit the search's LDS beside the centres; from there on no
+    // more tiles than it takes, since loading them costs more than searching longer ones (2^21 positions, one centre: 24 us with
     // 16384 tiles, 20 with 8192)
     size_t nt, fixed;
     for (a.shift = 0;; ++a.shift) {
@@ -686,10 +714,9 @@ extern "C" int s3_select_spans(const float* scores, int64_t n_positions, const f
         if (nt <= kNmsTilesMin || (a.shift == 0 && nt <= kNmsTiles && fixed <= kNmsLds)) break;
     }
     // the convolution leaves one key per tile of the search, as far as a workgroup's positions reach
-    a.kshift = a.shift < kConvKeyShift ? a.shift : kConvKeyShift;
+    a.kshift = slots ? 0 : (a.shift < kConvKeyShift ? a.shift : kConvKeyShift);
     a.nckey = a.kshift ? (l.nblk + (1 << a.kshift) - 1) >> a.kshift : 0;
-    const bool cached = fixed + (size_t)n_positions * 4 <= kNmsLds;                  // about 36000 positions (shift is 0)
-    a.dead = cached ? nullptr : (unsigned long long*)(base + l.dead);
+    a.dead = slots ? nullptr : (unsigned long long*)(base + l.dead);
     a.center = center; a.center_density = center_density; a.span_lo = span_lo; a.span_hi = span_hi; a.n_found = n_found;
     hipStream_t st = (hipStream_t)stream;
     const bool large = n_positions >= kConvLargeFrom;
@@ -698,15 +725,31 @@ extern "C" int s3_select_spans(const float* scores, int64_t n_positions, const f
     const dim3 grid((unsigned)((n_positions + per_wg - 1) / per_wg));
     if (large) hipLaunchKernelGGL(sel_conv_kernel<kConvLarge>, grid, dim3(kConvLarge), lds, st, a);
     else hipLaunchKernelGGL(sel_conv_kernel<kConvSmall>, grid, dim3(kConvSmall), lds, st, a);
-    // us a round, radius 48: 1.2 in tiles of one block (two or four groups per lane), 1.5 of two blocks, 2.0 of four
-    // searched whole and 1.7 to 1.8 by their keys
-    static S3LdsOnce once[5];
-    void (*const ways[5])(SelArgs) = {sel_nms_kernel, sel_nms_long_kernel<1, 2>, sel_nms_long_kernel<1, 4>, sel_nms_long_kernel<2, 2>,
-                                      sel_nms_long_kernel<0, 2>};
-    const int way = cached ? 0 : (a.shift == 0 ? (nt <= kNmsTilesMin ? 1 : 2) : (a.shift == 1 ? 3 : 4));
-    const auto nms = ways[way];
-    if (int rc = s3_allow_lds(once[way], (const void*)nms, kNmsLds)) return rc;
-    hipLaunchKernelGGL(nms, dim3(1), dim3(kNmsThreads), fixed + (cached ? (size_t)n_positions * 4 : 0), st, a);
+    void (*nms)(SelArgs);
+    int way, bytes, most;
+    if (slots) {
+        static void (*const ways[16])(SelArgs) = {
+            sel_peaks_kernel<1, 64>, sel_peaks_kernel<1, 128>, sel_peaks_kernel<1, 256>, sel_peaks_kernel<1, 512>,
+            sel_peaks_kernel<16, 64>, sel_peaks_kernel<16, 128>, sel_peaks_kernel<16, 256>, sel_peaks_kernel<16, 512>,
+            sel_nms_kernel<1, 1>, sel_nms_kernel<1, 2>, sel_nms_kernel<1, 4>, sel_nms_kernel<1, 9>,
+            sel_nms_kernel<16, 1>, sel_nms_kernel<16, 2>, sel_nms_kernel<16, 4>, sel_nms_kernel<16, 9>};
+        way = (sw.rounds ? 0 : 8) + (l.nblk <= kNmsThreads ? 0 : 4) + sw.up;
+        nms = ways[way];
+        bytes = s3greedy::lds_bytes<unsigned>(sw.cap) + (sw.rounds ? sw.room * 8 : 0);
+        most = s3greedy::lds_bytes<unsigned>(sw.cap) + (sw.rounds ? s3greedy::kListMax * 8 : 0);
+    } else {
+        // us a round, radius 48: 1.2 in tiles of one block (two or four groups per lane), 1.5 of two blocks, 2.0 of four
+        // searched whole and 1.7 to 1.8 by their keys
+        static void (*const ways[4])(SelArgs) = {sel_nms_long_kernel<1, 2>, sel_nms_long_kernel<1, 4>, sel_nms_long_kernel<2, 2>, sel_nms_long_kernel<0, 2>};
+        const int w = a.shift == 0 ? (nt <= kNmsTilesMin ? 0 : 1) : (a.shift == 1 ? 2 : 3);
+        way = 16 + w;
+        nms = ways[w];
+        most = kNmsLds;
+        bytes = (int)fixed;
+    }
+    static S3LdsOnce once[20];
+    if (int rc = s3_allow_lds(once[way], (const void*)nms, most)) return rc;
+    hipLaunchKernelGGL(nms, dim3(1), dim3(kNmsThreads), (size_t)bytes, st, a);
     S3_HIP(hipGetLastError());
     return S3_OK;
 }

@@ -1,0 +1,71 @@
+"""The greedy searches that bring the blocks their choices can lie in into LDS: numbers of blocks and of slots around the sizes
+at which another build or another kernel takes over, and more equal block maxima than there are slots."""
+import numpy as np
+import pytest
+
+from oracle import s3_oracle as orc
+from tests.test_gpu_index_score import check_score, gpu_index, oracle_score, run_gpu_score
+from tests.test_gpu_select import oracle_select
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,span_len,top_b,nms", [
+    (2 * 64 + 31, 32, 4, True),              # three blocks, all in slots
+    (64 * 64 + 7, 8, 65, False),             # 65 slots asked for of 64 blocks
+    (128 * 64 + 65, 66, 43, True),           # 127 of 128 blocks: two slots per lane
+    (20_000, 64, 86, True),                  # 256 of 312 blocks, the most that LDS holds
+    (20_000, 64, 87, True),                  # 259: maxima in registers, windows in memory
+    (20_000, 300, 60, True),
+    (65_536 + 63, 64, 16, True),             # 1024 maxima, one per thread; one more below
+    (65_536 + 64, 64, 16, True),
+    ((1 << 18) + 63, 64, 40, True),          # four per thread; sixteen below
+    ((1 << 18) + 64, 64, 80, True),
+    ((1 << 20) + 63, 64, 30, True),          # the most maxima
+])
+def test_spans_around_the_numbers_of_slots(T, span_len, top_b, nms):
+    rng = np.random.default_rng(T + top_b)
+    n = min(T, 20_000)
+    at = np.sort(rng.permutation(T)[:n])
+    ids = np.zeros((1, T, 1), np.int32)
+    ids[0, at, 0] = 1 + rng.permutation(n)
+    qids = (1 + np.arange(n, dtype=np.int32))[None, :, None].copy()
+    qvals = (rng.random((1, n, 1)) + 0.01).astype(np.float32)
+    ix = gpu_index(ids, n + 1)
+    S, W, st_o, sc_o = oracle_score(ids, qids, qvals, n + 1, T, span_len, top_b, 0, nms)
+    out = run_gpu_score(ix, qids, qvals, T, span_len, top_b, 0, nms)
+    check_score(out, S, W, st_o, sc_o, span_len, nms)
+    assert out[0][:out[2]].tolist() == list(st_o)
+
+
+@pytest.mark.parametrize("T,span_len,top_b", [(20_000, 40, 12), (70_000, 64, 30)])
+def test_equal_spans_are_taken_from_the_front(T, span_len, top_b):
+    """One feature in every position: all windows are equal, and there are more equal block maxima than slots."""
+    ids = np.zeros((1, T, 1), np.int32)
+    ix = gpu_index(ids, 2)
+    st, _, nf, _ = run_gpu_score(ix, np.zeros((1, 1, 1), np.int32), np.ones((1, 1, 1), np.float32), T, span_len, top_b, 0, True)
+    assert nf == top_b and st.tolist() == [i * span_len for i in range(top_b)]
+
+
+@pytest.mark.parametrize("L,radius,n_centers,levels", [
+    (36_864, 64, 40, 3), (36_865, 64, 40, 3),      # 576 blocks, all in slots; one more
+    (40_000, 64, 192, 2), (40_000, 64, 193, 2),    # 574 and 577 slots asked for
+    (50_000, 33, 22, 0),                           # 64 slots, all densities equal
+    (65_536, 1, 100, 2), (65_537, 1, 100, 2),      # 1024 maxima, one per thread; one more
+    (70_000, 0, 64, 1), (70_000, 0, 65, 1),        # no suppression beyond the centre: 64 and 65 slots
+    (1 << 20, 64, 130, 4), ((1 << 20) + 1, 64, 130, 4),      # sixteen per thread; tiles of two blocks
+])
+def test_peaks_around_the_numbers_of_slots(L, radius, n_centers, levels):
+    """Few distinct densities, so that block maxima tie; `levels` 0: one."""
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(L + n_centers)
+    S = rng.integers(0, levels + 1, L).astype(np.float32) if levels else np.ones(L, np.float32)
+    g = s3.smoothing_kernel(s3.KERNEL_BOX, 1)
+    c, dc, lo, hi, nf, D = s3.select_spans(torch.from_numpy(S).cuda(), g, n_centers, radius, 0.5, 70, want_density=True)
+    torch.cuda.synchronize()
+    D32, c_o, pk_o, lo_o, hi_o = oracle_select(S, g.cpu().numpy(), n_centers, radius, 0.5, 70)
+    n = int(nf.item())
+    assert np.array_equal(D.cpu().numpy(), D32) and n == len(c_o)
+    assert np.array_equal(c.cpu().numpy()[:n], c_o) and np.array_equal(dc.cpu().numpy()[:n], pk_o.astype(np.float32))
+    assert np.array_equal(lo.cpu().numpy()[:n], lo_o) and np.array_equal(hi.cpu().numpy()[:n], hi_o)
