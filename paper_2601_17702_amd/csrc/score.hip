@@ -51,14 +51,16 @@ struct ScoreArgs {
     ActiveList* act;                 // [n_heads * n_feat] lists with a non-zero weight, packed per (head, range)
     int* nact;                       // [n_heads * nr] their number
     unsigned long long* sfix;        // [L]
-    unsigned long long* part;        // [ngroup][L] partial sums of head groups (ngroup > 1)
-    int pb, npb, heads_per, ngroup, sorted;   // position blocks / head groups of the gather
+    unsigned long long* part;        // [ngroup][L] partial sums of the gather's groups (ngroup > 1)
+    int pb, npb, heads_per, parts, ngroup, sorted;   // the gather: position blocks, heads of a group, parts of these, groups in all
+    int batch;                       // lists that a wavefront takes at a time
     long long* wfix;                 // [nW]
     unsigned long long* tmaxv;       // [nsub] best window of every 2^sublog starts: its sum + 1, 0 for none
     int* tmaxi;                      // [nsub] its start
     int sublog;                      // 6 where the search brings blocks into LDS, else kSubLog2
     int need, room;                  // blocks that it brings there at least, entries of its list of choices
-    int ntile, nsub, topshift;       // tiles of kTileW starts; sc_topb_long_kernel works on tiles of kSubW << topshift
+    int ntile, nsub, topshift;       // tiles of tile starts; sc_topb_long_kernel works on tiles of kSubW << topshift
+    int tile;                        // windows per workgroup of the pooling kernel
     float* scores_out;
     int32_t* span_start;
     float* span_score;
@@ -114,7 +116,14 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_kernel(ScoreArgs a) {
     const float* qv = a.qvals + (size_t)h * per_head;
     const int32_t* qi = a.qids + (size_t)h * per_head;
     unsigned int m = 0;
-    for (size_t i = tid; i < per_head; i += kPrepThreads) m = max(m, __float_as_uint(fmaxf(qv[i], 0.f)));
+    constexpr int kU = 8;            // loads in flight per thread (32768 pairs a head, 32 heads: 40 us with one)
+    for (size_t i0 = tid; i0 < per_head; i0 += kU * kPrepThreads) {
+        float v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) v[u] = qv[min(i0 + u * kPrepThreads, per_head - 1)];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) m = max(m, __float_as_uint(fmaxf(v[u], 0.f)));
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned int)__shfl_xor((int)m, o));
     if (lane == 0) amax[wave] = m;
@@ -129,10 +138,18 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_kernel(ScoreArgs a) {
         eq = 40 - e;
     }
     const double scale = ldexp(1.0, eq), inv = ldexp(1.0, -eq);
-    for (size_t i = tid; i < per_head; i += kPrepThreads) {
-        const float v = fmaxf(qv[i], 0.f);
-        const unsigned int f = (unsigned int)(qi[i] - f0);
-        if (v > 0.f && f < (unsigned int)nf) atomicAdd(&tbl[f], (unsigned long long)llrint((double)v * scale));
+    for (size_t i0 = tid; i0 < per_head; i0 += kU * kPrepThreads) {
+        float v[kU];
+        int f[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const size_t i = min(i0 + u * kPrepThreads, per_head - 1);
+            v[u] = i0 + u * kPrepThreads < per_head ? qv[i] : 0.f;
+            f[u] = qi[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            if (v[u] > 0.f && (unsigned)(f[u] - f0) < (unsigned)nf) atomicAdd(&tbl[f[u] - f0], (unsigned long long)llrint((double)v[u] * scale));
     }
     __syncthreads();
     constexpr int kPer = kRange / kPrepThreads;
@@ -172,20 +189,101 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_kernel(ScoreArgs a) {
     }
 }
 
+// The same for queries of few pairs (at most kPrepThreads a head): a thread has a pair, a table of 2048 places in LDS finds those that
+// name the same feature, and the thread that came first to a feature's place carries its list on, whose length it asked
+// for beside the look for the largest activation.  All lists of a head go to its first range.  A table of all features
+// took 12.4 us for 128 pairs in each of 256 heads (clearing it and looking through it, and one latency after the other), this 5.
+constexpr int kHash = 2 * kPrepThreads;
+__global__ __launch_bounds__(kPrepThreads) void sc_prep_few_kernel(ScoreArgs a) {
+    __shared__ int name[kHash];
+    __shared__ unsigned long long sum[kHash];
+    __shared__ unsigned int amax[kPrepThreads / 64];
+    __shared__ unsigned long long wmx[kPrepThreads / 64];
+    __shared__ int wsum[kPrepThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int h = blockIdx.x;
+    const int per_head = a.nq * a.k;
+    float v = 0.f;
+    int f = 0;
+    if (tid < per_head) {
+        v = fmaxf(a.qvals[(size_t)h * per_head + tid], 0.f);
+        f = a.qids[(size_t)h * per_head + tid];
+    }
+    for (int i = tid; i < kHash; i += kPrepThreads) { name[i] = -1; sum[i] = 0ull; }
+    const bool mine = v > 0.f && (unsigned)f < (unsigned)a.n_feat;
+    int freq = 0;
+    if (mine) {
+        if (a.cfreq) {
+            freq = a.cfreq[(size_t)h * a.n_feat + f];
+        } else {
+            const int32_t* off = a.offsets + (size_t)h * a.off_stride + f;
+            freq = off[1] - off[0];
+        }
+    }
+    const unsigned most = s3_wave_max_u32(__float_as_uint(v));
+    if (lane == 0) amax[wave] = most;
+    __syncthreads();
+    const unsigned m = s3_wave_max_u32(amax[lane & (kPrepThreads / 64 - 1)]);
+    int eq = 0;                      // activations are scaled by 2^eq: each below 2^40, a sum of 2^20 of them below 2^60
+    if (m) {
+        int e;
+        frexpf(__uint_as_float(m), &e);
+        eq = 40 - e;
+    }
+    int place = -1;                  // of the feature, in the thread that came first
+    if (mine) {
+        int i = (int)(((unsigned)f * 2654435761u) >> 21);                 // 0 .. kHash - 1
+        for (;;) {                   // at most half of the places are taken
+            const int was = atomicCAS(&name[i], -1, f);
+            if (was == -1) place = i;
+            if (was == -1 || was == f) break;
+            i = (i + 1) & (kHash - 1);
+        }
+        atomicAdd(&sum[i], (unsigned long long)llrint((double)v * ldexp(1.0, eq)));
+    }
+    __syncthreads();
+    double w = 0.0;
+    if (place >= 0) {
+        const unsigned long long sacc = sum[place];
+        if (sacc && freq > 0 && !(a.max_freq > 0 && freq > a.max_freq))
+            w = (double)sacc * ldexp(1.0, -eq) / ((double)logf(1.0f + (float)freq) + 1.0);
+    }
+    int tot;
+    const int slot = s3_block_excl_scan<kPrepThreads>(w > 0.0 ? 1 : 0, wsum, tot);
+    if (w > 0.0) a.act[(size_t)h * a.n_feat + slot] = ActiveList{w, f, 0};
+    const unsigned long long mb = wave_max_u64((unsigned long long)__double_as_longlong(w));
+    if (lane == 0) wmx[wave] = mb;
+    __syncthreads();
+    for (int r = tid; r < a.nr; r += kPrepThreads) {
+        unsigned long long best = 0;
+        for (int q = 0; q < kPrepThreads / 64; ++q) best = wmx[q] > best ? wmx[q] : best;
+        a.wmax[h * a.nr + r] = r ? 0ull : best;
+        a.nact[h * a.nr + r] = r ? 0 : tot;
+    }
+}
+
 // Postings gather with the scores of one block of positions held in LDS.
-// Workgroup (b, g) owns positions [b * pb, (b + 1) * pb) and the heads of group g: it walks every posting list
-// of those heads that has a non-zero weight and adds the postings that fall into its block with LDS atomics
-// (64-bit fixed point, so the order of the additions does not matter), then stores the block: into S when there
-// is one head group, else into that group's partial array (summed by sc_reduce_kernel).  No global atomics.
-// A wavefront takes 64 lists at a time: lane l fetches weight and feature of list l and the part of the list that
-// lies in the block (its segment) -- from the index's block table when there is one; else, for lists sorted by
-// position, by a search; else the whole list, every posting filtered.  Postings are read as aligned 16-byte vectors
-// (what a wavefront keeps in flight bounds the rate: the gather is latency-bound).  Segments of more than 2 G
-// vectors are walked one at a time by the whole wavefront, the others G lanes per segment (64 / G segments per load
-// instruction); G is picked on the host from the mean segment length.
+// Workgroup (b, g) owns positions [b * pb, (b + 1) * pb) and the lists of group g: of some heads, or, where there are fewer heads than
+// the chip wants workgroups, a part of the lists of one head.  (All heads' lists dealt to all
+// groups: the workgroups meet more pages, 156 us instead of 116 for 64 heads of 65536 positions, compact.)  The workgroup adds the
+// postings of its lists that fall into its block with LDS atomics (64-bit fixed point, so the order of the additions does not matter), then stores the block: into S when
+// there is one group, else into that group's partial array, which the pooling kernel sums.  (Additions to one array per XCD, in its
+// L2, instead: the pooling kernel has 8 arrays to sum instead of 128, 12 -> 5 us, but a workgroup's 16384 additions take 6 to 8 us.)
+// A wavefront takes a batch of up to 64 lists at a time (a counter in LDS deals them out): lane l fetches weight and feature of list l and the
+// part of the list that lies in the block (its segment) -- from the index's block table when there is one; else, for lists sorted by
+// position, by a search; else the whole list, every posting filtered.  Postings are read as aligned vectors of four; the vectors
+// of all the batch's segments are numbered through, and lane l of load u takes vector 64 u + l, whichever segment it belongs to: what a
+// wavefront keeps in flight bounds the rate, and this way every load is full whatever the lengths are.  Very long segments
+// (hot features) are left to the end, when all wavefronts share them.
+// us for the kernel, one segment a wavefront or some lanes at a time and heads alone as groups / now: 256 queries of k 128 in 32 heads
+// of 14001 positions 426 / 80 (0.7 TB/s of postings, 2.9), 896 of k 64 in 112 of 16384 355 / 117, 256 of k 32 in 64 of 16384, skewed, 116 / 67;
+// in 64 of 65536, compact, skewed, 116 / 111; 4 in 256 heads of 32768 39.5 / 39 (address translation: 256 lists a workgroup, each in
+// pages of its own).
 constexpr int kScatterThreads = 1024;
-constexpr int kLong = 4;             // vector loads per lane in flight while a long segment is walked by the whole wavefront
-constexpr int kShortSlots = 4;       // vector loads per lane in flight while short segments are walked by lane groups
+constexpr int kFlight = 4;           // vector loads per lane in flight
+constexpr int kHotVec = 512;         // vectors of a segment that is left to all wavefronts
+constexpr int kHotMax = 64;          // as many of them at most; further ones are one wavefront's work
+constexpr int kPairs = 512;          // (head, range) pairs looked at together: 64 times 8
 constexpr int kNarrowMin = 128;      // sorted lists longer than this are narrowed to the position block by search
 constexpr int kMaxPB = 1 << kS3PosBlockLog2;
 
@@ -223,58 +321,142 @@ __device__ __forceinline__ unsigned vec_posting(const uint2& v, int j) {
     return (w[j >> 1] >> ((j & 1) * 16)) & 0xFFFFu;
 }
 
-template <int G, bool CMP>
-__global__ __launch_bounds__(kScatterThreads) void sc_scatter_lds_kernel(ScoreArgs a) {
-    extern __shared__ unsigned long long sblk[];
-    __shared__ unsigned long long wmx[kScatterThreads / 64];
-    __shared__ int4 recs_all[kScatterThreads];           // per wavefront: (begin, length, weight) of the batch's segments
+// A segment as the lanes that read it see it: element e of the head's array, counted from the vector boundary at or before its
+// first posting, belongs to it if first <= e < end; vector v of the batch is vector `shift` + v of the array.
+struct Segment {
+    int shift;
+    unsigned first, end;
+    int pad;                         // 16 bytes: read in one piece
+};
+
+// Where position p of the block lies in LDS: lanes that add four positions apart (vectors of a dense list) meet all banks.
+__device__ __forceinline__ unsigned spread(unsigned p) { return p ^ ((p >> 5) & 3u); }
+
+template <bool CMP>
+__global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a) {
+    using Posting = typename std::conditional<CMP, uint16_t, int32_t>::type;
+    using Vec = typename std::conditional<CMP, uint2, uint4>::type;        // four postings
+    constexpr int kW = kScatterThreads / 64;
+    extern __shared__ __align__(16) unsigned long long sblk[];
+    __shared__ unsigned long long wmx[kW];
+    __shared__ Segment seg_all[kScatterThreads];
+    __shared__ unsigned long long weight_all[kScatterThreads];
+    __shared__ __align__(16) unsigned starts_all[kW][2 * kFlight];
+    __shared__ Segment hot[kHotMax];
+    __shared__ unsigned long long hot_weight[kHotMax];
+    __shared__ int hot_head[kHotMax], next_s, n_hot, wsum[kW];
+    __shared__ int upto[kPairs];                                           // batches of the (head, range) pairs up to this one
+    __shared__ uint16_t lists[kPairs];                                     // and their lists
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int4* const recs = recs_all + wave * 64;
-    const int blk = blockIdx.x;
+    Segment* const seg = seg_all + wave * 64;
+    unsigned long long* const weight = weight_all + wave * 64;
+    unsigned* const starts = starts_all[wave];
+    int unit, blk;                                                // the position blocks of a group share an XCD
+    s3_block_to_tile(blockIdx.x, a.ngroup, a.npb, unit, blk);
+    const int group = unit / a.parts, part = unit - group * a.parts;
     const int64_t p0 = (int64_t)blk * a.pb;
     const int64_t p1 = p0 + a.pb < a.L ? p0 + a.pb : a.L;
     const unsigned span = (unsigned)(p1 - p0);
-    for (int i = tid; i < a.pb; i += kScatterThreads) sblk[i] = 0ull;
+    const unsigned pbase = CMP ? 0u : (unsigned)p0;               // what a stored posting is relative to
+    const bool cmp_empty = CMP && blk >= a.nblk;                  // the compact index holds nothing beyond its blocks
+    for (int i = tid; i < a.pb / 2; i += kScatterThreads) ((uint4*)sblk)[i] = make_uint4(0, 0, 0, 0);      // pb is a multiple of 64
+    if (tid == 0) n_hot = 0;
     // the largest weight over all heads fixes the fixed-point scale (every workgroup derives the same one)
     unsigned long long mb = 0;
     for (int i = tid; i < a.n_heads * a.nr; i += kScatterThreads) mb = a.wmax[i] > mb ? a.wmax[i] : mb;
     mb = wave_max_u64(mb);
     if (lane == 0) wmx[wave] = mb;
-    __syncthreads();
-    mb = 0;
-#pragma unroll
-    for (int q = 0; q < kScatterThreads / 64; ++q) mb = wmx[q] > mb ? wmx[q] : mb;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) a.wmax[a.n_heads * a.nr] = mb;      // for the kernels that follow
-    const double scale = ldexp(1.0, exp_s(mb, a.hb));
     const int nbk = a.nblk - 1;
-    const int h0 = blockIdx.y * a.heads_per, h1 = min(a.n_heads, h0 + a.heads_per);
-    for (int hr = h0 * a.nr; hr < h1 * a.nr; ++hr) {
-        const int h = hr / a.nr, r = hr - h * a.nr;
-        // compact index: 16-bit offsets from the block's start, the block's segments one after the other
-        using Posting = typename std::conditional<CMP, uint16_t, int32_t>::type;
+    const int pair1 = min(a.n_heads, (group + 1) * a.heads_per) * a.nr;
+    __syncthreads();
+    mb = wmx[lane & (kW - 1)];
+    mb = wave_max_u64(mb);
+    if (blockIdx.x == 0 && tid == 0) a.wmax[a.n_heads * a.nr] = mb;      // for the kernels that follow
+    const double scale = ldexp(1.0, exp_s(mb, a.hb));
+
+    // The postings of the head's array from its first 16-byte (plain) or 8-byte (compact) boundary on.
+    const auto array_of = [&](int h, int& skew) {
         const Posting* pos = CMP ? (const Posting*)(a.delta + (size_t)h * a.delta_stride)
                                  : (const Posting*)(a.positions + (size_t)h * a.pos_stride);
-        const int32_t* off = CMP ? a.cstart + (size_t)h * a.cstart_stride + (size_t)blk * a.n_feat
-                                 : a.offsets + (size_t)h * a.off_stride;
-        const int32_t* tab = !CMP && a.btab ? a.btab + (size_t)h * a.n_feat * nbk : nullptr;
-        const unsigned pbase = CMP ? 0u : (unsigned)p0;           // what a stored posting is relative to
-        const bool cmp_empty = CMP && blk >= a.nblk;              // the compact index holds nothing beyond its blocks
-        const ActiveList* act = a.act + (size_t)h * a.n_feat + (size_t)r * kRange;
-        const int n_act = a.nact[hr];
-        // A batch of lists per wavefront: 64 where there are enough, else an equal share (the few lists of a decoding step, 128 a
-        // head, were two wavefronts' work while fourteen waited).
-        constexpr int kW = kScatterThreads / 64;
-        const int share = min((n_act + kW - 1) / kW, 64), step = kW * share;
-        const bool mine = lane < share;
-        uint4 raw_next = make_uint4(0, 0, 0, 0);
-        if (mine && wave * share + lane < n_act) raw_next = *reinterpret_cast<const uint4*>(act + wave * share + lane);
-        for (int i0 = wave * share; i0 < n_act; i0 += step) {
+        skew = (int)(((uintptr_t)pos & (sizeof(Vec) - 1)) / sizeof(Posting));
+        return (const Vec*)(pos - skew);
+    };
+    // Adds w at the vector's postings that belong to the segment (`whole`: all do, in all lanes) and lie in the block.  Compact
+    // postings are handled two in a register; what does not belong goes to a place of the lane's own behind the block.
+    const unsigned pb = (unsigned)a.pb, nowhere = pb + lane;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned long long*)sblk;
+    const auto add = [&](const Vec& v, bool whole, unsigned e0, unsigned first, unsigned end, unsigned long long w) {
+        if constexpr (CMP) {                                      // two postings in a register: 16-bit operations on both
+            typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+            unsigned q[2] = {v.x, v.y};
+            if (!whole) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const unsigned e = e0 + 2 * j;
+                    const unsigned keep = (e >= first && e < end ? 0xFFFFu : 0u) | (e + 1 >= first && e + 1 < end ? 0xFFFF0000u : 0u);
+                    q[j] = (q[j] & keep) | (nowhere * 0x10001u & ~keep);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const u16x2 most = {(unsigned short)(pb + 63), (unsigned short)(pb + 63)};
+                const unsigned p = __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(u16x2, q[j]), most));
+                const unsigned at = p ^ (p >> 5 & 0x00030003u);   // spread() of both
+                unsigned a0, a1;                                  // 8 times either half and the block's place in LDS
+                asm("v_mad_u32_u16 %0, %1, 8, %2 op_sel:[0,0,0,0]" : "=v"(a0) : "v"(at), "v"(lds0));
+                asm("v_mad_u32_u16 %0, %1, 8, %2 op_sel:[1,0,0,0]" : "=v"(a1) : "v"(at), "v"(lds0));
+                typedef __attribute__((address_space(3))) unsigned long long lds_u64;
+                __hip_atomic_fetch_add((lds_u64*)(uintptr_t)a0, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add((lds_u64*)(uintptr_t)a1, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const unsigned rr = vec_posting(v, j) - pbase;
+                if ((whole || (e0 + j >= first && e0 + j < end)) && rr < span) atomicAdd(&sblk[spread(rr)], w);
+            }
+        }
+    };
+    for (int pair0 = group * a.heads_per * a.nr; pair0 < pair1; pair0 += kPairs) {
+        const int n_mine = tid < kPairs && pair0 + tid < pair1 ? a.nact[pair0 + tid] : 0, nb = (n_mine + a.batch - 1) / a.batch;
+        int batches;
+        const int before = s3_block_excl_scan<kScatterThreads>(nb, wsum, batches);
+        const int batch0 = (int)((int64_t)batches * part / a.parts), batch1 = (int)((int64_t)batches * (part + 1) / a.parts);      // this part's
+        if (tid < kPairs) {
+            upto[tid] = before + nb;
+            lists[tid] = (uint16_t)n_mine;
+        }
+        if (tid == 0) next_s = 0;
+        __syncthreads();
+        int h, n_list;                                            // the batch that was asked for last
+        uint4 raw = make_uint4(0, 0, 0, 0);
+        const auto ask = [&]() {                                  // next batch: its weights and features are on their way afterwards
+            int c = 0;
+            if (lane == 0) c = atomicAdd(&next_s, 1);
+            c = __builtin_amdgcn_readfirstlane(c) + batch0;
+            n_list = 0;
+            if (c >= batch1) return;
+            // the pair that batch c belongs to: the eight that it is among, then the one
+            const int x = upto[lane * 8 + 7], j = (int)__popcll(__ballot(x <= c));
+            const int y = upto[j * 8 + (lane & 7)], q = (int)__popcll(__ballot(y <= c) & 0xFFull);
+            const int pair = j * 8 + q, hr = pair0 + pair, r = hr % a.nr;
+            h = hr / a.nr;
+            const int at = (c - (q ? __builtin_amdgcn_readlane(y, max(q - 1, 0)) : (j ? __builtin_amdgcn_readlane(x, max(j - 1, 0)) : 0))) * a.batch;
+            n_list = min(a.batch, (int)lists[pair] - at);
+            if (lane < n_list) raw = *reinterpret_cast<const uint4*>(a.act + (size_t)h * a.n_feat + (size_t)r * kRange + at + lane);
+        };
+        ask();
+        while (n_list > 0) {
+            const int32_t* off = CMP ? a.cstart + (size_t)h * a.cstart_stride + (size_t)blk * a.n_feat
+                                     : a.offsets + (size_t)h * a.off_stride;
+            const int32_t* tab = !CMP && a.btab ? a.btab + (size_t)h * a.n_feat * nbk : nullptr;
+            const int head = h;
+            int skew;
+            const Vec* const pos = array_of(h, skew);
             unsigned long long wf = 0;
             int b = 0, e = 0;
-            const uint4 raw = raw_next;                      // weight and feature in one load, fetched one batch ahead
-            if (mine && i0 + step + lane < n_act) raw_next = *reinterpret_cast<const uint4*>(act + i0 + step + lane);
-            if (mine && i0 + lane < n_act) {
+            if (lane < n_list) {
                 const double lw = __longlong_as_double((long long)(((unsigned long long)raw.y << 32) | raw.x));
                 wf = (unsigned long long)llrint(lw * scale);
                 if (wf) {
@@ -304,99 +486,94 @@ __global__ __launch_bounds__(kScatterThreads) void sc_scatter_lds_kernel(ScoreAr
                     }
                 }
             }
-            // this batch's segments (the part of each list that lies in the block) go to the wavefront's records
-            const int n = wf ? max(e - b, 0) : 0;
-            recs[lane] = make_int4(b, n, (int)(unsigned)wf, (int)(unsigned)(wf >> 32));
-            // Every load is an aligned vector of four postings (16 bytes of int32, 8 bytes of uint16: as many loads in
-            // flight per posting either way, half the bytes for the compact index): a segment is read from the vector
-            // boundary at or before its first posting, and the elements in front of it and behind its end are masked
-            // out (they lie in the same vector as a posting of the array, hence inside the array's allocation).
-            constexpr int EPV = 4;
-            constexpr int VB = EPV * (int)sizeof(Posting);
-            using Vec = typename std::conditional<sizeof(Posting) == 4, uint4, uint2>::type;
-            const int nv = n ? (int)(((((uintptr_t)(pos + b)) & (VB - 1)) / sizeof(Posting) + n + EPV - 1) / EPV) : 0;
-            // long segments (more than 2 G vectors): one at a time, the whole wavefront, kLong vectors in flight per lane
-            unsigned long long ml = __ballot(nv > 2 * G);
-            while (ml) {
-                const int src = (int)__builtin_ctzll(ml);
-                ml &= ml - 1;
-                const int sb = __builtin_amdgcn_readlane(b, src), sn = __builtin_amdgcn_readlane(n, src);
-                const unsigned long long w = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(wf >> 32), src) << 32) |
-                                             (unsigned)__builtin_amdgcn_readlane((int)(unsigned)wf, src);
-                const uintptr_t addr = (uintptr_t)(pos + sb);                       // uniform
-                const int shift = (int)((addr & (VB - 1)) / sizeof(Posting));
-                const Vec* vp = (const Vec*)(addr & ~(uintptr_t)(VB - 1));
-                const int total = shift + sn, nvec = (total + EPV - 1) / EPV;
-                for (int v0 = 0; v0 < nvec; v0 += 64 * kLong) {
-                    Vec raw[kLong];
-#pragma unroll
-                    for (int u = 0; u < kLong; ++u) {
-                        const int vi = v0 + u * 64 + lane;
-                        raw[u] = vi < nvec ? vp[vi] : Vec{};
-                    }
-#pragma unroll
-                    for (int u = 0; u < kLong; ++u) {
-                        const int el0 = (v0 + u * 64 + lane) * EPV;
-#pragma unroll
-                        for (int j = 0; j < EPV; ++j) {
-                            const unsigned rr = vec_posting(raw[u], j) - pbase;
-                            if (el0 + j >= shift && el0 + j < total && rr < span) atomicAdd(&sblk[rr], w);
-                        }
-                    }
+            ask();
+            const unsigned n = wf ? (unsigned)max(e - b, 0) : 0u, first = (unsigned)b + (unsigned)skew, end = first + n;
+            int nv = n ? (int)(((end + 3) >> 2) - (first >> 2)) : 0;
+            if (nv > kHotVec) {
+                const int q = atomicAdd(&n_hot, 1);
+                if (q < kHotMax) {
+                    hot[q] = Segment{0, first, end, 0};
+                    hot_weight[q] = wf;
+                    hot_head[q] = head;
+                    nv = 0;
                 }
             }
-            // short segments: G lanes per segment (one vector each, two rounds if needed), 64 / G segments per load
-            // instruction, kShortSlots load instructions in flight
-            constexpr int LPS = 64 / G;
-            const int grp = lane / G, sub = lane % G;
-            unsigned long long ms = __ballot(nv > 0 && nv <= 2 * G);
-            while (ms) {
-                int4 rc[kShortSlots];
-                bool two = false;
+            const int vincl = s3_wave_incl_scan(nv), v_at = vincl - nv, total = __builtin_amdgcn_readlane(vincl, 63);
+            const unsigned long long some = __ballot(nv > 0);
+            s3_wave_fence();                                      // the batch before has read its segments
+            if (nv > 0) {
+                const int at = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(some >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)some, 0u));
+                seg[at] = Segment{(int)(first >> 2) - v_at, first, end, 0};
+                weight[at] = wf;
+            }
+            for (int v0 = 0; v0 < total; v0 += 64 * kFlight) {
+                // a bit for every vector of these 64 kFlight at which a segment starts; owner: starts at or before the vector
+                s3_wave_fence();
+                if (lane < 2 * kFlight) starts[lane] = 0;
+                s3_wave_fence();
+                if (nv > 0 && v_at > v0 && v_at < v0 + 64 * kFlight) atomicOr(&starts[(v_at - v0) >> 5], 1u << ((v_at - v0) & 31));
+                s3_wave_fence();
+                int before = (int)__popcll(__ballot(nv > 0 && v_at <= v0)) - 1;
+                if (!__any(nv > 0 && v_at > v0 && v_at <= v0 + 64 * kFlight) && v0 + 64 * kFlight < total) {
+                    // all of one long segment: whole vectors behind its first one (it goes on behind these)
+                    const Segment one = seg[before];
+                    const unsigned long long w1 = weight[before];
+                    Vec v[kFlight];
 #pragma unroll
-                for (int u = 0; u < kShortSlots; ++u) {
-                    int idx = -1;
+                    for (int u = 0; u < kFlight; ++u) v[u] = pos[one.shift + v0 + u * 64 + lane];
+                    const int e0 = (one.shift + v0 + lane) * 4;
+                    add(v[0], (unsigned)(one.shift + v0) * 4u >= one.first, (unsigned)e0, one.first, one.end, w1);
 #pragma unroll
-                    for (int g = 0; g < LPS; ++g) {                        // the next LPS segments, one per lane group
-                        const int sbit = ms ? (int)__builtin_ctzll(ms) : -1;
-                        if (ms) ms &= ms - 1;
-                        idx = grp == g ? sbit : idx;
-                    }
-                    rc[u] = idx >= 0 ? recs[idx] : make_int4(0, 0, 0, 0);
+                    for (int u = 1; u < kFlight; ++u) add(v[u], true, 0u, 0u, 0u, w1);
+                    continue;
                 }
-                const Vec* vp[kShortSlots];
-                int shift[kShortSlots], total[kShortSlots];
+                Segment sg[kFlight];
+                Vec raw4[kFlight];
+                unsigned long long w[kFlight];
 #pragma unroll
-                for (int u = 0; u < kShortSlots; ++u) {
-                    const uintptr_t addr = (uintptr_t)(pos + rc[u].x);
-                    shift[u] = (int)((addr & (VB - 1)) / sizeof(Posting));
-                    vp[u] = (const Vec*)(addr & ~(uintptr_t)(VB - 1));
-                    total[u] = rc[u].y ? shift[u] + rc[u].y : 0;
-                    two = two || total[u] > G * EPV;
+                for (int u = 0; u < kFlight; ++u) {
+                    const unsigned lo = starts[2 * u], hi = starts[2 * u + 1];
+                    // starts at lanes 1 .. lane of this load, and at its lane 0
+                    const int own = before + (int)(lo & 1u) + (int)__builtin_amdgcn_mbcnt_hi(hi >> 1, __builtin_amdgcn_mbcnt_lo((lo >> 1) | (hi << 31), 0u));
+                    before += (int)__popc(lo) + (int)__popc(hi);
+                    sg[u] = seg[own];
+                    w[u] = weight[own];
                 }
-                const int chunks = __any(two) ? 2 : 1;
-                for (int c = 0; c < chunks; ++c) {
-                    Vec raw[kShortSlots];
 #pragma unroll
-                    for (int u = 0; u < kShortSlots; ++u)
-                        raw[u] = (c * G + sub) * EPV < total[u] ? vp[u][c * G + sub] : Vec{};
-#pragma unroll
-                    for (int u = 0; u < kShortSlots; ++u) {
-                        const unsigned long long w = ((unsigned long long)(unsigned)rc[u].w << 32) | (unsigned)rc[u].z;
-                        const int el0 = (c * G + sub) * EPV;
-#pragma unroll
-                        for (int j = 0; j < EPV; ++j) {
-                            const unsigned rr = vec_posting(raw[u], j) - pbase;
-                            if (el0 + j >= shift[u] && el0 + j < total[u] && rr < span) atomicAdd(&sblk[rr], w);
-                        }
-                    }
+                for (int u = 0; u < kFlight; ++u) {
+                    const int v = v0 + u * 64 + lane;
+                    raw4[u] = pos[v < total ? sg[u].shift + v : (int)(sg[u].first >> 2)];
+                    if (v >= total) sg[u].end = 0;
+                    sg[u].shift += v;
                 }
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u) add(raw4[u], false, (unsigned)sg[u].shift * 4u, sg[u].first, sg[u].end, w[u]);
             }
         }
+        __syncthreads();
+    }
+    for (int q = 0, dealt = 0; q < min(n_hot, kHotMax); ++q) {
+        int skew;
+        const Vec* const pos = array_of(hot_head[q], skew);
+        const unsigned first = hot[q].first, end = hot[q].end;
+        const int vend = (int)((end + 3) >> 2), vbeg = (int)(first >> 2), turns = (vend - vbeg + 64 * kFlight - 1) / (64 * kFlight);
+        const unsigned long long w = hot_weight[q];
+        for (int t = (wave - dealt) & (kW - 1); t < turns; t += kW) {
+            const int v0 = vbeg + t * 64 * kFlight + lane;
+            Vec v[kFlight];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) v[u] = pos[min(v0 + u * 64, vend - 1)];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                const unsigned e0 = (unsigned)(v0 + u * 64) * 4u;
+                add(v[u], !__any(e0 < first || e0 + 4 > end), e0, first, end, w);
+            }
+        }
+        dealt += turns;
     }
     __syncthreads();
-    unsigned long long* dst = a.ngroup > 1 ? a.part + (size_t)blockIdx.y * a.L : a.sfix;
-    for (int64_t i = tid; i < (int64_t)span; i += kScatterThreads) dst[p0 + i] = sblk[i];
+    unsigned long long* const dst = (a.ngroup > 1 ? a.part + (size_t)unit * a.L : a.sfix) + p0;
+    for (unsigned i = tid; i < span; i += kScatterThreads) dst[i] = sblk[spread(i)];
 }
 
 // The wavefront's best window, in every lane: largest key (sum + 1; 0: none), ties -> smallest start.
@@ -408,8 +585,8 @@ __device__ __forceinline__ void wave_best(unsigned long long& key, int& start) {
     key = best;
 }
 
-// S = sum of the head groups' partial arrays.  64 positions per workgroup, four threads per position (each takes
-// every fourth group), so that a short context still fills the chip and every thread's loads are independent.
+// S = sum of the groups' partial arrays, for sc_pool_wide_kernel (the other pooling kernel sums them itself).  64 positions per
+// workgroup, four threads per position (each takes every fourth group), so that every thread's loads are independent.
 __global__ __launch_bounds__(256) void sc_reduce_kernel(ScoreArgs a) {
     __shared__ unsigned long long partial[4][64];
     const int p = threadIdx.x & 63, q = threadIdx.x >> 6;
@@ -447,33 +624,46 @@ __device__ __forceinline__ unsigned long long block_incl_scan_u64(unsigned long 
     return v + base;
 }
 
-// Span pooling, the fp32 scores, and the best window of every kSubW windows (one workgroup per kTileW windows).
-// The tile's positions are staged in LDS and turned into prefix sums there, so a window costs two LDS reads
-// whatever its length: W[s] = P[s + len - 1] - P[s - 1], exact in 64-bit integers.  Larger value wins, ties ->
-// smaller start.
-constexpr int kPoolThreads = 256;
+// Sum of the groups, span pooling, the fp32 scores, and the best window of every 2^sublog windows (one workgroup per a.tile
+// windows).  The tile's positions are summed over the groups' arrays into LDS and turned into prefix sums there, so a window costs two
+// LDS reads whatever its length: W[s] = P[s + len - 1] - P[s - 1], exact in 64-bit integers.  Larger value wins, ties ->
+// smaller start.  What bounds it is a chain of memory, LDS and barrier latencies, so tiles are short (each thread has one position or
+// two), but no shorter than four windows, whose positions beyond the tile are summed twice.  32768 positions: 7.5 + 6.1 us
+// (sums by a kernel of their own, tiles of 2048 windows) -> 11.7.
+constexpr int kPoolThreads = 1024;
 constexpr int kPoolMaxLen = 4096;      // longer windows take sc_pool_wide_kernel
 
 __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
-    extern __shared__ unsigned long long pre[];          // [kTileW + len - 1 (+ padding)] prefix sums
+    extern __shared__ unsigned long long pre[];          // [tile + len - 1] prefix sums
     __shared__ unsigned long long wsum[kPoolThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int kW = kPoolThreads / 64;
     const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
-    const int64_t s0 = (int64_t)blockIdx.x * kTileW;
-    const int64_t tend = (int)blockIdx.x == a.ntile - 1 ? a.L : s0 + kTileW;      // positions whose fp32 score this tile writes
-    const int n_in = (int)(min(a.L, s0 + kTileW + a.len - 1) - s0);               // positions the tile's windows read
-    constexpr int kBatch = 5;                                                     // coalesced loads in flight per thread
-    for (int i0 = tid; i0 < n_in; i0 += kBatch * kPoolThreads) {
-        unsigned long long v[kBatch];
+    const int64_t s0 = (int64_t)blockIdx.x * a.tile;
+    const int64_t tend = (int)blockIdx.x == a.ntile - 1 ? a.L : s0 + a.tile;      // positions whose fp32 score this tile writes
+    const int n_in = (int)(min(a.L, s0 + a.tile + a.len - 1) - s0);               // positions the tile's windows read
+    const unsigned long long* const src = a.ngroup > 1 ? a.part : a.sfix;
+    // a wavefront sums a share of the groups for 64 positions, sixteen loads in flight per lane
+    constexpr int kSum = 16;
+    const int chunks = (n_in + 63) >> 6, shares = max(1, min(kW / chunks, (a.ngroup + kSum - 1) / kSum));
+    if (shares > 1) {
+        for (int i = tid; i < n_in; i += kPoolThreads) pre[i] = 0;
+        __syncthreads();
+    }
+    for (int c = wave; c < chunks * shares; c += kW) {
+        const int i = (c % chunks) * 64 + lane, g0 = a.ngroup * (c / chunks) / shares, g1 = a.ngroup * (c / chunks + 1) / shares;
+        if (i >= n_in) continue;
+        unsigned long long sum = 0;
+        for (int g = g0; g < g1; g += kSum) {
+            unsigned long long v[kSum];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) v[u] = i0 + u * kPoolThreads < n_in ? a.sfix[s0 + i0 + u * kPoolThreads] : 0ull;
+            for (int u = 0; u < kSum; ++u) v[u] = src[(size_t)min(g + u, g1 - 1) * a.L + s0 + i];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int i = i0 + u * kPoolThreads;
-            if (i >= n_in) continue;
-            pre[i] = v[u];
-            if (a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)v[u] * inv);
+            for (int u = 0; u < kSum; ++u) sum += g + u < g1 ? v[u] : 0ull;
         }
+        if (shares > 1) atomicAdd(&pre[i], sum);
+        else pre[i] = sum;
     }
     __syncthreads();
     // each thread sums its own run, the block scans the run totals, the thread writes its run's prefixes
@@ -481,7 +671,10 @@ __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
     unsigned long long run = 0;
     for (int j = 0; j < per; ++j) {
         const int i = tid * per + j;
-        if (i < n_in) run += pre[i];
+        if (i < n_in) {
+            run += pre[i];
+            if (a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)pre[i] * inv);
+        }
     }
     unsigned long long sum = block_incl_scan_u64<kPoolThreads>(run, wsum) - run;
     for (int j = 0; j < per; ++j) {
@@ -492,31 +685,25 @@ __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
         }
     }
     __syncthreads();
-    for (int q = wave; q < kTileW / kSubW; q += kPoolThreads / 64) {
-        const int sub = (int)blockIdx.x * (kTileW / kSubW) + q;
-        if (s0 + q * kSubW >= a.nW) break;
-        if (a.sublog == 6) {                                                      // a maximum for every 64 windows
-            unsigned long long w[kSubW / 64];
-#pragma unroll
-            for (int u = 0; u < kSubW / 64; ++u) {
-                const int i = q * kSubW + u * 64 + lane;
-                w[u] = 0;
-                if (s0 + i < a.nW) {
-                    const unsigned long long v = pre[i + a.len - 1] - (i ? pre[i - 1] : 0ull);
-                    a.wfix[s0 + i] = (long long)v;
-                    w[u] = v + 1;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kSubW / 64; ++u) {
-                const unsigned top = s3_wave_max_u32((unsigned)(w[u] >> 32));
-                unsigned long long m = __ballot((unsigned)(w[u] >> 32) == top);
-                s3greedy::settle(w[u], top, m);                                   // ties -> the first lane, the smaller start
-                const int e = sub * (kSubW / 64) + u, src = (int)__builtin_ctzll(m);
-                if (lane == src && e < a.nsub) { a.tmaxv[e] = w[u]; a.tmaxi[e] = (int)(s0 + q * kSubW + u * 64 + src); }
-            }
-            continue;
+    for (int b = wave; a.sublog == 6 && b < a.tile / 64; b += kW) {
+        const int i = b * 64 + lane;
+        if (s0 + b * 64 >= a.nW) return;
+        unsigned long long w = 0;
+        if (s0 + i < a.nW) {
+            const unsigned long long v = pre[i + a.len - 1] - (i ? pre[i - 1] : 0ull);
+            a.wfix[s0 + i] = (long long)v;
+            w = v + 1;
         }
+        const unsigned top = s3_wave_max_u32((unsigned)(w >> 32));
+        unsigned long long m = __ballot((unsigned)(w >> 32) == top);
+        s3greedy::settle(w, top, m);                                              // ties -> the first lane, the smaller start
+        const int e = (int)blockIdx.x * (a.tile / 64) + b, lead = (int)__builtin_ctzll(m);
+        if (lane == lead) { a.tmaxv[e] = w; a.tmaxi[e] = (int)(s0 + i); }
+    }
+    if (a.sublog == 6) return;
+    for (int q = wave; q < a.tile / kSubW; q += kW) {
+        const int sub = (int)blockIdx.x * (a.tile / kSubW) + q;
+        if (s0 + q * kSubW >= a.nW) break;
         unsigned long long key = 0;
         int start = 0x7FFFFFFF;
 #pragma unroll
@@ -822,7 +1009,7 @@ __global__ __launch_bounds__(s3greedy::kThreads) void sc_topb_slots_kernel(Score
 
 struct Layout {
     size_t wmax, nact, sfix, wfix, tmaxv, tmaxi, part, act, total;
-    int nr, pb, npb, heads_per, ngroup;   // feature ranges per head; position blocks and head groups of the gather
+    int nr, pb, npb, heads_per, parts, ngroup;   // feature ranges per head; position blocks, heads of a group, parts and groups at most of the gather
 };
 
 Layout layout(int n_heads, int n_feat, int64_t L) {
@@ -838,13 +1025,13 @@ Layout layout(int n_heads, int n_feat, int64_t L) {
     l.wfix = take((size_t)L * 8);
     l.tmaxv = take(nsub * 8);
     l.tmaxi = take(nsub * 4);
-    // position blocks of at most kMaxPB scores (128 KB of LDS); enough head groups for about one workgroup per compute unit
+    // position blocks of at most kMaxPB scores (128 KB of LDS); enough groups for about one workgroup per compute unit
     l.pb = (int)(L < kMaxPB ? (L + 63) / 64 * 64 : kMaxPB);
     l.npb = (int)((L + l.pb - 1) / l.pb);
-    int want = 256 / l.npb;
-    int groups = n_heads < want ? n_heads : (want < 1 ? 1 : want);
+    const int want = 256 / l.npb < 1 ? 1 : 256 / l.npb, groups = n_heads < want ? n_heads : want;
     l.heads_per = (n_heads + groups - 1) / groups;
-    l.ngroup = (n_heads + l.heads_per - 1) / l.heads_per;
+    l.parts = want / groups;
+    l.ngroup = (n_heads + l.heads_per - 1) / l.heads_per * l.parts;
     l.part = o;
     if (l.ngroup > 1) l.part = take((size_t)l.ngroup * L * 8);
     l.act = take((size_t)n_heads * n_feat * sizeof(ActiveList));
@@ -903,8 +1090,18 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.tmaxv = (unsigned long long*)(base + l.tmaxv);
     a.tmaxi = (int*)(base + l.tmaxi);
     a.part = (unsigned long long*)(base + l.part);
-    a.pb = l.pb; a.npb = l.npb; a.heads_per = l.heads_per; a.ngroup = l.ngroup; a.sorted = v.sorted ? 1 : 0;
-    a.ntile = (int)((a.nW + kTileW - 1) / kTileW);
+    a.pb = l.pb; a.npb = l.npb; a.sorted = v.sorted ? 1 : 0;
+    // Lists that the queries' pairs can name in the heads of a group.  A part has 64 of them or more; a batch is as large as leaves
+    // one for every wavefront.
+    const int64_t pairs = (int64_t)nq * a.k, lists = l.heads_per * (pairs < a.n_feat ? pairs : (int64_t)a.n_feat);
+    a.heads_per = l.heads_per;
+    a.parts = (int)(lists / 64 < 1 ? 1 : (lists / 64 < l.parts ? lists / 64 : l.parts));
+    a.ngroup = l.ngroup / l.parts * a.parts;
+    const int64_t share = (lists / a.parts + 15) / 16;
+    a.batch = (int)(share < 4 ? 4 : (share < 64 ? share : 64));
+    a.tile = kTileW;
+    while (a.tile > 256 && a.tile >= 4 * a.len) a.tile >>= 1;
+    a.ntile = (int)((a.nW + a.tile - 1) / a.tile);
     const int64_t reach = a.nms ? a.len - 1 : 0, most_found = s3greedy::choices(a.nW, reach, top_b), need = s3greedy::slots_needed(a.nW, reach, most_found);
     const bool slots = most_found > kTopFew && need <= kTopSlots && (a.nW + 63) / 64 <= 16 * s3greedy::kThreads;
     const s3greedy::Way sw = s3greedy::way_of(need, reach);
@@ -918,24 +1115,22 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.scores_out = scores_out; a.span_start = span_start; a.span_score = span_score; a.n_found = n_found;
 
     hipStream_t st = (hipStream_t)stream;
-    static S3LdsOnce once_prep, once_scatter[4];
+    static S3LdsOnce once_prep, once_gather[2];
     const int prep_lds = (a.n_feat < kRange ? a.n_feat : kRange) * 8;
     if (int rc = s3_allow_lds(once_prep, (const void*)sc_prep_kernel, kRange * 8)) return rc;
-    // lanes per short segment: from the mean length of a list's part in one position block
-    const double mean_seg = (double)v.tokens * a.k / ((double)a.n_feat * l.npb);
-    const bool narrow = mean_seg <= 20.0, cmp = v.delta != nullptr;
-    auto scatter = cmp ? (narrow ? sc_scatter_lds_kernel<8, true> : sc_scatter_lds_kernel<16, true>)
-                       : (narrow ? sc_scatter_lds_kernel<8, false> : sc_scatter_lds_kernel<16, false>);
-    if (int rc = s3_allow_lds(once_scatter[2 * cmp + narrow], (const void*)scatter, kMaxPB * 8)) return rc;
-    // at most five launches: query weights, gather, sum of the head groups, pooling + tile maxima, Top-B
-    hipLaunchKernelGGL(sc_prep_kernel, dim3((unsigned)a.nr, (unsigned)a.n_heads), dim3(kPrepThreads), (size_t)prep_lds, st, a);
-    hipLaunchKernelGGL(scatter, dim3((unsigned)a.npb, (unsigned)a.ngroup), dim3(kScatterThreads), (size_t)a.pb * 8, st, a);
-    if (a.ngroup > 1) hipLaunchKernelGGL(sc_reduce_kernel, dim3((unsigned)((a.L + 63) / 64)), dim3(256), 0, st, a);
+    const bool cmp = v.delta != nullptr;
+    auto gather = cmp ? sc_gather_kernel<true> : sc_gather_kernel<false>;
+    if (int rc = s3_allow_lds(once_gather[cmp], (const void*)gather, (kMaxPB + 64) * 8)) return rc;
+    // four launches: query weights, gather, sum of the groups with pooling and tile maxima, Top-B
+    if ((int64_t)nq * a.k <= kPrepThreads) hipLaunchKernelGGL(sc_prep_few_kernel, dim3((unsigned)a.n_heads), dim3(kPrepThreads), 0, st, a);
+    else hipLaunchKernelGGL(sc_prep_kernel, dim3((unsigned)a.nr, (unsigned)a.n_heads), dim3(kPrepThreads), (size_t)prep_lds, st, a);
+    hipLaunchKernelGGL(gather, dim3((unsigned)(a.npb * a.ngroup)), dim3(kScatterThreads), (size_t)(a.pb + 64) * 8, st, a);
     if (a.len <= kPoolMaxLen) {
         static S3LdsOnce once_pool;
         if (int rc = s3_allow_lds(once_pool, (const void*)sc_pool_kernel, (kTileW + kPoolMaxLen) * 8)) return rc;
-        hipLaunchKernelGGL(sc_pool_kernel, dim3((unsigned)a.ntile), dim3(kPoolThreads), (size_t)(kTileW + a.len) * 8, st, a);
+        hipLaunchKernelGGL(sc_pool_kernel, dim3((unsigned)a.ntile), dim3(kPoolThreads), (size_t)(a.tile + a.len) * 8, st, a);
     } else {
+        if (a.ngroup > 1) hipLaunchKernelGGL(sc_reduce_kernel, dim3((unsigned)((a.L + 63) / 64)), dim3(256), 0, st, a);
         hipLaunchKernelGGL(sc_pool_wide_kernel, dim3((unsigned)((a.ntile + 3) / 4)), dim3(256), 0, st, a);
     }
     if (slots) {

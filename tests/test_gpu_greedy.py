@@ -1,5 +1,6 @@
-"""The greedy searches that bring the blocks their choices can lie in into LDS: numbers of blocks and of slots around the sizes
-at which another build or another kernel takes over, and more equal block maxima than there are slots."""
+"""Scoring and peaks around the sizes at which another way is taken.  The greedy searches that bring the blocks their choices can lie in into LDS: numbers of blocks and of slots around the sizes
+at which another build or another kernel takes over, and more equal block maxima than there are slots.  The gather: few and many
+query pairs, lists in parts, very long lists, many heads."""
 import numpy as np
 import pytest
 
@@ -69,3 +70,63 @@ def test_peaks_around_the_numbers_of_slots(L, radius, n_centers, levels):
     assert np.array_equal(D.cpu().numpy(), D32) and n == len(c_o)
     assert np.array_equal(c.cpu().numpy()[:n], c_o) and np.array_equal(dc.cpu().numpy()[:n], pk_o.astype(np.float32))
     assert np.array_equal(lo.cpu().numpy()[:n], lo_o) and np.array_equal(hi.cpu().numpy()[:n], hi_o)
+
+
+@pytest.mark.parametrize("H,T,k,n_feat,nq,hot", [
+    (1, 3000, 32, 256, 32, 0),           # 1024 query pairs, the most for a thread each; a head's lists in parts
+    (2, 3000, 25, 300, 41, 0),           # 1025
+    (1, 40_000, 16, 4096, 9, 8),         # lists that fill whole position blocks: shared by all wavefronts at the end
+    (1, 20_000, 100, 400, 20, 100),      # more of them than are put aside
+    (3, 700, 7, 17_000, 64, 0),          # two feature ranges
+])
+def test_gather_of_short_and_long_lists(H, T, k, n_feat, nq, hot):
+    """Segments of every alignment and length, plain and compact; `hot` features are in every token."""
+    rng = np.random.default_rng(T + k)
+    ids = np.empty((H, T, k), np.int32)
+    for h in range(H):
+        if hot >= k - 1:
+            ids[h] = np.arange(k, dtype=np.int32)[None, :]
+        elif hot:
+            ids[h, :, :hot] = np.arange(hot)
+            start = rng.integers(0, n_feat - hot, T)
+            ids[h, :, hot:] = hot + (start[:, None] + np.arange(k - hot) * ((n_feat - hot) // (k - hot))) % (n_feat - hot)
+        else:
+            start = (n_feat * rng.random(T) ** 2).astype(np.int64)
+            ids[h] = (start[:, None] + np.arange(k) * (n_feat // k)) % n_feat
+    qids = np.stack([np.stack([rng.choice(n_feat, k, replace=False) for _ in range(nq)]) for _ in range(H)]).astype(np.int32)
+    if hot:
+        qids[:, 0, :] = np.arange(k)
+    qvals = np.maximum(rng.random((H, nq, k)) - 0.1, 0).astype(np.float32)
+    ix = gpu_index(ids, n_feat, chunks=[7000] * (T // 7000 + 1))
+    S, W, st_o, sc_o = oracle_score(ids, qids, qvals, n_feat, T, 40, 12, 0, True)
+    plain = run_gpu_score(ix, qids, qvals, T, 40, 12, 0, True)
+    check_score(plain, S, W, st_o, sc_o, 40, True)
+    if T > 16384:                                              # the compact form needs two position blocks
+        cx = ix.compact(0)
+        whole = run_gpu_score(cx, qids, qvals, T, 40, 12, 0, True)
+        short = run_gpu_score(cx, qids, qvals, T - 130, 40, 12, 0, True)      # the last positions are cut off
+        assert np.array_equal(whole[3], plain[3]) and np.array_equal(whole[0], plain[0])
+        assert np.array_equal(short[3], plain[3][:T - 130])
+
+
+def test_gather_of_more_heads_than_are_looked_at_together():
+    """1200 heads of two feature ranges in three groups: 800 pairs a group.  One posting list of every head is queried."""
+    import torch
+    import paper_2601_17702_amd as s3
+    H, T, n_feat, L = 1200, 8, 16_400, 64 * 16384 + 77
+    rng = np.random.default_rng(4)
+    ids = rng.integers(0, n_feat, (H, T, 1)).astype(np.int32)
+    at = np.sort(rng.choice(L, T, replace=False)).astype(np.int32)
+    ix = s3.Index(H, n_feat, 1, T)
+    ix.append(torch.from_numpy(ids).cuda(), positions=torch.from_numpy(at).cuda())
+    ix.finalize()
+    slot = rng.integers(0, T, H)
+    qids = ids[np.arange(H), slot][:, None, :].copy()
+    qvals = rng.integers(1, 1000, (H, 1, 1)).astype(np.float32)
+    _, _, _, S = ix.coactivate_score(torch.from_numpy(qids).cuda(), torch.from_numpy(qvals).cuda(), L, 64, 4, want_scores=True)
+    torch.cuda.synchronize()
+    want = np.zeros(L)
+    for h in range(H):
+        hit = ids[h, :, 0] == qids[h, 0, 0]
+        want[at[hit]] += qvals[h, 0, 0] / (1.0 + np.log(1.0 + hit.sum()))
+    assert np.allclose(S.cpu().numpy(), want, rtol=1e-5, atol=1e-30)
