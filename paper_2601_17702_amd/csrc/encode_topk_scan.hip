@@ -503,10 +503,17 @@ __device__ __forceinline__ void sort_to(double (&v)[E]) {          // runs of S 
     }
 }
 template <int X>
-__device__ __forceinline__ double lane_xor(double d) {             // the value of lane ^ X, X = 1, 2, 3
+__device__ __forceinline__ double lane_xor(double d) {             // the value of lane ^ X, X = 1 .. 7
+    if constexpr (X > 3) {                                         // lanes of eight mirrored, then inside four
+        d = __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(d), 0x141, 0xf, 0xf, true),
+                             __builtin_amdgcn_update_dpp(0, __double2loint(d), 0x141, 0xf, 0xf, true));
+        if constexpr (X == 7) return d;
+        else return lane_xor<X ^ 7>(d);
+    } else {
     constexpr int ctrl = X == 1 ? 0xB1 : (X == 2 ? 0x4E : 0x1B);
     return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(d), ctrl, 0xf, 0xf, true),
                             __builtin_amdgcn_update_dpp(0, __double2loint(d), ctrl, 0xf, 0xf, true));
+    }
 }
 template <int X>
 __device__ __forceinline__ void lane_clean(double (&v)[E], int q) {
@@ -803,13 +810,63 @@ __global__ __launch_bounds__(kThreads, 2) void enc_scan_kernel(ScanArgs a) {
 
 // Selects from the lists that the ranges of the features left, a wavefront per token.  Tokens
 // that have too few candidates (a first threshold that was too high) are left to the walk behind this.
-template <int LR>
-__global__ __launch_bounds__(256) void enc_join_kernel(ScanArgs a) {
-    __shared__ float lval[4][64 * LR];
-    __shared__ uint16_t lid[4][64 * LR];
+//
+// TOK: tokens per workgroup.  Sixteen where they carry bounds, which then go to the head's in one go (additions to a head's few
+// values from 128 workgroups were half of the time: 4096 tokens of 8 heads, k 32, 33 -> 18 us); else four, which leave their
+// compute unit earlier (16384 tokens, k 32: 48 / 31).
+// LR 4 (k > 64): the list is sorted whole; ranks by a comparison of every survivor with every other one, after a cut to about k of
+// them, are two and a half times the instructions (4096 tokens, k 128: 33 -> 23 us).
+template <int X>
+__device__ __forceinline__ double wave_xor(double d) {     // the value of lane ^ X
+    if constexpr (X <= 7) return lane_xor<X>(d);
+    else if constexpr (X == 8 || X == 15) {
+        constexpr int ctrl = X == 8 ? 0x128 : 0x140;       // rows of 16 turned by eight, mirrored
+        return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(d), ctrl, 0xf, 0xf, true),
+                                __builtin_amdgcn_update_dpp(0, __double2loint(d), ctrl, 0xf, 0xf, true));
+    } else return __hiloint2double(__shfl_xor(__double2hiint(d), X), __shfl_xor(__double2loint(d), X));
+}
+template <int X>
+__device__ __forceinline__ void wave_step(double (&v)[4], int lane, bool mirrored) {       // the larger ones to the lower lane of each pair
+    constexpr int top = X <= 1 ? 1 : (X <= 3 ? 2 : (X <= 7 ? 4 : (X <= 15 ? 8 : (X <= 31 ? 16 : 32))));
+    const bool up = (lane & top) == 0;
+    double o[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = wave_xor<X>(v[mirrored ? 3 - i : i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const double x = fmax(v[i], o[i]), y = fmin(v[i], o[i]);
+        v[i] = up ? x : y;
+    }
+}
+template <int N>
+__device__ __forceinline__ void wave_clean(double (&v)[4], int lane) {      // bitonic over N lanes -> descending
+    if constexpr (N >= 2) {
+        wave_step<N / 2>(v, lane, false);
+        wave_clean<N / 2>(v, lane);
+    } else {
+        exch(v[0], v[2]); exch(v[1], v[3]);
+        exch(v[0], v[1]); exch(v[2], v[3]);
+    }
+}
+template <int N>
+__device__ __forceinline__ void wave_sort(double (&v)[4], int lane) {       // place 4 lane + i, descending inside N lanes
+    if constexpr (N == 1) {
+        exch(v[0], v[1]); exch(v[2], v[3]);
+        exch(v[0], v[3]); exch(v[1], v[2]);
+        exch(v[0], v[1]); exch(v[2], v[3]);
+    } else {
+        wave_sort<N / 2>(v, lane);
+        wave_step<N - 1>(v, lane, true);
+        wave_clean<N / 2>(v, lane);
+    }
+}
+template <int LR, int TOK>
+__global__ __launch_bounds__(64 * TOK) void enc_join_kernel(ScanArgs a) {
+    __shared__ float lval[TOK][64 * LR];
+    __shared__ uint16_t lid[TOK][64 * LR];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    __shared__ float seen[4][2];               // k-th value and |x| of the block's tokens
-    constexpr int kPerBlock = 4;
+    __shared__ float seen[TOK][2];             // k-th value and |x| of the block's tokens
+    constexpr int kPerBlock = TOK, kU = TOK > 4 ? 8 : 4;        // kU: loads in flight per lane
     const int tile = blockIdx.x / (kTokWG / kPerBlock), t = (blockIdx.x % (kTokWG / kPerBlock)) * kPerBlock + wv;
     const int head = tile / a.tiles_per_head, tok0 = (tile - head * a.tiles_per_head) * kTokWG;
     const int lists = 2 * a.parts, log2n = 32 - __builtin_clz((unsigned)(lists - 1)), p = lane & ((1 << log2n) - 1);
@@ -828,33 +885,50 @@ __global__ __launch_bounds__(256) void enc_join_kernel(ScanArgs a) {
             s3_wave_fence();
             int n = 0;
             float tau = -INFINITY;
-            for (int i0 = 0; i0 < most; i0 += 4 * step) {
-                uint2 u[4];
+            for (int i0 = 0; i0 < most; i0 += kU * step) {
+                uint2 u[kU];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < kU; ++j) {
                     const int i = i0 + j * step + slot;
                     u[j] = i < c ? src[(size_t)i * kLanes] : make_uint2(__float_as_uint(-INFINITY), 0u);
                 }
-                const float v[4] = {__uint_as_float(u[0].x), __uint_as_float(u[1].x), __uint_as_float(u[2].x), __uint_as_float(u[3].x)};
+                float v[kU];
+#pragma unroll
+                for (int j = 0; j < kU; ++j) v[j] = __uint_as_float(u[j].x);
                 const float before = tau;
-                s3topk::take<4, LR>(v, [&](int j) { return u[j].y; }, a.k, a.k + (a.k >> 3) + 2, lval[wv], lid[wv], n, tau);
+                s3topk::take<kU, LR>(v, [&](int j) { return u[j].y; }, a.k, a.k + (a.k >> 3) + 2, lval[wv], lid[wv], n, tau);
                 // the elements come in no order of ids: one that equals the threshold may still belong to the k best
                 if (tau != before) {
                     const unsigned key = key_of(tau);
                     tau = value_of(key == 0x80000000u ? key - 2 : key - 1);        // below 0 comes the first negative, not -0
                 }
             }
-            unsigned key[LR], id[LR];
-            int rank[LR];
-            s3topk::finish<LR>(a.k, lval[wv], lid[wv], n, key, id, rank);
             const size_t row = ((size_t)head * a.T + tok0 + t) * a.k;
+            if constexpr (LR == 4) {
+                double v[4];
 #pragma unroll
-            for (int i = 0; i < LR; ++i)
-                if (rank[i] >= 0) {
-                    a.ids[row + rank[i]] = (int32_t)id[i];
-                    a.vals[row + rank[i]] = fmaxf(value_of(key[i]), 0.f);
-                    if (rank[i] == a.k - 1) z = value_of(key[i]);
-                }
+                for (int i = 0; i < 4; ++i) v[i] = i * 64 + lane < n ? pack(lval[wv][i * 64 + lane], lid[wv][i * 64 + lane]) : 0.0;
+                wave_sort<64>(v, lane);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (4 * lane + i < a.k) {
+                        const float zi = pack_value(v[i]);
+                        a.ids[row + 4 * lane + i] = (int32_t)pack_id(v[i]);
+                        a.vals[row + 4 * lane + i] = fmaxf(zi, 0.f);
+                        if (4 * lane + i == a.k - 1) z = zi;
+                    }
+            } else {
+                unsigned key[LR], id[LR];
+                int rank[LR];
+                s3topk::finish<LR>(a.k, lval[wv], lid[wv], n, key, id, rank);
+#pragma unroll
+                for (int i = 0; i < LR; ++i)
+                    if (rank[i] >= 0) {
+                        a.ids[row + rank[i]] = (int32_t)id[i];
+                        a.vals[row + rank[i]] = fmaxf(value_of(key[i]), 0.f);
+                        if (rank[i] == a.k - 1) z = value_of(key[i]);
+                    }
+            }
             if (a.hint) {
                 z = value_of(s3_wave_max_u32(key_of(z)));
                 xn = a.norm[(size_t)head * a.T + tok0 + t];
@@ -867,18 +941,19 @@ __global__ __launch_bounds__(256) void enc_join_kernel(ScanArgs a) {
         seen[wv][1] = xn;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    float r = INFINITY, m = INFINITY, s_tau = 0.f, s_x = 0.f, s_n = 0.f;
-    for (int q = 0; q < 4; ++q) {
-        const float zq = seen[q][0], xq = seen[q][1];
-        if (!(zq > -INFINITY)) continue;
-        if (xq > 0.f) r = fminf(r, zq / xq);
-        m = fminf(m, zq);
-        s_tau += zq;
-        s_x += xq;
-        s_n += 1.f;
+    if (threadIdx.x >= TOK) return;
+    const float zq = seen[threadIdx.x][0], xq = seen[threadIdx.x][1];
+    const bool use = zq > -INFINITY;
+    float r = use && xq > 0.f ? zq / xq : INFINITY, m = use ? zq : INFINITY, s_tau = use ? zq : 0.f, s_x = use ? xq : 0.f, s_n = use ? 1.f : 0.f;
+#pragma unroll
+    for (int d = TOK / 2; d > 0; d >>= 1) {
+        r = fminf(r, __shfl_xor(r, d));
+        m = fminf(m, __shfl_xor(m, d));
+        s_tau += __shfl_xor(s_tau, d);
+        s_x += __shfl_xor(s_x, d);
+        s_n += __shfl_xor(s_n, d);
     }
-    if (s_n > 0.f) {
+    if (threadIdx.x == 0 && s_n > 0.f) {
         if (r < INFINITY) atomicMin(&a.hint_out[2 * head], key_of(r));
         atomicMin(&a.hint_out[2 * head + 1], key_of(m));
         atomicAdd(&a.hint_sum[3 * head], s_tau);
@@ -1034,7 +1109,8 @@ int launch_scan(const ScanArgs& a, const Plan& p, hipStream_t st) {
     hipLaunchKernelGGL(scan, dim3((unsigned)p.units), dim3(kThreads), kLds, st, a);
     if (p.parts > 1) {
         if (int rc = s3_allow_lds(once[1], (const void*)redo, kLds)) return rc;
-        hipLaunchKernelGGL((enc_join_kernel<LR>), dim3((unsigned)p.n_tiles * (kTokWG / 4)), dim3(256), 0, st, a);
+        if (a.hint) hipLaunchKernelGGL((enc_join_kernel<LR, 16>), dim3((unsigned)p.n_tiles * (kTokWG / 16)), dim3(64 * 16), 0, st, a);
+        else hipLaunchKernelGGL((enc_join_kernel<LR, 4>), dim3((unsigned)p.n_tiles * (kTokWG / 4)), dim3(64 * 4), 0, st, a);
         hipLaunchKernelGGL(redo, dim3((unsigned)p.n_tiles), dim3(kThreads), kLds, st, a);
     }
     return S3_OK;
