@@ -53,7 +53,7 @@ struct ScoreArgs {
     unsigned long long* sfix;        // [L]
     unsigned long long* part;        // [ngroup][L] partial sums of the gather's groups (ngroup > 1)
     int pb, npb, heads_per, parts, ngroup, sorted;   // the gather: position blocks, heads of a group, parts of these, groups in all
-    int batch;                       // lists that a wavefront takes at a time
+    int mixed;                       // lists of several heads and ranges may be looked at together
     long long* wfix;                 // [nW]
     unsigned long long* tmaxv;       // [nsub] best window of every 2^sublog starts: its sum + 1, 0 for none
     int* tmaxi;                      // [nsub] its start
@@ -264,26 +264,23 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_few_kernel(ScoreArgs a) 
 
 // Postings gather with the scores of one block of positions held in LDS.
 // Workgroup (b, g) owns positions [b * pb, (b + 1) * pb) and the lists of group g: of some heads, or, where there are fewer heads than
-// the chip wants workgroups, a part of the lists of one head.  (All heads' lists dealt to all
-// groups: the workgroups meet more pages, 156 us instead of 116 for 64 heads of 65536 positions, compact.)  The workgroup adds the
-// postings of its lists that fall into its block with LDS atomics (64-bit fixed point, so the order of the additions does not matter), then stores the block: into S when
-// there is one group, else into that group's partial array, which the pooling kernel sums.  (Additions to one array per XCD, in its
-// L2, instead: the pooling kernel has 8 arrays to sum instead of 128, 12 -> 5 us, but a workgroup's 16384 additions take 6 to 8 us.)
-// A wavefront takes a batch of up to 64 lists at a time (a counter in LDS deals them out): lane l fetches weight and feature of list l and the
-// part of the list that lies in the block (its segment) -- from the index's block table when there is one; else, for lists sorted by
-// position, by a search; else the whole list, every posting filtered.  Postings are read as aligned vectors of four; the vectors
-// of all the batch's segments are numbered through, and lane l of load u takes vector 64 u + l, whichever segment it belongs to: what a
-// wavefront keeps in flight bounds the rate, and this way every load is full whatever the lengths are.  Very long segments
-// (hot features) are left to the end, when all wavefronts share them.
-// us for the kernel, one segment a wavefront or some lanes at a time and heads alone as groups / now: 256 queries of k 128 in 32 heads
-// of 14001 positions 426 / 80 (0.7 TB/s of postings, 2.9), 896 of k 64 in 112 of 16384 355 / 117, 256 of k 32 in 64 of 16384, skewed, 116 / 67;
-// in 64 of 65536, compact, skewed, 116 / 111; 4 in 256 heads of 32768 39.5 / 39 (address translation: 256 lists a workgroup, each in
-// pages of its own).
+// the chip wants workgroups, a part of the lists of one head.  (All heads' lists dealt to all groups: the workgroups meet more
+// pages, 156 us instead of 116 for 64 heads of 65536 positions, compact.)  The workgroup adds the postings of its lists that fall into
+// its block with LDS atomics (64-bit fixed point, so the order of the additions does not matter), then stores the block: into S
+// when there is one group, else into that group's partial array, which the pooling kernel sums.  (Additions to one array per XCD, in
+// its L2, instead: the pooling kernel has 8 arrays to sum instead of 128, 12 -> 5 us, but a workgroup's 16384 additions take 6 to 8 us.)
+// 1024 lists at a time, a thread fetches weight and feature of a list and the part of the list that lies in the block (its
+// segment) -- from the index's block table when there is one; else, for lists sorted by position, by a search; else the whole
+// list, every posting filtered.  Postings are read as aligned vectors of four; the vectors of all the segments are numbered through,
+// the wavefronts take 64 kFlight of them in turn, and lane l of load u has vector 64 u + l, whichever segment it belongs to: what
+// is in flight bounds the rate, and this way every load is full and every wavefront has as much to do whatever the lengths are.
+// us for the kernel, one segment a wavefront or some lanes at a time, heads alone as groups / batches of 64 lists
+// a wavefront / now: 256 queries of k 128 in 32 heads of 14001 positions 426 / 80 / 65, 896 of k 64 in 112 of 16384 355 / 117 / 121, 256 of
+// k 32 in 64 of 16384, skewed, 116 / 67 / 44, in 64 of 65536, compact, skewed, 116 / 113 / 87; 4 in 256 heads of 32768 39.5 / 40 / 32; a
+// whole look-up of 5 queries in 64 heads of 97420 positions, skewed, 216 / 295 / 135.
 constexpr int kScatterThreads = 1024;
 constexpr int kFlight = 4;           // vector loads per lane in flight
-constexpr int kHotVec = 512;         // vectors of a segment that is left to all wavefronts
-constexpr int kHotMax = 64;          // as many of them at most; further ones are one wavefront's work
-constexpr int kPairs = 512;          // (head, range) pairs looked at together: 64 times 8
+constexpr int kPairs = 512;          // (head, range) pairs looked at together
 constexpr int kNarrowMin = 128;      // sorted lists longer than this are narrowed to the position block by search
 constexpr int kMaxPB = 1 << kS3PosBlockLog2;
 
@@ -321,12 +318,11 @@ __device__ __forceinline__ unsigned vec_posting(const uint2& v, int j) {
     return (w[j >> 1] >> ((j & 1) * 16)) & 0xFFFFu;
 }
 
-// A segment as the lanes that read it see it: element e of the head's array, counted from the vector boundary at or before its
-// first posting, belongs to it if first <= e < end; vector v of the batch is vector `shift` + v of the array.
+// A segment: vector v (of those numbered through) lies at base + v vectors, and element 4 v + j of it is the segment's if
+// first <= 4 v + j < end.
 struct Segment {
-    int shift;
+    uint64_t base;
     unsigned first, end;
-    int pad;                         // 16 bytes: read in one piece
 };
 
 // Where position p of the block lies in LDS: lanes that add four positions apart (vectors of a dense list) meet all banks.
@@ -339,18 +335,14 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
     constexpr int kW = kScatterThreads / 64;
     extern __shared__ __align__(16) unsigned long long sblk[];
     __shared__ unsigned long long wmx[kW];
-    __shared__ Segment seg_all[kScatterThreads];
-    __shared__ unsigned long long weight_all[kScatterThreads];
+    __shared__ Segment seg[kScatterThreads];
+    __shared__ unsigned long long weight[kScatterThreads];
+    __shared__ int start[kScatterThreads];                                 // the segments' first vectors
     __shared__ __align__(16) unsigned starts_all[kW][2 * kFlight];
-    __shared__ Segment hot[kHotMax];
-    __shared__ unsigned long long hot_weight[kHotMax];
-    __shared__ int hot_head[kHotMax], next_s, n_hot, wsum[kW];
-    __shared__ int upto[kPairs];                                           // batches of the (head, range) pairs up to this one
-    __shared__ uint16_t lists[kPairs];                                     // and their lists
+    __shared__ int upto[kPairs];                                           // lists of the (head, range) pairs up to this one
+    __shared__ int wsum[kW], wcnt[kW];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    Segment* const seg = seg_all + wave * 64;
-    unsigned long long* const weight = weight_all + wave * 64;
     unsigned* const starts = starts_all[wave];
     int unit, blk;                                                // the position blocks of a group share an XCD
     s3_block_to_tile(blockIdx.x, a.ngroup, a.npb, unit, blk);
@@ -361,7 +353,6 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
     const unsigned pbase = CMP ? 0u : (unsigned)p0;               // what a stored posting is relative to
     const bool cmp_empty = CMP && blk >= a.nblk;                  // the compact index holds nothing beyond its blocks
     for (int i = tid; i < a.pb / 2; i += kScatterThreads) ((uint4*)sblk)[i] = make_uint4(0, 0, 0, 0);      // pb is a multiple of 64
-    if (tid == 0) n_hot = 0;
     // the largest weight over all heads fixes the fixed-point scale (every workgroup derives the same one)
     unsigned long long mb = 0;
     for (int i = tid; i < a.n_heads * a.nr; i += kScatterThreads) mb = a.wmax[i] > mb ? a.wmax[i] : mb;
@@ -375,13 +366,6 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
     if (blockIdx.x == 0 && tid == 0) a.wmax[a.n_heads * a.nr] = mb;      // for the kernels that follow
     const double scale = ldexp(1.0, exp_s(mb, a.hb));
 
-    // The postings of the head's array from its first 16-byte (plain) or 8-byte (compact) boundary on.
-    const auto array_of = [&](int h, int& skew) {
-        const Posting* pos = CMP ? (const Posting*)(a.delta + (size_t)h * a.delta_stride)
-                                 : (const Posting*)(a.positions + (size_t)h * a.pos_stride);
-        skew = (int)(((uintptr_t)pos & (sizeof(Vec) - 1)) / sizeof(Posting));
-        return (const Vec*)(pos - skew);
-    };
     // Adds w at the vector's postings that belong to the segment (`whole`: all do, in all lanes) and lie in the block.  Compact
     // postings are handled two in a register; what does not belong goes to a place of the lane's own behind the block.
     const unsigned pb = (unsigned)a.pb, nowhere = pb + lane;
@@ -419,44 +403,42 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
         }
     };
     for (int pair0 = group * a.heads_per * a.nr; pair0 < pair1; pair0 += kPairs) {
-        const int n_mine = tid < kPairs && pair0 + tid < pair1 ? a.nact[pair0 + tid] : 0, nb = (n_mine + a.batch - 1) / a.batch;
-        int batches;
-        const int before = s3_block_excl_scan<kScatterThreads>(nb, wsum, batches);
-        const int batch0 = (int)((int64_t)batches * part / a.parts), batch1 = (int)((int64_t)batches * (part + 1) / a.parts);      // this part's
-        if (tid < kPairs) {
-            upto[tid] = before + nb;
-            lists[tid] = (uint16_t)n_mine;
-        }
-        if (tid == 0) next_s = 0;
+        const int n_pairs = min(kPairs, pair1 - pair0), n_mine = tid < n_pairs ? a.nact[pair0 + tid] : 0;
+        int lists;
+        const int ahead = s3_block_excl_scan<kScatterThreads>(n_mine, wsum, lists);
+        if (tid < kPairs) upto[tid] = ahead + n_mine;
         __syncthreads();
-        int h, n_list;                                            // the batch that was asked for last
+        const int list1 = (int)((int64_t)lists * (part + 1) / a.parts);      // this part's: [list0, list1)
+        int list0 = (int)((int64_t)lists * part / a.parts);
+        const auto pair_of = [&](int i) {                         // the pair that list i belongs to
+            int q = 0;
+            for (int s = kPairs / 2; s > 0; s >>= 1)
+                if (q + s < n_pairs && upto[q + s - 1] <= i) q += s;
+            return q;
+        };
+        int pair = 0;
         uint4 raw = make_uint4(0, 0, 0, 0);
-        const auto ask = [&]() {                                  // next batch: its weights and features are on their way afterwards
-            int c = 0;
-            if (lane == 0) c = atomicAdd(&next_s, 1);
-            c = __builtin_amdgcn_readfirstlane(c) + batch0;
-            n_list = 0;
-            if (c >= batch1) return;
-            // the pair that batch c belongs to: the eight that it is among, then the one
-            const int x = upto[lane * 8 + 7], j = (int)__popcll(__ballot(x <= c));
-            const int y = upto[j * 8 + (lane & 7)], q = (int)__popcll(__ballot(y <= c) & 0xFFull);
-            const int pair = j * 8 + q, hr = pair0 + pair, r = hr % a.nr;
-            h = hr / a.nr;
-            const int at = (c - (q ? __builtin_amdgcn_readlane(y, max(q - 1, 0)) : (j ? __builtin_amdgcn_readlane(x, max(j - 1, 0)) : 0))) * a.batch;
-            n_list = min(a.batch, (int)lists[pair] - at);
-            if (lane < n_list) raw = *reinterpret_cast<const uint4*>(a.act + (size_t)h * a.n_feat + (size_t)r * kRange + at + lane);
+        const auto ask = [&]() {                                  // a list's weight and feature
+            const int i = list0 + tid;
+            if (i >= list1) return;
+            pair = n_pairs > 1 ? pair_of(i) : 0;
+            const int hr = pair0 + pair, h = hr / a.nr;
+            const int at = i - (pair ? upto[pair - 1] : 0);
+            raw = *reinterpret_cast<const uint4*>(a.act + (size_t)h * a.n_feat + (size_t)(hr - h * a.nr) * kRange + at);
         };
         ask();
-        while (n_list > 0) {
-            const int32_t* off = CMP ? a.cstart + (size_t)h * a.cstart_stride + (size_t)blk * a.n_feat
-                                     : a.offsets + (size_t)h * a.off_stride;
-            const int32_t* tab = !CMP && a.btab ? a.btab + (size_t)h * a.n_feat * nbk : nullptr;
-            const int head = h;
-            int skew;
-            const Vec* const pos = array_of(h, skew);
+        while (list0 < list1) {
+            // without a bound on the segments' lengths, the lists of one pair at a time: their vectors fit 32 bits
+            const int here = a.mixed ? list1 : min(list1, upto[pair_of(list0)]), next = min(here, list0 + kScatterThreads);
             unsigned long long wf = 0;
             int b = 0, e = 0;
-            if (lane < n_list) {
+            uint64_t pos = 0;
+            if (list0 + tid < next) {
+                const int h = (pair0 + pair) / a.nr;
+                const int32_t* off = CMP ? a.cstart + (size_t)h * a.cstart_stride + (size_t)blk * a.n_feat
+                                         : a.offsets + (size_t)h * a.off_stride;
+                const int32_t* tab = !CMP && a.btab ? a.btab + (size_t)h * a.n_feat * nbk : nullptr;
+                pos = CMP ? (uint64_t)(uintptr_t)(a.delta + (size_t)h * a.delta_stride) : (uint64_t)(uintptr_t)(a.positions + (size_t)h * a.pos_stride);
                 const double lw = __longlong_as_double((long long)(((unsigned long long)raw.y << 32) | raw.x));
                 wf = (unsigned long long)llrint(lw * scale);
                 if (wf) {
@@ -486,47 +468,55 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
                     }
                 }
             }
-            ask();
-            const unsigned n = wf ? (unsigned)max(e - b, 0) : 0u, first = (unsigned)b + (unsigned)skew, end = first + n;
-            int nv = n ? (int)(((end + 3) >> 2) - (first >> 2)) : 0;
-            if (nv > kHotVec) {
-                const int q = atomicAdd(&n_hot, 1);
-                if (q < kHotMax) {
-                    hot[q] = Segment{0, first, end, 0};
-                    hot_weight[q] = wf;
-                    hot_head[q] = head;
-                    nv = 0;
-                }
-            }
-            const int vincl = s3_wave_incl_scan(nv), v_at = vincl - nv, total = __builtin_amdgcn_readlane(vincl, 63);
+            list0 = next;
+            const unsigned n = wf ? (unsigned)max(e - b, 0) : 0u;
+            const uint64_t at = pos + (uint64_t)(unsigned)b * sizeof(Posting);
+            const unsigned skip = (unsigned)(at & (sizeof(Vec) - 1)) / (unsigned)sizeof(Posting);
+            const int nv = n ? (int)((skip + n + 3) >> 2) : 0;
+            const int vincl = s3_wave_incl_scan(nv);
             const unsigned long long some = __ballot(nv > 0);
-            s3_wave_fence();                                      // the batch before has read its segments
+            if (lane == 63) { wsum[wave] = vincl; wcnt[wave] = (int)__popcll(some); }
+            __syncthreads();
+            const int vs = s3_row_incl_scan(wsum[lane & (kW - 1)]), cs = s3_row_incl_scan(wcnt[lane & (kW - 1)]);
+            const int total = __builtin_amdgcn_readlane(vs, kW - 1), n_seg = __builtin_amdgcn_readlane(cs, kW - 1);
             if (nv > 0) {
-                const int at = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(some >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)some, 0u));
-                seg[at] = Segment{(int)(first >> 2) - v_at, first, end, 0};
-                weight[at] = wf;
+                const int v_at = (wave ? __builtin_amdgcn_readlane(vs, max(wave - 1, 0)) : 0) + vincl - nv;
+                const int s = (wave ? __builtin_amdgcn_readlane(cs, max(wave - 1, 0)) : 0) +
+                              (int)__builtin_amdgcn_mbcnt_hi((unsigned)(some >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)some, 0u));
+                seg[s] = Segment{at - skip * sizeof(Posting) - (uint64_t)(unsigned)v_at * sizeof(Vec), 4u * (unsigned)v_at + skip, 4u * (unsigned)v_at + skip + n};
+                weight[s] = wf;
+                start[s] = v_at;
             }
-            for (int v0 = 0; v0 < total; v0 += 64 * kFlight) {
-                // a bit for every vector of these 64 kFlight at which a segment starts; owner: starts at or before the vector
-                s3_wave_fence();
-                if (lane < 2 * kFlight) starts[lane] = 0;
-                s3_wave_fence();
-                if (nv > 0 && v_at > v0 && v_at < v0 + 64 * kFlight) atomicOr(&starts[(v_at - v0) >> 5], 1u << ((v_at - v0) & 31));
-                s3_wave_fence();
-                int before = (int)__popcll(__ballot(nv > 0 && v_at <= v0)) - 1;
-                if (!__any(nv > 0 && v_at > v0 && v_at <= v0 + 64 * kFlight) && v0 + 64 * kFlight < total) {
-                    // all of one long segment: whole vectors behind its first one (it goes on behind these)
+            __syncthreads();
+            ask();                                                // the next lists' are on their way beside the postings
+            for (int v0 = wave * 64 * kFlight; v0 < total; v0 += kScatterThreads * kFlight) {
+                // the segment that vector v0 belongs to: the last that starts at or before it
+                const int x = lane * 16 + 15 < n_seg ? start[lane * 16 + 15] : 0x7FFFFFFF, j16 = (int)__popcll(__ballot(x <= v0)) * 16;
+                const int y = j16 + (lane & 15) < n_seg ? start[j16 + (lane & 15)] : 0x7FFFFFFF;
+                int before = j16 + (int)__popcll(__ballot(y <= v0) & 0xFFFFull) - 1;
+                const int v1 = v0 + 64 * kFlight;
+                if (v1 < total && !(before + 1 < n_seg && start[before + 1] <= v1)) {
+                    // all of one segment that goes on behind: whole vectors, but perhaps the first
                     const Segment one = seg[before];
                     const unsigned long long w1 = weight[before];
                     Vec v[kFlight];
 #pragma unroll
-                    for (int u = 0; u < kFlight; ++u) v[u] = pos[one.shift + v0 + u * 64 + lane];
-                    const int e0 = (one.shift + v0 + lane) * 4;
-                    add(v[0], (unsigned)(one.shift + v0) * 4u >= one.first, (unsigned)e0, one.first, one.end, w1);
+                    for (int u = 0; u < kFlight; ++u) v[u] = ((const Vec*)one.base)[v0 + u * 64 + lane];
+                    add(v[0], 4u * (unsigned)v0 >= one.first, 4u * (unsigned)(v0 + lane), one.first, one.end, w1);
 #pragma unroll
                     for (int u = 1; u < kFlight; ++u) add(v[u], true, 0u, 0u, 0u, w1);
                     continue;
                 }
+                // a bit for every vector of these at which a further segment starts; a vector's segment: starts at or before it
+                s3_wave_fence();
+                if (lane < 2 * kFlight) starts[lane] = 0;
+                s3_wave_fence();
+                for (int s = before + 1;; s += 64) {
+                    const int at_v = s + lane < n_seg ? start[s + lane] : 0x7FFFFFFF;
+                    if (at_v < v1) atomicOr(&starts[(at_v - v0) >> 5], 1u << ((at_v - v0) & 31));
+                    if (__ballot(at_v < v1) != ~0ull) break;
+                }
+                s3_wave_fence();
                 Segment sg[kFlight];
                 Vec raw4[kFlight];
                 unsigned long long w[kFlight];
@@ -542,34 +532,14 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
 #pragma unroll
                 for (int u = 0; u < kFlight; ++u) {
                     const int v = v0 + u * 64 + lane;
-                    raw4[u] = pos[v < total ? sg[u].shift + v : (int)(sg[u].first >> 2)];
+                    raw4[u] = ((const Vec*)sg[u].base)[v < total ? v : (int)(sg[u].first >> 2)];
                     if (v >= total) sg[u].end = 0;
-                    sg[u].shift += v;
                 }
 #pragma unroll
-                for (int u = 0; u < kFlight; ++u) add(raw4[u], false, (unsigned)sg[u].shift * 4u, sg[u].first, sg[u].end, w[u]);
+                for (int u = 0; u < kFlight; ++u) add(raw4[u], false, 4u * (unsigned)(v0 + u * 64 + lane), sg[u].first, sg[u].end, w[u]);
             }
+            __syncthreads();                                      // the segments are read
         }
-        __syncthreads();
-    }
-    for (int q = 0, dealt = 0; q < min(n_hot, kHotMax); ++q) {
-        int skew;
-        const Vec* const pos = array_of(hot_head[q], skew);
-        const unsigned first = hot[q].first, end = hot[q].end;
-        const int vend = (int)((end + 3) >> 2), vbeg = (int)(first >> 2), turns = (vend - vbeg + 64 * kFlight - 1) / (64 * kFlight);
-        const unsigned long long w = hot_weight[q];
-        for (int t = (wave - dealt) & (kW - 1); t < turns; t += kW) {
-            const int v0 = vbeg + t * 64 * kFlight + lane;
-            Vec v[kFlight];
-#pragma unroll
-            for (int u = 0; u < kFlight; ++u) v[u] = pos[min(v0 + u * 64, vend - 1)];
-#pragma unroll
-            for (int u = 0; u < kFlight; ++u) {
-                const unsigned e0 = (unsigned)(v0 + u * 64) * 4u;
-                add(v[u], !__any(e0 < first || e0 + 4 > end), e0, first, end, w);
-            }
-        }
-        dealt += turns;
     }
     __syncthreads();
     unsigned long long* const dst = (a.ngroup > 1 ? a.part + (size_t)unit * a.L : a.sfix) + p0;
@@ -1091,14 +1061,13 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.tmaxi = (int*)(base + l.tmaxi);
     a.part = (unsigned long long*)(base + l.part);
     a.pb = l.pb; a.npb = l.npb; a.sorted = v.sorted ? 1 : 0;
-    // Lists that the queries' pairs can name in the heads of a group.  A part has 64 of them or more; a batch is as large as leaves
-    // one for every wavefront.
+    // Lists that the queries' pairs can name in the heads of a group.  A part has 64 of them or more.
     const int64_t pairs = (int64_t)nq * a.k, lists = l.heads_per * (pairs < a.n_feat ? pairs : (int64_t)a.n_feat);
     a.heads_per = l.heads_per;
     a.parts = (int)(lists / 64 < 1 ? 1 : (lists / 64 < l.parts ? lists / 64 : l.parts));
     a.ngroup = l.ngroup / l.parts * a.parts;
-    const int64_t share = (lists / a.parts + 15) / 16;
-    a.batch = (int)(share < 4 ? 4 : (share < 64 ? share : 64));
+    // a segment is at most a block of the compact index or of the block table, else a whole list
+    a.mixed = v.delta || (v.btab && l.npb > 1) || v.tokens < (1 << 20) ? 1 : 0;
     a.tile = kTileW;
     while (a.tile > 256 && a.tile >= 4 * a.len) a.tile >>= 1;
     a.ntile = (int)((a.nW + a.tile - 1) / a.tile);
