@@ -68,7 +68,9 @@ struct TokArgs {
 
 // Step 3: one wavefront per token; lane l holds columns 2 l and 2 l + 1.  The token's ids and values are read once
 // (entry i in lane i % 64, register i / 64; k <= 128) and handed out by readlane, and the decoder rows are fetched
-// four at a time, so that no load waits for the previous row's arithmetic; the sums keep the order of the entries.
+// kRows at a time, so that no load waits for the previous row's arithmetic; the sums keep the order of the entries.
+// Latency bounds it: 4096 x 128 tokens, 16384 latents, k 128: 55 us with four rows in flight, 52 with eight.
+constexpr int kRows = 8;
 __global__ __launch_bounds__(kTokThreads) void tr_token_kernel(TokArgs a) {
     const int lane = threadIdx.x & 63;
     const int t = blockIdx.x * (kTokThreads / 64) + (threadIdx.x >> 6);
@@ -90,18 +92,18 @@ __global__ __launch_bounds__(kTokThreads) void tr_token_kernel(TokArgs a) {
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int kk = min(a.k - 64 * r, 64);
-        for (int i0 = 0; i0 < kk; i0 += 4) {
-            float2 row[4];
-            float v[4];
+        for (int i0 = 0; i0 < kk; i0 += kRows) {
+            float2 row[kRows];
+            float v[kRows];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {        // entries past the end repeat the group's first one with value 0
+            for (int q = 0; q < kRows; ++q) {        // entries past the end repeat the group's first one with value 0
                 const int i = i0 + q < kk ? i0 + q : i0;
                 const int f = __builtin_amdgcn_readlane(my_id[r], i);
                 v[q] = i0 + q < kk ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v[r]), i)) : 0.f;
                 row[q] = *(const float2*)(w_dec + (size_t)f * DH + 2 * lane);
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < kRows; ++q) {
                 acc.x += v[q] * row[q].x;
                 acc.y += v[q] * row[q].y;
             }
@@ -117,12 +119,12 @@ __global__ __launch_bounds__(kTokThreads) void tr_token_kernel(TokArgs a) {
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int kk = min(a.k - 64 * r, 64);
-        for (int i0 = 0; i0 < kk; i0 += 4) {
-            float2 row[4];
-            uint32_t we[4];
-            float v[4], dz[4];
+        for (int i0 = 0; i0 < kk; i0 += kRows) {
+            float2 row[kRows];
+            uint32_t we[kRows];
+            float v[kRows], dz[kRows];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < kRows; ++q) {
                 const int i = i0 + q < kk ? i0 + q : i0;
                 const int f = __builtin_amdgcn_readlane(my_id[r], i);
                 v[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v[r]), i));
@@ -130,12 +132,12 @@ __global__ __launch_bounds__(kTokThreads) void tr_token_kernel(TokArgs a) {
                 we[q] = *(const uint32_t*)(w_bf + (size_t)f * DH + 2 * lane);
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {        // four independent reductions: their lane shifts interleave
+            for (int q = 0; q < kRows; ++q) {        // independent reductions: their lane shifts interleave
                 const float dot = wave_sum(gx * row[q].x + gy * row[q].y);
                 dz[q] = (i0 + q < kk && v[q] > 0.f) ? dot : 0.f;
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < kRows; ++q) {
                 if (lane == 0 && i0 + q < kk) dz_out[64 * r + i0 + q] = dz[q];
                 dux += dz[q] * __uint_as_float(we[q] << 16);
                 duy += dz[q] * __uint_as_float(we[q] & 0xFFFF0000u);
@@ -145,6 +147,16 @@ __global__ __launch_bounds__(kTokThreads) void tr_token_kernel(TokArgs a) {
     *(float2*)(a.du + (size_t)t * DH + 2 * lane) = make_float2(dux, duy);
 }
 
+// Adam (step 7) on one value.
+struct AdamArgs {
+    float lr, b1, b2, eps, c1, c2;      // c1 = 1 - b1^t, c2 = 1 - b2^t
+};
+__device__ __forceinline__ void adam(const AdamArgs& a, float g, float& p, float& m, float& v) {
+    m = a.b1 * m + (1.f - a.b1) * g;
+    v = a.b2 * v + (1.f - a.b2) * g * g;
+    p -= a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+}
+
 struct FeatArgs {
     const int32_t* offsets;
     const int32_t* slots;
@@ -152,24 +164,32 @@ struct FeatArgs {
     const float* dz;
     const float* g;
     const uint16_t* u_bf;
-    float* g_w_enc;
-    float* g_b_enc;
-    float* g_w_dec;
+    float* grads;         // W_enc | b_enc | W_dec | b_dec, or null
+    float* w_enc;
+    float* b_enc;
+    float* w_dec;
+    float* m;             // both moments in the gradients' order
+    float* v;
+    AdamArgs adam;
     int n_feat, k;
     uint32_t kinv;        // ceil(2^32 / k): slot / k for slot < 2^24
-    int per_wg;           // features per workgroup
+    int n_long, per;      // workgroups that look for long lists, features each of them looks at
 };
 
-// Step 5: one wavefront per feature; its postings (flat slot = token * k + slot in the row, ascending) are taken 64 at
-// a time -- each lane fetches one posting's scalars, then the wavefront walks them in order.  A posting is 8 bytes a lane from
-// two rows (latency, four in flight: 0.125 us each), so one list of all 4096 tokens took 511 us: lists of more than kLongList are
-// split over the sixteen wavefronts of the workgroup, whose sums are added in list order (4096 x 128 tokens, a few features in
-// every token's selection).  A workgroup has sixteen features, or fewer where that would be less than a workgroup per compute unit:
-// there the lists are long, and a workgroup takes its long lists one after the other (a step of 4096 tokens, k 128, 128
-// latents: 876 us with a wavefront a list, 1065 with sixteen features a workgroup, 209 now; 8192 x 1024, k 64: 356 / 328 / 220).
-constexpr int kFeatWaves = 16;
-constexpr int kFeatUnits = 256;
-constexpr int kLongList = 128;
+// Step 5, and step 7 for W_enc, b_enc and W_dec: one wavefront per feature; its postings (flat slot = token * k + slot in the
+// row, ascending) are taken 64 at a time -- each lane fetches one posting's scalars, then the wavefront walks them in order.  A
+// posting is 8 bytes a lane from two rows (latency: 0.125 us each with four in flight, eight now), so one list of all 4096 tokens
+// took 511 us: lists of more than kLongList are shared by the wavefronts of a workgroup, whose sums are added in list order
+// (4096 x 128 tokens, a few features in every token's selection).  The first workgroups of the launch look for these, kLongPer
+// features each, so that they run beside the short lists (a launch of their own behind those: 64 + 26 to 40 us after hundreds of
+// steps on one batch, now 71).  Below kFewFeat features lists are long: a workgroup of sixteen wavefronts each (a step of 4096
+// tokens, k 128, 128 latents: 417 us with eight and four features a workgroup, 200 before, now 187).
+// Adam on the feature's two rows and its bias follows at once: the gradients need not be written and read again, and one
+// wavefront's parameters and moments come while others walk lists (4096 x 128 tokens, 16384 latents, k 128: 64 us and 20 for Adam on
+// all parameters -> 67; in workgroups of sixteen features, which all wait for their longest, 97).
+constexpr int kLongList = 256;
+constexpr int kLongPer = 4;
+constexpr int kFewFeat = 4096;
 
 struct FeatSums {
     float ex, ey, dx, dy, sb;
@@ -186,12 +206,12 @@ __device__ __forceinline__ FeatSums feature_sums(const FeatArgs& a, int beg, int
             my_v = a.vals[s];
             my_dz = a.dz[s];
         }
-        for (int q0 = 0; q0 < n; q0 += 4) {      // four postings' rows in flight; the sums keep the posting order
-            float2 gv[4];
-            uint32_t uu[4];
-            float v[4], dz[4];
+        for (int q0 = 0; q0 < n; q0 += kRows) {  // kRows postings' rows in flight; the sums keep the posting order
+            float2 gv[kRows];
+            uint32_t uu[kRows];
+            float v[kRows], dz[kRows];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {        // postings past the end repeat the last one with weights 0
+            for (int j = 0; j < kRows; ++j) {        // postings past the end repeat the last one with weights 0
                 const int q = min(q0 + j, n - 1);
                 const int t = __builtin_amdgcn_readlane(my_t, q);
                 v[j] = q0 + j < n ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), q)) : 0.f;
@@ -200,7 +220,7 @@ __device__ __forceinline__ FeatSums feature_sums(const FeatArgs& a, int beg, int
                 uu[j] = *(const uint32_t*)(a.u_bf + (size_t)t * DH + 2 * lane);
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < kRows; ++j) {
                 r.dx += v[j] * gv[j].x;
                 r.dy += v[j] * gv[j].y;
                 r.ex += dz[j] * __uint_as_float(uu[j] << 16);
@@ -211,28 +231,73 @@ __device__ __forceinline__ FeatSums feature_sums(const FeatArgs& a, int beg, int
     }
     return r;
 }
-__device__ __forceinline__ void feature_store(const FeatArgs& a, int f, int lane, const FeatSums& r) {
-    *(float2*)(a.g_w_enc + (size_t)f * DH + 2 * lane) = make_float2(r.ex, r.ey);
-    *(float2*)(a.g_w_dec + (size_t)f * DH + 2 * lane) = make_float2(r.dx, r.dy);
-    if (lane == 0) a.g_b_enc[f] = r.sb;
+// A feature's parameters and moments: two columns of both rows per lane, the bias in all lanes.  The arrays may lie at any float.
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef f32x2 f32x2u __attribute__((aligned(4)));
+struct FeatState {
+    f32x2 pe, me, ve, pd, md, vd;
+    float pb, mb, vb;
+};
+__device__ __forceinline__ FeatState feature_load(const FeatArgs& a, int f, int lane) {
+    const size_t e = (size_t)f * DH + 2 * lane, nw = (size_t)a.n_feat * DH, b = nw + f, d = nw + a.n_feat + e;
+    FeatState s;
+    s.pe = *(const f32x2u*)(a.w_enc + e);
+    s.me = *(const f32x2u*)(a.m + e);
+    s.ve = *(const f32x2u*)(a.v + e);
+    s.pd = *(const f32x2u*)(a.w_dec + e);
+    s.md = *(const f32x2u*)(a.m + d);
+    s.vd = *(const f32x2u*)(a.v + d);
+    s.pb = a.b_enc[f];
+    s.mb = a.m[b];
+    s.vb = a.v[b];
+    return s;
 }
-__global__ __launch_bounds__(kFeatWaves * 64) void tr_feature_kernel(FeatArgs a) {
-    __shared__ float4 part[kFeatWaves][64];
-    __shared__ float part_b[kFeatWaves];
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int f0 = blockIdx.x * a.per_wg, fn = min(a.per_wg, a.n_feat - f0);
-    int beg = 0, end = 0;
-    if (wv < fn) {
-        beg = a.offsets[f0 + wv];
-        end = a.offsets[f0 + wv + 1];
-        if (end - beg <= kLongList) feature_store(a, f0 + wv, lane, feature_sums(a, beg, end, lane));
+__device__ __forceinline__ void adam2(const AdamArgs& a, float gx, float gy, f32x2& p, f32x2& m, f32x2& v) {
+    float px = p[0], mx = m[0], vx = v[0], py = p[1], my = m[1], vy = v[1];
+    adam(a, gx, px, mx, vx);
+    adam(a, gy, py, my, vy);
+    p = f32x2{px, py};
+    m = f32x2{mx, my};
+    v = f32x2{vx, vy};
+}
+__device__ __forceinline__ void feature_store(const FeatArgs& a, int f, int lane, const FeatSums& r) {
+    FeatState s = feature_load(a, f, lane);
+    const size_t e = (size_t)f * DH + 2 * lane, nw = (size_t)a.n_feat * DH, b = nw + f, d = nw + a.n_feat + e;
+    if (a.grads) {
+        *(f32x2u*)(a.grads + e) = f32x2{r.ex, r.ey};
+        *(f32x2u*)(a.grads + d) = f32x2{r.dx, r.dy};
+        if (lane == 0) a.grads[b] = r.sb;
     }
-    if (!__syncthreads_or(end - beg > kLongList)) return;
-    for (int i = 0; i < fn; ++i) {
-        beg = a.offsets[f0 + i];                 // the same in every wavefront
-        end = a.offsets[f0 + i + 1];
-        if (end - beg <= kLongList) continue;
-        const int per = ((end - beg + kFeatWaves - 1) / kFeatWaves + 3) & ~3;
+    adam2(a.adam, r.ex, r.ey, s.pe, s.me, s.ve);
+    adam2(a.adam, r.dx, r.dy, s.pd, s.md, s.vd);
+    adam(a.adam, r.sb, s.pb, s.mb, s.vb);
+    *(f32x2u*)(a.w_enc + e) = s.pe;
+    *(f32x2u*)(a.m + e) = s.me;
+    *(f32x2u*)(a.v + e) = s.ve;
+    *(f32x2u*)(a.w_dec + e) = s.pd;
+    *(f32x2u*)(a.m + d) = s.md;
+    *(f32x2u*)(a.v + d) = s.vd;
+    if (lane == 0) { a.b_enc[f] = s.pb; a.m[b] = s.mb; a.v[b] = s.vb; }
+}
+template <int W>                             // wavefronts per workgroup
+__global__ __launch_bounds__(W * 64) void tr_feature_kernel(FeatArgs a) {
+    __shared__ float4 part[W][64];
+    __shared__ float part_b[W];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if ((int)blockIdx.x >= a.n_long) {
+        const int f = ((int)blockIdx.x - a.n_long) * W + wv;
+        if (f >= a.n_feat) return;
+        const int beg = a.offsets[f], end = a.offsets[f + 1];
+        if (end - beg <= kLongList) feature_store(a, f, lane, feature_sums(a, beg, end, lane));
+        return;
+    }
+    const int f0 = blockIdx.x * a.per, fn = min(a.per, a.n_feat - f0);
+    const int at = f0 + min(lane, fn - 1);
+    const int my_beg = a.offsets[at], my_end = a.offsets[at + 1];
+    for (unsigned long long todo = __ballot(lane < fn && my_end - my_beg > kLongList); todo; todo &= todo - 1) {
+        const int i = (int)__builtin_ctzll(todo);          // the same in every wavefront
+        const int beg = __builtin_amdgcn_readlane(my_beg, i), end = __builtin_amdgcn_readlane(my_end, i);
+        const int per = ((end - beg + W - 1) / W + kRows - 1) & ~(kRows - 1);
         const FeatSums r = feature_sums(a, min(beg + wv * per, end), min(beg + (wv + 1) * per, end), lane);
         part[wv][lane] = make_float4(r.ex, r.ey, r.dx, r.dy);
         if (lane == 0) part_b[wv] = r.sb;
@@ -240,7 +305,7 @@ __global__ __launch_bounds__(kFeatWaves * 64) void tr_feature_kernel(FeatArgs a)
         if (wv == 0) {
             FeatSums t = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int w = 0; w < kFeatWaves; ++w) {
+            for (int w = 0; w < W; ++w) {
                 const float4 p = part[w][lane];
                 t.ex += p.x;
                 t.ey += p.y;
@@ -255,76 +320,72 @@ __global__ __launch_bounds__(kFeatWaves * 64) void tr_feature_kernel(FeatArgs a)
 }
 
 // Step 6, first half: column sums of g - du and the loss parts of one chunk of tokens, rows in order.
+constexpr int kColRows = 16;
 __global__ __launch_bounds__(DH) void tr_colpart_kernel(const float* g, const float* du, const double* lossp, int B,
                                                         float* colpart, double* losspart) {
     const int c = threadIdx.x, t0 = blockIdx.x * kChunk, t1 = min(B, t0 + kChunk);
     float s = 0.f;
-    for (int t = t0; t < t1; ++t) s += g[(size_t)t * DH + c] - du[(size_t)t * DH + c];
-    colpart[(size_t)blockIdx.x * DH + c] = s;
-    if (c == 0) {
-        double l = 0.0;
-        for (int t = t0; t < t1; ++t) l += lossp[t];
-        losspart[blockIdx.x] = l;
+    double l = 0.0;
+    for (int ta = t0; ta < t1; ta += kColRows) {          // 11 us with one row in flight, 4.7 with sixteen
+        float gv[kColRows], dv[kColRows];
+        double lv[kColRows];
+#pragma unroll
+        for (int j = 0; j < kColRows; ++j) {
+            const size_t t = min(ta + j, t1 - 1);
+            gv[j] = g[t * DH + c];
+            dv[j] = du[t * DH + c];
+            lv[j] = lossp[t];
+        }
+#pragma unroll
+        for (int j = 0; j < kColRows; ++j) {
+            s += ta + j < t1 ? gv[j] - dv[j] : 0.f;
+            l += ta + j < t1 ? lv[j] : 0.0;
+        }
     }
+    colpart[(size_t)blockIdx.x * DH + c] = s;
+    if (c == 0) losspart[blockIdx.x] = l;
 }
-// second half: the chunks in order (eight loads in flight; the loss parts are summed by a wavefront of their own)
+// second half: the chunks in order (32 loads in flight; the loss parts are summed by a wavefront of their own), and Adam on b_dec
+constexpr int kFinRows = 32;
 __global__ __launch_bounds__(2 * DH) void tr_colfin_kernel(const float* __restrict__ colpart, const double* __restrict__ losspart,
-                                                           int nchunk, double inv_n, float* g_b_dec, float* loss_out) {
+                                                           int nchunk, double inv_n, float* g_b_dec, float* b_dec, float* m, float* v,
+                                                           AdamArgs ad, float* loss_out) {
     const int c = threadIdx.x;
     if (c < DH) {
-        float s = 0.f;
-        for (int q0 = 0; q0 < nchunk; q0 += 8) {
-            float v[8];
+        float s = 0.f, pc = b_dec[c], mc = m[c], vc = v[c];
+        for (int q0 = 0; q0 < nchunk; q0 += kFinRows) {
+            float x[kFinRows];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = q0 + j < nchunk ? colpart[(size_t)(q0 + j) * DH + c] : 0.f;
+            for (int j = 0; j < kFinRows; ++j) x[j] = colpart[(size_t)min(q0 + j, nchunk - 1) * DH + c];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) s += v[j];
+            for (int j = 0; j < kFinRows; ++j) s += q0 + j < nchunk ? x[j] : 0.f;
         }
-        g_b_dec[c] = s;
+        if (g_b_dec) g_b_dec[c] = s;
+        adam(ad, s, pc, mc, vc);
+        b_dec[c] = pc;
+        m[c] = mc;
+        v[c] = vc;
     } else if (c == DH) {
         double l = 0.0;
-        for (int q0 = 0; q0 < nchunk; q0 += 8) {
-            double v[8];
+        for (int q0 = 0; q0 < nchunk; q0 += kFinRows) {
+            double x[kFinRows];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = q0 + j < nchunk ? losspart[q0 + j] : 0.0;
+            for (int j = 0; j < kFinRows; ++j) x[j] = losspart[min(q0 + j, nchunk - 1)];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) l += v[j];
+            for (int j = 0; j < kFinRows; ++j) l += q0 + j < nchunk ? x[j] : 0.0;
         }
         loss_out[0] = (float)(l * inv_n);
     }
 }
 
-struct AdamArgs {
-    float* p[4];
-    int64_t end[4];       // end of each parameter array in the packed order W_enc | b_enc | W_dec | b_dec
-    const float* grad;
-    float* m;
-    float* v;
-    float lr, b1, b2, eps, c1, c2;      // c1 = 1 - b1^t, c2 = 1 - b2^t
-};
-
-__global__ void tr_adam_kernel(AdamArgs a) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.end[3]) return;
-    const int seg = i < a.end[0] ? 0 : (i < a.end[1] ? 1 : (i < a.end[2] ? 2 : 3));
-    float* p = a.p[seg] + (i - (seg ? a.end[seg - 1] : 0));
-    const float g = a.grad[i];
-    const float m = a.b1 * a.m[i] + (1.f - a.b1) * g;
-    const float v = a.b2 * a.v[i] + (1.f - a.b2) * g * g;
-    a.m[i] = m;
-    a.v[i] = v;
-    *p -= a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
-}
-
 struct Layout {
-    size_t u_bf, w_bf, ids, vals, ews, g, dz, du, lossp, offsets, slots, grads, colpart, losspart, iws, total, iws_bytes, ews_bytes;
+    size_t u_bf, w_bf, ids, vals, ews, g, dz, du, lossp, offsets, slots, colpart, losspart, iws, total, iws_bytes, ews_bytes;
 };
 
 Layout layout(int B, int n_feat, int k) {
     Layout L;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += s3_align(bytes); return at; };
-    const size_t P = 2 * (size_t)n_feat * DH + n_feat + DH;
     const int nchunk = (B + kChunk - 1) / kChunk;
     L.u_bf = take((size_t)B * DH * 2);
     L.w_bf = take((size_t)n_feat * DH * 2);
@@ -338,7 +399,6 @@ Layout layout(int B, int n_feat, int k) {
     L.lossp = take((size_t)B * 8);
     L.offsets = take((size_t)(n_feat + 1) * 4);
     L.slots = take((size_t)B * k * 4);
-    L.grads = take(P * 4);
     L.colpart = take((size_t)nchunk * DH * 4);
     L.losspart = take((size_t)nchunk * 8);
     L.iws_bytes = s3_index_build_workspace(B * k, 1, n_feat);
@@ -388,7 +448,6 @@ int s3_sae_train_step(const float* x, int B, int d_head, int n_feat, int k, floa
     double* lossp = (double*)(base + L.lossp);
     int32_t* offsets = (int32_t*)(base + L.offsets);
     int32_t* slots = (int32_t*)(base + L.slots);
-    float* grads = grads_out ? grads_out : (float*)(base + L.grads);
     float* colpart = (float*)(base + L.colpart);
     double* losspart = (double*)(base + L.losspart);
     const int64_t n_x = (int64_t)B * DH, n_w = (int64_t)n_feat * DH;
@@ -403,27 +462,20 @@ int s3_sae_train_step(const float* x, int B, int d_head, int n_feat, int k, floa
     hipLaunchKernelGGL(tr_token_kernel, dim3((unsigned)((B + 3) / 4)), dim3(kTokThreads), 0, st, ta);
     rc = s3_index_build(ids, nullptr, B * k, 1, n_feat, offsets, slots, base + L.iws, L.iws_bytes, stream);
     if (rc) return rc;
-    float* g_w_enc = grads;
-    float* g_b_enc = g_w_enc + n_w;
-    float* g_w_dec = g_b_enc + n_feat;
-    float* g_b_dec = g_w_dec + n_w;
-    FeatArgs fa{offsets, slots, vals, dz, g, u_bf, g_w_enc, g_b_enc, g_w_dec, n_feat, k,
+    const AdamArgs ad{lr, beta1, beta2, eps, (float)(1.0 - pow((double)beta1, (double)step)), (float)(1.0 - pow((double)beta2, (double)step))};
+    const bool few = n_feat < kFewFeat;
+    const int per = few ? 1 : kLongPer;
+    FeatArgs fa{offsets, slots, vals, dz, g, u_bf, grads_out, w_enc, b_enc, w_dec, adam_m, adam_v, ad, n_feat, k,
                 k > 1 ? (uint32_t)(((1ull << 32) + (uint32_t)k - 1) / (uint32_t)k) : 0u,
-                n_feat >= kFeatWaves * kFeatUnits ? kFeatWaves : (n_feat + kFeatUnits - 1) / kFeatUnits};
-    hipLaunchKernelGGL(tr_feature_kernel, dim3((unsigned)((n_feat + fa.per_wg - 1) / fa.per_wg)), dim3(kFeatWaves * 64), 0, st, fa);
+                B > kLongList ? (n_feat + per - 1) / per : 0, per};
+    const int waves = few ? 16 : 8;
+    hipLaunchKernelGGL(few ? tr_feature_kernel<16> : tr_feature_kernel<8>, dim3((unsigned)(fa.n_long + (n_feat + waves - 1) / waves)), dim3(waves * 64), 0, st, fa);
     const int nchunk = (B + kChunk - 1) / kChunk;
     hipLaunchKernelGGL(tr_colpart_kernel, dim3((unsigned)nchunk), dim3(DH), 0, st, (const float*)g, (const float*)du,
                        (const double*)lossp, B, colpart, losspart);
+    const int64_t at_b = 2 * n_w + n_feat;               // of b_dec among all parameters
     hipLaunchKernelGGL(tr_colfin_kernel, dim3(1), dim3(2 * DH), 0, st, (const float*)colpart, (const double*)losspart, nchunk,
-                       1.0 / ((double)B * DH), g_b_dec, loss_out);
-    AdamArgs aa;
-    aa.p[0] = w_enc; aa.p[1] = b_enc; aa.p[2] = w_dec; aa.p[3] = b_dec;
-    aa.end[0] = n_w; aa.end[1] = n_w + n_feat; aa.end[2] = 2 * n_w + n_feat; aa.end[3] = 2 * n_w + n_feat + DH;
-    aa.grad = grads; aa.m = adam_m; aa.v = adam_v;
-    aa.lr = lr; aa.b1 = beta1; aa.b2 = beta2; aa.eps = eps;
-    aa.c1 = (float)(1.0 - pow((double)beta1, (double)step));
-    aa.c2 = (float)(1.0 - pow((double)beta2, (double)step));
-    hipLaunchKernelGGL(tr_adam_kernel, dim3((unsigned)((aa.end[3] + 255) / 256)), dim3(256), 0, st, aa);
+                       1.0 / ((double)B * DH), grads_out ? grads_out + at_b : nullptr, b_dec, adam_m + at_b, adam_v + at_b, ad, loss_out);
     S3_HIP(hipGetLastError());
     return S3_OK;
 }

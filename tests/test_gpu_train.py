@@ -148,3 +148,30 @@ def test_lists_that_several_wavefronts_share(B, n_feat, k):
     M, V = [np.zeros_like(p) for p in P64], [np.zeros_like(p) for p in P64]
     tr = s3.SaeTrainer(*[torch.from_numpy(p).cuda() for p in P], k=k, batch=B)
     check_step(tr, x, P64, M, V, k, 1, 1e-3)
+
+
+@pytest.mark.parametrize("B,n_feat,k,hot", [
+    (256, 256, 8, 3), (257, 256, 8, 3),          # lists of as many postings as one wavefront takes, and of one more
+    (600, 3968, 16, 9), (600, 4096, 16, 9),      # a workgroup for each of few features; four features each from here on
+    (1030, 4224, 40, 30),
+])
+def test_long_posting_lists(B, n_feat, k, hot):
+    """`hot` features, neighbours among them, are in every token's selection; encoder rows at an odd place in memory."""
+    import torch
+    import paper_2601_17702_amd as s3
+    lr = 1e-3
+    x, P32 = make_problem(B + n_feat, B, n_feat)
+    rng = np.random.default_rng(B)
+    u = rng.standard_normal(128).astype(np.float32)
+    u /= np.linalg.norm(u)
+    x += 9 * u                                   # a direction that all tokens share, and the hot features look along
+    at = rng.permutation(np.r_[0:2, 5:6, n_feat - hot:n_feat])[:hot]
+    P32[0][at] = u + 0.02 * rng.standard_normal((hot, 128)).astype(np.float32)
+    gpu = [torch.from_numpy(p.copy()).cuda() for p in P32]
+    room = torch.empty(gpu[0].numel() + 1, device="cuda")
+    gpu[0] = room[1:].view_as(gpu[0]).copy_(gpu[0])
+    tr = s3.SaeTrainer(*gpu, k=k, batch=B, lr=lr)
+    P64 = [p.astype(np.float64) for p in P32]
+    M = [np.zeros_like(p) for p in P64]
+    V = [np.zeros_like(p) for p in P64]
+    check_step(tr, x, P64, M, V, k, 1, lr)
