@@ -85,6 +85,7 @@ struct ScanArgs {
     int vec;                         // outputs can be written 16 bytes at a time
     uint2* list;                     // [slot][wave][cap][128]
     int* count;                      // [tile][part][wave][128] (parts > 1)
+    int* few;                        // [tile] whether a token has too few candidates (parts > 1)
     float* norm;                     // [n_heads * T] (parts > 1, streamed)
     float* tau0;                     // [n_heads * T]
     const float* hint;               // [n_heads][2] or null
@@ -669,6 +670,7 @@ __global__ __launch_bounds__(kThreads, 2) void enc_scan_kernel(ScanArgs a) {
         const int tok0 = tt * kTokWG + wv * kTokWave;
         const bool active = tok0 < a.T, mine = tok0 + lane < a.T;     // lane t answers for token t of the wavefront
         const int tile = head * a.tiles_per_head + tt;
+        if (REDO && a.few[tile] == 0) continue;
         const size_t slot = a.parts > 1 ? (size_t)tile * a.parts + part : blockIdx.x;
         uint2* const list = a.list + (slot * kWaves + wv) * wstride;
         int* const count = a.count + (size_t)tile * a.parts * (kWaves * kLanes) + wv * kLanes;
@@ -879,6 +881,7 @@ __global__ __launch_bounds__(64 * TOK) void enc_join_kernel(ScanArgs a) {
         const int c = p < lists ? a.count[part * (kWaves * kLanes) + w * kLanes + l] : 0;
         const int incl = s3_wave_incl_scan(lane < lists ? c : 0);
         const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (total < a.k && lane == 0) a.few[tile] = 1;
         if (total >= a.k) {
             const uint2* const src = a.list + (part * kWaves + w) * wstride + l;
             const int most = (int)s3_wave_max_u32((unsigned)c);
@@ -976,6 +979,8 @@ __global__ __launch_bounds__(kThreads) void enc_start_kernel(ScanArgs a) {
         for (int i = tid; i < 2 * a.n_heads; i += kThreads) a.hint_out[i] = 0xFFFFFFFFu;
         for (int i = tid; i < 3 * a.n_heads; i += kThreads) a.hint_sum[i] = 0.f;
     }
+    if (a.parts > 1 && blockIdx.x == 0)
+        for (int i = tid; i < a.n_tiles; i += kThreads) a.few[i] = 0;
     constexpr int kTok = WS > 1 ? kTokWave : kTokWG;
     const int per_head = (a.T + kTok - 1) / kTok;
     for (int unit = blockIdx.x; unit < a.n_heads * per_head; unit += gridDim.x) {
@@ -1067,7 +1072,7 @@ __global__ void enc_carry_kernel(ScanArgs a) {
 // How a call is laid out.
 struct Plan {
     int tiles_per_head, n_tiles, parts, per, cap, sample, units;
-    size_t fail, hout, hsum, tau0, norm, count, list, total;
+    size_t fail, hout, hsum, few, tau0, norm, count, list, total;
 };
 constexpr int kMaxParts = 16;
 constexpr int kFewTiles = 128;          // so many tiles or fewer are split: 256 tiles in two ranges each waited longer for their join (k 128: 916 / 617 us)
@@ -1092,6 +1097,7 @@ Plan plan(int n_heads, int T, int n_feat, int k) {
     p.fail = take((size_t)n_heads * 4);
     p.hout = take((size_t)n_heads * 8);
     p.hsum = take((size_t)n_heads * 12);
+    p.few = take(p.parts > 1 ? (size_t)kFewTiles * 4 : 0);
     p.tau0 = take((size_t)n_heads * T * 4);
     p.norm = take(p.parts > 1 ? (size_t)n_heads * T * 4 : 0);
     p.count = take((size_t)p.units * kWaves * kLanes * 4);
@@ -1155,7 +1161,7 @@ size_t s3_encode_scan_workspace_max(int n_heads, int T) {
     const long long split = tiles > kFewTiles ? kSlots : (tiles * kMaxParts < kSlots ? tiles * kMaxParts : kSlots), whole = tiles < kSlots ? tiles : kSlots;
     const long long units = split > whole ? split : whole;
     const size_t tokens = (size_t)n_heads * T, norms = tokens < (size_t)kFewTiles * kTokWG ? tokens : (size_t)kFewTiles * kTokWG;
-    return s3_align((size_t)n_heads * 4) + s3_align((size_t)n_heads * 8) + s3_align((size_t)n_heads * 12) + s3_align(tokens * 4) +
+    return s3_align((size_t)n_heads * 4) + s3_align((size_t)n_heads * 8) + s3_align((size_t)n_heads * 12) + s3_align(kFewTiles * 4) + s3_align(tokens * 4) +
            s3_align(norms * 4) + s3_align((size_t)units * kWaves * kLanes * 4) + s3_align((size_t)units * kWaves * kLanes * cap_of(S3_MAX_K) * sizeof(uint2));
 }
 
@@ -1176,6 +1182,7 @@ int s3_encode_scan(const EncParams& e, float* hint, void* ws, hipStream_t st) {
     a.hint_out = (unsigned*)(base + p.hout);
     a.hint_sum = (float*)(base + p.hsum);
     a.n_fail = (int*)(base + p.fail);
+    a.few = (int*)(base + p.few);
     switch (sample_rank(e.k)) {
         case 8: launch_start<8>(a, st); break;
         case 12: launch_start<12>(a, st); break;
