@@ -96,12 +96,13 @@ __device__ __forceinline__ int split_rank(const int* cnt_row, unsigned m) {
     return cnt_row[m & 0xFFu] + (int)((m >> 8) & 0x3FFFu);
 }
 
-// cnt: [kSplitWaves][nd] counts -> running bases; dstart[d] / dcount[d]: first rank and number of entries of digit d
+// cnt: [NT / 64][nd] counts -> running bases; dstart[d] / dcount[d]: first rank and number of entries of digit d
+template <int NT = kSplitThreads>
 __device__ __forceinline__ void split_scan(int* cnt, int nd, int* dstart, int* dcount, int* wsum) {
     const int tid = threadIdx.x;
-    constexpr int per = kSplitWaves * 256 / kSplitThreads;     // 4 entries per thread when nd = 256
-    // entry e = d * kSplitWaves + w; thread t owns e = per t .. per t + per - 1 (one digit: per divides kSplitWaves)
-    const int d = tid * per / kSplitWaves, w0 = tid * per % kSplitWaves;
+    constexpr int W = NT / 64, per = 4;                        // entries per thread: W * 256 of them when nd = 256
+    // entry e = d * W + w; thread t owns e = per t .. per t + per - 1 (one digit: per divides W)
+    const int d = tid * per / W, w0 = tid * per % W;
     int v[per], s = 0;
 #pragma unroll
     for (int j = 0; j < per; ++j) {
@@ -109,7 +110,7 @@ __device__ __forceinline__ void split_scan(int* cnt, int nd, int* dstart, int* d
         s += v[j];
     }
     int tot;
-    int ex = s3_block_excl_scan<kSplitThreads>(s, wsum, tot);
+    int ex = s3_block_excl_scan<NT>(s, wsum, tot);
     if (d < nd) {
         int run = ex;
 #pragma unroll
@@ -118,11 +119,11 @@ __device__ __forceinline__ void split_scan(int* cnt, int nd, int* dstart, int* d
             run += v[j];
         }
     }
-    // the kSplitWaves / per threads of a digit are adjacent lanes: their sum is the digit's count
-    static_assert(kSplitWaves / per == 2 || kSplitWaves / per == 4, "a digit's threads are an aligned group of 2 or 4 lanes");
+    // the W / per threads of a digit are adjacent lanes: their sum is the digit's count
+    static_assert(W / per == 1 || W / per == 4, "a digit's threads are one lane or an aligned group of 4 lanes");
     int dc = s;
-    dc += __builtin_amdgcn_update_dpp(0, dc, 0xB1, 0xf, 0xf, false);     // lanes 1 0 3 2 of each group of four
-    if (kSplitWaves / per == 4) dc += __builtin_amdgcn_update_dpp(0, dc, 0x4E, 0xf, 0xf, false);     // lanes 2 3 0 1
+    if (W / per == 4) dc += __builtin_amdgcn_update_dpp(0, dc, 0xB1, 0xf, 0xf, false);     // lanes 1 0 3 2 of each group of four
+    if (W / per == 4) dc += __builtin_amdgcn_update_dpp(0, dc, 0x4E, 0xf, 0xf, false);     // lanes 2 3 0 1
     if (d < nd && w0 == 0) { dstart[d] = ex; dcount[d] = dc; }
     __syncthreads();
 }
@@ -232,16 +233,16 @@ __global__ __launch_bounds__(256) void idx_bucket_scan_kernel(IdxDev d) {
 // entries read one after the other, 1024 pieces were 64 such chains in a row.  So the words come from LDS, a half wavefront takes a
 // piece (32 entries where 256 buckets share 8192) and has four pieces, or four loads of a long one, in flight: the one-shot index of
 // 131072 tokens, k 64, 65536 features (one workgroup per bucket) 115.4 -> 105.6 us.
-template <class E>
+template <int NT, class E>
 __device__ __forceinline__ void count_pieces(const E* in, int tile_post, const uint32_t* pinfo, int m, uint32_t mask, int* hist) {
     const int hw = threadIdx.x >> 5, l0 = threadIdx.x & 31;
-    for (int j0 = hw; j0 < m; j0 += 4 * (kSplitThreads / 32)) {
+    for (int j0 = hw; j0 < m; j0 += 4 * (NT / 32)) {
         const E* sp[4];
         int cc[4];
         uint32_t v[4], v2[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int j = j0 + q * (kSplitThreads / 32);
+            const int j = j0 + q * (NT / 32);
             const uint32_t pj = j < m ? pinfo[j] : 0u;
             cc[q] = (int)(pj & 0xFFFFu);
             sp[q] = in + (size_t)(j < m ? j : 0) * tile_post + (pj >> 16);
@@ -271,22 +272,30 @@ __device__ __forceinline__ void count_pieces(const E* in, int tile_post, const u
 // One (head, bucket): gather its pieces in tile order, split by the low feature bits, write the CSR.
 // A bucket of at most kSortCap postings (the usual case) is done in one round: its sorted positions are
 // staged in LDS and written as one contiguous run.  A larger bucket (a very frequent feature) is counted
-// first and then taken in rounds of whole pieces, each round writing behind per-feature cursors.
-template <int NBITS>
-__global__ __launch_bounds__(kSplitThreads, kSplitOcc) void idx_bucket_sort_kernel(IdxDev d, int n_tiles) {
+// first and then taken in rounds of whole pieces, each round writing its sorted positions behind per-feature cursors.
+// NT: threads; a round takes as many postings with 256 as with 1024.  With 256 four workgroups share a compute unit instead of two and a
+// barrier waits for four wavefronts instead of sixteen: few_threads() says where the line lies.
+// ORDERED: the positions of several rounds go out in sorted order (run_finalize).
+template <int NBITS, int NT, bool ORDERED = false>
+__global__ __launch_bounds__(NT, NT == kSplitThreads ? kSplitOcc : 4) void idx_bucket_sort_kernel(IdxDev d, int n_tiles) {
     extern __shared__ __align__(16) uint32_t dyn[];
+    constexpr int W = NT / 64, R = kSortCap / NT;
+    static_assert(!ORDERED || (2 * NT + 1) * 4 >= kSortCap, "room for the digits of a round");
     uint32_t* bufa = dyn;                          // [kSortCap] gathered entries of the round; once every wavefront
     int32_t* bufb = (int32_t*)dyn;                 // holds its entries in registers: the sorted positions (same memory)
-    int* pref = (int*)(dyn + kSortCap);            // [kSplitThreads + 1]
-    uint32_t* pinfo = (uint32_t*)(pref + kSplitThreads + 1);   // [kSplitThreads] piece words of the round
-    int* wsum = (int*)(pinfo + kSplitThreads);     // [16]
-    int* hist = wsum + 16;                         // [256] whole-bucket counts (before the first round only)
+    int* pref = (int*)(dyn + kSortCap);            // [NT + 1]
+    uint32_t* pinfo = (uint32_t*)(pref + NT + 1);  // [NT] piece words of the round
+    uint8_t* digit = (uint8_t*)pref;               // [kSortCap] (ORDERED) digits of the sorted positions, once the pieces are gathered
+    int* wsum = (int*)(pinfo + NT);                // [16]
+    int* hist = wsum + 16;                         // [nd] whole-bucket counts (before the first round only)
     int* rcount = hist;                            //       per-round counts afterwards
-    int* cursor = hist + 256;                      // [256]
-    int* rstart = cursor + 256;                    // [256]
-    int* lstart = rstart + 256;                    // [256] where each list starts in the head's positions array
-    int* nextj = lstart + 256;                     // [256] first block whose start in the list is not known yet
-    int* cnt = nextj + 256;                        // [kSplitWaves << S]
+    const int nd = 1 << d.S;
+    const int nds = NT == kSplitThreads ? 256 : nd;
+    int* cursor = hist + nds;                      // [nd] each
+    int* rstart = cursor + nds;
+    int* lstart = rstart + nds;                    // where each list starts in the head's positions array
+    int* nextj = lstart + nds;                     // first block whose start in the list is not known yet
+    int* cnt = nextj + nds;                        // [W << S]
 
     const int tid = threadIdx.x, lane = tid & 63, head = blockIdx.y;
     // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  The pieces of adjacent buckets are
@@ -299,7 +308,6 @@ __global__ __launch_bounds__(kSplitThreads, kSplitOcc) void idx_bucket_sort_kern
     uint32_t p_next = tid < n_tiles ? pc[tid] : 0u;
     const int n_b = d.total[(size_t)head * d.NB + b];
     const int out_base = d.bbase[(size_t)head * (d.NB + 1) + b];
-    const int nd = 1 << d.S;
     const int nfl = min(nd, d.n_feat - (b << d.S));
     const uint32_t mask = (1u << d.S) - 1u;
     int32_t* offs = d.offsets + (size_t)head * d.off_stride + ((size_t)b << d.S);
@@ -315,23 +323,23 @@ __global__ __launch_bounds__(kSplitThreads, kSplitOcc) void idx_bucket_sort_kern
     // entry i of the head's intermediate array (16-bit entries carry the row inside their tile: the caller adds the tile's first row)
     const uint16_t* inter16 = (const uint16_t*)d.inter + (size_t)head * d.inter_stride;
     int32_t* posout = d.positions + (size_t)head * d.pos_stride;
-    const bool multi = n_b > kSortCap || n_tiles > kSplitThreads;   // more than one round of pieces
+    const bool multi = n_b > kSortCap || n_tiles > NT;   // more than one round of pieces
 
-    if (tid < 256) nextj[tid] = 1;
+    if (tid < nd) nextj[tid] = 1;
     if (multi) {   // count the whole bucket first: the CSR offsets are needed before the first round is written
-        if (tid < 256) hist[tid] = 0;
+        if (tid < nd) hist[tid] = 0;
         __syncthreads();
-        for (int t0 = 0; t0 < n_tiles; t0 += kSplitThreads) {
-            const int m = min(n_tiles - t0, kSplitThreads);
+        for (int t0 = 0; t0 < n_tiles; t0 += NT) {
+            const int m = min(n_tiles - t0, NT);
             if (t0) __syncthreads();               // the piece words before are still being read
             pinfo[tid] = t0 == 0 ? p_next : (tid < m ? pc[t0 + tid] : 0u);
             __syncthreads();
-            if (d.w16) count_pieces(inter16 + (size_t)t0 * d.tile_post, d.tile_post, pinfo, m, mask, hist);
-            else count_pieces(d.inter + (size_t)head * d.inter_stride + (size_t)t0 * d.tile_post, d.tile_post, pinfo, m, mask, hist);
+            if (d.w16) count_pieces<NT>(inter16 + (size_t)t0 * d.tile_post, d.tile_post, pinfo, m, mask, hist);
+            else count_pieces<NT>(d.inter + (size_t)head * d.inter_stride + (size_t)t0 * d.tile_post, d.tile_post, pinfo, m, mask, hist);
         }
         __syncthreads();
         int tot;
-        int ex = s3_block_excl_scan<kSplitThreads>(tid < nd ? hist[tid] : 0, wsum, tot);
+        int ex = s3_block_excl_scan<NT>(tid < nd ? hist[tid] : 0, wsum, tot);
         if (tid < nd) cursor[tid] = lstart[tid] = out_base + ex;
         if (tid < nfl) offs[tid] = out_base + ex;
         __syncthreads();
@@ -342,24 +350,24 @@ __global__ __launch_bounds__(kSplitThreads, kSplitOcc) void idx_bucket_sort_kern
         const uint32_t p = p_next;
         const int c = (int)(p & 0xFFFFu);
         int tot;
-        const int ex = s3_block_excl_scan<kSplitThreads>(c, wsum, tot);
+        const int ex = s3_block_excl_scan<NT>(c, wsum, tot);
         pref[tid] = ex;
         pinfo[tid] = p;
-        if (tid == kSplitThreads - 1) pref[kSplitThreads] = tot;
+        if (tid == NT - 1) pref[NT] = tot;
         int m = __syncthreads_count(ex + c <= kSortCap);    // prefix property: the first m threads qualify
         m = min(m, n_tiles - tp);
         const int n_r = pref[m];
         // gather: a half wavefront copies one piece, four pieces per step
         {
             const int hw = tid >> 5, l0 = tid & 31;
-            for (int j0 = hw; j0 < m; j0 += 4 * (kSplitThreads / 32)) {
+            for (int j0 = hw; j0 < m; j0 += 4 * (NT / 32)) {
                 size_t sp[4];                      // first entry of the piece in the head's intermediate array
                 int dst[4], cc[4];
                 uint32_t v[4], v2[4], add[4];      // add: what turns a 16-bit entry into the 32-bit form (its tile's first row)
                 const uint32_t* in32 = d.inter + (size_t)head * d.inter_stride;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int j = j0 + q * (kSplitThreads / 32);
+                    const int j = j0 + q * (NT / 32);
                     const uint32_t pj = j < m ? pinfo[j] : 0u;
                     const int tile = tp + (j < m ? j : 0);
                     cc[q] = (int)(pj & 0xFFFFu);
@@ -391,15 +399,15 @@ __global__ __launch_bounds__(kSplitThreads, kSplitOcc) void idx_bucket_sort_kern
                         bufa[dst[q] + l] = (d.w16 ? (uint32_t)inter16[sp[q] + l] : in32[sp[q] + l]) + add[q];
             }
         }
-        for (int i = tid; i < kSplitWaves * nd; i += kSplitThreads) cnt[i] = 0;
+        for (int i = tid; i < W * nd; i += NT) cnt[i] = 0;
         __syncthreads();
 
         int* row = cnt + wave * nd;
-        const int seg = ((n_r + kSplitWaves - 1) / kSplitWaves + 63) & ~63;      // entries per wavefront (<= 64 kSplitRounds)
-        int32_t pos[kSplitRounds];
-        unsigned meta[kSplitRounds];       // split_round()
+        const int seg = ((n_r + W - 1) / W + 63) & ~63;      // entries per wavefront (<= 64 R)
+        int32_t pos[R];
+        unsigned meta[R];       // split_round()
 #pragma unroll
-        for (int r = 0; r < kSplitRounds; ++r) {
+        for (int r = 0; r < R; ++r) {
             if (r * 64 >= seg) {          // uniform: this round is past the wavefront's share
                 meta[r] = 0u;
                 pos[r] = 0;
@@ -412,7 +420,7 @@ __global__ __launch_bounds__(kSplitThreads, kSplitOcc) void idx_bucket_sort_kern
             pos[r] = d.pos_affine ? d.pos0 + (int32_t)(e >> d.S) : d.pos_log[e >> d.S];
         }
 #pragma unroll
-        for (int r = 0; r < kSplitRounds; ++r) {
+        for (int r = 0; r < R; ++r) {
             if (r * 64 >= seg) {          // uniform: this round is past the wavefront's share
                 meta[r] = 0u;
                 continue;
@@ -421,21 +429,22 @@ __global__ __launch_bounds__(kSplitThreads, kSplitOcc) void idx_bucket_sort_kern
             meta[r] = split_round<NBITS>(row, meta[r] & mask, valid);
         }
         __syncthreads();
-        split_scan(cnt, nd, rstart, rcount, wsum);
+        split_scan<NT>(cnt, nd, rstart, rcount, wsum);
         if (!multi && tid < nfl) offs[tid] = out_base + rstart[tid];
         if (multi) {
 #pragma unroll
-            for (int r = 0; r < kSplitRounds; ++r)
+            for (int r = 0; r < R; ++r)
                 if (r * 64 < seg && (meta[r] & kSplitValid)) {
                     const unsigned fl = meta[r] & 0xFFu;
                     const int i = split_rank(row, meta[r]);
-                    posout[cursor[fl] + (i - rstart[fl])] = pos[r];
-                    if (nbk) bufb[i] = pos[r];
+                    if (ORDERED) digit[i] = (uint8_t)fl;
+                    else posout[cursor[fl] + (i - rstart[fl])] = pos[r];
+                    if (ORDERED || nbk) bufb[i] = pos[r];
                 }
         } else {
             if (tid < nd) lstart[tid] = out_base + rstart[tid];
 #pragma unroll
-            for (int r = 0; r < kSplitRounds; ++r)
+            for (int r = 0; r < R; ++r)
                 if (r * 64 < seg && (meta[r] & kSplitValid)) bufb[split_rank(row, meta[r])] = pos[r];
         }
         __syncthreads();
@@ -461,10 +470,17 @@ __global__ __launch_bounds__(kSplitThreads, kSplitOcc) void idx_bucket_sort_kern
             nextj[tid] = j;
         }
         if (multi) {
+            if (ORDERED) {
+                for (int i = tid; i < n_r; i += NT) {
+                    const int fl = digit[i];
+                    posout[cursor[fl] + (i - rstart[fl])] = bufb[i];
+                }
+                __syncthreads();
+            }
             if (tid < nd) cursor[tid] += rcount[tid];
         } else {
             if (tid < nd) cursor[tid] = lstart[tid] + rcount[tid];
-            for (int i = tid; i < n_r; i += kSplitThreads) posout[out_base + i] = bufb[i];
+            for (int i = tid; i < n_r; i += NT) posout[out_base + i] = bufb[i];
         }
         tp += m;
         if (tp < n_tiles) p_next = tp + tid < n_tiles ? pc[tp + tid] : 0u;
@@ -481,9 +497,9 @@ __global__ void idx_fill_positions_kernel(int32_t* dst, int n, int32_t base) {
     if (i < n) dst[i] = base + i;
 }
 
-size_t bucket_sort_lds(int S) {
-    return (size_t)kSortCap * 4 + (kSplitThreads + 1) * 4 + kSplitThreads * 4 + 16 * 4 + 5 * 256 * 4 +
-           ((size_t)kSplitWaves << S) * 4;
+size_t bucket_sort_lds(int S, int threads) {
+    const size_t per_digit = (size_t)5 * (threads == kSplitThreads ? 256 : 1 << S) * 4 + ((size_t)(threads / 64) << S) * 4;
+    return (size_t)kSortCap * 4 + (2 * threads + 1) * 4 + 16 * 4 + per_digit;
 }
 
 struct Geometry {
@@ -512,15 +528,40 @@ int run_partition(const int32_t* src, int64_t head_stride, int rows, int tile0, 
     return S3_OK;
 }
 
-int run_finalize(const IdxDev& d, int n_heads, int n_tiles, hipStream_t st) {
+// Threads of the bucket sort: 256, four workgroups to a compute unit, where there are workgroups enough to fill the chip twice and an
+// average bucket is small against their number.  A frequent feature's bucket is one workgroup's chain of rounds, slower with fewer
+// threads: the more workgroups there are, the more work hides it.  The piece words of a bucket have to fit one load: 256 tiles at most.
+// Whole finalize, 1024 -> 256 threads, even features / one feature in every token and the rest skewed:
+//     256 heads x 2048 tokens, k 32, 16384 features (65536 buckets of 256)      870 -> 569 us      874 -> 560
+//       8 x 3000, k 128                             ( 2048 of 1500)            64.1 -> 55.8       61.0 -> 53.3
+//      64 x 32768, k 32                             (16384 of 4096)             591 -> 577         860 -> 841
+//       4 x 16384, k 32                             ( 1024 of 2048)            38.5 -> 33.0       74.4 -> 121.9: stays with 1024
+//       1 x 8192, k 32                              (  256 of 1024)            22.8 -> 23.7       35.2 -> 44.0: stays with 1024
+constexpr int kSmallThreads = 256, kSmallGroups = 2048;
+
+bool few_threads(const IdxDev& d, int n_heads, int n_tiles, int64_t tokens) {
+    const int64_t groups = (int64_t)d.NB * n_heads, most = std::min<int64_t>(kSortCap, groups * 3 / 4);
+    return n_tiles <= kSmallThreads && groups >= kSmallGroups && tokens * d.k <= most * d.NB;
+}
+
+int run_finalize(const IdxDev& d, int n_heads, int n_tiles, int64_t tokens, hipStream_t st) {
     hipLaunchKernelGGL(idx_totals_kernel, dim3(d.NB, n_heads), dim3(256), 0, st, d, n_tiles);
     hipLaunchKernelGGL(idx_bucket_scan_kernel, dim3(n_heads), dim3(256), 0, st, d);
     // one ballot per low feature bit: the widths that the supported SAE sizes use most get their own build
-    const dim3 grid(d.NB, n_heads), block(kSplitThreads);
-    const size_t lds = bucket_sort_lds(d.S);       // < 64 KB: two workgroups per compute unit
-    if (d.S <= 6) hipLaunchKernelGGL(idx_bucket_sort_kernel<6>, grid, block, lds, st, d, n_tiles);
-    else if (d.S == 7) hipLaunchKernelGGL(idx_bucket_sort_kernel<7>, grid, block, lds, st, d, n_tiles);
-    else hipLaunchKernelGGL(idx_bucket_sort_kernel<8>, grid, block, lds, st, d, n_tiles);
+    const bool small = few_threads(d, n_heads, n_tiles, tokens);
+    const int nt = small ? kSmallThreads : kSplitThreads;
+    const dim3 grid(d.NB, n_heads), block(nt);
+    const size_t lds = bucket_sort_lds(d.S, nt);       // < 64 KB: two workgroups per compute unit, four of 256 threads
+    constexpr int F = kSmallThreads, A = kSplitThreads;
+    auto sort = d.S <= 6 ? idx_bucket_sort_kernel<6, A> : d.S == 7 ? idx_bucket_sort_kernel<7, A> : idx_bucket_sort_kernel<8, A>;
+    if (small) sort = d.S <= 6 ? idx_bucket_sort_kernel<6, F> : d.S == 7 ? idx_bucket_sort_kernel<7, F> : idx_bucket_sort_kernel<8, F>;
+    // Several rounds: a lane that writes where it ranked its entry has a list of its own, so where buckets are that long on average the
+    // positions go out in sorted order, neighbours mostly of one list (256 buckets of 32768, 131072 tokens, k 64, 65536 features: this
+    // kernel 85 -> 65 us).  It costs a barrier a round, which a frequent feature's chain of rounds feels: 8 heads x 100000 tokens, k 32,
+    // 8192 features (buckets of 12500) 264 -> 249 us, but 419 -> 433 with a feature in every token, hence the line above that.
+    if (tokens * d.k > (int64_t)2 * kSortCap * d.NB)
+        sort = d.S <= 6 ? idx_bucket_sort_kernel<6, A, true> : d.S == 7 ? idx_bucket_sort_kernel<7, A, true> : idx_bucket_sort_kernel<8, A, true>;
+    hipLaunchKernelGGL(sort, grid, block, lds, st, d, n_tiles);
     S3_HIP(hipGetLastError());
     return S3_OK;
 }
@@ -604,7 +645,7 @@ static int index_build_impl(const char* who, const int32_t* ids, const int32_t* 
     if (positions) S3_HIP(hipMemcpyAsync(plog, positions, (size_t)T * 4, hipMemcpyDeviceToDevice, st));
     int rc = run_partition(ids, 0, T, 0, 1, d, st);
     if (rc) return rc;
-    return run_finalize(d, 1, d.max_tiles, st);
+    return run_finalize(d, 1, d.max_tiles, T, st);
 }
 
 // Scratch of s3_index_build_static: one array per GPU the library runs on, held until the process ends.  The name
@@ -773,7 +814,7 @@ int s3_index_finalize(s3_index* idx, void* stream) {
     IdxDev df = d;
     df.pos_affine = idx->affine ? 1 : 0;
     df.pos0 = idx->pos0;
-    int rc = run_finalize(df, idx->n_heads, n_tiles, st);
+    int rc = run_finalize(df, idx->n_heads, n_tiles, idx->tokens, st);
     if (rc) return rc;
     idx->finalized = true;
     return S3_OK;

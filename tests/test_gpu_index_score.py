@@ -106,6 +106,34 @@ def test_one_shot_index_build_matches():
         assert np.array_equal(off.cpu().numpy(), off_o) and np.array_equal(pos.cpu().numpy(), pos_o)
 
 
+@pytest.mark.parametrize("H,T,k,n_feat,hot", [
+    (8, 3072, 128, 16384, 5),        # 2048 workgroups, 1536 postings a bucket: the most they take with 256 threads ...
+    (8, 3073, 128, 16384, 5),        # ... and a token more: 1024 threads
+    (7, 600, 16, 16384, None),       # 1792 workgroups: 1024 threads
+    (8, 9000, 30, 4096, 5),          # a bucket of more than 8192 postings in a build of 256 threads
+    (8, 4096, 64, 512, 5),           # two features a bucket
+    (8, 1300, 64, 65536, 65535),     # 256 features a bucket
+    (14, 700, 8, 300, 299),          # 2100 workgroups, the last bucket
+    (32, 256 * 64, 128, 65536, 9),   # 256 tiles, a full round's average: the piece words fit one load of 256 threads ...
+    (32, 256 * 64 + 1, 128, 65536, 9),  # ... and one tile more: 1024
+    (1, 2 * 8192 * 2, 128, 16384, 9),  # 16384 postings a bucket: where each lane ranked its entry ...
+    (1, 2 * 8192 * 2 + 1, 128, 16384, 9),  # ... and one token more: several rounds in sorted order
+])
+def test_bucket_sort_of_either_width(H, T, k, n_feat, hot):
+    """Average buckets and tile counts on both sides of the line between 256 and 1024 threads, in 2 chunks, against the oracle."""
+    rng = np.random.default_rng(H * T + k)
+    step = n_feat // k
+    base = rng.integers(0, step, (H, T, 1))
+    ids = (base + np.arange(k) * step).astype(np.int32)              # distinct in a row
+    if hot is not None:
+        col = hot // step if hot < k * step else k - 1
+        ids[:, :, col] = hot                                         # the only feature of its column that is in every row
+    ix = gpu_index(ids, n_feat, chunks=[T // 3 + 1, T])
+    for h in {0, H // 2, H - 1}:
+        _, (off_o, pos_o) = oracle_csr(ids[h], np.arange(T, dtype=np.int32), n_feat)
+        assert_csr_equal(ix, h, off_o, pos_o)
+
+
 @pytest.mark.parametrize("T,k,n_feat,hot", [
     (32768, 1, 1, False),             # one bucket of two rounds
     (150001, 8, 40, False),           # single-feature buckets, three workgroups each
