@@ -967,11 +967,16 @@ __global__ __launch_bounds__(64 * TOK) void enc_join_kernel(ScanArgs a) {
 
 // First thresholds of tokens whose head carries no bound: the R-th largest maximum of 16 features over every eighth stage, the
 // smaller one of the token's two lanes.  R is 3 standard deviations above the number that the sample is expected to hold of the k best, so
-// about one token in 10^6 starts too high; the others have about 16 R candidates (128 for k 32).  WS wavefronts share 64 tokens' stages; W
-// comes straight from L2 (a wavefront's stages are its own, or its neighbours read the same lines).
+// about one token in 10^6 starts too high; the others have about 16 R candidates (128 for k 32).
+// WS == 1: a wavefront has 64 tokens, and the workgroup's four share the stages through LDS, two a barrier, two more on their way.  Each
+// read its fragments from L2 before: 16 bytes of 32 rows a load, which the address unit of a compute unit took as long for as three
+// times the MFMAs (256 heads x 2048 tokens, k 32: 654 -> 290 us).  WS > 1: that many wavefronts share 64 tokens' stages, W straight from
+// L2 (a stage is read by one of them only).
 template <int R, int WS>
 __global__ __launch_bounds__(kThreads) void enc_start_kernel(ScanArgs a) {
-    __shared__ float part[WS > 1 ? WS : 1][2][R][64];
+    __shared__ float part[WS > 1 ? WS : 1][2][WS > 1 ? R : 1][64];
+    __shared__ __align__(16) char ring[WS > 1 ? 16 : 4 * kStageB];      // two pairs of stages: one is read, the other written
+    __shared__ __align__(16) float ring_b[4][kFT];
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, half = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (a.hint && blockIdx.x == 0) {           // streamed calls: the call's minima and sums start empty
@@ -988,13 +993,10 @@ __global__ __launch_bounds__(kThreads) void enc_start_kernel(ScanArgs a) {
         s3_block_to_tile((unsigned)unit, a.n_heads, per_head, head, tt);
         if (a.hint && !no_bound(a.hint, head)) continue;
         const int tok0 = tt * kTok + (WS > 1 ? 0 : wv * kTokWave);
-        if (tok0 >= a.T) continue;                 // WS == 1 only: no barrier below then
         Tokens tk;
         load_set(tk.a, a.x, head, a.T, tok0 + n, half);
         load_set(tk.b, a.x, head, a.T, tok0 + 32 + n, half);
         const int nst = a.n_feat / kFT;
-        const char* const wp = a.w + (size_t)head * a.n_feat * RB + n * RB + half * 16;
-        const float* const bp = a.b + (size_t)head * a.n_feat + half * 4;
         float la[R], lb[R];
 #pragma unroll
         for (int i = 0; i < R; ++i) la[i] = lb[i] = -INFINITY;
@@ -1003,30 +1005,78 @@ __global__ __launch_bounds__(kThreads) void enc_start_kernel(ScanArgs a) {
             for (int i = R - 1; i > 0; --i) l[i] = __builtin_amdgcn_fmed3f(l[i - 1], l[i], m);
             l[0] = fmaxf(l[0], m);
         };
-        bf16x8 f[NS];
-        f32x16 c;
-        auto load = [&](int j) {
-            const int s = (int)((long long)min(j, a.sample - 1) * nst / a.sample);
-#pragma unroll
-            for (int i = 0; i < NS; ++i) f[i] = *(const bf16x8*)(wp + (size_t)s * kFT * RB + i * 32);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 u = *(const f32x4u*)(bp + s * kFT + q * 8);
-                c[4 * q] = u[0]; c[4 * q + 1] = u[1]; c[4 * q + 2] = u[2]; c[4 * q + 3] = u[3];
-            }
-        };
-        const int j0 = WS > 1 ? wv : 0;
-        load(j0);
-        for (int j = j0; j < a.sample; j += WS) {
+        auto stage_of = [&](int j) { return (int)((long long)min(j, a.sample - 1) * nst / a.sample); };
+        auto product = [&](bf16x8 (&f)[NS], const f32x16& c, auto between) {
             f32x16 accA = c, accB = c;
 #pragma unroll
             for (int i = 0; i < NS; ++i) {
                 accA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], tk.a[i], accA, 0, 0, 0);
                 accB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], tk.b[i], accB, 0, 0, 0);
             }
-            load(j + WS);
+            between();                             // the fragments are used up
             insert(la, max16(accA));
             insert(lb, max16(accB));
+        };
+        if constexpr (WS == 1) {
+            u32x4 r[4];
+            float bb;
+            auto gload = [&](int j) {
+                const char* const w0 = a.w + ((size_t)head * a.n_feat + (size_t)stage_of(j) * kFT) * RB + tid * 16;
+                const char* const w1 = a.w + ((size_t)head * a.n_feat + (size_t)stage_of(j + 1) * kFT) * RB + tid * 16;
+                r[0] = *(const u32x4*)w0;
+                r[1] = *(const u32x4*)(w0 + kThreads * 16);
+                r[2] = *(const u32x4*)w1;
+                r[3] = *(const u32x4*)(w1 + kThreads * 16);
+                bb = a.b[(size_t)head * a.n_feat + stage_of(j + (lane >> 5)) * kFT + n];
+            };
+            auto put = [&](int pair) {
+                char* const dst = ring + pair * (2 * kStageB) + (tid >> 4) * kRow + (tid & 15) * 16;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *(u32x4*)(dst + i * (16 * kRow)) = r[i];
+                if (tid < 64) ring_b[2 * pair + half][n] = bb;
+            };
+            auto take = [&](int slot) {
+                bf16x8 f[NS];
+                f32x16 c;
+                const char* const src = ring + slot * kStageB + n * kRow + half * 16;
+#pragma unroll
+                for (int i = 0; i < NS; ++i) f[i] = *(const bf16x8*)(src + i * 32);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 u = *(const f32x4*)&ring_b[slot][half * 4 + q * 8];
+                    c[4 * q] = u[0]; c[4 * q + 1] = u[1]; c[4 * q + 2] = u[2]; c[4 * q + 3] = u[3];
+                }
+                product(f, c, [] {});
+            };
+            gload(0);
+            put(0);
+            gload(2);
+            lds_barrier();
+            for (int j = 0; j < a.sample; j += 2) {
+                const int pair = (j >> 1) & 1;
+                put(pair ^ 1);                     // read in the turn before, behind the barrier at its end
+                gload(j + 4);
+                take(2 * pair);
+                if (j + 1 < a.sample) take(2 * pair + 1);
+                lds_barrier();
+            }
+        } else {
+            const char* const wp = a.w + (size_t)head * a.n_feat * RB + n * RB + half * 16;
+            const float* const bp = a.b + (size_t)head * a.n_feat + half * 4;
+            bf16x8 f[NS];
+            f32x16 c;
+            auto load = [&](int j) {
+                const int s = stage_of(j);
+#pragma unroll
+                for (int i = 0; i < NS; ++i) f[i] = *(const bf16x8*)(wp + (size_t)s * kFT * RB + i * 32);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 u = *(const f32x4u*)(bp + s * kFT + q * 8);
+                    c[4 * q] = u[0]; c[4 * q + 1] = u[1]; c[4 * q + 2] = u[2]; c[4 * q + 3] = u[3];
+                }
+            };
+            load(wv);
+            for (int j = wv; j < a.sample; j += WS) product(f, c, [&] { load(j + WS); });
         }
         if constexpr (WS > 1) {
 #pragma unroll
@@ -1124,7 +1174,9 @@ int launch_scan(const ScanArgs& a, const Plan& p, hipStream_t st) {
 template <int R>
 void launch_start(const ScanArgs& a, hipStream_t st) {
     const long long groups = (long long)a.n_heads * ((a.T + kTokWave - 1) / kTokWave);
-    if (groups <= 2048) hipLaunchKernelGGL((enc_start_kernel<R, kWaves>), dim3((unsigned)groups), dim3(kThreads), 0, st, a);
+    // Up to 640 groups of 64 tokens both take as long; beyond, the stages of 256 tokens are better shared (first chunk of a stream, 16384
+    // features, WS kWaves / 1: 40 heads x 2048, k 64, 867 / 823 us; 64, k 64, 1144 / 1050; 32, k 128, 1232 / 1196), below, a chip is not full.
+    if (groups <= 512) hipLaunchKernelGGL((enc_start_kernel<R, kWaves>), dim3((unsigned)groups), dim3(kThreads), 0, st, a);
     else hipLaunchKernelGGL((enc_start_kernel<R, 1>), dim3((unsigned)(a.n_tiles < 4096 ? a.n_tiles : 4096)), dim3(kThreads), 0, st, a);
 }
 

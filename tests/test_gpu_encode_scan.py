@@ -107,6 +107,28 @@ def test_streamed_and_plain_calls_equal_the_other_kernels(H, T, nf, k, plain):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("H,T,nf,k", [
+    (128, 256, 12544, 48),           # 512 groups of 64 tokens: the most whose samples four wavefronts share
+    (103, 300, 12544, 48),           # 515: four groups a workgroup, 49 sampled stages, three wavefronts without a token
+    (103, 300, 12544, 100),
+    (130, 300, 16640, 30),           # 65 sampled stages
+    (1, 33000, 12544, 64),           # one head
+])
+@pytest.mark.timeout(100)
+def test_first_thresholds_from_odd_samples(H, T, nf, k):
+    """Stages sampled in pairs, the last without a partner; biases at an odd float; results exact, also from call to call."""
+    import torch
+    import paper_2601_17702_amd as s3
+    x, W, b = problem(H, T, nf, H + T + k)
+    b = torch.cat([torch.zeros(1, device="cuda"), b.reshape(-1)])[1:].view(H, nf)
+    want = plain_without_scratch(x, W, b, k)
+    hint = s3.new_tau_hint(H)
+    same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+    hint.fill_(float("-inf"))
+    same(s3.sae_encode_topk_stream(x, W, b, k, hint), want)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("H,T,k", [(8, 512, 32), (70, 512, 48), (70, 512, 128)])
 @pytest.mark.timeout(100)
 def test_some_tokens_start_too_high(H, T, k):
