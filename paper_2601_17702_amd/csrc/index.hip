@@ -290,8 +290,8 @@ __global__ __launch_bounds__(NT, NT == kSplitThreads ? kSplitOcc : 4) void idx_b
     int* hist = wsum + 16;                         // [nd] whole-bucket counts (before the first round only)
     int* rcount = hist;                            //       per-round counts afterwards
     const int nd = 1 << d.S;
-    const int nds = NT == kSplitThreads ? 256 : nd;
-    int* cursor = hist + nds;                      // [nd] each
+    const int nds = NT == kSplitThreads ? 256 : nd;        // 1024 threads: a constant (with nd the kernels spilled twice as much)
+    int* cursor = hist + nds;                      // [nds] each
     int* rstart = cursor + nds;
     int* lstart = rstart + nds;                    // where each list starts in the head's positions array
     int* nextj = lstart + nds;                     // first block whose start in the list is not known yet
@@ -325,9 +325,9 @@ __global__ __launch_bounds__(NT, NT == kSplitThreads ? kSplitOcc : 4) void idx_b
     int32_t* posout = d.positions + (size_t)head * d.pos_stride;
     const bool multi = n_b > kSortCap || n_tiles > NT;   // more than one round of pieces
 
-    if (tid < nd) nextj[tid] = 1;
+    if (tid < nds) nextj[tid] = 1;
     if (multi) {   // count the whole bucket first: the CSR offsets are needed before the first round is written
-        if (tid < nd) hist[tid] = 0;
+        if (tid < nds) hist[tid] = 0;
         __syncthreads();
         for (int t0 = 0; t0 < n_tiles; t0 += NT) {
             const int m = min(n_tiles - t0, NT);
@@ -529,18 +529,20 @@ int run_partition(const int32_t* src, int64_t head_stride, int rows, int tile0, 
 }
 
 // Threads of the bucket sort: 256, four workgroups to a compute unit, where there are workgroups enough to fill the chip twice and an
-// average bucket is small against their number.  A frequent feature's bucket is one workgroup's chain of rounds, slower with fewer
-// threads: the more workgroups there are, the more work hides it.  The piece words of a bucket have to fit one load: 256 tiles at most.
-// Whole finalize, 1024 -> 256 threads, even features / one feature in every token and the rest skewed:
+// average bucket has no more postings than there are workgroups, nor more than a round takes.  A frequent feature's bucket is one
+// workgroup's chain of rounds, slower with fewer threads: the more workgroups there are, the more work hides it.  The piece words of a
+// bucket have to fit one load: 256 tiles at most.
+// Append and finalize, 1024 -> 256 threads, even features / one feature in every token and the rest skewed:
 //     256 heads x 2048 tokens, k 32, 16384 features (65536 buckets of 256)      870 -> 569 us      874 -> 560
-//       8 x 3000, k 128                             ( 2048 of 1500)            64.1 -> 55.8       61.0 -> 53.3
-//      64 x 32768, k 32                             (16384 of 4096)             591 -> 577         860 -> 841
+//       8 x 4000, k 128                             ( 2048 of 2000)            68.8 -> 60.2       65.8 -> 59.2
+//      32 x 14001, k 128                            ( 8192 of 7000)             411 -> 415         526 -> 487
+//      28 x 28672, k 64, 32768 features             ( 7168 of 7168)             388 -> 382         551 -> 531
 //       4 x 16384, k 32                             ( 1024 of 2048)            38.5 -> 33.0       74.4 -> 121.9: stays with 1024
 //       1 x 8192, k 32                              (  256 of 1024)            22.8 -> 23.7       35.2 -> 44.0: stays with 1024
 constexpr int kSmallThreads = 256, kSmallGroups = 2048;
 
 bool few_threads(const IdxDev& d, int n_heads, int n_tiles, int64_t tokens) {
-    const int64_t groups = (int64_t)d.NB * n_heads, most = std::min<int64_t>(kSortCap, groups * 3 / 4);
+    const int64_t groups = (int64_t)d.NB * n_heads, most = std::min<int64_t>(kSortCap, groups);
     return n_tiles <= kSmallThreads && groups >= kSmallGroups && tokens * d.k <= most * d.NB;
 }
 

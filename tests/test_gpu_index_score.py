@@ -107,8 +107,8 @@ def test_one_shot_index_build_matches():
 
 
 @pytest.mark.parametrize("H,T,k,n_feat,hot", [
-    (8, 3072, 128, 16384, 5),        # 2048 workgroups, 1536 postings a bucket: the most they take with 256 threads ...
-    (8, 3073, 128, 16384, 5),        # ... and a token more: 1024 threads
+    (8, 4096, 128, 16384, 5),        # 2048 workgroups, 2048 postings a bucket: the most they take with 256 threads ...
+    (8, 4097, 128, 16384, 5),        # ... and a token more: 1024 threads
     (7, 600, 16, 16384, None),       # 1792 workgroups: 1024 threads
     (8, 9000, 30, 4096, 5),          # a bucket of more than 8192 postings in a build of 256 threads
     (8, 4096, 64, 512, 5),           # two features a bucket
