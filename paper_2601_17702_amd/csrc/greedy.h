@@ -253,15 +253,9 @@ __device__ __forceinline__ void fill(const Slots<Key>& s, const Key (&key)[P], c
     __syncthreads();
 }
 
-constexpr int kListMax = 1024;
-// The choices in few rounds, by the whole workgroup, over C slots.  A position that is the best within its reach is chosen
-// whatever happens elsewhere, so a round takes all slots' best positions that beat everything in the blocks they may reach into
-// (the best of all always does), removes what they reach and searches the blocks concerned again.  That goes on until `want`
-// choices are better than everything left; one to four rounds are usual; among equal values it may be
-// one choice a round.  T threads have a slot, so
-// that 512 threads do all this, two wavefronts a SIMD (a round takes 1.5 to 2 us; with all sixteen 2.8, with four 2.1).
-// list_key, list_at (LDS): the choices; a slot has at most 64 / (reach + 1) of them, rounded up, kListMax all together.
-// Then put(r, key, at) for the r-th best one, r < want, by some thread each.  Returns how many there are, in every thread.
+template <int R, class Key, class Put>                 // below
+__device__ int walk(const Slots<Key>& s, unsigned n, unsigned reach, int want, Key& best, int& at, Put put);
+
 template <int X>
 __device__ __forceinline__ unsigned quad_xor(unsigned v) {
     return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, X == 1 ? 0xB1 : (X == 2 ? 0x4E : 0x141), 0xf, 0xf, true);      // 4: the other four, mirrored
@@ -270,12 +264,25 @@ template <int X>
 __device__ __forceinline__ unsigned long long quad_xor(unsigned long long v) {
     return ((unsigned long long)quad_xor<X>((unsigned)(v >> 32)) << 32) | quad_xor<X>((unsigned)v);
 }
+constexpr int kListMax = 1024;
+constexpr int kFewChoices = 4;
+// The choices in few rounds, by the whole workgroup, over C slots.  A position that is the best within its reach is chosen
+// whatever happens elsewhere, so a round takes all slots' best positions that beat everything in the blocks they may reach into
+// (the best of all always does), removes what they reach and searches the blocks concerned again.  That goes on until `want`
+// choices come before everything left (larger value first, ties -> smaller position); one to four rounds are usual.
+// Among equal values a position beats the ones behind it only, and a round may take as little as one choice.  So where a round adds
+// fewer than kFewChoices, what is missing is left to walk(), which takes a quarter of a round for each: 64 windows of 16 among
+// equal ones 890 us in rounds until every slot was used up, 40 peaks of radius 8 on a level curve 1300.
+// T threads have a slot, so that 512 threads do all this, two wavefronts a SIMD (a round takes 1.5 to 2 us; with all sixteen 2.8,
+// with four 2.1).
+// list_key, list_at (LDS): the choices; a slot has at most 64 / (reach + 1) of them, rounded up, kListMax all together.
+// Then put(r, key, at) for the r-th best one, r < want, by some thread each.  Returns how many there are, in every thread.
 template <int C, class Key, class Put>
 __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* list_at, unsigned n, unsigned reach, int want, Put put) {
     constexpr int T = 512 / C;
     constexpr int V = 16 / (int)sizeof(Key), U = 64 / V / T;          // values a read, reads a thread
     static_assert(T == 1 || T == 2 || T == 4 || T == 8);
-    __shared__ int buf[2][kWaves], blk[C], won[C], n_list;
+    __shared__ int buf[2][kWaves], blk[C], won[C], n_list, left_at[3];
     __shared__ Key shown[C], left[3];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool active = wave < C * T / 64;
@@ -288,9 +295,12 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
     unsigned long long live = ~0ull;
     if (active && j == 0) { blk[me] = b; shown[me] = k; }
     if (tid == 0) n_list = 0;
-    if (tid < 3) left[tid] = 0;
+    if (tid < 3) { left[tid] = 0; left_at[tid] = 0x7FFFFFFF; }
     __syncthreads();
-    Key rest = 0;
+    Key rest = 0;                                     // the best of what is left
+    int rest_at = 0;
+    const auto final = [&](int i) { return list_key[i] > rest || (list_key[i] == rest && list_at[i] < rest_at); };
+    int was = 0, was_final = 0;
     reach = min(reach, n);
     int t0 = me, t1 = me;                             // the slots that a choice in this one may reach into, and the other way round
     if (k) {
@@ -369,18 +379,42 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
             settle(k, top, m);
             const Key most = of_lane(k, (int)__builtin_ctzll(m));
             if (lane == 0) atomicMax(&left[turn], most);
-            if (tid == 0) left[turn == 2 ? 0 : turn + 1] = 0;
+            if (tid == 0) { left[turn == 2 ? 0 : turn + 1] = 0; left_at[turn == 2 ? 0 : turn + 1] = 0x7FFFFFFF; }
         }
         __syncthreads();                              // what is left
         rest = left[turn];
         if (rest == 0) break;
-        if (chosen >= want) {
+        if (chosen >= want || chosen - was < kFewChoices) {
+            if (active && j == 0 && k == rest) atomicMin(&left_at[turn], p);
+            __syncthreads();
+            rest_at = left_at[turn];
             int c = 0, before;
-            for (int i = tid; i < chosen; i += kThreads) c += (int)__popcll(__ballot(list_key[i] > rest));
-            if (block_sum(sums, __builtin_amdgcn_readlane(c, 0), before) >= want) break;
+            for (int i = tid; i < chosen; i += kThreads) c += (int)__popcll(__ballot(final(i)));
+            const int done = block_sum(sums, __builtin_amdgcn_readlane(c, 0), before);
+            if (done >= want) break;
+            if (done - was_final < kFewChoices) {
+                if (active) {                         // walk() goes on from the values and the slots' best ones in LDS
+                    for (int i = j; ~live && i < 64; i += T)
+                        if (!(live >> i & 1)) s.val[me * kRow<Key> + i] = 0;
+                    if (j == 0) { s.key[me] = k; s.at[me] = p; }
+                }
+                __syncthreads();
+                if (wave == 0) {
+                    const int more = walk<C / 64, Key>(s, n, reach, want - done, rest, rest_at, [&](int r, Key x, int at) {
+                        if (lane == 0) { list_key[chosen + r] = x; list_at[chosen + r] = at; }
+                    });
+                    if (lane == 0) { n_list = chosen + more; left[0] = rest; left_at[0] = rest_at; }
+                }
+                __syncthreads();
+                rest = left[0];
+                rest_at = left_at[0];
+                break;
+            }
+            was_final = done;
         }
+        was = chosen;
     }
-    // Those that are better than what is left, in their order: 64 of them a wavefront, against a part of all.
+    // Those that come before what is left, in their order: 64 of them a wavefront, against a part of all.
     Key* const key = s.val;
     int* const at = (int*)(key + kListMax);
     int* const rank = at + kListMax;
@@ -388,7 +422,7 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
     if (tid == 0) won[0] = 0;
     __syncthreads();
     for (int i = tid; i < total; i += kThreads)
-        if (list_key[i] > rest) {
+        if (final(i)) {
             const int o = atomicAdd(&won[0], 1);
             key[o] = list_key[i];
             at[o] = list_at[i];
@@ -416,6 +450,7 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
         if (rank[i] < want) put(rank[i], key[i], at[i]);
     return min(valid, want);
 }
+
 // How a search with at least `need` slots runs: in rounds, with 64, 128, 256 or 512 slots (up = 0 .. 3), where the list of choices
 // has at most kListMax entries; else one choice after the other, with 64, 128, 256 or 576 slots.
 struct Way {
@@ -434,10 +469,11 @@ inline Way way_of(int64_t need, int64_t reach) {
 
 // The choices one after the other, by one wavefront, over 64 R slots and n positions: the slots' maxima are in its registers, a
 // round wipes what it removes in the blocks at both ends and searches those again, beside the reduction over the other slots and
-// not behind it (0.5 to 0.55 us a round).  No lane reads an LDS value of another one: value i of a slot is lane i's: put(r, key, at) for the r-th choice.  Returns how many there were
-// (fewer than `want` if nothing live was left).  Larger value first, ties -> smaller position.
+// not behind it (0.5 to 0.55 us a round).  No lane reads an LDS value of another one: value i of a slot is lane i's.  Then put(r, key, at)
+// for the r-th choice.  Returns how many there were (fewer than `want` if nothing live was left); best, at: what would come
+// next (best 0: nothing).  Larger value first, ties -> smaller position.
 template <int R, class Key, class Put>
-__device__ __forceinline__ int walk(const Slots<Key>& s, unsigned n, unsigned reach, int want, Put put) {
+__device__ __forceinline__ int walk(const Slots<Key>& s, unsigned n, unsigned reach, int want, Key& best, int& at, Put put) {
     const int lane = threadIdx.x & 63;
     Key k[R], lk = 0;
     int p[R], lp = 0;                                 // slot lane R + q
@@ -450,8 +486,8 @@ __device__ __forceinline__ int walk(const Slots<Key>& s, unsigned n, unsigned re
     unsigned top = s3_wave_max_u32(top_word(lk));
     unsigned long long m = __ballot(top_word(lk) == top);
     settle(lk, top, m);
-    Key best = of_lane(lk, (int)__builtin_ctzll(m));
-    int at = (int)of_lane((unsigned)lp, (int)__builtin_ctzll(m));
+    best = of_lane(lk, (int)__builtin_ctzll(m));
+    at = (int)of_lane((unsigned)lp, (int)__builtin_ctzll(m));
     int found = 0;
     while (found < want && best) {
         put(found++, best, at);

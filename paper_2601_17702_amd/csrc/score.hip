@@ -967,7 +967,9 @@ __global__ __launch_bounds__(s3greedy::kThreads) void sc_topb_slots_kernel(Score
     const double inv = ldexp(1.0, -exp_s(a.wmax[a.n_heads * a.nr], a.hb));
     top_fill<P>(a, slots);
     if (threadIdx.x >= 64) return;
-    const int found = s3greedy::walk<R, unsigned long long>(slots, (unsigned)a.nW, a.nms ? (unsigned)(a.len - 1) : 0u, a.top_b,
+    unsigned long long left;
+    int left_at;
+    const int found = s3greedy::walk<R, unsigned long long>(slots, (unsigned)a.nW, a.nms ? (unsigned)(a.len - 1) : 0u, a.top_b, left, left_at,
                                                             [&](int r, unsigned long long k, int w) {
         if (lane == 0) {
             a.span_start[r] = w;

@@ -342,7 +342,9 @@ __global__ __launch_bounds__(s3greedy::kThreads) void sel_nms_kernel(SelArgs a) 
     const auto slots = s3greedy::slots_of<unsigned>(nms_lds, 64 * R);
     nms_fill<P>(a, slots);
     if (wave == 0) {
-        const int found = s3greedy::walk<R, unsigned>(slots, (unsigned)a.L, (unsigned)a.radius, a.n_centers, [&](int r, unsigned k, int t) {
+        unsigned left;
+        int left_at;
+        const int found = s3greedy::walk<R, unsigned>(slots, (unsigned)a.L, (unsigned)a.radius, a.n_centers, left, left_at, [&](int r, unsigned k, int t) {
             if (lane == 0) { a.center[r] = t; a.center_density[r] = __uint_as_float(k); }
         });
         if (lane == 0) found_s = found;

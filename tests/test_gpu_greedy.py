@@ -48,6 +48,85 @@ def test_equal_spans_are_taken_from_the_front(T, span_len, top_b):
     assert nf == top_b and st.tolist() == [i * span_len for i in range(top_b)]
 
 
+def plateaus(rng, n, high):
+    """0 / 1 in long stretches, with `high` positions above: most choices fall among equal values."""
+    v = np.zeros(n, np.int32)
+    edge = np.sort(rng.choice(n, 12, replace=False))
+    for lo, hi in zip(edge[::2], edge[1::2]):
+        v[lo:hi] = 1
+    v[rng.choice(n, high, replace=False)] = 2 + np.arange(high)
+    return v
+
+
+@pytest.mark.parametrize("T,span_len,top_b,high", [
+    (20_000, 9, 20, 3), (20_000, 9, 20, 0),  # 64 slots
+    (20_000, 9, 60, 7),                      # 128
+    (20_000, 34, 80, 30), (300, 34, 80, 1),  # 256; more asked for than there are
+    (70_000, 34, 80, 5),                     # four maxima per thread
+])
+def test_spans_that_end_among_equal_ones(T, span_len, top_b, high):
+    """Fewer windows stand out than are asked for: the others come in ascending order."""
+    ids = plateaus(np.random.default_rng(T + top_b + high), T, high).reshape(1, T, 1)
+    n_feat = high + 3
+    qids = np.arange(1, n_feat, dtype=np.int32).reshape(1, -1, 1).copy()
+    qvals = np.linspace(1.0, 3.0, qids.size).astype(np.float32).reshape(qids.shape)
+    ix = gpu_index(ids, n_feat)
+    S, W, st_o, sc_o = oracle_score(ids, qids, qvals, n_feat, T, span_len, top_b, 0, True)
+    out = run_gpu_score(ix, qids, qvals, T, span_len, top_b, 0, True)
+    check_score(out, S, W, st_o, sc_o, span_len, True)
+    # a position has one weight: as whole numbers of 40 bits the window sums are exact in fp64, and equal where members are
+    fixed = np.concatenate([[0], np.cumsum(np.rint(S / S.max() * 2.0 ** 40))])
+    st_x, _ = orc.topb(fixed[span_len:] - fixed[:-span_len], span_len, top_b)
+    assert out[0][:out[2]].tolist() == st_x.tolist()
+
+
+@pytest.mark.parametrize("L,radius,n_centers,high", [
+    (20_000, 8, 20, 3), (20_000, 8, 20, 0),  # 64 slots
+    (20_000, 8, 60, 7),                      # 128
+    (20_000, 33, 60, 30), (70_000, 33, 60, 5),      # 256
+    (70_000, 33, 150, 40), (70_000, 40, 150, 0),    # 512
+])
+def test_peaks_that_end_among_equal_ones(L, radius, n_centers, high):
+    check_peaks(plateaus(np.random.default_rng(L + n_centers + high), L, high).astype(np.float32), radius, n_centers)
+
+
+def best_us(fn, reps=5, calls=10):
+    import torch
+    fn()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            fn()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1000 / calls)
+    return best
+
+
+@pytest.mark.parametrize("span_len,top_b", [(16, 64), (32, 8), (64, 64)])
+def test_a_query_without_matches_costs_what_another_one_does(span_len, top_b):
+    """All windows are equal: half a microsecond a choice, and at most twice that here."""
+    import torch
+    T = 16_384
+    ids = (np.arange(T, dtype=np.int32) * 7 % 4096).reshape(1, T, 1)
+    ix = gpu_index(ids, 4096)
+    qids = torch.arange(512, dtype=torch.int32, device="cuda").view(1, 512, 1)
+    some, none = torch.rand(1, 512, 1, device="cuda"), torch.zeros(1, 512, 1, device="cuda")
+    us = [best_us(lambda: ix.coactivate_score(qids, q, T, span_len, top_b)) for q in (some, none)]
+    assert us[1] < us[0] + 1.2 * top_b + 5, us
+
+
+@pytest.mark.parametrize("radius,n_centers", [(8, 9), (8, 40), (48, 128), (64, 40)])
+def test_a_level_curve_costs_what_another_one_does(radius, n_centers):
+    import torch
+    import paper_2601_17702_amd as s3
+    g = s3.smoothing_kernel(s3.KERNEL_BOX, 1)
+    us = [best_us(lambda: s3.select_spans(S, g, n_centers, radius, 0.5, 64)) for S in (torch.rand(32_768, device="cuda"), torch.ones(32_768, device="cuda"))]
+    assert us[1] < us[0] + 1.2 * n_centers + 5, us
+
+
 @pytest.mark.parametrize("L,radius,n_centers,levels", [
     (36_864, 64, 40, 3), (36_865, 64, 40, 3),      # 576 blocks, all in slots; one more
     (40_000, 64, 192, 2), (40_000, 64, 193, 2),    # 574 and 577 slots asked for
@@ -58,10 +137,13 @@ def test_equal_spans_are_taken_from_the_front(T, span_len, top_b):
 ])
 def test_peaks_around_the_numbers_of_slots(L, radius, n_centers, levels):
     """Few distinct densities, so that block maxima tie; `levels` 0: one."""
+    rng = np.random.default_rng(L + n_centers)
+    check_peaks(rng.integers(0, levels + 1, L).astype(np.float32) if levels else np.ones(L, np.float32), radius, n_centers)
+
+
+def check_peaks(S, radius, n_centers):
     import torch
     import paper_2601_17702_amd as s3
-    rng = np.random.default_rng(L + n_centers)
-    S = rng.integers(0, levels + 1, L).astype(np.float32) if levels else np.ones(L, np.float32)
     g = s3.smoothing_kernel(s3.KERNEL_BOX, 1)
     c, dc, lo, hi, nf, D = s3.select_spans(torch.from_numpy(S).cuda(), g, n_centers, radius, 0.5, 70, want_density=True)
     torch.cuda.synchronize()
