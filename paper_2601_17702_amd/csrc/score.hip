@@ -932,11 +932,12 @@ __global__ __launch_bounds__(kTopThreads) void sc_topb_long_kernel(ScoreArgs a) 
 template <int P>
 __device__ __forceinline__ void top_fill(const ScoreArgs& a, const s3greedy::Slots<unsigned long long>& slots) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int per = P == 1 ? 1 : s3greedy::per_thread(a.nsub);
     unsigned long long key[P];
     int at[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-        const int b = (wave * P + q) * 64 + lane;
+        const int b = q < per ? (wave * per + q) * 64 + lane : a.nsub;
         key[q] = b < a.nsub ? a.tmaxv[b] : 0ull;
         at[q] = b < a.nsub ? a.tmaxi[b] : 0;
     }

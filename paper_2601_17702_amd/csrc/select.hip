@@ -306,11 +306,12 @@ __device__ __forceinline__ void nms_spans(const SelArgs& a, const int* cen, cons
 template <int P>
 __device__ __forceinline__ void nms_fill(const SelArgs& a, const s3greedy::Slots<unsigned>& slots) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int per = P == 1 ? 1 : s3greedy::per_thread(a.nblk);
     unsigned key[P];
     int at[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-        const int b = (wave * P + q) * 64 + lane;
+        const int b = q < per ? (wave * per + q) * 64 + lane : a.nblk;
         const unsigned long long v = b < a.nblk ? a.tkey[b] : 0ull;
         key[q] = (unsigned)(v >> 32);
         at[q] = (int)~(unsigned)v;
