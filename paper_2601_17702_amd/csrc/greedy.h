@@ -198,7 +198,7 @@ __device__ __forceinline__ void fill(const Slots<Key>& s, const Key (&key)[P], c
         clo = block_count(sums, key, lo);
     }
     if (clo > s.cap) {                                // P > 1, or ties
-        raise(lo, (Key)(best + 1), clo, need, s.cap, [&](Key t) { return block_count(sums, key, t); }, [&](Key& l, Key& h) {
+        if (lo != best) raise(lo, (Key)(best + 1), clo, need, s.cap, [&](Key t) { return block_count(sums, key, t); }, [&](Key& l, Key& h) {
             Key least = ~Key(0), largest = 0;
 #pragma unroll
             for (int q = 0; q < P; ++q) {
@@ -257,8 +257,8 @@ __device__ __forceinline__ void fill(const Slots<Key>& s, const Key (&key)[P], c
     __syncthreads();
 }
 
-template <int R, class Key, class Put>                 // below
-__device__ int walk(const Slots<Key>& s, unsigned n, unsigned reach, int want, Key& best, int& at, Put put);
+template <int R, class Key, class Put, class Enough>   // below
+__device__ int walk(const Slots<Key>& s, unsigned n, unsigned reach, int want, Key& next, int& next_at, Put put, Enough enough);
 
 template <int X>
 __device__ __forceinline__ unsigned quad_xor(unsigned v) {
@@ -269,21 +269,21 @@ __device__ __forceinline__ unsigned long long quad_xor(unsigned long long v) {
     return ((unsigned long long)quad_xor<X>((unsigned)(v >> 32)) << 32) | quad_xor<X>((unsigned)v);
 }
 constexpr int kListMax = 1024;
-constexpr int kFewChoices = 4;
 // The choices in few rounds, by the whole workgroup, over C slots.  A position that is the best within its reach is chosen
 // whatever happens elsewhere, so a round takes all slots' best positions that beat everything in the blocks they may reach into
 // (the best of all always does), removes what they reach and searches the blocks concerned again.  That goes on until `want`
 // choices come before everything left (larger value first, ties -> smaller position); one to four rounds are usual.
-// Among equal values a position beats the ones behind it only, and a round may take as little as one choice.  So where a round adds
-// fewer than kFewChoices, what is missing is left to walk(), which takes a quarter of a round for each: 64 windows of 16 among
-// equal ones 890 us in rounds until every slot was used up, 40 peaks of radius 8 on a level curve 1300.
+// Among equal values a position beats the ones behind it only, and a round may take as little as one choice, no faster than walk()
+// takes two to four.  So where a round takes fewer than `few`, or two in a row settle fewer each, walk() goes on, until it and the
+// rounds have `want` together.  us for a look-up, in rounds until every slot was used up / now: 64 windows of 16 among equal ones
+// 890 / 54; 40 peaks of radius 8 on a level curve 1310 / 49.
 // T threads have a slot, so that 512 threads do all this, two wavefronts a SIMD (a round takes 1.5 to 2 us; with all sixteen 2.8,
 // with four 2.1).
 // list_key, list_at (LDS): the choices; a slot has at most 64 / (reach + 1) of them, rounded up, kListMax all together.
 // Then put(r, key, at) for the r-th best one, r < want, by some thread each.  Returns how many there are, in every thread.
 template <int C, class Key, class Put>
 __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* list_at, unsigned n, unsigned reach, int want, Put put) {
-    constexpr int T = 512 / C;
+    constexpr int T = 512 / C, few = 4;
     constexpr int V = 16 / (int)sizeof(Key), U = 64 / V / T;          // values a read, reads a thread
     static_assert(T == 1 || T == 2 || T == 4 || T == 8);
     __shared__ int buf[2][kWaves], blk[C], won[C], n_list, left_at[3];
@@ -303,8 +303,8 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
     __syncthreads();
     Key rest = 0;                                     // the best of what is left
     int rest_at = 0;
-    const auto final = [&](int i) { return list_key[i] > rest || (list_key[i] == rest && list_at[i] < rest_at); };
-    int was = 0, was_final = 0;
+    const auto before_rest = [&](int i) { return list_key[i] > rest || (list_key[i] == rest && list_at[i] < rest_at); };
+    int was = 0, was_done = 0, slow = 0;              // slow: rounds one after the other that brought few choices
     reach = min(reach, n);
     int t0 = me, t1 = me;                             // the slots that a choice in this one may reach into, and the other way round
     if (k) {
@@ -388,15 +388,24 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
         __syncthreads();                              // what is left
         rest = left[turn];
         if (rest == 0) break;
-        if (chosen >= want || chosen - was < kFewChoices) {
-            if (active && j == 0 && k == rest) atomicMin(&left_at[turn], p);
-            __syncthreads();
-            rest_at = left_at[turn];
-            int c = 0, before;
-            for (int i = tid; i < chosen; i += kThreads) c += (int)__popcll(__ballot(final(i)));
-            const int done = block_sum(sums, __builtin_amdgcn_readlane(c, 0), before);
+        if (chosen >= want || chosen - was < few) {
+            const auto count = [&]() {
+                int c = 0, before;
+                for (int i = tid; i < chosen; i += kThreads) c += (int)__popcll(__ballot(before_rest(i)));
+                return block_sum(sums, __builtin_amdgcn_readlane(c, 0), before);
+            };
+            rest_at = 0;                              // the larger ones alone
+            int done = count();
             if (done >= want) break;
-            if (done - was_final < kFewChoices) {
+            slow = done - was_done < few ? slow + 1 : 0;
+            if (slow) {
+                if (active && j == 0 && k == rest) atomicMin(&left_at[turn], p);
+                __syncthreads();
+                rest_at = left_at[turn];
+                done = count();
+                if (done >= want) break;
+            }
+            if (slow == 2 || (slow && chosen - was < few)) {
                 if (active) {                         // walk() goes on from the values and the slots' best ones in LDS
                     for (int i = j; ~live && i < 64; i += T)
                         if (!(live >> i & 1)) s.val[me * kRow<Key> + i] = 0;
@@ -406,6 +415,14 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
                 if (wave == 0) {
                     const int more = walk<C / 64, Key>(s, n, reach, want - done, rest, rest_at, [&](int r, Key x, int at) {
                         if (lane == 0) { list_key[chosen + r] = x; list_at[chosen + r] = at; }
+                    }, [&](int found, Key x, int at) {    // those of the rounds that its choices have caught up with
+                        if (chosen == done) return false;
+                        int c = found;
+                        for (int i0 = 0; i0 < chosen; i0 += 64) {
+                            const int i = min(i0 + lane, chosen - 1);
+                            c += (int)__popcll(__ballot(i0 + lane < chosen && (list_key[i] > x || (list_key[i] == x && list_at[i] < at))));
+                        }
+                        return c >= want;
                     });
                     if (lane == 0) { n_list = chosen + more; left[0] = rest; left_at[0] = rest_at; }
                 }
@@ -414,7 +431,7 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
                 rest_at = left_at[0];
                 break;
             }
-            was_final = done;
+            was_done = done;
         }
         was = chosen;
     }
@@ -426,7 +443,7 @@ __device__ __forceinline__ int rounds(const Slots<Key>& s, Key* list_key, int* l
     if (tid == 0) won[0] = 0;
     __syncthreads();
     for (int i = tid; i < total; i += kThreads)
-        if (final(i)) {
+        if (before_rest(i)) {
             const int o = atomicAdd(&won[0], 1);
             key[o] = list_key[i];
             at[o] = list_at[i];
@@ -474,10 +491,10 @@ inline Way way_of(int64_t need, int64_t reach) {
 // The choices one after the other, by one wavefront, over 64 R slots and n positions: the slots' maxima are in its registers, a
 // round wipes what it removes in the blocks at both ends and searches those again, beside the reduction over the other slots and
 // not behind it (0.5 to 0.55 us a round).  No lane reads an LDS value of another one: value i of a slot is lane i's.  Then put(r, key, at)
-// for the r-th choice.  Returns how many there were (fewer than `want` if nothing live was left); best, at: what would come
-// next (best 0: nothing).  Larger value first, ties -> smaller position.
-template <int R, class Key, class Put>
-__device__ __forceinline__ int walk(const Slots<Key>& s, unsigned n, unsigned reach, int want, Key& best, int& at, Put put) {
+// for the r-th choice.  Returns how many there were (fewer than `want` if nothing live was left); next, next_at: what would come
+// then (next 0: nothing).  enough(found, next, next_at), asked after every fourth choice: whether to stop.  Larger value first, ties -> smaller position.
+template <int R, class Key, class Put, class Enough>
+__device__ __forceinline__ int walk(const Slots<Key>& s, unsigned n, unsigned reach, int want, Key& next, int& next_at, Put put, Enough enough) {
     const int lane = threadIdx.x & 63;
     Key k[R], lk = 0;
     int p[R], lp = 0;                                 // slot lane R + q
@@ -490,10 +507,10 @@ __device__ __forceinline__ int walk(const Slots<Key>& s, unsigned n, unsigned re
     unsigned top = s3_wave_max_u32(top_word(lk));
     unsigned long long m = __ballot(top_word(lk) == top);
     settle(lk, top, m);
-    best = of_lane(lk, (int)__builtin_ctzll(m));
-    at = (int)of_lane((unsigned)lp, (int)__builtin_ctzll(m));
+    Key best = of_lane(lk, (int)__builtin_ctzll(m));
+    int at = (int)of_lane((unsigned)lp, (int)__builtin_ctzll(m));
     int found = 0;
-    while (found < want && best) {
+    while (found < want && best && !(found > 0 && (found & 3) == 0 && enough(found, best, at))) {
         put(found++, best, at);
         const unsigned lo = (unsigned)at > reach ? (unsigned)at - reach : 0u, hi = min((unsigned)at + reach, n - 1);
         const int tl = (int)(lo >> 6), span = (int)(hi >> 6) - tl;
@@ -546,6 +563,8 @@ __device__ __forceinline__ int walk(const Slots<Key>& s, unsigned n, unsigned re
         if (k0 > best || (k0 == best && p0 < at)) { best = k0; at = p0; }
         if (k1 > best || (k1 == best && p1 < at)) { best = k1; at = p1; }
     }
+    next = best;
+    next_at = at;
     return found;
 }
 

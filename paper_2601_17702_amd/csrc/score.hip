@@ -976,7 +976,7 @@ __global__ __launch_bounds__(s3greedy::kThreads) void sc_topb_slots_kernel(Score
             a.span_start[r] = w;
             a.span_score[r] = (float)((double)(long long)(k - 1) * inv);
         }
-    });
+    }, [](int, unsigned long long, int) { return false; });
     top_finish(a, found, lane);
 }
 

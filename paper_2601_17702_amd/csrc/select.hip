@@ -347,7 +347,7 @@ __global__ __launch_bounds__(s3greedy::kThreads) void sel_nms_kernel(SelArgs a) 
         int left_at;
         const int found = s3greedy::walk<R, unsigned>(slots, (unsigned)a.L, (unsigned)a.radius, a.n_centers, left, left_at, [&](int r, unsigned k, int t) {
             if (lane == 0) { a.center[r] = t; a.center_density[r] = __uint_as_float(k); }
-        });
+        }, [](int, unsigned, int) { return false; });
         if (lane == 0) found_s = found;
     }
     __syncthreads();                          // the centres were written by this workgroup
