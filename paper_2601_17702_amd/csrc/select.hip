@@ -24,9 +24,14 @@ constexpr int64_t kConvLargeFrom = 1 << 18; // 64 threads fill the chip up to 2^
 constexpr int kTile = 64;                   // positions per block: one bit or one lane each
 constexpr int kConvKeyShift = 4;            // blocks per workgroup of the large convolution: 2^4
 constexpr int kNmsThreads = s3greedy::kThreads;
-constexpr int kNmsFew = 8;                  // for so many centres or fewer that is not worth its beginning: us for a whole selection without
-                                            // / with it, 1 centre of 8000 positions 9.4 / 14.3, 8 of 1000 to 300000 15 to 20 / 14 to 20,
-                                            // at a radius of 1000 20 / 25 to 38; 40 of 8000 48 / 19
+// Which searches bring blocks into LDS (the others take 1.1 us a centre, and begin sooner): those for more than so many centres, the
+// more the more blocks a choice may reach into, which are all looked through in every round.  us for a whole selection without /
+// with it, curves of noise, smoothed or not: 8 centres of 1000 to 300000 positions 15 to 20 / 14 to 20; 40 of 8000 48 / 19; 12 at a
+// radius of 300 20 to 24 / 17 to 25; 9 at 500 19 to 22 / 19 to 27, 16 25 to 35 / 21 to 36, 20 31 / 26; at 1000 16 of 70000 positions
+// 25 / 36, 20 of 20000 25 / 30, 33 of 32768 39 / 30.  And where more than 512 blocks of many are asked for, which are taken one choice
+// a round (0.9 us) behind a threshold between 512 and 576 counts, for more than kNmsManyTight: 32 at 500 of 70000 47 / 57.
+constexpr int kNmsFew = 8, kNmsManyTight = 64;
+inline bool nms_many(int64_t found, int64_t radius) { return found > kNmsFew && found > (radius + 16) / 32; }
 constexpr int kNmsSlots = 576;              // blocks that the peak search holds in LDS at most (151 KB)
 constexpr int kNmsTiles = 16384;            // tile maxima that the peak search keeps in LDS at most (128 KB): four groups of 64 per lane
 constexpr int kNmsTilesMin = 8192;          // as many fit beside the most centres
@@ -703,8 +708,9 @@ extern "C" int s3_select_spans(const float* scores, int64_t n_positions, const f
     a.ckey = (unsigned long long*)(base + l.ckey);
     a.nblk = l.nblk;
     const int64_t most_found = s3greedy::choices(n_positions, nms_radius, n_centers), need = s3greedy::slots_needed(n_positions, nms_radius, most_found);
-    const bool slots = most_found > kNmsFew && need <= kNmsSlots && l.nblk <= 16 * kNmsThreads;
     const s3greedy::Way sw = s3greedy::way_of(need, nms_radius);
+    const bool slots = nms_many(most_found, nms_radius) && need <= kNmsSlots &&
+                       (need <= 512 || l.nblk <= kNmsSlots || most_found > kNmsManyTight) && l.nblk <= 16 * kNmsThreads;
     a.need = (int)(slots ? need : 0);
     a.room = sw.room;
     // sel_nms_long_kernel: tiles of one block as long as their maxima fit the search's LDS beside the centres; from there on no

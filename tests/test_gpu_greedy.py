@@ -90,6 +90,17 @@ def test_peaks_that_end_among_equal_ones(L, radius, n_centers, high):
     check_peaks(plateaus(np.random.default_rng(L + n_centers + high), L, high).astype(np.float32), radius, n_centers)
 
 
+@pytest.mark.parametrize("L,radius,n_centers", [
+    (40_000, 271, 8), (40_000, 271, 9), (40_000, 272, 9), (40_000, 272, 10),      # from so many centres on in LDS
+    (90_000, 500, 16), (90_000, 500, 17), (32_768, 1000, 40),
+    (45_000, 64, 171), (45_000, 300, 52), (40_000, 300, 49),     # 511 of 704 blocks asked for; 562, few centres; 529 of 625
+    (36_864, 300, 52),                       # 562 of 576
+    (300_000, 130, 40),                      # five maxima per thread
+])
+def test_peaks_around_the_radii(L, radius, n_centers):
+    check_peaks(np.random.default_rng(L + radius).random(L).astype(np.float32) ** 2, radius, n_centers)
+
+
 def best_us(fn, reps=5, calls=10):
     import torch
     fn()
@@ -125,6 +136,15 @@ def test_a_level_curve_costs_what_another_one_does(radius, n_centers):
     g = s3.smoothing_kernel(s3.KERNEL_BOX, 1)
     us = [best_us(lambda: s3.select_spans(S, g, n_centers, radius, 0.5, 64)) for S in (torch.rand(32_768, device="cuda"), torch.ones(32_768, device="cuda"))]
     assert us[1] < us[0] + 1.2 * n_centers + 5, us
+
+
+@pytest.mark.parametrize("L,radius", [(70_000, 2000), (300_000, 2000), (70_000, 1000)])
+def test_one_more_centre_of_a_large_radius(L, radius):
+    import torch
+    import paper_2601_17702_amd as s3
+    g, S = s3.smoothing_kernel(s3.KERNEL_GAUSSIAN, 48), torch.rand(L, device="cuda")
+    us = [best_us(lambda: s3.select_spans(S, g, n, radius, 0.5, 64)) for n in (8, 9)]
+    assert us[1] < 1.2 * us[0] + 2, us
 
 
 @pytest.mark.parametrize("L,radius,n_centers,levels", [
