@@ -192,7 +192,10 @@ int s3_index_build_static(const int32_t* ids, const int32_t* positions, int T, i
  *                                 the caller has already mapped each Q head to its KV head)
  *   scores_out [n_positions] fp32 or NULL; span_start [top_b] int32; span_score [top_b] fp32;
  *   n_found [1] int32.  Entries past n_found are set to -1 / 0.
- *   ws: s3_coactivate_score_workspace(idx, n_positions) bytes, 256-byte aligned.
+ *   ws: s3_coactivate_score_workspace(idx, n_positions) bytes, 256-byte aligned; no smaller for a larger
+ *       n_positions, so that the longest context's serves them all.  Up to 34 MB of it are for workgroups that
+ *       share a head's lists: with less the call runs without these, in one group of heads per workgroup;
+ *       S3_ECAPACITY if that does not fit either.
  * Sums are accumulated in 64-bit fixed point, so the result is independent of execution order
  * (bit-identical from run to run) and W[s] is exactly the sum of its members before the final
  * rounding to fp32.

@@ -240,10 +240,8 @@ class Index:
         assert qids.dtype == torch.int32 and qvals.dtype == torch.float32 and qids.dim() == 3
         assert qids.shape[0] == self.n_heads and qids.shape[2] == self.k and qvals.shape == qids.shape
         dev = qids.device
-        need = self.score_workspace(n_positions)
         if ws is None:
-            ws = torch.empty(need, dtype=torch.uint8, device=dev)
-        assert ws.numel() >= need
+            ws = torch.empty(self.score_workspace(n_positions), dtype=torch.uint8, device=dev)
         starts = torch.empty(top_b, dtype=torch.int32, device=dev)
         scores = torch.empty(top_b, dtype=torch.float32, device=dev)
         found = torch.empty(1, dtype=torch.int32, device=dev)
@@ -304,10 +302,8 @@ class CompactIndex:
         assert qids.dtype == torch.int32 and qvals.dtype == torch.float32 and qids.dim() == 3
         assert qids.shape[0] == self.n_heads and qids.shape[2] == self.k and qvals.shape == qids.shape
         dev = qids.device
-        need = self.score_workspace(n_positions)
         if ws is None:
-            ws = torch.empty(need, dtype=torch.uint8, device=dev)
-        assert ws.numel() >= need
+            ws = torch.empty(self.score_workspace(n_positions), dtype=torch.uint8, device=dev)
         starts = torch.empty(top_b, dtype=torch.int32, device=dev)
         scores = torch.empty(top_b, dtype=torch.float32, device=dev)
         found = torch.empty(1, dtype=torch.int32, device=dev)

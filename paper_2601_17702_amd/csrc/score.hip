@@ -980,17 +980,23 @@ __global__ __launch_bounds__(s3greedy::kThreads) void sc_topb_slots_kernel(Score
     top_finish(a, found, lane);
 }
 
+// Scratch of a call.  `full`: what the entry points ask for, room for kGroups workgroups' partial sums of a position block and for the
+// maxima of blocks of 64 windows; it does not shrink for longer contexts, more heads or more features.  Else the least that a call
+// takes, as much as one did before a head's lists were shared by several workgroups: heads in groups, maxima of 256 windows.
 struct Layout {
     size_t wmax, nact, sfix, wfix, tmaxv, tmaxi, part, act, total;
     int nr, pb, npb, heads_per, parts, ngroup;   // feature ranges per head; position blocks, heads of a group, parts and groups at most of the gather
+    bool full;
 };
+constexpr int kGroups = 256;
 
-Layout layout(int n_heads, int n_feat, int64_t L) {
+Layout layout(int n_heads, int n_feat, int64_t L, bool full) {
     Layout l;
+    l.full = full;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += s3_align(bytes); return at; };
     const int64_t nW_max = L;
-    const size_t nsub = (size_t)(nW_max + 63) / 64;
+    const size_t nsub = full ? (size_t)(nW_max + 63) / 64 : (size_t)(nW_max + kSubW - 1) / kSubW;
     l.nr = (n_feat + kRange - 1) / kRange;
     l.wmax = take(((size_t)n_heads * l.nr + 1) * 8);
     l.nact = take((size_t)n_heads * l.nr * 4);
@@ -1001,12 +1007,13 @@ Layout layout(int n_heads, int n_feat, int64_t L) {
     // position blocks of at most kMaxPB scores (128 KB of LDS); enough groups for about one workgroup per compute unit
     l.pb = (int)(L < kMaxPB ? (L + 63) / 64 * 64 : kMaxPB);
     l.npb = (int)((L + l.pb - 1) / l.pb);
-    const int want = 256 / l.npb < 1 ? 1 : 256 / l.npb, groups = n_heads < want ? n_heads : want;
+    const int want = kGroups / l.npb < 1 ? 1 : kGroups / l.npb, groups = n_heads < want ? n_heads : want;
     l.heads_per = (n_heads + groups - 1) / groups;
-    l.parts = want / groups;
+    l.parts = full ? want / groups : 1;
     l.ngroup = (n_heads + l.heads_per - 1) / l.heads_per * l.parts;
     l.part = o;
-    if (l.ngroup > 1) l.part = take((size_t)l.ngroup * L * 8);
+    if (full) l.part = take((size_t)kGroups * (L < kMaxPB ? L : kMaxPB) * 8);      // ngroup <= kGroups / npb arrays of L
+    else if (l.ngroup > 1) l.part = take((size_t)l.ngroup * L * 8);
     l.act = take((size_t)n_heads * n_feat * sizeof(ActiveList));
     l.total = o;
     return l;
@@ -1038,7 +1045,8 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.btab = v.btab; a.nblk = v.nblk;
     a.delta = v.delta; a.cstart = v.cstart; a.cfreq = v.cfreq; a.delta_stride = v.delta_stride; a.cstart_stride = v.cstart_stride;
     if ((int64_t)nq * a.k > (1 << 20)) return s3_fail(S3_EINVAL, "%s: nq * k %lld > 2^20", who, (long long)nq * a.k);
-    const Layout l = layout(a.n_heads, a.n_feat, n_positions);
+    Layout l = layout(a.n_heads, a.n_feat, n_positions, true);
+    if (ws_bytes < l.total) l = layout(a.n_heads, a.n_feat, n_positions, false);
     if (ws_bytes < l.total) return s3_fail(S3_ECAPACITY, "%s: workspace %zu < %zu bytes", who, ws_bytes, l.total);
     if ((uintptr_t)ws & 255) return s3_fail(S3_EINVAL, "%s: workspace must be 256-byte aligned", who);
 
@@ -1075,7 +1083,7 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     while (a.tile > 256 && a.tile >= 4 * a.len) a.tile >>= 1;
     a.ntile = (int)((a.nW + a.tile - 1) / a.tile);
     const int64_t reach = a.nms ? a.len - 1 : 0, most_found = s3greedy::choices(a.nW, reach, top_b), need = s3greedy::slots_needed(a.nW, reach, most_found);
-    const bool slots = most_found > kTopFew && need <= kTopSlots && (a.nW + 63) / 64 <= 16 * s3greedy::kThreads;
+    const bool slots = l.full && most_found > kTopFew && need <= kTopSlots && (a.nW + 63) / 64 <= 16 * s3greedy::kThreads;
     const s3greedy::Way sw = s3greedy::way_of(need, reach);
     a.need = (int)(slots ? need : 0);
     a.room = sw.room;
@@ -1130,7 +1138,7 @@ extern "C" size_t s3_coactivate_score_workspace(const s3_index* idx, int64_t n_p
     if (!idx || n_positions < 1) return 0;
     S3IndexView v;
     s3_index_view(idx, &v);
-    return layout(v.n_heads, v.n_feat, n_positions).total;
+    return layout(v.n_heads, v.n_feat, n_positions, true).total;
 }
 
 extern "C" int s3_coactivate_score(const s3_index* idx, const int32_t* qids, const float* qvals, int nq,
@@ -1154,7 +1162,7 @@ extern "C" size_t s3_coactivate_score_compact_workspace(const s3_cindex* cidx, i
     if (!cidx || n_positions < 1) return 0;
     S3CompactView c;
     s3_cindex_view(cidx, &c);
-    return layout(c.n_heads, c.n_feat, n_positions).total;
+    return layout(c.n_heads, c.n_feat, n_positions, true).total;
 }
 
 extern "C" int s3_coactivate_score_compact(const s3_cindex* cidx, const int32_t* qids, const float* qvals, int nq,

@@ -476,3 +476,41 @@ def test_scoring_with_shifted_positions_and_index_reuse():
         else:
             with pytest.raises(s3.S3Error):
                 ix.compact(0)
+
+
+def least_scratch(H, n_feat, L):
+    """Bytes of the arrays that a scoring call cannot do without, each padded to 256: weights' maxima, numbers of lists, scores,
+    window sums, maxima of 256 windows, partial sums of the groups of heads, packed lists."""
+    pad = lambda b: (b + 255) // 256 * 256
+    nr = -(-n_feat // 16384)
+    npb = -(-L // (-(-L // 64) * 64 if L < 16384 else 16384))
+    groups = min(H, max(1, 256 // npb))
+    ngroup = -(-H // -(-H // groups))
+    nsub = -(-L // 256)
+    return (pad((H * nr + 1) * 8) + pad(H * nr * 4) + 2 * pad(L * 8) + pad(nsub * 8) + pad(nsub * 4)
+            + (pad(ngroup * L * 8) if ngroup > 1 else 0) + pad(H * n_feat * 16))
+
+
+@pytest.mark.parametrize("H,n_feat,k,T", [(1, 300, 4, 40_000), (8, 16384, 4, 24_000), (32, 700, 2, 70_000), (300, 128, 1, 33_000)])
+def test_scratch_of_a_longer_context_serves_a_shorter_one(H, n_feat, k, T):
+    import torch
+    import paper_2601_17702_amd as s3
+    rng = np.random.default_rng(H)
+    ids = ((rng.integers(0, n_feat, (H, T, 1)) + np.arange(k) * (n_feat // k)) % n_feat).astype(np.int32)
+    ix = gpu_index(ids, n_feat)
+    lengths = [1, 63, 64, 1000, 16_000, 16_384, 16_385, 20_000, 24_000, 32_768, 40_000, 65_536, 70_000, 200_000, 1 << 20, 1 << 23]
+    for x in (ix, ix.compact(0)):
+        sizes = [x.score_workspace(L) for L in lengths]
+        assert sizes == sorted(sizes), list(zip(lengths, sizes))
+        qids = torch.from_numpy(rng.integers(0, n_feat, (H, 70, k)).astype(np.int32)).cuda()
+        qvals = torch.rand(H, 70, k, device="cuda")
+        ws = torch.empty(x.score_workspace(T), dtype=torch.uint8, device="cuda")
+        for L in [L for L in lengths[3:] if L < T] + [T]:
+            want = x.coactivate_score(qids, qvals, L, 24, 9, want_scores=True)
+            least = least_scratch(H, n_feat, L)
+            for w in (ws, ws[:least]):
+                got = x.coactivate_score(qids, qvals, L, 24, 9, want_scores=True, ws=w)
+                assert all(torch.equal(a, b) for a, b in zip(got, want)), (L, w.numel())
+            with pytest.raises(s3.S3Error) as e:
+                x.coactivate_score(qids, qvals, L, 24, 9, ws=ws[:least - 1])
+            assert e.value.code == -3
