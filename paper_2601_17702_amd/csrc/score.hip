@@ -52,6 +52,7 @@ struct ScoreArgs {
     int* nact;                       // [n_heads * nr] their number
     unsigned long long* sfix;        // [L]
     unsigned long long* part;        // [ngroup][L] partial sums of the gather's groups (ngroup > 1)
+    int nsum;                        // arrays that the pooling sums: part's, or 1 if sfix holds the scores
     int pb, npb, heads_per, parts, ngroup, sorted;   // the gather: position blocks, heads of a group, parts of these, groups in all
     int mixed;                       // lists of several heads and ranges may be looked at together
     long long* wfix;                 // [nW]
@@ -73,7 +74,11 @@ constexpr int kRun = 32;             // consecutive windows per thread (sliding 
 constexpr int kTileW = 64 * kRun;    // windows per tile = per wavefront of the pooling kernel
 constexpr int kSubLog2 = 8;
 constexpr int kSubW = 1 << kSubLog2; // windows per entry of the tile maxima (sc_topb_kernel, sc_topb_long_kernel)
-constexpr int kTopFew = 4;           // for so many spans or fewer that is not worth its beginning (4 spans of 1000 to 1000000 positions: as long; 1: 6 us more)
+// For so few spans, or so few that reach into so many blocks, bringing blocks into LDS is not worth its beginning: us for a look-up
+// with the maxima in registers / blocks in LDS, 5 spans of 64 in 1000 to 1000000 positions 22 to 39 / 22 to 38, without a match 20 to 36 /
+// 23 to 42; 8 of 64 26 to 44 / 22 to 38; 5 of 512 23 to 41 / 27 to 44, 12 35 to 52 / 29 to 46; 16 of 1024 in 16384 positions 37 / 45.
+constexpr int kTopFew = 5;
+inline bool top_many(int64_t found, int64_t reach) { return found > kTopFew && found > reach / 50; }
 constexpr int kTopSlots = 256;       // blocks of 64 windows that sc_topb_slots_kernel holds in LDS at most (131 KB)
 constexpr int kTopRegs = 4;          // registers per lane for the maxima of a short context
 constexpr int kTopThreads = 1024;    // long contexts: all of them load the tile maxima, one wavefront searches
@@ -597,11 +602,16 @@ __device__ __forceinline__ unsigned long long block_incl_scan_u64(unsigned long 
 // Sum of the groups, span pooling, the fp32 scores, and the best window of every 2^sublog windows (one workgroup per a.tile
 // windows).  The tile's positions are summed over the groups' arrays into LDS and turned into prefix sums there, so a window costs two
 // LDS reads whatever its length: W[s] = P[s + len - 1] - P[s - 1], exact in 64-bit integers.  Larger value wins, ties ->
-// smaller start.  What bounds it is a chain of memory, LDS and barrier latencies, so tiles are short (each thread has one position or
-// two), but no shorter than four windows, whose positions beyond the tile are summed twice.  32768 positions: 7.5 + 6.1 us
-// (sums by a kernel of their own, tiles of 2048 windows) -> 11.7.
+// smaller start.  What bounds it is a chain of memory, LDS and barrier latencies, so tiles are short where they are few: down to
+// kTilesMost of them or 256 windows, but no shorter than a window.  Longer ones for 1000000 positions: look-up of 2 queries in one
+// head 88 -> 39 us (tiles of 256), 300000: 33 -> 30.5 (at most 256 tiles instead of 128).
+// The positions of a tile's last windows lie beyond it and are summed twice.  So where the groups' arrays are many and windows long
+// (together more than kSumMost positions a tile), sc_reduce_kernel sums them first.  us for a look-up, sums here / by it: 256 arrays,
+// windows of 64 44 / 45, 256 50 / 46, 1024 92 / 46, 4096 206 / 46; 16 arrays, 256 29.4 / 30.1, 1024 32.1 / 30.4; 4 arrays, 1024 25.2 / 25.7.
 constexpr int kPoolThreads = 1024;
 constexpr int kPoolMaxLen = 4096;      // longer windows take sc_pool_wide_kernel
+constexpr int kTilesMost = 128;
+constexpr int64_t kSumMost = 16384;
 
 __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
     extern __shared__ unsigned long long pre[];          // [tile + len - 1] prefix sums
@@ -613,27 +623,45 @@ __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
     const int64_t s0 = (int64_t)blockIdx.x * a.tile;
     const int64_t tend = (int)blockIdx.x == a.ntile - 1 ? a.L : s0 + a.tile;      // positions whose fp32 score this tile writes
     const int n_in = (int)(min(a.L, s0 + a.tile + a.len - 1) - s0);               // positions the tile's windows read
-    const unsigned long long* const src = a.ngroup > 1 ? a.part : a.sfix;
-    // a wavefront sums a share of the groups for 64 positions, sixteen loads in flight per lane
-    constexpr int kSum = 16;
-    const int chunks = (n_in + 63) >> 6, shares = max(1, min(kW / chunks, (a.ngroup + kSum - 1) / kSum));
-    if (shares > 1) {
-        for (int i = tid; i < n_in; i += kPoolThreads) pre[i] = 0;
-        __syncthreads();
-    }
-    for (int c = wave; c < chunks * shares; c += kW) {
-        const int i = (c % chunks) * 64 + lane, g0 = a.ngroup * (c / chunks) / shares, g1 = a.ngroup * (c / chunks + 1) / shares;
-        if (i >= n_in) continue;
-        unsigned long long sum = 0;
-        for (int g = g0; g < g1; g += kSum) {
-            unsigned long long v[kSum];
+    if (a.nsum == 1) {
+        constexpr int kBatch = 4;                        // coalesced loads in flight per thread
+        for (int i0 = tid; i0 < n_in; i0 += kBatch * kPoolThreads) {
+            unsigned long long v[kBatch];
 #pragma unroll
-            for (int u = 0; u < kSum; ++u) v[u] = src[(size_t)min(g + u, g1 - 1) * a.L + s0 + i];
+            for (int u = 0; u < kBatch; ++u) v[u] = i0 + u * kPoolThreads < n_in ? a.sfix[s0 + i0 + u * kPoolThreads] : 0ull;
 #pragma unroll
-            for (int u = 0; u < kSum; ++u) sum += g + u < g1 ? v[u] : 0ull;
+            for (int u = 0; u < kBatch; ++u) {
+                const int i = i0 + u * kPoolThreads;
+                if (i >= n_in) continue;
+                pre[i] = v[u];
+                if (a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)v[u] * inv);
+            }
         }
-        if (shares > 1) atomicAdd(&pre[i], sum);
-        else pre[i] = sum;
+    } else {
+        // a wavefront sums a share of the groups for 64 positions, sixteen loads in flight per lane
+        constexpr int kSum = 16;
+        const int chunks = (n_in + 63) >> 6, shares = max(1, min(kW / chunks, (a.nsum + kSum - 1) / kSum));
+        if (shares > 1) {
+            for (int i = tid; i < n_in; i += kPoolThreads) pre[i] = 0;
+            __syncthreads();
+        }
+        for (int c = wave; c < chunks * shares; c += kW) {
+            const int i = (c % chunks) * 64 + lane, g0 = a.nsum * (c / chunks) / shares, g1 = a.nsum * (c / chunks + 1) / shares;
+            if (i >= n_in) continue;
+            unsigned long long sum = 0;
+            const auto take = [&](int g, auto n) {
+                unsigned long long v[n];
+#pragma unroll
+                for (int u = 0; u < n; ++u) v[u] = a.part[(size_t)min(g + u, g1 - 1) * a.L + s0 + i];
+#pragma unroll
+                for (int u = 0; u < n; ++u) sum += g + u < g1 ? v[u] : 0ull;
+            };
+            int g = g0;
+            for (; g + kSum / 2 < g1; g += kSum) take(g, std::integral_constant<int, kSum>());
+            for (; g < g1; g += kSum / 4) take(g, std::integral_constant<int, kSum / 4>());
+            if (shares > 1) atomicAdd(&pre[i], sum);
+            else pre[i] = sum;
+        }
     }
     __syncthreads();
     // each thread sums its own run, the block scans the run totals, the thread writes its run's prefixes
@@ -643,7 +671,7 @@ __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
         const int i = tid * per + j;
         if (i < n_in) {
             run += pre[i];
-            if (a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)pre[i] * inv);
+            if (a.nsum > 1 && a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)pre[i] * inv);
         }
     }
     unsigned long long sum = block_incl_scan_u64<kPoolThreads>(run, wsum) - run;
@@ -1072,18 +1100,27 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.tmaxi = (int*)(base + l.tmaxi);
     a.part = (unsigned long long*)(base + l.part);
     a.pb = l.pb; a.npb = l.npb; a.sorted = v.sorted ? 1 : 0;
-    // Lists that the queries' pairs can name in the heads of a group.  A part has 64 of them or more.
+    // Parts of a group's lists: one more saves gathering, about 0.27 ns a posting, and is one more array to write and to sum, 5 ps a
+    // position (with as many parts as have 64 lists each / now, us for a look-up: 16 queries of k 16 in 64 heads of 16384 positions 47 / 34,
+    // 100 in 16 heads 54 / 44, 16 in one head of 1000000 52 / 41; 300 of k 32 in one head of 16384 58 / 46).  The postings are those that as
+    // many lists of average length as the queries' pairs can name have in a position block.
+    const int groups = l.ngroup / l.parts;
     const int64_t pairs = (int64_t)nq * a.k, lists = l.heads_per * (pairs < a.n_feat ? pairs : (int64_t)a.n_feat);
+    const double postings = (double)lists * (double)v.tokens * a.k / ((double)a.n_feat * l.npb);
+    const int parts = (int)(sqrt(64.0 * postings / ((double)groups * (double)a.L)) + 0.5);
     a.heads_per = l.heads_per;
-    a.parts = (int)(lists / 64 < 1 ? 1 : (lists / 64 < l.parts ? lists / 64 : l.parts));
-    a.ngroup = l.ngroup / l.parts * a.parts;
+    a.parts = parts < 1 ? 1 : (parts < l.parts ? parts : l.parts);
+    a.ngroup = groups * a.parts;
     // a segment is at most a block of the compact index or of the block table, else a whole list
     a.mixed = v.delta || (v.btab && l.npb > 1) || v.tokens < (1 << 20) ? 1 : 0;
+    // sc_pool_kernel: its tiles, and whether the groups' arrays are summed before it
     a.tile = kTileW;
-    while (a.tile > 256 && a.tile >= 4 * a.len) a.tile >>= 1;
+    while (a.tile > 256 && a.tile >= 2 * a.len && (a.nW + a.tile - 1) / a.tile < kTilesMost) a.tile >>= 1;
+    const bool apart = a.ngroup > 1 && (a.len > kPoolMaxLen || (int64_t)a.ngroup * a.len > kSumMost);
+    a.nsum = apart ? 1 : a.ngroup;
     a.ntile = (int)((a.nW + a.tile - 1) / a.tile);
     const int64_t reach = a.nms ? a.len - 1 : 0, most_found = s3greedy::choices(a.nW, reach, top_b), need = s3greedy::slots_needed(a.nW, reach, most_found);
-    const bool slots = l.full && most_found > kTopFew && need <= kTopSlots && (a.nW + 63) / 64 <= 16 * s3greedy::kThreads;
+    const bool slots = l.full && top_many(most_found, reach) && need <= kTopSlots && (a.nW + 63) / 64 <= 16 * s3greedy::kThreads;
     const s3greedy::Way sw = s3greedy::way_of(need, reach);
     a.need = (int)(slots ? need : 0);
     a.room = sw.room;
@@ -1105,12 +1142,12 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     if ((int64_t)nq * a.k <= kPrepThreads) hipLaunchKernelGGL(sc_prep_few_kernel, dim3((unsigned)a.n_heads), dim3(kPrepThreads), 0, st, a);
     else hipLaunchKernelGGL(sc_prep_kernel, dim3((unsigned)a.nr, (unsigned)a.n_heads), dim3(kPrepThreads), (size_t)prep_lds, st, a);
     hipLaunchKernelGGL(gather, dim3((unsigned)(a.npb * a.ngroup)), dim3(kScatterThreads), (size_t)(a.pb + 64) * 8, st, a);
+    if (apart) hipLaunchKernelGGL(sc_reduce_kernel, dim3((unsigned)((a.L + 63) / 64)), dim3(256), 0, st, a);
     if (a.len <= kPoolMaxLen) {
         static S3LdsOnce once_pool;
         if (int rc = s3_allow_lds(once_pool, (const void*)sc_pool_kernel, (kTileW + kPoolMaxLen) * 8)) return rc;
         hipLaunchKernelGGL(sc_pool_kernel, dim3((unsigned)a.ntile), dim3(kPoolThreads), (size_t)(a.tile + a.len) * 8, st, a);
     } else {
-        if (a.ngroup > 1) hipLaunchKernelGGL(sc_reduce_kernel, dim3((unsigned)((a.L + 63) / 64)), dim3(256), 0, st, a);
         hipLaunchKernelGGL(sc_pool_wide_kernel, dim3((unsigned)((a.ntile + 3) / 4)), dim3(256), 0, st, a);
     }
     if (slots) {

@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
     (20_000, 64, 86, True),                  # 256 of 312 blocks, the most that LDS holds
     (20_000, 64, 87, True),                  # 259: maxima in registers, windows in memory
     (20_000, 300, 60, True),
+    (16_384, 64, 5, True), (16_384, 64, 6, True),      # from so many spans on in LDS
+    (16_384, 501, 10, True), (16_384, 501, 11, True), (9000, 768, 40, True),      # the longer, the more
     (65_536 + 63, 64, 16, True),             # 1024 maxima, one per thread; one more below
     (65_536 + 64, 64, 16, True),
     ((1 << 18) + 63, 64, 40, True),          # four per thread; sixteen below
@@ -129,6 +131,33 @@ def test_a_query_without_matches_costs_what_another_one_does(span_len, top_b):
     assert us[1] < us[0] + 1.2 * top_b + 5, us
 
 
+def look_up(H, L, nq, span_len, k=16, n_feat=8192):
+    """A look-up of four spans, to be timed: features evenly drawn, lists of L k / n_feat positions."""
+    import torch
+    import paper_2601_17702_amd as s3
+    ix = s3.Index(H, n_feat, k, L)
+    for t in range(0, L, 32_768):
+        start = torch.randint(0, n_feat, (H, min(32_768, L - t), 1), device="cuda", dtype=torch.int32)
+        ix.append(((start + n_feat // k * torch.arange(k, device="cuda", dtype=torch.int32)) % n_feat).contiguous(), base_pos=t)
+    ix.finalize()
+    q = torch.randint(0, n_feat, (H, nq, k), device="cuda", dtype=torch.int32)
+    v = torch.rand(H, nq, k, device="cuda")
+    ws = torch.empty(ix.score_workspace(L), dtype=torch.uint8, device="cuda")
+    return best_us(lambda: ix.coactivate_score(q, v, L, span_len, 4, want_scores=True, ws=ws))
+
+
+@pytest.mark.parametrize("a,b,factor", [
+    ((64, 16_384, 16, 1024), (64, 16_384, 16, 64), 1.5),       # longer windows are pooled by as many workgroups
+    ((256, 8000, 16, 4000), (256, 8000, 16, 64), 1.5),
+    ((1, 1_000_000, 2, 64), (1, 250_000, 2, 64), 1.6),         # tiles grow with the context
+    ((64, 16_384, 16, 64), (64, 16_384, 2, 64), 1.3),         # lists are shared where that is worth a further array
+], ids=str)
+def test_times_of_look_ups(a, b, factor):
+    """(heads, positions, queries, window) and one that takes nearly as long."""
+    us = look_up(*a), look_up(*b)
+    assert us[0] < factor * us[1], us
+
+
 @pytest.mark.parametrize("radius,n_centers", [(8, 9), (8, 40), (48, 128), (64, 40)])
 def test_a_level_curve_costs_what_another_one_does(radius, n_centers):
     import torch
@@ -172,6 +201,21 @@ def check_peaks(S, radius, n_centers):
     assert np.array_equal(D.cpu().numpy(), D32) and n == len(c_o)
     assert np.array_equal(c.cpu().numpy()[:n], c_o) and np.array_equal(dc.cpu().numpy()[:n], pk_o.astype(np.float32))
     assert np.array_equal(lo.cpu().numpy()[:n], lo_o) and np.array_equal(hi.cpu().numpy()[:n], hi_o)
+
+
+@pytest.mark.parametrize("H,T,span_len", [
+    (2, 5000, 64), (5, 3000, 700), (9, 2500, 100), (17, 4100, 33), (25, 1000, 10),       # arrays in batches of sixteen and four
+    (24, 1300, 682), (24, 1300, 683), (100, 900, 163), (100, 900, 164),      # summed by the pooling, and before it
+    (1, 40_000, 128), (1, 70_000, 2000), (1, 300_000, 64), (1, 9000, 4096), (3, 9000, 4097),      # tiles of 256 to 2048 windows
+])
+def test_pooling_over_the_groups(H, T, span_len):
+    rng = np.random.default_rng(H * T + span_len)
+    ids = ((rng.integers(0, 25, (H, T, 1)) + np.arange(2) * 25) % 50).astype(np.int32)
+    qids = rng.integers(0, 50, (H, 3, 2)).astype(np.int32)
+    qvals = rng.random((H, 3, 2)).astype(np.float32)
+    ix = gpu_index(ids, 50)
+    S, W, st_o, sc_o = oracle_score(ids, qids, qvals, 50, T, span_len, 8, 0, True)
+    check_score(run_gpu_score(ix, qids, qvals, T, span_len, 8, 0, True), S, W, st_o, sc_o, span_len, True)
 
 
 @pytest.mark.parametrize("H,T,k,n_feat,nq,hot", [
