@@ -1103,11 +1103,12 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     // Parts of a group's lists: one more saves gathering, about 0.27 ns a posting, and is one more array to write and to sum, 5 ps a
     // position (with as many parts as have 64 lists each / now, us for a look-up: 16 queries of k 16 in 64 heads of 16384 positions 47 / 34,
     // 100 in 16 heads 54 / 44, 16 in one head of 1000000 52 / 41; 300 of k 32 in one head of 16384 58 / 46).  The postings are those that as
-    // many lists of average length as the queries' pairs can name have in a position block.
+    // many lists of average length as the queries' pairs can name have in a position block; a part has 1024 of them or more (2 queries in
+    // 1000 positions: the gather 6.1 us in one part, 7.0 in six).
     const int groups = l.ngroup / l.parts;
     const int64_t pairs = (int64_t)nq * a.k, lists = l.heads_per * (pairs < a.n_feat ? pairs : (int64_t)a.n_feat);
     const double postings = (double)lists * (double)v.tokens * a.k / ((double)a.n_feat * l.npb);
-    const int parts = (int)(sqrt(64.0 * postings / ((double)groups * (double)a.L)) + 0.5);
+    const int parts = (int)fmin(sqrt(64.0 * postings / ((double)groups * (double)a.L)) + 0.5, postings / 1024);
     a.heads_per = l.heads_per;
     a.parts = parts < 1 ? 1 : (parts < l.parts ? parts : l.parts);
     a.ngroup = groups * a.parts;
