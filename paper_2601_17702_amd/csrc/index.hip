@@ -273,7 +273,7 @@ __device__ __forceinline__ void count_pieces(const E* in, int tile_post, const u
 // A bucket of at most kSortCap postings (the usual case) is done in one round: its sorted positions are
 // staged in LDS and written as one contiguous run.  A larger bucket (a very frequent feature) is counted
 // first and then taken in rounds of whole pieces, each round writing its sorted positions behind per-feature cursors.
-// NT: threads; a round takes as many postings with 256 as with 1024.  With 256 four workgroups share a compute unit instead of two and a
+// NT: threads; a round takes as many postings with 256 as with 1024.  With 256 four workgroups (S 8: three) share a compute unit instead of two and a
 // barrier waits for four wavefronts instead of sixteen: few_threads() says where the line lies.
 // ORDERED: the positions of several rounds go out in sorted order (run_finalize).
 template <int NBITS, int NT, bool ORDERED = false>
@@ -528,22 +528,25 @@ int run_partition(const int32_t* src, int64_t head_stride, int rows, int tile0, 
     return S3_OK;
 }
 
-// Threads of the bucket sort: 256, four workgroups to a compute unit, where there are workgroups enough to fill the chip twice and an
-// average bucket has no more postings than there are workgroups, nor more than a round takes.  A frequent feature's bucket is one
-// workgroup's chain of rounds, slower with fewer threads: the more workgroups there are, the more work hides it.  The piece words of a
-// bucket have to fit one load: 256 tiles at most.
-// Append and finalize, 1024 -> 256 threads, even features / one feature in every token and the rest skewed:
-//     256 heads x 2048 tokens, k 32, 16384 features (65536 buckets of 256)      870 -> 569 us      874 -> 560
-//       8 x 4000, k 128                             ( 2048 of 2000)            68.8 -> 60.2       65.8 -> 59.2
-//      32 x 14001, k 128                            ( 8192 of 7000)             411 -> 415         526 -> 487
-//      28 x 28672, k 64, 32768 features             ( 7168 of 7168)             388 -> 382         551 -> 531
-//       4 x 16384, k 32                             ( 1024 of 2048)            38.5 -> 33.0       74.4 -> 121.9: stays with 1024
-//       1 x 8192, k 32                              (  256 of 1024)            22.8 -> 23.7       35.2 -> 44.0: stays with 1024
-constexpr int kSmallThreads = 256, kSmallGroups = 2048;
+// Threads of the bucket sort: 256, four workgroups to a compute unit (three of eight-bit digits, 44 KB of LDS each), where there are
+// workgroups enough to fill the chip twice and buckets are short on average.  A frequent feature's bucket is one workgroup's chain of
+// rounds, slower with fewer threads: it has to fit one round with a feature of every token, or there are enough workgroups to hide it.
+// The piece words of a bucket have to fit one load: 256 tiles at most.
+// Append and finalize, us with 1024 / 256 threads, even features and with one feature in every token:
+//     8 heads x  4096, k 128, 16384 features ( 2048 buckets of 2048)   61 / 51      57 / 50
+//     8 x 16384, k 32                        ( 2048 of 2048)           63 / 54      93 / 129: stays with 1024
+//    32 x 16384, k 32                        ( 8192 of 2048)          199 / 163    282 / 254
+//    32 x 32768, k 32                        ( 8192 of 4096)          291 / 270    465 / 460
+//    32 x 48000, k 32                        ( 8192 of 6000)          416 / 404    656 / 675: stays with 1024
+//   128 x 32768, k 32                        (32768 of 4096)         1164 / 1129  1706 / 1655
+//    32 x 16384, k 32, 65536 features        ( 8192 of 2048)          216 / 195    312 / 300
+//    32 x 32768, k 32, 65536 features        ( 8192 of 4096)          313 / 313    510 / 536: stays with 1024
+constexpr int kSmallThreads = 256, kSmallGroups = 2048, kManyGroups = 8192;
 
 bool few_threads(const IdxDev& d, int n_heads, int n_tiles, int64_t tokens) {
-    const int64_t groups = (int64_t)d.NB * n_heads, most = std::min<int64_t>(kSortCap, groups);
-    return n_tiles <= kSmallThreads && groups >= kSmallGroups && tokens * d.k <= most * d.NB;
+    const int64_t groups = (int64_t)d.NB * n_heads, postings = tokens * d.k, most = std::min<int64_t>(d.S < 8 ? 4096 : 2048, groups);
+    return n_tiles <= kSmallThreads && groups >= kSmallGroups && postings <= most * d.NB &&
+           (groups >= kManyGroups || tokens * d.NB + postings <= (int64_t)kSortCap * d.NB);
 }
 
 int run_finalize(const IdxDev& d, int n_heads, int n_tiles, int64_t tokens, hipStream_t st) {
@@ -553,7 +556,7 @@ int run_finalize(const IdxDev& d, int n_heads, int n_tiles, int64_t tokens, hipS
     const bool small = few_threads(d, n_heads, n_tiles, tokens);
     const int nt = small ? kSmallThreads : kSplitThreads;
     const dim3 grid(d.NB, n_heads), block(nt);
-    const size_t lds = bucket_sort_lds(d.S, nt);       // < 64 KB: two workgroups per compute unit, four of 256 threads
+    const size_t lds = bucket_sort_lds(d.S, nt);       // < 64 KB: two workgroups per compute unit, four of 256 threads (S 8: three)
     constexpr int F = kSmallThreads, A = kSplitThreads;
     auto sort = d.S <= 6 ? idx_bucket_sort_kernel<6, A> : d.S == 7 ? idx_bucket_sort_kernel<7, A> : idx_bucket_sort_kernel<8, A>;
     if (small) sort = d.S <= 6 ? idx_bucket_sort_kernel<6, F> : d.S == 7 ? idx_bucket_sort_kernel<7, F> : idx_bucket_sort_kernel<8, F>;

@@ -107,15 +107,20 @@ def test_one_shot_index_build_matches():
 
 
 @pytest.mark.parametrize("H,T,k,n_feat,hot", [
-    (8, 4096, 128, 16384, 5),        # 2048 workgroups, 2048 postings a bucket: the most they take with 256 threads ...
+    (8, 4096, 128, 16384, 5),        # 2048 workgroups, 2048 postings a bucket: 256 threads ...
     (8, 4097, 128, 16384, 5),        # ... and a token more: 1024 threads
+    (8, 7281, 32, 16384, 5),         # a bucket with a feature of every token fits one round: 256 ...
+    (8, 7283, 32, 16384, 5),         # ... or not: 1024, with so few workgroups
     (7, 600, 16, 16384, None),       # 1792 workgroups: 1024 threads
     (8, 9000, 30, 4096, 5),          # a bucket of more than 8192 postings in a build of 256 threads
     (8, 4096, 64, 512, 5),           # two features a bucket
     (8, 1300, 64, 65536, 65535),     # 256 features a bucket
     (14, 700, 8, 300, 299),          # 2100 workgroups, the last bucket
-    (32, 256 * 64, 128, 65536, 9),   # 256 tiles, a full round's average: the piece words fit one load of 256 threads ...
-    (32, 256 * 64 + 1, 128, 65536, 9),  # ... and one tile more: 1024
+    (32, 256 * 64, 128, 65536, 9),   # 256 tiles; the average too long for 256 threads
+    (32, 256 * 64 + 1, 128, 65536, 9),
+    (32, 4096, 128, 65536, 9), (32, 4097, 128, 65536, 9),      # 2048 postings a bucket of 256 features, the most they take, and more
+    (32, 8192, 128, 16384, 9), (32, 8193, 128, 16384, 9),      # 4096 of 64
+    (64, 256 * 64, 64, 16384, 9), (64, 256 * 64 + 1, 64, 16384, 9),
     (1, 2 * 8192 * 2, 128, 16384, 9),  # 16384 postings a bucket: where each lane ranked its entry ...
     (1, 2 * 8192 * 2 + 1, 128, 16384, 9),  # ... and one token more: several rounds in sorted order
 ])
@@ -132,6 +137,29 @@ def test_bucket_sort_of_either_width(H, T, k, n_feat, hot):
     for h in {0, H // 2, H - 1}:
         _, (off_o, pos_o) = oracle_csr(ids[h], np.arange(T, dtype=np.int32), n_feat)
         assert_csr_equal(ix, h, off_o, pos_o)
+
+
+def test_a_feature_of_every_token_in_few_heads():
+    """Eight heads make 2048 workgroups, seven 1792: the eighth must not change how long the frequent feature's bucket takes."""
+    import torch
+    import paper_2601_17702_amd as s3
+    T, k, n_feat, us = 16_384, 32, 16_384, []
+    for H in (7, 8):
+        ids = (torch.randint(0, n_feat, (H, T, 1), device="cuda", dtype=torch.int32) + n_feat // k * torch.arange(k, device="cuda", dtype=torch.int32)) % n_feat
+        ids[:, :, 0] = 5
+        ids, ix, best = ids.contiguous(), s3.Index(H, n_feat, k, T), float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ix.reset()
+                ix.append(ids)
+                ix.finalize()
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 100)
+        us.append(best)
+    assert us[1] < 1.2 * us[0], us
 
 
 @pytest.mark.parametrize("T,k,n_feat,hot", [
