@@ -174,20 +174,23 @@ struct FeatArgs {
     int n_feat, k;
     uint32_t kinv;        // ceil(2^32 / k): slot / k for slot < 2^24
     int n_long, per;      // workgroups that look for long lists, features each of them looks at
+    int long_list;        // longer than this
 };
 
 // Step 5, and step 7 for W_enc, b_enc and W_dec: one wavefront per feature; its postings (flat slot = token * k + slot in the
 // row, ascending) are taken 64 at a time -- each lane fetches one posting's scalars, then the wavefront walks them in order.  A
 // posting is 8 bytes a lane from two rows (latency: 0.125 us each with four in flight, eight now), so one list of all 4096 tokens
-// took 511 us: lists of more than kLongList are shared by the wavefronts of a workgroup, whose sums are added in list order
+// took 511 us: lists of more than long_list are shared by the wavefronts of a workgroup, whose sums are added in list order
 // (4096 x 128 tokens, a few features in every token's selection).  The first workgroups of the launch look for these, kLongPer
 // features each, so that they run beside the short lists (a launch of their own behind those: 64 + 26 to 40 us after hundreds of
 // steps on one batch, now 71).  Below kFewFeat features lists are long: a workgroup of sixteen wavefronts each (a step of 4096
-// tokens, k 128, 128 latents: 417 us with eight and four features a workgroup, 200 before, now 187).
+// tokens, k 128, 128 latents: 417 us with eight and four features a workgroup, 200 before, now 187), and from kLongListFew postings on,
+// unless the batch is small and features are met seldom (200 tokens, k 4, 3968 latents 55 / 61 us with workgroups that find no list;
+// 256 tokens, k 128, 128 latents, lists of 256: 154 / 109).
 // Adam on the feature's two rows and its bias follows at once: the gradients need not be written and read again, and one
 // wavefront's parameters and moments come while others walk lists (4096 x 128 tokens, 16384 latents, k 128: 64 us and 20 for Adam on
 // all parameters -> 67; in workgroups of sixteen features, which all wait for their longest, 97).
-constexpr int kLongList = 256;
+constexpr int kLongList = 256, kLongListFew = 128;
 constexpr int kLongPer = 4;
 constexpr int kFewFeat = 4096;
 
@@ -288,13 +291,13 @@ __global__ __launch_bounds__(W * 64) void tr_feature_kernel(FeatArgs a) {
         const int f = ((int)blockIdx.x - a.n_long) * W + wv;
         if (f >= a.n_feat) return;
         const int beg = a.offsets[f], end = a.offsets[f + 1];
-        if (end - beg <= kLongList) feature_store(a, f, lane, feature_sums(a, beg, end, lane));
+        if (end - beg <= a.long_list) feature_store(a, f, lane, feature_sums(a, beg, end, lane));
         return;
     }
     const int f0 = blockIdx.x * a.per, fn = min(a.per, a.n_feat - f0);
     const int at = f0 + min(lane, fn - 1);
     const int my_beg = a.offsets[at], my_end = a.offsets[at + 1];
-    for (unsigned long long todo = __ballot(lane < fn && my_end - my_beg > kLongList); todo; todo &= todo - 1) {
+    for (unsigned long long todo = __ballot(lane < fn && my_end - my_beg > a.long_list); todo; todo &= todo - 1) {
         const int i = (int)__builtin_ctzll(todo);          // the same in every wavefront
         const int beg = __builtin_amdgcn_readlane(my_beg, i), end = __builtin_amdgcn_readlane(my_end, i);
         const int per = ((end - beg + W - 1) / W + kRows - 1) & ~(kRows - 1);
@@ -465,9 +468,10 @@ int s3_sae_train_step(const float* x, int B, int d_head, int n_feat, int k, floa
     const AdamArgs ad{lr, beta1, beta2, eps, (float)(1.0 - pow((double)beta1, (double)step)), (float)(1.0 - pow((double)beta2, (double)step))};
     const bool few = n_feat < kFewFeat;
     const int per = few ? 1 : kLongPer;
+    const int line = few && (B > kLongList || (int64_t)B * k >= 16 * (int64_t)n_feat) ? kLongListFew : kLongList;
     FeatArgs fa{offsets, slots, vals, dz, g, u_bf, grads_out, w_enc, b_enc, w_dec, adam_m, adam_v, ad, n_feat, k,
                 k > 1 ? (uint32_t)(((1ull << 32) + (uint32_t)k - 1) / (uint32_t)k) : 0u,
-                B > kLongList ? (n_feat + per - 1) / per : 0, per};
+                B > line ? (n_feat + per - 1) / per : 0, per, line};
     const int waves = few ? 16 : 8;
     hipLaunchKernelGGL(few ? tr_feature_kernel<16> : tr_feature_kernel<8>, dim3((unsigned)(fa.n_long + (n_feat + waves - 1) / waves)), dim3(waves * 64), 0, st, fa);
     const int nchunk = (B + kChunk - 1) / kChunk;

@@ -151,7 +151,10 @@ def test_lists_that_several_wavefronts_share(B, n_feat, k):
 
 
 @pytest.mark.parametrize("B,n_feat,k,hot", [
-    (256, 256, 8, 3), (257, 256, 8, 3),          # lists of as many postings as one wavefront takes, and of one more
+    (128, 256, 8, 3), (129, 256, 8, 3),          # lists of as many postings as one wavefront takes, and of one more
+    (256, 256, 8, 3), (257, 256, 8, 3),
+    (256, 4096, 4, 3), (257, 4096, 4, 3),        # more of them where there are many features
+    (256, 512, 31, 3), (256, 512, 32, 3),        # few features, met seldom and more often
     (600, 3968, 16, 9), (600, 4096, 16, 9),      # a workgroup for each of few features; four features each from here on
     (1030, 4224, 40, 30),
 ])
@@ -175,3 +178,24 @@ def test_long_posting_lists(B, n_feat, k, hot):
     M = [np.zeros_like(p) for p in P64]
     V = [np.zeros_like(p) for p in P64]
     check_step(tr, x, P64, M, V, k, 1, lr)
+
+
+def test_lists_of_256_postings_take_no_longer_than_of_257():
+    import torch
+    import paper_2601_17702_amd as s3
+    us = []
+    for B in (257, 256):
+        x, P32 = make_problem(B, B, 128)
+        tr = s3.SaeTrainer(*[torch.from_numpy(p.copy()).cuda() for p in P32], k=128, batch=B, lr=1e-8)
+        xg, best = torch.from_numpy(x).cuda(), float("inf")
+        tr.step(xg)
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(8):
+                tr.step(xg)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 125)
+        us.append(best)
+    assert us[1] < 1.15 * us[0], us
