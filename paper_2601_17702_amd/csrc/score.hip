@@ -1112,8 +1112,9 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.heads_per = l.heads_per;
     a.parts = parts < 1 ? 1 : (parts < l.parts ? parts : l.parts);
     a.ngroup = groups * a.parts;
-    // a segment is at most a block of the compact index or of the block table, else a whole list
-    a.mixed = v.delta || (v.btab && l.npb > 1) || v.tokens < (1 << 20) ? 1 : 0;
+    // The elements of 1024 segments are numbered in 32 bits.  A segment is at most a block of the compact index or of the block table,
+    // else a whole list, which an id that stands in a row more than once makes longer than there are tokens.
+    a.mixed = v.delta || (v.btab && l.npb > 1) || (v.tokens < (1 << 20) && (int64_t)l.heads_per * v.tokens * a.k < (1LL << 31)) ? 1 : 0;
     // sc_pool_kernel: its tiles, and whether the groups' arrays are summed before it
     a.tile = kTileW;
     while (a.tile > 256 && a.tile >= 2 * a.len && (a.nW + a.tile - 1) / a.tile < kTilesMost) a.tile >>= 1;

@@ -1,6 +1,8 @@
-"""Scoring and peaks around the sizes at which another way is taken.  The greedy searches that bring the blocks their choices can lie in into LDS: numbers of blocks and of slots around the sizes
-at which another build or another kernel takes over, and more equal block maxima than there are slots.  The gather: few and many
-query pairs, lists in parts, very long lists, many heads."""
+"""Scoring and peaks around the sizes at which another way is taken.  The greedy searches that bring the blocks their choices can
+lie in into LDS: numbers of blocks and of slots around the sizes at which another build or another kernel takes over, more equal
+block maxima than there are slots, choices that end among equal values.  The gather: few and many query pairs, lists in parts,
+segments around the numbers of vectors and of lists that are taken together, very long lists, many heads.  The pooling over the
+groups.  And times of calls that differ in one of these alone."""
 import numpy as np
 import pytest
 
@@ -221,8 +223,8 @@ def test_pooling_over_the_groups(H, T, span_len):
 @pytest.mark.parametrize("H,T,k,n_feat,nq,hot", [
     (1, 3000, 32, 256, 32, 0),           # 1024 query pairs, the most for a thread each; a head's lists in parts
     (2, 3000, 25, 300, 41, 0),           # 1025
-    (1, 40_000, 16, 4096, 9, 8),         # lists that fill whole position blocks: shared by all wavefronts at the end
-    (1, 20_000, 100, 400, 20, 100),      # more of them than are put aside
+    (1, 40_000, 16, 4096, 9, 8),         # lists that fill whole position blocks, beside short ones
+    (1, 20_000, 100, 400, 20, 100),      # a hundred of them
     (3, 700, 7, 17_000, 64, 0),          # two feature ranges
 ])
 def test_gather_of_short_and_long_lists(H, T, k, n_feat, nq, hot):
@@ -253,6 +255,49 @@ def test_gather_of_short_and_long_lists(H, T, k, n_feat, nq, hot):
         short = run_gpu_score(cx, qids, qvals, T - 130, 40, 12, 0, True)      # the last positions are cut off
         assert np.array_equal(whole[3], plain[3]) and np.array_equal(whole[0], plain[0])
         assert np.array_equal(short[3], plain[3][:T - 130])
+
+
+@pytest.mark.parametrize("n_lists", [1024, 1025])
+def test_gather_of_as_many_lists_as_are_numbered_together(n_lists):
+    """One head, one part: 1024 segments at a time."""
+    rng = np.random.default_rng(n_lists)
+    T, n_feat = 1500, 1100
+    ids = np.concatenate([np.arange(n_feat), rng.integers(0, n_feat, T - n_feat)]).astype(np.int32)
+    ids = rng.permutation(ids).reshape(1, T, 1)
+    qids = rng.permutation(n_feat)[:n_lists].astype(np.int32).reshape(1, -1, 1).copy()
+    qvals = (rng.random(qids.shape) + 0.1).astype(np.float32)
+    S, W, st_o, sc_o = oracle_score(ids, qids, qvals, n_feat, T, 16, 8, 0, True)
+    check_score(run_gpu_score(gpu_index(ids, n_feat), qids, qvals, T, 16, 8, 0, True), S, W, st_o, sc_o, 16, True)
+
+
+def test_gather_of_segments_around_a_wavefronts_load():
+    """A wavefront has 256 vectors of four postings in flight: lists of 1023 to 1025 postings at each alignment, and longer ones,
+    each with a weight of its own.  One position block, one part."""
+    rng = np.random.default_rng(3)
+    lengths = [1023, 1, 1024, 2, 1025, 3, 1024, 1, 1023, 4, 1022, 1, 1026, 2, 1021, 1, 3000, 1, 2048]
+    T, n_feat = sum(lengths), 16 * len(lengths)
+    ids = rng.permutation(np.repeat(np.arange(len(lengths)), lengths)).astype(np.int32).reshape(1, T, 1)
+    qids = np.arange(len(lengths), dtype=np.int32).reshape(1, -1, 1).copy()
+    qvals = (1 + rng.random(qids.shape)).astype(np.float32)
+    S, W, st_o, sc_o = oracle_score(ids, qids, qvals, n_feat, T, 16, 8, 0, True)
+    check_score(run_gpu_score(gpu_index(ids, n_feat), qids, qvals, T, 16, 8, 0, True), S, W, st_o, sc_o, 16, True)
+
+
+def test_gather_of_whole_lists_of_many_tokens():
+    """More than 2^20 tokens at given positions: no block table, and the lists of one head at a time."""
+    rng = np.random.default_rng(8)
+    T, n_feat, H = (1 << 20) + 300, 16, 2
+    ids = rng.integers(0, n_feat, (H, T, 1)).astype(np.int32)
+    qids = np.stack([rng.permutation(n_feat)[:5] for _ in range(H)]).astype(np.int32).reshape(H, 5, 1).copy()
+    qvals = (1 + rng.random(qids.shape)).astype(np.float32)
+    at = rng.permutation(T).astype(np.int32)
+    for positions in (at, np.sort(at)):
+        ix = gpu_index(ids, n_feat, positions=positions)
+        S, W, st_o, sc_o = oracle_score(ids, qids, qvals, n_feat, T, 64, 8, 0, True, positions=positions)
+        full = run_gpu_score(ix, qids, qvals, T, 64, 8, 0, True)
+        check_score(full, S, W, st_o, sc_o, 64, True)
+        for L in (16_384, 10_001):
+            assert np.array_equal(run_gpu_score(ix, qids, qvals, L, 64, 8, 0, True)[3], full[3][:L])
 
 
 def test_gather_of_more_heads_than_are_looked_at_together():
