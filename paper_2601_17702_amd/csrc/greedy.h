@@ -3,7 +3,7 @@
 //
 // Positions are looked at in blocks of 64.  A choice touches at most c = (2 reach - 1) / 64 + 2 blocks (one if reach is 0), so when
 // `want` positions are chosen, each lies in one of the c (want - 1) + 1 blocks with the best maxima: among so many at least one is
-// untouched by the choices before, and what is chosen is no worse than its maximum.  Only these blocks are brought into LDS (as
+// untouched by the choices before, and what is chosen is no worse than its maximum (of equal maxima the first).  Only these blocks are brought into LDS (as
 // "slots", in ascending order; fill()), and a round touches nothing else.  rounds() takes all choices that do not depend on each
 // other at once; walk() takes one a round, for choices that remove few positions.
 //
@@ -16,6 +16,7 @@
 namespace s3greedy {
 
 constexpr int kThreads = 1024, kWaves = kThreads / 64;
+constexpr int kListMax = 1024;                        // choices of rounds()
 constexpr int kNone = -0x7FFFFFFF - 1;                // the place of a slot that holds nothing
 
 // The most choices there can be.
@@ -46,6 +47,8 @@ template <class Key>
 constexpr int kRow = 64 + 16 / (int)sizeof(Key);
 template <class Key>
 constexpr int lds_bytes(int cap) { return cap * ((kRow<Key> + 1) * (int)sizeof(Key) + 4); }
+constexpr int kLdsMost = 160 << 10;
+constexpr int lds_static(int slots) { return 512 + 16 * slots; }      // the kernels' own variables, rounded up; in rounds four words a slot at most
 
 template <class Key>
 struct Slots {
@@ -268,7 +271,6 @@ template <int X>
 __device__ __forceinline__ unsigned long long quad_xor(unsigned long long v) {
     return ((unsigned long long)quad_xor<X>((unsigned)(v >> 32)) << 32) | quad_xor<X>((unsigned)v);
 }
-constexpr int kListMax = 1024;
 // The choices in few rounds, by the whole workgroup, over C slots.  A position that is the best within its reach is chosen
 // whatever happens elsewhere, so a round takes all slots' best positions that beat everything in the blocks they may reach into
 // (the best of all always does), removes what they reach and searches the blocks concerned again.  That goes on until `want`

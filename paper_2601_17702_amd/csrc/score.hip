@@ -79,7 +79,8 @@ constexpr int kSubW = 1 << kSubLog2; // windows per entry of the tile maxima (sc
 // 23 to 42; 8 of 64 26 to 44 / 22 to 38; 5 of 512 23 to 41 / 27 to 44, 12 35 to 52 / 29 to 46; 16 of 1024 in 16384 positions 37 / 45.
 constexpr int kTopFew = 5;
 inline bool top_many(int64_t found, int64_t reach) { return found > kTopFew && found > reach / 50; }
-constexpr int kTopSlots = 256;       // blocks of 64 windows that sc_topb_slots_kernel holds in LDS at most (131 KB)
+constexpr int kTopSlots = 256;       // blocks of 64 windows that the search holds in LDS at most (135 KB, and 12 of choices in rounds)
+static_assert(s3greedy::lds_bytes<unsigned long long>(kTopSlots) + s3greedy::kListMax * 12 + s3greedy::lds_static(kTopSlots) <= s3greedy::kLdsMost);
 constexpr int kTopRegs = 4;          // registers per lane for the maxima of a short context
 constexpr int kTopThreads = 1024;    // long contexts: all of them load the tile maxima, one wavefront searches
 constexpr int kTopTiles = 4096;      // tiles of the Top-B search: 64 groups of 64, one group per lane
@@ -560,7 +561,7 @@ __device__ __forceinline__ void wave_best(unsigned long long& key, int& start) {
     key = best;
 }
 
-// S = sum of the groups' partial arrays, for sc_pool_wide_kernel (the other pooling kernel sums them itself).  64 positions per
+// S = sum of the groups' partial arrays, where the pooling kernel does not sum them itself (score_run).  64 positions per
 // workgroup, four threads per position (each takes every fourth group), so that every thread's loads are independent.
 __global__ __launch_bounds__(256) void sc_reduce_kernel(ScoreArgs a) {
     __shared__ unsigned long long partial[4][64];
@@ -758,7 +759,7 @@ __global__ __launch_bounds__(256) void sc_pool_wide_kernel(ScoreArgs a) {
 //
 // sc_topb_rounds_kernel, sc_topb_slots_kernel: the blocks of 64 windows that the choices can lie in are brought into LDS (greedy.h),
 // for up to kTopSlots such blocks.  The first takes all choices that do not depend on each other at once, the second (few
-// windows suppressed by each, or none) one a round.
+// windows suppressed by each, or none) one a round, by one wavefront.
 // The others, for more: one wavefront walks the rounds without a barrier, with maxima of blocks of 256 windows in its registers.
 // A round takes the best, clears the tiles that the suppression covers whole and searches the two blocks of kSubW windows at its
 // ends again, loads of both in flight together.  A window that is gone is marked -1 in memory; window s belongs to lane s % 64 in
@@ -770,9 +771,9 @@ __global__ __launch_bounds__(256) void sc_pool_wide_kernel(ScoreArgs a) {
 // kTopTiles blocks a tile has several; their maxima come from memory beside the windows, block e belongs to the same lane in
 // every round, too.
 //
-// us for a whole look-up of 4 queries in one index, with these two / with blocks in LDS: 16 spans of 64, 8000 positions 51 / 33,
-// 200000 57 / 33, 1000000 64 / 41; 64 spans of 64, 8000 positions 133 / 36, 200000 156 / 42; 16 spans of 8, 33000 positions 47 / 31; 16
-// spans of 256 53 / 40; 16 windows that may overlap, 33000 positions 45 / 36.
+// us for a whole look-up of 8 queries in two indexes, with these two / with blocks in LDS: 16 spans of 64, 8000 positions 48 / 27,
+// 300000 59 / 37, 1000000 73 / 49; 64 spans of 64, 8000 positions 128 / 31, 300000 160 / 44; in 32768 positions 16 spans of 8 45 / 28, of
+// 256 51 / 36, of 64 that may overlap 42 / 32.
 // The line between these two, 16 spans: 65536 positions take 51 us in 4 registers, 57 in groups; with 8 registers 131072
 // take 55.5 instead of 56.5, but 32768 take 56 instead of 51.
 struct TopBest {
@@ -1140,7 +1141,7 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     const bool cmp = v.delta != nullptr;
     auto gather = cmp ? sc_gather_kernel<true> : sc_gather_kernel<false>;
     if (int rc = s3_allow_lds(once_gather[cmp], (const void*)gather, (kMaxPB + 64) * 8)) return rc;
-    // four launches: query weights, gather, sum of the groups with pooling and tile maxima, Top-B
+    // four or five launches: query weights, gather, perhaps the sum of the groups, pooling (with that sum) and tile maxima, Top-B
     if ((int64_t)nq * a.k <= kPrepThreads) hipLaunchKernelGGL(sc_prep_few_kernel, dim3((unsigned)a.n_heads), dim3(kPrepThreads), 0, st, a);
     else hipLaunchKernelGGL(sc_prep_kernel, dim3((unsigned)a.nr, (unsigned)a.n_heads), dim3(kPrepThreads), (size_t)prep_lds, st, a);
     hipLaunchKernelGGL(gather, dim3((unsigned)(a.npb * a.ngroup)), dim3(kScatterThreads), (size_t)(a.pb + 64) * 8, st, a);

@@ -32,7 +32,9 @@ constexpr int kNmsThreads = s3greedy::kThreads;
 // a round (0.9 us) behind a threshold between 512 and 576 counts, for more than kNmsManyTight: 32 at 500 of 70000 47 / 57.
 constexpr int kNmsFew = 8, kNmsManyTight = 64;
 inline bool nms_many(int64_t found, int64_t radius) { return found > kNmsFew && found > (radius + 16) / 32; }
-constexpr int kNmsSlots = 576;              // blocks that the peak search holds in LDS at most (151 KB)
+constexpr int kNmsSlots = 576;              // blocks that the peak search holds in LDS at most (157.5 KB; in rounds 512, 140 KB and 8 of choices)
+static_assert(s3greedy::lds_bytes<unsigned>(kNmsSlots) + s3greedy::lds_static(0) <= s3greedy::kLdsMost &&
+              s3greedy::lds_bytes<unsigned>(512) + s3greedy::kListMax * 8 + s3greedy::lds_static(512) <= s3greedy::kLdsMost);
 constexpr int kNmsTiles = 16384;            // tile maxima that the peak search keeps in LDS at most (128 KB): four groups of 64 per lane
 constexpr int kNmsTilesMin = 8192;          // as many fit beside the most centres
 static_assert(kConvLarge * kConvPer == kTile << kConvKeyShift && kConvLargeFrom <= (int64_t)kNmsTilesMin * kTile);
@@ -146,9 +148,9 @@ __global__ __launch_bounds__(NT) void sel_conv_kernel(SelArgs a) {
 // the latency of a round.
 //
 // sel_peaks_kernel, sel_nms_kernel: the blocks that the choices can lie in are brought into LDS (greedy.h), for up to 512 or 576
-// such blocks (always below 32769 or 36865 positions, else three a centre at a radius of 64).  The first takes all choices that do not
-// depend on each other at once, the second (small radii, where there may be many) one a round.
-// sel_nms_long_kernel, for more centres: one wavefront walks the rounds without a barrier over all tiles: maxima of groups of 64
+// such blocks (all of them below 32769 or 36865 positions, else three a centre at a radius of 64).  The first takes all choices that do not
+// depend on each other at once, the second (small radii, where there may be many) one a round, by one wavefront.
+// sel_nms_long_kernel, for few centres (nms_many()) and for more than that: one wavefront walks the rounds without a barrier over all tiles: maxima of groups of 64
 // tiles are in its registers, the tile maxima in LDS.  A round takes the best group, clears the tiles that the suppression
 // covers whole and searches the two blocks of 64 positions at its ends again; the groups at both ends are reduced in the
 // next round, beside its search and not behind this one's.  The curve is read from memory beside a bit per position that says
