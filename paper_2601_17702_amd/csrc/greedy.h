@@ -201,6 +201,10 @@ __device__ __forceinline__ void fill(const Slots<Key>& s, const Key (&key)[P], c
         clo = block_count(sums, key, lo);
     }
     if (clo > s.cap) {                                // P > 1, or ties
+        if (lo != best && best - lo < Key(1) << shift_of(best)) {      // the best to 32 bits, perhaps all of them
+            const int c = block_count(sums, key, best);
+            if (c >= need) { lo = best; clo = c; }
+        }
         if (lo != best) raise(lo, (Key)(best + 1), clo, need, s.cap, [&](Key t) { return block_count(sums, key, t); }, [&](Key& l, Key& h) {
             Key least = ~Key(0), largest = 0;
 #pragma unroll
