@@ -47,12 +47,14 @@ struct ScoreArgs {
     int64_t L, nW;
     int len, top_b, nms, hb;
     int32_t max_freq;
-    unsigned long long* wmax;        // [n_heads * nr] bits (as double) of each range's largest weight; [n_heads * nr]: of all
+    unsigned long long* wmax;        // [n_heads * nr] bits (as double) of each range's largest weight; [n_heads * nr]: of all; behind it the
+                                     // number of partial arrays that were written (post)
     ActiveList* act;                 // [n_heads * n_feat] lists with a non-zero weight, packed per (head, range)
     int* nact;                       // [n_heads * nr] their number
+    int* post;                       // [n_heads * nr] their postings / 64, for kernels that decide how many parts there are (else null)
     unsigned long long* sfix;        // [L]
     unsigned long long* part;        // [ngroup][L] partial sums of the gather's groups (ngroup > 1)
-    int nsum;                        // arrays that the pooling sums: part's, or 1 if sfix holds the scores
+    int nsum;                        // arrays that the pooling sums at most: part's, or 1 if sfix holds the scores
     int pb, npb, heads_per, parts, ngroup, sorted;   // the gather: position blocks, heads of a group, parts of these, groups in all
     int mixed;                       // lists of several heads and ranges may be looked at together
     long long* wfix;                 // [nW]
@@ -113,7 +115,7 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_kernel(ScoreArgs a) {
     extern __shared__ unsigned long long tbl[];
     __shared__ unsigned int amax[kPrepThreads / 64];
     __shared__ unsigned long long wmx[kPrepThreads / 64];
-    __shared__ int wsum[kPrepThreads / 64];
+    __shared__ int wsum[kPrepThreads / 64], psum[kPrepThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = blockIdx.y, r = blockIdx.x;
     const int f0 = r * kRange, nf = min(kRange, a.n_feat - f0);
@@ -161,7 +163,7 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_kernel(ScoreArgs a) {
     constexpr int kPer = kRange / kPrepThreads;
     const int32_t* off = a.cfreq ? nullptr : a.offsets + (size_t)h * a.off_stride + f0;
     double w[kPer];
-    int c = 0;
+    int c = 0, postings = 0;
     double mx = 0.0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
@@ -171,8 +173,10 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_kernel(ScoreArgs a) {
             const unsigned long long sacc = tbl[i];
             if (sacc) {
                 const int freq = a.cfreq ? a.cfreq[(size_t)h * a.n_feat + f0 + i] : off[i + 1] - off[i];
-                if (freq > 0 && !(a.max_freq > 0 && freq > a.max_freq))
+                if (freq > 0 && !(a.max_freq > 0 && freq > a.max_freq)) {
                     w[j] = (double)sacc * inv / ((double)logf(1.0f + (float)freq) + 1.0);
+                    postings += freq;
+                }
             }
         }
         c += w[j] > 0.0 ? 1 : 0;
@@ -185,13 +189,16 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_kernel(ScoreArgs a) {
     for (int j = 0; j < kPer; ++j)
         if (w[j] > 0.0) out[slot++] = ActiveList{w[j], f0 + j * kPrepThreads + tid, 0};
     const unsigned long long mb = wave_max_u64((unsigned long long)__double_as_longlong(mx));
-    if (lane == 0) wmx[wave] = mb;
+    const int wp = s3_wave_incl_scan(postings);
+    if (lane == 63) { wmx[wave] = mb; psum[wave] = wp; }
     __syncthreads();
     if (tid == 0) {
         unsigned long long best = 0;
-        for (int q = 0; q < kPrepThreads / 64; ++q) best = wmx[q] > best ? wmx[q] : best;
+        int sum = 0;
+        for (int q = 0; q < kPrepThreads / 64; ++q) { best = wmx[q] > best ? wmx[q] : best; sum += psum[q]; }
         a.wmax[h * a.nr + r] = best;
         a.nact[h * a.nr + r] = tot;
+        if (a.post) a.post[h * a.nr + r] = sum >> 6;
     }
 }
 
@@ -205,7 +212,7 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_few_kernel(ScoreArgs a) 
     __shared__ unsigned long long sum[kHash];
     __shared__ unsigned int amax[kPrepThreads / 64];
     __shared__ unsigned long long wmx[kPrepThreads / 64];
-    __shared__ int wsum[kPrepThreads / 64];
+    __shared__ int wsum[kPrepThreads / 64], psum[kPrepThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = blockIdx.x;
     const int per_head = a.nq * a.k;
@@ -258,14 +265,37 @@ __global__ __launch_bounds__(kPrepThreads) void sc_prep_few_kernel(ScoreArgs a) 
     const int slot = s3_block_excl_scan<kPrepThreads>(w > 0.0 ? 1 : 0, wsum, tot);
     if (w > 0.0) a.act[(size_t)h * a.n_feat + slot] = ActiveList{w, f, 0};
     const unsigned long long mb = wave_max_u64((unsigned long long)__double_as_longlong(w));
-    if (lane == 0) wmx[wave] = mb;
+    const int wp = s3_wave_incl_scan(w > 0.0 ? freq : 0);
+    if (lane == 63) { wmx[wave] = mb; psum[wave] = wp; }
     __syncthreads();
     for (int r = tid; r < a.nr; r += kPrepThreads) {
         unsigned long long best = 0;
-        for (int q = 0; q < kPrepThreads / 64; ++q) best = wmx[q] > best ? wmx[q] : best;
+        int sum = 0;
+        for (int q = 0; q < kPrepThreads / 64; ++q) { best = wmx[q] > best ? wmx[q] : best; sum += psum[q]; }
         a.wmax[h * a.nr + r] = r ? 0ull : best;
         a.nact[h * a.nr + r] = r ? 0 : tot;
+        if (a.post) a.post[h * a.nr + r] = r ? 0 : sum >> 6;
     }
+}
+
+// Parts of a group's lists that are worth it, for a group with so many postings in a position block: one more saves gathering, about
+// 0.27 ns a posting, and is one more array to write and to sum, 5 ps a position of all groups (as many as 4096, for the
+// latency of few); a part has 1024 postings or more.
+// The host knows how many lists there can be, not how long they are: it reckons as many as the square root of their share of the features
+// would have of all postings, since queries name the features that many tokens have too (1 to 65 times the average list in 120 calls whose
+// queries are encoded like their context), and with 64 lists a part or more.  The kernels know the lists, which may be few or none (queries
+// without a match, max_freq), and leave workgroups idle that four times their postings are not worth.  That is 0.7 us in the way of the sums, so
+// it is asked where the arrays have more than kArraysMost positions (179 queries of k 32 without a match, 13 heads of 28741
+// positions: 33 us in one part, 60 with one for every 64 lists, 34 so).
+// More time than with the best number of parts for each call: 120 calls whose queries are encoded like their context, a part for every 64
+// lists 3.5 %, postings of average lists alone 4.4 % (up to a sixth), this 3.0 %; 432 whose queries name features at random 6.3, 2.4 and 3.6 %.
+// us for a look-up, a part for every 64 lists / this: 16 queries of k 16 in 64 heads of 16384 positions 48 / 34, 100 in 16 heads 55 / 42; 300 of
+// k 32 in one head 48 / 41; 2 in 1000 positions the gather 7.0 in six parts / 6.1 in one.
+constexpr int kPartLists = 64;
+constexpr int64_t kArraysMost = 1 << 20;
+inline __host__ __device__ int parts_worth(float postings, int groups, int64_t L) {
+    const int parts = (int)fminf(sqrtf(64.f * postings / ((float)groups * (float)(L > 4096 ? L : 4096))) + 0.5f, postings * (1.f / 1024.f));
+    return parts > 1 ? parts : 1;
 }
 
 // Postings gather with the scores of one block of positions held in LDS.
@@ -361,15 +391,29 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
     for (int i = tid; i < a.pb / 2; i += kScatterThreads) ((uint4*)sblk)[i] = make_uint4(0, 0, 0, 0);      // pb is a multiple of 64
     // the largest weight over all heads fixes the fixed-point scale (every workgroup derives the same one)
     unsigned long long mb = 0;
-    for (int i = tid; i < a.n_heads * a.nr; i += kScatterThreads) mb = a.wmax[i] > mb ? a.wmax[i] : mb;
+    int postings = 0;
+    for (int i = tid; i < a.n_heads * a.nr; i += kScatterThreads) {
+        const unsigned long long w = a.wmax[i];
+        if (a.post) postings += a.post[i];
+        mb = w > mb ? w : mb;
+    }
     mb = wave_max_u64(mb);
-    if (lane == 0) wmx[wave] = mb;
+    postings = s3_wave_incl_scan(postings);
+    if (lane == 63) { wmx[wave] = mb; wcnt[wave] = postings; }
     const int nbk = a.nblk - 1;
     const int pair1 = min(a.n_heads, (group + 1) * a.heads_per) * a.nr;
     __syncthreads();
     mb = wmx[lane & (kW - 1)];
     mb = wave_max_u64(mb);
     if (blockIdx.x == 0 && tid == 0) a.wmax[a.n_heads * a.nr] = mb;      // for the kernels that follow
+    int parts = a.parts;                                          // the same in every workgroup
+    if (a.post) {
+        const int groups = a.ngroup / a.parts;
+        postings = __builtin_amdgcn_readlane(s3_row_incl_scan(wcnt[lane & (kW - 1)]), kW - 1);
+        parts = min(a.parts, parts_worth(256.f * (float)postings / ((float)groups * (float)a.npb), groups, a.L));
+        if (blockIdx.x == 0 && tid == 0) a.wmax[a.n_heads * a.nr + 1] = (unsigned long long)(groups * parts);
+        if (part >= parts) return;
+    }
     const double scale = ldexp(1.0, exp_s(mb, a.hb));
 
     // Adds w at the vector's postings that belong to the segment (`whole`: all do, in all lanes) and lie in the block.  Compact
@@ -414,8 +458,8 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
         const int ahead = s3_block_excl_scan<kScatterThreads>(n_mine, wsum, lists);
         if (tid < kPairs) upto[tid] = ahead + n_mine;
         __syncthreads();
-        const int list1 = (int)((int64_t)lists * (part + 1) / a.parts);      // this part's: [list0, list1)
-        int list0 = (int)((int64_t)lists * part / a.parts);
+        const int list1 = (int)((int64_t)lists * (part + 1) / parts);      // this part's: [list0, list1)
+        int list0 = (int)((int64_t)lists * part / parts);
         const auto pair_of = [&](int i) {                         // the pair that list i belongs to
             int q = 0;
             for (int s = kPairs / 2; s > 0; s >>= 1)
@@ -548,7 +592,7 @@ __global__ __launch_bounds__(kScatterThreads) void sc_gather_kernel(ScoreArgs a)
         }
     }
     __syncthreads();
-    unsigned long long* const dst = (a.ngroup > 1 ? a.part + (size_t)unit * a.L : a.sfix) + p0;
+    unsigned long long* const dst = (a.ngroup > 1 ? a.part + ((size_t)group * parts + part) * a.L : a.sfix) + p0;
     for (unsigned i = tid; i < span; i += kScatterThreads) dst[i] = sblk[spread(i)];
 }
 
@@ -561,24 +605,34 @@ __device__ __forceinline__ void wave_best(unsigned long long& key, int& start) {
     key = best;
 }
 
-// S = sum of the groups' partial arrays, where the pooling kernel does not sum them itself (score_run).  64 positions per
-// workgroup, four threads per position (each takes every fourth group), so that every thread's loads are independent.
-__global__ __launch_bounds__(256) void sc_reduce_kernel(ScoreArgs a) {
-    __shared__ unsigned long long partial[4][64];
-    const int p = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int64_t t = (int64_t)blockIdx.x * 64 + p;
-    unsigned long long s0 = 0, s1 = 0;
-    if (t < a.L) {
-        int g = q;
-        for (; g + 4 < a.ngroup; g += 8) {
-            s0 += a.part[(size_t)g * a.L + t];
-            s1 += a.part[(size_t)(g + 4) * a.L + t];
-        }
-        if (g < a.ngroup) s0 += a.part[(size_t)g * a.L + t];
+// Partial arrays that the gather wrote.
+__device__ __forceinline__ int arrays_of(const ScoreArgs& a) {
+    return a.post ? __builtin_amdgcn_readfirstlane((int)a.wmax[a.n_heads * a.nr + 1]) : a.ngroup;
+}
+
+// S = sum of the groups' partial arrays, where the pooling kernel does not sum them itself (score_run).  64 positions per workgroup,
+// whose wavefronts (four, or sixteen for many arrays) take the arrays in turn, eight loads in flight per thread: with few positions
+// it is the chain of a wavefront's loads that takes the time (256 arrays of 5115 positions 11.3 us with four wavefronts and two loads, 5.2 now).
+constexpr int kReduceFew = 32;
+__global__ __launch_bounds__(1024) void sc_reduce_kernel(ScoreArgs a) {
+    __shared__ unsigned long long partial[16][64];
+    constexpr int U = 8;
+    const int p = threadIdx.x & 63, q = threadIdx.x >> 6, nw = blockDim.x >> 6, n = arrays_of(a);
+    const int64_t t = (int64_t)blockIdx.x * 64 + p, at = t < a.L ? t : a.L - 1;
+    unsigned long long sum = 0;
+    for (int g = q; g < n; g += U * nw) {
+        unsigned long long v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = a.part[(size_t)min(g + u * nw, n - 1) * a.L + at];
+#pragma unroll
+        for (int u = 0; u < U; ++u) sum += g + u * nw < n ? v[u] : 0ull;
     }
-    partial[q][p] = s0 + s1;
+    partial[q][p] = sum;
     __syncthreads();
-    if (q == 0 && t < a.L) a.sfix[t] = partial[0][p] + partial[1][p] + partial[2][p] + partial[3][p];
+    if (q == 0 && t < a.L) {
+        for (int w = 1; w < nw; ++w) sum += partial[w][p];
+        a.sfix[t] = sum;
+    }
 }
 
 // Inclusive prefix sum of one 64-bit value per thread over the block (wrap-around arithmetic: exact differences).
@@ -624,12 +678,14 @@ __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
     const int64_t s0 = (int64_t)blockIdx.x * a.tile;
     const int64_t tend = (int)blockIdx.x == a.ntile - 1 ? a.L : s0 + a.tile;      // positions whose fp32 score this tile writes
     const int n_in = (int)(min(a.L, s0 + a.tile + a.len - 1) - s0);               // positions the tile's windows read
-    if (a.nsum == 1) {
+    const int nsum = a.nsum == 1 ? 1 : arrays_of(a);
+    if (nsum == 1) {
+        const unsigned long long* const src = a.nsum == 1 ? a.sfix : a.part;
         constexpr int kBatch = 4;                        // coalesced loads in flight per thread
         for (int i0 = tid; i0 < n_in; i0 += kBatch * kPoolThreads) {
             unsigned long long v[kBatch];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) v[u] = i0 + u * kPoolThreads < n_in ? a.sfix[s0 + i0 + u * kPoolThreads] : 0ull;
+            for (int u = 0; u < kBatch; ++u) v[u] = i0 + u * kPoolThreads < n_in ? src[s0 + i0 + u * kPoolThreads] : 0ull;
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
                 const int i = i0 + u * kPoolThreads;
@@ -641,13 +697,13 @@ __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
     } else {
         // a wavefront sums a share of the groups for 64 positions, sixteen loads in flight per lane
         constexpr int kSum = 16;
-        const int chunks = (n_in + 63) >> 6, shares = max(1, min(kW / chunks, (a.nsum + kSum - 1) / kSum));
+        const int chunks = (n_in + 63) >> 6, shares = max(1, min(kW / chunks, (nsum + kSum - 1) / kSum));
         if (shares > 1) {
             for (int i = tid; i < n_in; i += kPoolThreads) pre[i] = 0;
             __syncthreads();
         }
         for (int c = wave; c < chunks * shares; c += kW) {
-            const int i = (c % chunks) * 64 + lane, g0 = a.nsum * (c / chunks) / shares, g1 = a.nsum * (c / chunks + 1) / shares;
+            const int i = (c % chunks) * 64 + lane, g0 = nsum * (c / chunks) / shares, g1 = nsum * (c / chunks + 1) / shares;
             if (i >= n_in) continue;
             unsigned long long sum = 0;
             const auto take = [&](int g, auto n) {
@@ -672,7 +728,7 @@ __global__ __launch_bounds__(kPoolThreads) void sc_pool_kernel(ScoreArgs a) {
         const int i = tid * per + j;
         if (i < n_in) {
             run += pre[i];
-            if (a.nsum > 1 && a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)pre[i] * inv);
+            if (nsum > 1 && a.scores_out && s0 + i < tend) a.scores_out[s0 + i] = (float)((double)pre[i] * inv);
         }
     }
     unsigned long long sum = block_incl_scan_u64<kPoolThreads>(run, wsum) - run;
@@ -1013,7 +1069,7 @@ __global__ __launch_bounds__(s3greedy::kThreads) void sc_topb_slots_kernel(Score
 // maxima of blocks of 64 windows; it does not shrink for longer contexts, more heads or more features.  Else the least that a call
 // takes, as much as one did before a head's lists were shared by several workgroups: heads in groups, maxima of 256 windows.
 struct Layout {
-    size_t wmax, nact, sfix, wfix, tmaxv, tmaxi, part, act, total;
+    size_t wmax, nact, post, sfix, wfix, tmaxv, tmaxi, part, act, total;
     int nr, pb, npb, heads_per, parts, ngroup;   // feature ranges per head; position blocks, heads of a group, parts and groups at most of the gather
     bool full;
 };
@@ -1027,8 +1083,9 @@ Layout layout(int n_heads, int n_feat, int64_t L, bool full) {
     const int64_t nW_max = L;
     const size_t nsub = full ? (size_t)(nW_max + 63) / 64 : (size_t)(nW_max + kSubW - 1) / kSubW;
     l.nr = (n_feat + kRange - 1) / kRange;
-    l.wmax = take(((size_t)n_heads * l.nr + 1) * 8);
+    l.wmax = take(((size_t)n_heads * l.nr + (full ? 2 : 1)) * 8);
     l.nact = take((size_t)n_heads * l.nr * 4);
+    l.post = full ? take((size_t)n_heads * l.nr * 4) : 0;
     l.sfix = take((size_t)L * 8);
     l.wfix = take((size_t)L * 8);
     l.tmaxv = take(nsub * 8);
@@ -1101,18 +1158,15 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     a.tmaxi = (int*)(base + l.tmaxi);
     a.part = (unsigned long long*)(base + l.part);
     a.pb = l.pb; a.npb = l.npb; a.sorted = v.sorted ? 1 : 0;
-    // Parts of a group's lists: one more saves gathering, about 0.27 ns a posting, and is one more array to write and to sum, 5 ps a
-    // position (with as many parts as have 64 lists each / now, us for a look-up: 16 queries of k 16 in 64 heads of 16384 positions 47 / 34,
-    // 100 in 16 heads 54 / 44, 16 in one head of 1000000 52 / 41; 300 of k 32 in one head of 16384 58 / 46).  The postings are those that as
-    // many lists of average length as the queries' pairs can name have in a position block; a part has 1024 of them or more (2 queries in
-    // 1000 positions: the gather 6.1 us in one part, 7.0 in six).
     const int groups = l.ngroup / l.parts;
-    const int64_t pairs = (int64_t)nq * a.k, lists = l.heads_per * (pairs < a.n_feat ? pairs : (int64_t)a.n_feat);
-    const double postings = (double)lists * (double)v.tokens * a.k / ((double)a.n_feat * l.npb);
-    const int parts = (int)fmin(sqrt(64.0 * postings / ((double)groups * (double)a.L)) + 0.5, postings / 1024);
+    const int64_t pairs = (int64_t)nq * a.k, named = pairs < a.n_feat ? pairs : (int64_t)a.n_feat, most = l.heads_per * named / kPartLists;
+    const double postings = l.heads_per * (double)v.tokens * a.k * sqrt((double)named / a.n_feat) / l.npb;
+    int parts = parts_worth((float)postings, groups, a.L);
+    if (parts > most) parts = most > 1 ? (int)most : 1;
     a.heads_per = l.heads_per;
-    a.parts = parts < 1 ? 1 : (parts < l.parts ? parts : l.parts);
+    a.parts = parts < l.parts ? parts : l.parts;
     a.ngroup = groups * a.parts;
+    a.post = a.parts > 1 && (int64_t)a.ngroup * a.L > kArraysMost ? (int*)(base + l.post) : nullptr;
     // The elements of 1024 segments are numbered in 32 bits.  A segment is at most a block of the compact index or of the block table,
     // else a whole list, which an id that stands in a row more than once makes longer than there are tokens.
     a.mixed = v.delta || (v.btab && l.npb > 1) || (v.tokens < (1 << 20) && (int64_t)l.heads_per * v.tokens * a.k < (1LL << 31)) ? 1 : 0;
@@ -1145,7 +1199,7 @@ static int score_run(const char* who, const ScoreSource& v, const int32_t* qids,
     if ((int64_t)nq * a.k <= kPrepThreads) hipLaunchKernelGGL(sc_prep_few_kernel, dim3((unsigned)a.n_heads), dim3(kPrepThreads), 0, st, a);
     else hipLaunchKernelGGL(sc_prep_kernel, dim3((unsigned)a.nr, (unsigned)a.n_heads), dim3(kPrepThreads), (size_t)prep_lds, st, a);
     hipLaunchKernelGGL(gather, dim3((unsigned)(a.npb * a.ngroup)), dim3(kScatterThreads), (size_t)(a.pb + 64) * 8, st, a);
-    if (apart) hipLaunchKernelGGL(sc_reduce_kernel, dim3((unsigned)((a.L + 63) / 64)), dim3(256), 0, st, a);
+    if (apart) hipLaunchKernelGGL(sc_reduce_kernel, dim3((unsigned)((a.L + 63) / 64)), dim3(a.ngroup <= kReduceFew ? 256 : 1024), 0, st, a);
     if (a.len <= kPoolMaxLen) {
         static S3LdsOnce once_pool;
         if (int rc = s3_allow_lds(once_pool, (const void*)sc_pool_kernel, (kTileW + kPoolMaxLen) * 8)) return rc;
