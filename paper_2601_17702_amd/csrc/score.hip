@@ -76,11 +76,12 @@ constexpr int kRun = 32;             // consecutive windows per thread (sliding 
 constexpr int kTileW = 64 * kRun;    // windows per tile = per wavefront of the pooling kernel
 constexpr int kSubLog2 = 8;
 constexpr int kSubW = 1 << kSubLog2; // windows per entry of the tile maxima (sc_topb_kernel, sc_topb_long_kernel)
-// For so few spans, or so few that reach into so many blocks, bringing blocks into LDS is not worth its beginning: us for a look-up
-// with the maxima in registers / blocks in LDS, 5 spans of 64 in 1000 to 1000000 positions 22 to 39 / 22 to 38, without a match 20 to 36 /
-// 23 to 42; 8 of 64 26 to 44 / 22 to 38; 5 of 512 23 to 41 / 27 to 44, 12 35 to 52 / 29 to 46; 16 of 1024 in 16384 positions 37 / 45.
-constexpr int kTopFew = 5;
-inline bool top_many(int64_t found, int64_t reach) { return found > kTopFew && found > reach / 50; }
+// For so few spans, or so few that reach into so many blocks, bringing blocks into LDS is not worth its beginning, nor where a span's
+// blocks take longer to look through than to read again: us for a look-up with the maxima in registers / blocks in LDS, 4 spans of 64 as
+// long; 5 of 64 in 1000 to 1000000 positions 27 to 49 / 26 to 48, without a match 22 to 44 / 25 to 49; 8 26 to 44 / 22 to 38; 5 of 512 29 to
+// 51 / 33 to 53, 8 35 to 58 / 33 to 55 (with few matches 28 to 52 / 30 to 65), 12 35 to 52 / 29 to 46; 16 of 1024 in 16384 positions 37 / 45.
+constexpr int kTopFew = 4;
+inline bool top_many(int64_t found, int64_t reach) { return found > kTopFew && found > reach / 50 && reach < 900; }
 constexpr int kTopSlots = 256;       // blocks of 64 windows that the search holds in LDS at most (135 KB, and 12 of choices in rounds)
 static_assert(s3greedy::lds_bytes<unsigned long long>(kTopSlots) + s3greedy::kListMax * 12 + s3greedy::lds_static(kTopSlots) <= s3greedy::kLdsMost);
 constexpr int kTopRegs = 4;          // registers per lane for the maxima of a short context

@@ -20,8 +20,8 @@ pytestmark = pytest.mark.gpu
     (20_000, 64, 86, True),                  # 256 of 312 blocks, the most that LDS holds
     (20_000, 64, 87, True),                  # 259: maxima in registers, windows in memory
     (20_000, 300, 60, True),
-    (16_384, 64, 5, True), (16_384, 64, 6, True),      # from so many spans on in LDS
-    (16_384, 501, 10, True), (16_384, 501, 11, True), (9000, 768, 40, True),      # the longer, the more
+    (16_384, 64, 4, True), (16_384, 64, 5, True),      # from so many spans on in LDS
+    (16_384, 501, 10, True), (16_384, 501, 11, True), (9000, 768, 40, True), (16_384, 900, 30, True), (16_384, 901, 30, True),      # the longer, the more
     (65_536 + 63, 64, 16, True),             # 1024 maxima, one per thread; one more below
     (65_536 + 64, 64, 16, True),
     ((1 << 18) + 63, 64, 40, True),          # four per thread; sixteen below
